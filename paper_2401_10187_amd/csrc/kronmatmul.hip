@@ -11,6 +11,7 @@
 #include "instances.hpp"
 #include "generic_kernel.hpp"
 #include "row_kernel.hpp"
+#include "row_mfma_kernel.hpp"
 #include "fused_kernel.hpp"          // the kernel headers below are only needed for their shape structs
 #include "fused_multi_kernel.hpp"
 #include "mfma_kernel.hpp"
@@ -124,6 +125,43 @@ static hipError_t launch_rows(const LaunchArgs& a)
     if (e != hipSuccess || a.prepare_only) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)st.grid), dim3((unsigned)st.block), (size_t)st.lds_bytes, a.stream,
                        (const T*)a.src, (T*)a.dst, fa, (int)st.k_in, (int)st.k_out, (int)maxw, pr.M);
+    return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t launch_rows_mfma(const LaunchArgs& a)
+{
+    const km_plan_step& st = *a.st;
+    const Problem& pr = *a.pr;
+    const RowmShape rs = rowm_shape(pr);
+    const int n = st.num_factors;
+    if (st.first_factor != 0 || n != pr.N || rs.threads == 0) return hipErrorInvalidValue;
+    if (st.grid < 1 || st.grid > pr.M || st.block != rs.threads || st.lds_bytes != rs.lds_bytes) return hipErrorInvalidValue;
+    auto kern = rs.threads == 1024 ? row_mfma_sliced_multiply<T, 16> : row_mfma_sliced_multiply<T, 4>;
+    static unsigned char lds_ok[2][64];
+    hipError_t e = allow_lds((const void*)kern, ROWM_LDS_LIMIT, lds_ok[rs.threads == 1024]);
+    if (e != hipSuccess || a.prepare_only) return e;
+    RowmArgs ra{};
+    ra.n = n;
+    ra.buf_elems = (int)rs.buf_elems;
+    auto magic = [](int d) { return d > 1 ? (unsigned)(((1ull << 32) + (unsigned)d - 1) / (unsigned)d) : 0u; };
+    int64_t w = st.k_in;
+    for (int i = 0; i < n; ++i) {                        // order of application: last factor first
+        const int f = n - 1 - i;
+        RowmStep& s = ra.step[i];
+        s.f = a.factors[f];
+        s.P = pr.P[f];
+        s.Q = pr.Q[f];
+        s.S = (int)(w / s.P);
+        s.blocks = (s.S + 15) / 16;
+        s.units = s.blocks * ((s.Q + 15) / 16);
+        s.blocks_magic = magic(s.blocks);
+        ra.magic[i] = rowm_slice_stride(s.P) != s.P ? magic(s.P) : 0;
+        w = (int64_t)s.S * s.Q;
+    }
+    if (w != st.k_out) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kern, dim3((unsigned)st.grid), dim3((unsigned)st.block), (size_t)st.lds_bytes, a.stream,
+                       (const T*)a.src, (T*)a.dst, ra, (int)st.k_in, (int)st.k_out, pr.M);
     return hipGetLastError();
 }
 
@@ -251,6 +289,8 @@ static hipError_t launch_step(const Problem& pr, const km_plan_step& st, const v
     LaunchArgs a{src, dst, F, &pr, &st, stream, prepare_only, keep_output};
     if (st.kernel == KM_KERNEL_GENERIC)
         return pr.dtype == KM_F32 ? launch_generic<float>(a) : launch_generic<double>(a);
+    if (st.kernel == KM_KERNEL_ROWS && st.variant == ROWM_VARIANT)
+        return pr.dtype == KM_F32 ? launch_rows_mfma<float>(a) : launch_rows_mfma<double>(a);
     if (st.kernel == KM_KERNEL_ROWS)
         return pr.dtype == KM_F32 ? launch_rows<float>(a) : launch_rows<double>(a);
     if (st.kernel == KM_KERNEL_MFMA_ANY)

@@ -212,6 +212,59 @@ KM_HOST_DEVICE inline void unit_of(int64_t b, int64_t tiles, int groups, int64_t
     }
 }
 
+// The whole-row MFMA kernel: up to ROWM_MAXF factors of at most ROWM_MAXP rows; slices of a multiple of 8
+// elements are padded by 4 in LDS (row_mfma_kernel.hpp says why).
+constexpr int ROWM_MAXF = 8, ROWM_MAXP = 80, ROWM_LDS_LIMIT = 96 * 1024, ROWM_ROWS = 1024;
+constexpr int ROWM_VARIANT = -2;           // km_plan_step.variant of its launches
+KM_HOST_DEVICE inline int rowm_slice_stride(int P) { return P + (P % 8 == 0 ? 4 : 0); }
+
+// How that kernel would run a problem (threads == 0: it cannot).
+struct RowmShape {
+    int threads = 0;
+    int64_t buf_elems = 0, lds_bytes = 0;
+    double seconds = 0;                    // estimate
+};
+inline RowmShape rowm_shape(const Problem& pr)
+{
+    RowmShape r;
+    if (pr.N > ROWM_MAXF || pr.M < 1) return r;
+    // a buffer holds the row as each step reads it, slices padded, and the result
+    int64_t w = pr.k_in;
+    r.buf_elems = pr.k_out;
+    for (int f = pr.N - 1; f >= 0; --f) {
+        if (pr.P[f] > ROWM_MAXP || w > 65535) return RowmShape();
+        const int64_t S = w / pr.P[f];
+        if (S * rowm_slice_stride(pr.P[f]) > r.buf_elems) r.buf_elems = S * rowm_slice_stride(pr.P[f]);
+        w = S * pr.Q[f];
+    }
+    r.buf_elems = (r.buf_elems + 7) / 4 * 4;              // (whole vectors, and a few elements that a masked read may touch)
+    r.lds_bytes = 2 * r.buf_elems * (int64_t)pr.esize;
+    if (r.lds_bytes > ROWM_LDS_LIMIT) return RowmShape();
+    // Four or sixteen wavefronts per row, by an estimate: a row takes about 1.2 us to load and store, a step
+    // 0.5 us and 0.15 us for each 16x16 block a wavefront computes in turn; 25 ns per block and 3.5 ns per
+    // MFMA (fp64 7) are the compute unit's, so the rows on it share them (registers allow 16 wavefronts per unit).
+    // Within 15 % of what was measured, the launch's 2.6 us aside, for 10 x (52x50, 65x20) (2.9 us, fp64 4.5),
+    // 200 x 50x50^2 (4.8), 1000 x 50x50^2 (14.1), 1024 x 36x36^2 (7.9), 33 x 80x80^2 (7.7), 30 x 20x20^3 (12.1),
+    // 50 x 17x17^3 fp64 (12.0) and 1 x (5x5^2, 2x2, 25x25) (6.7).
+    for (int nw = 16; nw >= 4; nw -= 12) {
+        int64_t per_cu = 160 * 1024 / r.lds_bytes;
+        if (per_cu > 16 / nw) per_cu = 16 / nw;
+        double row = 1.2e-6 + (double)pr.k_in / (nw * 64) * 0.02e-6, busy = 0;
+        w = pr.k_in;
+        for (int f = pr.N - 1; f >= 0; --f) {
+            const int64_t S = w / pr.P[f], units = (S + 15) / 16 * ((pr.Q[f] + 15) / 16);
+            row += 0.5e-6 + 0.15e-6 * (double)((units + nw - 1) / nw);
+            busy += (double)units * (25e-9 + (double)((pr.P[f] + 3) / 4) * (pr.esize == 4 ? 3.5e-9 : 7e-9));
+            w = S * pr.Q[f];
+        }
+        const int64_t rounds = (pr.M + 256 * per_cu - 1) / (256 * per_cu);
+        const int64_t together = pr.M < 256 * per_cu ? (pr.M + 255) / 256 : per_cu;
+        const double t = 1.15 * (double)rounds * (row + busy * (double)together);
+        if (r.threads == 0 || t < r.seconds) { r.threads = nw * 64; r.seconds = t; }
+    }
+    return r;
+}
+
 // A compiled instance chosen for one group of factors, with the slices per tile it will run with.
 // What the planner needs to know of the generic kernel: a workgroup of `threads` work-items takes
 // `tile_slices` slices and `tile_cols` factor columns at a time.
@@ -729,6 +782,29 @@ inline km_status finish_plan(const Problem& pr, const Options& opt, const Varian
     return KM_OK;
 }
 
+// Makes `plan` one launch of a whole-row kernel.
+inline void take_rows_plan(const Problem& pr, int variant, int threads, int64_t lds_bytes, Plan& plan)
+{
+    km_plan_step one{};
+    one.kernel = KM_KERNEL_ROWS;
+    one.variant = variant;
+    one.first_factor = 0;
+    one.num_factors = pr.N;
+    one.tile_slices = 1;
+    one.tile_rows = 1;
+    one.k_in = pr.k_in;
+    one.k_out = pr.k_out;
+    one.src = KM_BUF_X;
+    one.dst = KM_BUF_Y;
+    one.grid = pr.M < 65536 ? pr.M : 65536;              // the kernels stride over the rows
+    one.block = threads;
+    one.lds_bytes = (int)lds_bytes;
+    plan.steps.assign(1, one);
+    plan.ws0_bytes = plan.ws1_bytes = 0;
+    plan.bytes = (double)pr.M * ((double)pr.k_in + (double)pr.k_out) * (double)pr.esize;
+    for (int i = 0; i < pr.N; ++i) plan.bytes += (double)pr.P[i] * pr.Q[i] * pr.esize;
+}
+
 inline km_status make_plan(const Problem& pr, const Options& opt, const Variant* table, int count,
                            const GenericKernel& gen, Plan& plan)
 {
@@ -759,6 +835,7 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
     // threads taken when rows are few (fp64: 1.5 times that); rows run side by side as far as LDS
     // and 2048 threads per compute unit allow.
     const bool force_rows = opt.prefer_instance == count + 1;      // tuning aid: whenever it fits
+    double rows_cost = -1;
     if ((opt.kernels >> KM_KERNEL_ROWS & 1) && N >= 2 && N <= gen.row_max_factors && N <= opt.max_fuse &&
         (plan.steps.size() > 1 || force_rows)) {
         int64_t maxw = 0;
@@ -797,26 +874,47 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
             if (c < 4.5 * bytes) c = 4.5 * bytes;
             c += 2.5e7;
             if (c < best[N] || force_rows) {
-                km_plan_step one{};
-                one.kernel = KM_KERNEL_ROWS;
-                one.variant = -1;
-                one.first_factor = 0;
-                one.num_factors = N;
-                one.tile_slices = 1;
-                one.tile_rows = 1;
-                one.k_in = width[N];
-                one.k_out = width[0];
-                one.src = KM_BUF_X;
-                one.dst = KM_BUF_Y;
-                one.grid = pr.M < 65536 ? pr.M : 65536;     // the kernel strides over the rows
-                one.block = threads;
-                one.lds_bytes = (int)lds;
-                plan.steps.assign(1, one);
-                plan.ws0_bytes = plan.ws1_bytes = 0;
-                plan.bytes = bytes;
-                for (int i = 0; i < N; ++i) plan.bytes += (double)pr.P[i] * pr.Q[i] * pr.esize;
+                take_rows_plan(pr, -1, threads, lds, plan);
+                rows_cost = c;
             }
         }
+    }
+    // The same on the matrix cores (row_mfma_kernel.hpp), for up to ROWM_ROWS rows, in the place of a whole-row
+    // plan of the FMA kernel or of tiled launches without compiled shapes.  Launches of compiled instances are
+    // as quick on problems this small (16 x 16x16^3 6.9 us in three of them, 7.7 here; 128 x 32x32^2 4.9
+    // and 4.7), those without compiled shapes are not (10 x (52x50, 65x20) fp64 20.1 us in two, 7.1 here; 200
+    // x 50x50^2 20.2 and 7.4; 300 x (32x32, 64x3) on the FMA kernel 20.2 and 5.1).
+    bool compiled = true;
+    for (const km_plan_step& s1 : plan.steps) compiled = compiled && s1.variant >= 0;
+    if ((opt.kernels >> KM_KERNEL_ROWS & 1) && N >= 2 && N <= opt.max_fuse && pr.M <= ROWM_ROWS && !compiled) {
+        const RowmShape rs = rowm_shape(pr);
+        // what the plan at hand takes, a launch's 2.6 us (of the 5 that launch_cost charges) left out for one
+        double had = 0;
+        if (rows_cost >= 0) {
+            had = (rows_cost - 2.5e7) / 5e12;
+            // (steps with few results leave most of the FMA kernel's threads idle: a step then takes 70 ns for each
+            // of the P products one thread adds up: 300 x (32x32, 64x3) 17 us, 16 x (128x128, 4x4) 15)
+            double chain = 2.0e-6;
+            const int64_t threads = plan.steps[0].block;
+            for (int r = N; r >= 1; --r) {
+                const int64_t S = width[r] / pr.P[r - 1], units = (S + 1) / 2 * ((pr.Q[r - 1] + 3) / 4);
+                chain += 0.4e-6 + (double)((units + threads - 1) / threads) * pr.P[r - 1] * 0.07e-6;
+            }
+            if (had < chain) had = chain;
+        } else {
+            for (const km_plan_step& s1 : plan.steps) {
+                const double bytes = (double)pr.M * ((double)s1.k_in + (double)s1.k_out) * (double)pr.esize;
+                const int P = pr.P[s1.first_factor];
+                // (small launches of the run-time-shape MFMA kernel: 5.5 us when slices are whole 16-byte vectors and
+                // one chunk, 10 otherwise: 100 x 36x36^2 10.0 us in two, 200 x 50x50^2 20.2, 33 x 80x80^2 20.4)
+                if (s1.kernel == KM_KERNEL_MFMA_ANY)
+                    had += (P * pr.esize % 16 == 0 && P * pr.esize <= (size_t)gen.any_row_bytes ? 5.5e-6 : 9.5e-6) + bytes / 7e12;
+                else
+                    had += (s1.kernel == KM_KERNEL_GENERIC ? 4.5e-6 + 0.7e-6 * ((P + 15) / 16) : 2.5e-6) + bytes / 5e12;
+            }
+            had -= 2.6e-6;
+        }
+        if (rs.threads > 0 && rs.seconds < had) take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, plan);
     }
     return KM_OK;
 }

@@ -1,0 +1,235 @@
+// Every factor of a Kron-Matmul applied to a short row inside one launch, on the matrix cores, for problems
+// of few rows, which are bound by latency: by how long one workgroup takes from its start to its end.
+//
+// As in row_kernel.hpp the whole row is the tile: a workgroup loads one row of X, applies factor N, N-1,
+// ..., 1 by the rule of Algorithm 1 (slice s times column q goes to q*(K/P) + s) between two LDS buffers
+// and writes the row of Y; factor shapes are run-time values.  A step is the dense product
+// D[q][s] = sum_p F[p][q] * X[s*P + p] on the 16x16x4 MFMA of the element type: the factor is the A operand
+// (rows q), slices are the B operand (columns s), one contraction index per lane group and MFMA (p = 4t + g).
+// A unit is one 16x16 block of the result, units of one factor column block following each other; a wavefront
+// takes a run of them, so that it seldom changes its columns of the factor.
+//
+// What keeps the chain of latencies short: the A operand of a unit is read straight from global memory
+// into registers, and the loads of the next step's first unit are issued before this step's products, so a
+// factor costs neither a pass through LDS nor a memory latency of its own; the first step's are in flight
+// together with the row's.  No loop holds a division.  Contraction indices past P are zeroed in both operands
+// (what lies behind a slice may be NaN); rows q and columns s past the ends are computed on clamped
+// addresses and dropped.
+// Bound by latency: 10 x (52x50, 65x20), two steps, takes 5.5 us from launch to launch where an empty launch
+// takes 2.3 (13.7 on the FMA kernel, whose factors go through LDS and whose 130 busy threads add up 117
+// products one after the other; fp64 20.1 -> 7.0 against two launches); 200 x 50x50^2 20.2 -> 7.4, 33 x
+// 80x80^2 20.3 -> 10.3, 300 x (32x32, 64x3) 20.1 -> 5.1.  Sixteen wavefronts when units are many or rows few,
+// four (four rows to a compute unit) otherwise; a first version with the factors in LDS took 8.7 us on the
+// first of these, 1.2 of it staging them.
+// Slices of a multiple of 8 elements are padded by 4 in LDS, which spreads the 64 operand reads of an MFMA
+// (16 slices x 4 consecutive p) over the banks.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+#include "mfma_kernel.hpp"                 // MfmaF32x16, MfmaF64x16, Vec16, stream_load, stream_store
+#include "plan.hpp"                        // rowm_slice_stride, RowmShape
+
+namespace km {
+
+template <typename T> struct RowmOp;
+template <> struct RowmOp<float> { typedef MfmaF32x16 OP; };
+template <> struct RowmOp<double> { typedef MfmaF64x16 OP; };
+
+// One factor's step, in order of application (last factor of the product first).
+struct RowmStep {
+    const void* f;
+    int P, Q, S;                           // S: slices of the row the step reads
+    int units;                             // 16x16 blocks of its result
+    unsigned blocks_magic;                 // unit / slice blocks = (unit * blocks_magic) >> 32
+    int blocks;                            // slice blocks
+};
+struct RowmArgs {
+    RowmStep step[ROWM_MAXF];
+    unsigned magic[ROWM_MAXF];             // c / P of a step whose slices are padded (0: they are not): (c * magic) >> 32
+    int n;
+    int buf_elems;                         // elements of one row buffer; the second one follows it
+};
+
+// factor column block of a unit
+__device__ __forceinline__ int rowm_column_block(const RowmStep& st, int unit)
+{
+    return st.blocks == 1 ? unit : (int)__umulhi((unsigned)unit, st.blocks_magic);
+}
+
+// position in LDS of element c of a row that is read in slices of P elements
+__device__ __forceinline__ int rowm_at(int c, unsigned magic) { return magic ? c + 4 * (int)__umulhi((unsigned)c, magic) : c; }
+
+// Contraction indices are taken in chunks of 16, the first one holding what P leaves over (1 to 16 of them).
+__device__ __forceinline__ int rowm_first(int P) { return (P - 1) % 16 + 1; }
+// Is there a chunk c (of chunks 0 to `last`)?  The empty asm keeps the eight answers from being held in
+// scalar registers over a loop: asking costs one instruction.
+__device__ __forceinline__ bool rowm_chunk(int c, int last)
+{
+    asm volatile("" : "+s"(last));
+    return c <= last;
+}
+
+// Where a wavefront finds the A operand of a unit: element t of lane group g in chunk c is row
+// p = first + 16(c - 1) + 4t + g (4t + g in chunk 0) of factor column q, `step` bytes apart for each t.
+struct RowmOperand {
+    __amdgpu_buffer_rsrc_t rsrc;
+    int at, next, step, last;              // byte offsets in chunk 0 and chunk 1; the last chunk (-1: no unit)
+};
+template <typename T>
+__device__ __forceinline__ RowmOperand rowm_operand(const RowmStep& st, int unit, int j, int g)
+{
+    const int q = rowm_column_block(st, unit) * 16 + j;
+    RowmOperand o;
+    // (elements past the factor's last row, which chunk 0 may ask for, are past the end of the resource and read as zero)
+    o.rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(st.f), 0, st.P * st.Q * (int)sizeof(T), 0x00020000);
+    o.at = (g * st.Q + (q < st.Q ? q : st.Q - 1)) * (int)sizeof(T);
+    o.next = o.at + rowm_first(st.P) * st.Q * (int)sizeof(T);
+    o.step = 4 * st.Q * (int)sizeof(T);
+    o.last = (st.P - 1) / 16;
+    return o;
+}
+__device__ __forceinline__ void rowm_load(float& v, const RowmOperand& o, int at)
+{
+    v = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(o.rsrc, at, 0, 0));
+}
+__device__ __forceinline__ void rowm_load(double& v, const RowmOperand& o, int at)
+{
+    v = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(o.rsrc, at, 0, 0));
+}
+// chunk c of the operand (chunks are asked for in order)
+template <typename T>
+__device__ __forceinline__ void rowm_load_chunk(T (&a)[4], RowmOperand& o, int c)
+{
+    if (c == 1) o.at = o.next;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        rowm_load(a[t], o, o.at);
+        o.at += o.step;
+    }
+}
+
+template <typename T, int NW>
+__global__ __launch_bounds__(NW * 64, NW / 4)
+void row_mfma_sliced_multiply(const T* __restrict__ Xg, T* __restrict__ Yg, const RowmArgs ra,
+                              int k_in, int k_out, int64_t M)
+{
+    typedef typename RowmOp<T>::OP OP;
+    typedef typename Vec16<T>::type V;
+    constexpr int VN = Vec16<T>::N, NT = NW * 64, KC = ROWM_MAXP / 16;
+    extern __shared__ __attribute__((aligned(16))) unsigned char rowm_lds[];
+    T* const lds = reinterpret_cast<T*>(rowm_lds);
+    const int tid = threadIdx.x, lane = tid % 64;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+
+    for (int64_t row = blockIdx.x; row < M; row += gridDim.x) {
+        int own = lane;
+        asm volatile("" : "+v"(own));                    // (keeps addresses from being held in registers over the rows)
+        const int j = own % 16, g = own / 16;
+        T a[KC][4];                                      // A operand of the wavefront's next unit
+        auto first_unit = [&](const RowmStep& st) { return wave * ((st.units + NW - 1) / NW); };
+        if (first_unit(ra.step[0]) < ra.step[0].units) {
+            RowmOperand o = rowm_operand<T>(ra.step[0], first_unit(ra.step[0]), j, g);
+#pragma unroll
+            for (int c = 0; c < KC; ++c)
+                if (rowm_chunk(c, o.last)) rowm_load_chunk(a[c], o, c);
+        }
+        {
+            const T* src = Xg + row * k_in;
+            const unsigned magic = ra.magic[0];
+            if (k_in % VN == 0) {                        // (a padded slice is a multiple of 8 elements: a vector stays inside it)
+                for (int c0 = tid * VN; c0 < k_in; c0 += 4 * NT * VN) {
+                    V v[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (c0 + i * NT * VN < k_in) v[i] = stream_load(reinterpret_cast<const V*>(src + c0 + i * NT * VN));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (c0 + i * NT * VN < k_in) *reinterpret_cast<V*>(lds + rowm_at(c0 + i * NT * VN, magic)) = v[i];
+                }
+            } else {
+                for (int c0 = tid; c0 < k_in; c0 += 4 * NT) {
+                    T v[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (c0 + i * NT < k_in) v[i] = src[c0 + i * NT];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (c0 + i * NT < k_in) lds[rowm_at(c0 + i * NT, magic)] = v[i];
+                }
+            }
+        }
+        __syncthreads();
+
+        T* buf = lds;
+        T* out = lds + ra.buf_elems;
+        for (int i = 0; i < ra.n; ++i) {
+            const RowmStep st = ra.step[i];
+            const bool more = i + 1 < ra.n;
+            const unsigned next_magic = more ? ra.magic[i + 1] : 0;
+            const int first = rowm_first(st.P), last = (st.P - 1) / 16;
+            const int begin = first_unit(st), share = begin + (st.units + NW - 1) / NW, end = share < st.units ? share : st.units;
+            const int ahead = more ? first_unit(ra.step[i + 1]) : 0;
+            const bool wanted = more && ahead < ra.step[i + 1].units;
+            for (int unit = begin; unit < end; ++unit) {
+                const int qb = rowm_column_block(st, unit);
+                const int s = (unit - qb * st.blocks) * 16 + j;
+                const T* b = buf + (s < st.S ? s : st.S - 1) * rowm_slice_stride(st.P) + g;
+                // the wavefront's next unit, of this step or its first one of the next: its operand takes
+                // the registers of this one's as the products free them
+                RowmOperand o;
+                o.last = -1;
+                if (unit + 1 < end) {                    // (the same columns of the factor: it has the operand already)
+                    if (rowm_column_block(st, unit + 1) != qb) o = rowm_operand<T>(st, unit + 1, j, g);
+                } else if (wanted) {
+                    o = rowm_operand<T>(ra.step[i + 1], ahead, j, g);
+                }
+                typename OP::Acc acc;
+#pragma unroll
+                for (int v = 0; v < OP::NACC; ++v) acc[v] = T(0);
+#pragma unroll
+                for (int c = 0; c < KC; ++c) {
+                    if (c == 0) {
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+                            if (rowm_chunk(4 * t + 1, first)) {
+                                const bool in = 4 * t + g < first;
+                                const T x = b[in ? 4 * t : 0];
+                                acc = OP::mma(in ? a[0][t] : T(0), in ? x : T(0), acc);
+                            }
+                    } else if (rowm_chunk(c, last)) {
+                        T bv[4];
+                        const T* at = b + first + 16 * (c - 1);
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) bv[t] = at[4 * t];
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) acc = OP::mma(a[c][t], bv[t], acc);
+                    }
+                    if (rowm_chunk(c, o.last)) rowm_load_chunk(a[c], o, c);
+                }
+#pragma unroll
+                for (int v = 0; v < OP::NACC; ++v) {
+                    const int q = qb * 16 + OP::row_lane(lane) + OP::row_reg(v);
+                    if (q < st.Q && s < st.S) out[rowm_at(q * st.S + s, next_magic)] = acc[v];
+                }
+            }
+            if (begin >= end && wanted) {                // idle in this step
+                RowmOperand o = rowm_operand<T>(ra.step[i + 1], ahead, j, g);
+#pragma unroll
+                for (int c = 0; c < KC; ++c)
+                    if (rowm_chunk(c, o.last)) rowm_load_chunk(a[c], o, c);
+            }
+            __syncthreads();
+            T* other = buf; buf = out; out = other;
+        }
+
+        T* dst = Yg + row * k_out;
+        if (k_out % VN == 0) {
+            for (int c = tid * VN; c < k_out; c += NT * VN) stream_store(*reinterpret_cast<const V*>(buf + c), reinterpret_cast<V*>(dst + c));
+        } else {
+            for (int c = tid; c < k_out; c += NT) dst[c] = buf[c];
+        }
+        if (row + gridDim.x < M) __syncthreads();        // the result has left LDS
+    }
+}
+
+}  // namespace km
