@@ -227,17 +227,38 @@ def release():
     _check(lib().kronmatmul_release(), "kronmatmul_release")
 
 
+_raw_stream = None          # torch's (device index) -> hipStream_t of its current stream
+_entries = {}               # entry point name -> function of the library
+_int_arrays, _ptr_arrays = {}, {}      # ctypes array types by length
+
+
+def _current_stream(index):
+    """The raw handle of torch's current stream on a device.  torch has a call for just that, which takes 0.07 us
+    where building the Stream object takes 1.9; where a torch lacks it, the object is built."""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+            lambda i: torch.cuda.current_stream(i).cuda_stream)
+    return _raw_stream(index)
+
+
+def _entry(name):
+    fn = _entries.get(name)
+    if fn is None:
+        fn = _entries[name] = getattr(lib(), name)
+    return fn
+
+
 class Prepared:
     """A Kron-Matmul call with its arguments already checked and marshalled: calling it only crosses
     the C-ABI (for iterative callers that repeat one small problem, where marshalling would cost
     more than the kernels).  Keeps references to the tensors it was built from."""
 
     def __init__(self, X, Fs, Y=None, workspace=None, transposed=False):
-        import torch
-        self._torch = torch
         self.Y, self._args, self._ws_call, fptr = _marshal(X, Fs, Y, workspace, transposed)
         self._keep = (X, list(Fs), workspace, fptr)
-        self._device = X.device
+        self._device = X.get_device()
         self._what = _entry_name(self._ws_call, transposed)
         self._fn = getattr(lib(), self._what)
 
@@ -245,8 +266,8 @@ class Prepared:
         """Enqueue on `stream` (a raw hipStream_t value; default: torch's current stream).  The
         tensors' device must be the current device."""
         if stream is None:
-            stream = self._torch.cuda.current_stream(self._device).cuda_stream
-        st = self._fn(*self._args, ctypes.c_void_p(stream))
+            stream = _current_stream(self._device)
+        st = self._fn(*self._args, stream)
         if st != KM_OK:
             raise KronMatmulError(st, self._what)
         return self.Y
@@ -264,34 +285,40 @@ def _marshal(X, Fs, Y, workspace, transposed=False):
     import torch
     if not X.is_cuda or X.dim() != 2 or not X.is_contiguous():
         raise ValueError("X must be a contiguous 2-D CUDA tensor")
-    P, Q = [], []
-    for F in Fs:
-        if not F.is_cuda or F.dim() != 2 or not F.is_contiguous() or F.dtype != X.dtype or F.device != X.device:
-            raise ValueError("factors must be contiguous 2-D CUDA tensors of X's dtype and device")
-        P.append(F.shape[1] if transposed else F.shape[0])
-        Q.append(F.shape[0] if transposed else F.shape[1])
-    n, p, q = _shapes(P, Q)
+    dtype, index = X.dtype, X.get_device()      # (a number: comparing device objects costs more than all else here)
+    P, Q, ptrs = [], [], []
     kin = kout = 1
-    for a, b in zip(P, Q):
+    for F in Fs:
+        if F.dtype != dtype or F.get_device() != index or F.dim() != 2 or not F.is_contiguous():
+            raise ValueError("factors must be contiguous 2-D CUDA tensors of X's dtype and device")
+        a, b = F.shape
+        if transposed:
+            a, b = b, a
+        P.append(a)
+        Q.append(b)
         kin *= a
         kout *= b
-    M = X.shape[0]
-    if X.shape[1] != kin:
-        raise ValueError("X has %d columns, the factors need %d" % (X.shape[1], kin))
+        ptrs.append(F.data_ptr())
+    n = len(P)
+    ints, voids = _int_arrays.get(n), _ptr_arrays.get(n)
+    if ints is None:
+        ints = _int_arrays[n] = ctypes.c_int * max(n, 1)
+        voids = _ptr_arrays[n] = ctypes.c_void_p * max(n, 1)
+    M, K = X.shape
+    if K != kin:
+        raise ValueError("X has %d columns, the factors need %d" % (K, kin))
     if Y is None:
-        Y = torch.empty((M, kout), dtype=X.dtype, device=X.device)
-    elif (not Y.is_cuda or not Y.is_contiguous() or Y.dtype != X.dtype or tuple(Y.shape) != (M, kout)
-          or Y.device != X.device):
+        Y = X.new_empty((M, kout))
+    elif (Y.dtype != dtype or Y.get_device() != index or not Y.is_contiguous() or Y.shape != (M, kout)):
         raise ValueError("Y must be a contiguous CUDA tensor of shape (%d, %d)" % (M, kout))
-    code = _dtype_code(X.dtype)
-    fptr = (ctypes.c_void_p * max(n, 1))(*[F.data_ptr() for F in Fs])
-    head = (M, n, p, q, X.data_ptr(), ctypes.cast(fptr, ctypes.c_void_p), Y.data_ptr(), code)
+    code = KM_F32 if dtype is torch.float32 else _dtype_code(dtype)
+    fptr = voids(*ptrs)
+    head = (M, n, ints(*P), ints(*Q), X.data_ptr(), fptr, Y.data_ptr(), code)
     if workspace is None:
         return Y, head, False, fptr
-    if not workspace.is_cuda or not workspace.is_contiguous() or workspace.device != X.device:
+    if workspace.get_device() != index or not workspace.is_contiguous():
         raise ValueError("workspace must be a contiguous CUDA tensor on X's device")
-    nbytes = workspace.numel() * workspace.element_size()
-    return Y, head + (workspace.data_ptr(), nbytes), True, fptr
+    return Y, head + (workspace.data_ptr(), workspace.nbytes), True, fptr
 
 
 def kronmatmul(X, Fs, Y=None, workspace=None, stream=None, transposed=False, static=False):
@@ -305,9 +332,13 @@ def kronmatmul(X, Fs, Y=None, workspace=None, stream=None, transposed=False, sta
     if static and (workspace is not None or transposed):
         raise ValueError("static=True takes neither a workspace nor transposed factors")
     Y, args, with_ws, _fptr = _marshal(X, Fs, Y, workspace, transposed)
+    index = X.get_device()
     if stream is None:
-        stream = torch.cuda.current_stream(X.device).cuda_stream
+        stream = _current_stream(index)
     name = _entry_name(with_ws, transposed, static)
-    with torch.cuda.device(X.device):
-        _check(getattr(lib(), name)(*args, ctypes.c_void_p(stream)), name)
+    if torch.cuda.current_device() == index:
+        _check(_entry(name)(*args, stream), name)
+    else:
+        with torch.cuda.device(index):
+            _check(_entry(name)(*args, stream), name)
     return Y

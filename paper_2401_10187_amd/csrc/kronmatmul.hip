@@ -1,6 +1,8 @@
 // C-ABI of the Kron-Matmul library (see include/kronmatmul.h) and the launch loop of Algorithm 1:
 // one launch per plan step, buffers swapped between launches, everything on the caller's stream.
 #include <hip/hip_runtime.h>
+#include <atomic>
+#include <memory>
 #include <mutex>
 #include <vector>
 #include <string.h>
@@ -187,7 +189,7 @@ static __device__ __align__(256) unsigned char scratch[KM_STATIC_SCRATCH_BYTES];
 
 static std::mutex g_mutex;
 static Options g_options;
-static int g_profile = 0;
+static std::atomic<int> g_profile{0};      // written with g_mutex held
 // Launches other than a call's last whose output is between KEEP_MIN_MIB and g_keep_mib MiB write it
 // with ordinary stores (KM_OPT_KEEP_MIB; the chip's last-level cache holds 256 MB).  Measured, whole
 // call without -> with: 256 x 16x32^4 0.299 -> 0.266 ms, 256 x 8x8^6 0.201 -> 0.181, 16 x 32x32^4 (64 MiB)
@@ -205,12 +207,17 @@ static GenericKernel generic_kernel(int dtype)
 }
 
 // Plans are memoised: iterative callers repeat the same small problem thousands of times and the
-// planner should not show up next to a 6-microsecond kernel.
-struct CachedPlan {
-    int64_t M; int N; int dtype;
-    std::vector<int> P, Q;
-    Options opt;
+// planner should not show up next to a 6-microsecond kernel.  An entry never changes once it is in the
+// cache, so calls share it without a copy (a call that finds its problem takes 0.1 us for it, where building
+// the problem and copying the plan took 0.6) and it lives until the last of them is done.
+struct Planned {
+    Problem pr;
     Plan plan;
+};
+typedef std::shared_ptr<const Planned> PlannedRef;
+struct CachedPlan {
+    PlannedRef planned;
+    Options opt;
     bool tuned;          // measured by kronmatmul_tune: kept until kronmatmul_release
 };
 static std::vector<CachedPlan> g_plan_cache;      // most recently used first, guarded by g_mutex
@@ -218,7 +225,7 @@ constexpr size_t PLAN_CACHE_ENTRIES = 16, PLAN_CACHE_TUNED = 64;
 
 // Puts a plan at the head of the cache (g_mutex held).  A tuned plan replaces the entry of the same
 // problem; computed plans are dropped oldest first, tuned ones only when PLAN_CACHE_TUNED are held.
-static void cache_plan(const Problem& pr, const Options& opt, const Plan& plan, bool tuned);
+static void cache_plan(const PlannedRef& planned, const Options& opt, bool tuned);
 
 static bool same_options(const Options& a, const Options& b)
 {
@@ -228,46 +235,55 @@ static bool same_options(const Options& a, const Options& b)
            a.prefer_instance == b.prefer_instance;
 }
 
+static bool same_problem(const Problem& a, int64_t M, int N, const int* P, const int* Q, int dtype)
+{
+    return a.M == M && a.N == N && a.dtype == dtype && memcmp(a.P.data(), P, N * sizeof(int)) == 0 &&
+           memcmp(a.Q.data(), Q, N * sizeof(int)) == 0;
+}
+
 // HIP takes a launch only if its work-items, grid x block, number fewer than 2^32.
 static bool launchable(const km_plan_step& st)
 {
     return st.grid > 0 && st.block > 0 && (double)st.grid * (double)st.block < 4294967296.0;
 }
 
-static km_status plan_for(const Problem& pr, Plan& plan)
+// The plan of a problem with M > 0 rows, from the cache or made.
+static km_status plan_for(int M, int N, const int* P, const int* Q, int dtype, PlannedRef& out)
 {
     Options opt;
     {
         std::lock_guard<std::mutex> lock(g_mutex);
         opt = g_options;
-        for (size_t i = 0; i < g_plan_cache.size(); ++i) {
-            const CachedPlan& c = g_plan_cache[i];
-            if (c.M == pr.M && c.N == pr.N && c.dtype == pr.dtype && same_options(c.opt, opt) && c.P == pr.P && c.Q == pr.Q) {
-                plan = c.plan;
-                if (i) std::swap(g_plan_cache[0], g_plan_cache[i]);
-                return KM_OK;
+        if (P && Q)
+            for (size_t i = 0; i < g_plan_cache.size(); ++i) {
+                const CachedPlan& c = g_plan_cache[i];
+                if (same_problem(c.planned->pr, M, N, P, Q, dtype) && same_options(c.opt, opt)) {
+                    out = c.planned;
+                    if (i) std::swap(g_plan_cache[0], g_plan_cache[i]);
+                    return KM_OK;
+                }
             }
-        }
     }
-    km_status s = make_plan(pr, opt, g_variants, g_num_variants, generic_kernel(pr.dtype), plan);
+    auto made = std::make_shared<Planned>();
+    km_status s = make_problem(M, N, P, Q, dtype, made->pr);
     if (s != KM_OK) return s;
-    for (const km_plan_step& st : plan.steps)
+    s = make_plan(made->pr, opt, g_variants, g_num_variants, generic_kernel(dtype), made->plan);
+    if (s != KM_OK) return s;
+    for (const km_plan_step& st : made->plan.steps)
         if (!launchable(st)) return KM_EUNSUPPORTED;
-    {
-        std::lock_guard<std::mutex> lock(g_mutex);
-        cache_plan(pr, opt, plan, false);
-    }
+    out = made;
+    std::lock_guard<std::mutex> lock(g_mutex);
+    cache_plan(out, opt, false);
     return KM_OK;
 }
 
-static void cache_plan(const Problem& pr, const Options& opt, const Plan& plan, bool tuned)
+static void cache_plan(const PlannedRef& planned, const Options& opt, bool tuned)
 {
     size_t computed = 0, kept = 0;
+    const Problem& pr = planned->pr;
     for (size_t i = 0; i < g_plan_cache.size();) {
         const CachedPlan& c = g_plan_cache[i];
-        const bool same = c.M == pr.M && c.N == pr.N && c.dtype == pr.dtype && same_options(c.opt, opt) &&
-                          c.P == pr.P && c.Q == pr.Q;
-        if (same) {
+        if (same_problem(c.planned->pr, pr.M, pr.N, pr.P.data(), pr.Q.data(), pr.dtype) && same_options(c.opt, opt)) {
             if (c.tuned && !tuned) return;               // never replace a measured plan by a computed one
             g_plan_cache.erase(g_plan_cache.begin() + i);
             continue;
@@ -279,7 +295,7 @@ static void cache_plan(const Problem& pr, const Options& opt, const Plan& plan, 
     if ((tuned ? kept : computed) >= limit)
         for (size_t i = g_plan_cache.size(); i-- > 0;)
             if (g_plan_cache[i].tuned == tuned) { g_plan_cache.erase(g_plan_cache.begin() + i); break; }
-    g_plan_cache.insert(g_plan_cache.begin(), CachedPlan{pr.M, pr.N, pr.dtype, pr.P, pr.Q, opt, plan, tuned});
+    g_plan_cache.insert(g_plan_cache.begin(), CachedPlan{planned, opt, tuned});
 }
 
 static hipError_t launch_step(const Problem& pr, const km_plan_step& st, const void* src, void* dst,
@@ -304,27 +320,27 @@ static km_status run(const Problem& pr, const Plan& plan, const void* X, const v
 {
     char* ws0 = (char*)ws;
     char* ws1 = ws0 + plan.ws0_bytes;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return KM_ELAUNCH;
-    DeviceState& ds = g_dev[dev];
     const int n = (int)plan.steps.size();
-    int profile;
+    DeviceState* ds = nullptr;       // set when the call is profiled
     int ev0 = 0;
-    std::vector<hipEvent_t> ev;      // this call's events, copied while the lock is held: another thread may grow ds.events
-    {
+    std::vector<hipEvent_t> ev;      // this call's events, copied while the lock is held: another thread may grow ds->events
+    if (allow_profile && g_profile.load(std::memory_order_relaxed)) {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return KM_ELAUNCH;
         std::lock_guard<std::mutex> lock(g_mutex);
-        profile = allow_profile && g_profile && (int)ds.call_first.size() < MAX_PROFILED_CALLS;
-        if (profile) {
-            ev0 = ds.events_used;
-            while ((int)ds.events.size() < ev0 + n + 1) {
+        if (g_profile.load(std::memory_order_relaxed) && (int)g_dev[dev].call_first.size() < MAX_PROFILED_CALLS) {
+            ds = &g_dev[dev];
+            ev0 = ds->events_used;
+            while ((int)ds->events.size() < ev0 + n + 1) {
                 hipEvent_t e;
                 if (hipEventCreate(&e) != hipSuccess) return KM_ELAUNCH;
-                ds.events.push_back(e);
+                ds->events.push_back(e);
             }
-            ds.events_used = ev0 + n + 1;
-            ev.assign(ds.events.begin() + ev0, ds.events.begin() + ev0 + n + 1);
+            ds->events_used = ev0 + n + 1;
+            ev.assign(ds->events.begin() + ev0, ds->events.begin() + ev0 + n + 1);
         }
     }
+    const bool profile = ds != nullptr;
     if (profile && hipEventRecord(ev[0], stream) != hipSuccess) return KM_ELAUNCH;
     for (int i = 0; i < n; ++i) {
         const km_plan_step& st = plan.steps[i];
@@ -348,8 +364,8 @@ static km_status run(const Problem& pr, const Plan& plan, const void* X, const v
     }
     if (profile) {
         std::lock_guard<std::mutex> lock(g_mutex);
-        ds.call_first.push_back(ev0);
-        ds.call_steps.push_back(n);
+        ds->call_first.push_back(ev0);
+        ds->call_steps.push_back(n);
     }
     return KM_OK;
 }
@@ -652,14 +668,24 @@ static km_status execute(int M, int N, const int* P, const int* Q, const void* X
                          km_dtype dtype, WsKind kind, void* workspace, size_t workspace_bytes, void* stream,
                          bool transposed)
 {
-    Problem pr;
-    km_status s = make_problem(M, N, P, Q, (int)dtype, pr);
-    if (s != KM_OK) return s;
+    if (M == 0) {                    // a no-op, once its arguments are looked at
+        Problem empty;
+        km_status s0 = make_problem(M, N, P, Q, (int)dtype, empty);
+        return s0 != KM_OK ? s0 : check_pointers(empty, X, F, Y);
+    }
+    PlannedRef planned;
+    km_status s = plan_for(M, N, P, Q, (int)dtype, planned);
+    // (what is wrong with the pointers goes before a shape that nothing supports, as it did when they were checked first)
+    if (s != KM_OK && s != KM_EUNSUPPORTED) return s;
+    if (s == KM_EUNSUPPORTED) {
+        Problem shape;
+        make_problem(M, N, P, Q, (int)dtype, shape);
+        const km_status p = check_pointers(shape, X, F, Y);
+        return p != KM_OK ? p : s;
+    }
+    const Problem& pr = planned->pr;
+    const Plan& plan = planned->plan;
     s = check_pointers(pr, X, F, Y);
-    if (s != KM_OK) return s;
-    if (pr.M == 0) return KM_OK;
-    Plan plan;
-    s = plan_for(pr, plan);
     if (s != KM_OK) return s;
     const size_t plan_need = round_up(plan.ws0_bytes + plan.ws1_bytes, 256);
     const size_t need = transposed ? plan_need + factor_copy_bytes(pr) : plan.ws0_bytes + plan.ws1_bytes;
@@ -713,9 +739,10 @@ km_status kronmatmul_workspace_size(int M, int N, const int* P, const int* Q, km
     if (s != KM_OK) return s;
     *bytes = 0;
     if (pr.M == 0) return KM_OK;
-    Plan plan;
-    s = plan_for(pr, plan);
+    PlannedRef planned;
+    s = plan_for(M, N, P, Q, (int)dtype, planned);
     if (s != KM_OK) return s;
+    const Plan& plan = planned->plan;
     *bytes = plan.ws0_bytes + plan.ws1_bytes;
     return KM_OK;
 }
@@ -747,9 +774,10 @@ km_status kronmatmul_transposed_workspace_size(int M, int N, const int* P, const
     if (s != KM_OK) return s;
     *bytes = 0;
     if (pr.M == 0) return KM_OK;
-    Plan plan;
-    s = plan_for(pr, plan);
+    PlannedRef planned;
+    s = plan_for(M, N, P, Q, (int)dtype, planned);
     if (s != KM_OK) return s;
+    const Plan& plan = planned->plan;
     *bytes = round_up(plan.ws0_bytes + plan.ws1_bytes, 256) + factor_copy_bytes(pr);
     return KM_OK;
 }
@@ -781,13 +809,14 @@ km_status kronmatmul_tune(int M, int N, const int* P, const int* Q, km_dtype dty
         std::lock_guard<std::mutex> lock(g_mutex);
         opt = g_options;
     }
-    Plan plan;
-    s = tune(pr, opt, (hipStream_t)stream, plan, tuned_ms, default_ms);
+    auto made = std::make_shared<Planned>();
+    made->pr = pr;
+    s = tune(pr, opt, (hipStream_t)stream, made->plan, tuned_ms, default_ms);
     if (s != KM_OK) return s;
-    for (const km_plan_step& st : plan.steps)
+    for (const km_plan_step& st : made->plan.steps)
         if (!launchable(st)) return KM_EUNSUPPORTED;
     std::lock_guard<std::mutex> lock(g_mutex);
-    cache_plan(pr, opt, plan, true);
+    cache_plan(made, opt, true);
     return KM_OK;
 }
 
@@ -797,9 +826,10 @@ km_status kronmatmul_prepare(int M, int N, const int* P, const int* Q, km_dtype 
     km_status s = make_problem(M, N, P, Q, (int)dtype, pr);
     if (s != KM_OK) return s;
     if (pr.M == 0) return KM_OK;
-    Plan plan;
-    s = plan_for(pr, plan);
+    PlannedRef planned;
+    s = plan_for(M, N, P, Q, (int)dtype, planned);
     if (s != KM_OK) return s;
+    const Plan& plan = planned->plan;
     std::vector<const void*> none(pr.N, nullptr);
     for (const km_plan_step& st : plan.steps)
         if (launch_step(pr, st, nullptr, nullptr, none.data(), nullptr, true) != hipSuccess) return KM_ELAUNCH;
@@ -816,9 +846,10 @@ km_status kronmatmul_plan(int M, int N, const int* P, const int* Q, km_dtype dty
     if (s != KM_OK) return s;
     *nsteps = 0;
     if (pr.M == 0) return KM_OK;                 // nothing to launch
-    Plan plan;
-    s = plan_for(pr, plan);
+    PlannedRef planned;
+    s = plan_for(M, N, P, Q, (int)dtype, planned);
     if (s != KM_OK) return s;
+    const Plan& plan = planned->plan;
     *nsteps = (int)plan.steps.size();
     for (int i = 0; i < *nsteps && i < cap; ++i) steps[i] = plan.steps[i];
     return KM_OK;
@@ -841,9 +872,10 @@ km_status kronmatmul_cost(int M, int N, const int* P, const int* Q, km_dtype dty
         if (planned_bytes) *planned_bytes = 0;
         return KM_OK;
     }
-    Plan plan;
-    s = plan_for(pr, plan);
+    PlannedRef planned;
+    s = plan_for(M, N, P, Q, (int)dtype, planned);
     if (s != KM_OK) return s;
+    const Plan& plan = planned->plan;
     if (flops) *flops = plan.flops;
     if (planned_bytes) *planned_bytes = plan.bytes;
     return KM_OK;
