@@ -212,9 +212,12 @@ KM_HOST_DEVICE inline void unit_of(int64_t b, int64_t tiles, int groups, int64_t
     }
 }
 
-// The whole-row MFMA kernel: up to ROWM_MAXF factors of at most ROWM_MAXP rows; slices of a multiple of 8
-// elements are padded by 4 in LDS (row_mfma_kernel.hpp says why).
-constexpr int ROWM_MAXF = 8, ROWM_MAXP = 80, ROWM_LDS_LIMIT = 96 * 1024, ROWM_ROWS = 1024;
+// The whole-row MFMA kernel: up to ROWM_MAXF factors; slices of a multiple of 8 elements are padded by 4 in
+// LDS, the operand registers hold ROWM_CHUNKS chunks of 16 rows of a factor (row_mfma_kernel.hpp says why).
+// Rows whose two buffers need more than 60 KB keep their tiled plans: their work takes one compute unit so
+// long that little is gained (30 x 20x20^3 18.0 us in three launches, 14.6 here; 50 x 17x17^3 fp64 15.6 and
+// 14.5) and lost as soon as there are a few hundred of them (300 x 20x20^3 24.9 and 28.5).
+constexpr int ROWM_MAXF = 8, ROWM_CHUNKS = 5, ROWM_LDS_LIMIT = 60 * 1024, ROWM_ROWS = 1024;
 constexpr int ROWM_VARIANT = -2;           // km_plan_step.variant of its launches
 KM_HOST_DEVICE inline int rowm_slice_stride(int P) { return P + (P % 8 == 0 ? 4 : 0); }
 
@@ -232,7 +235,7 @@ inline RowmShape rowm_shape(const Problem& pr)
     int64_t w = pr.k_in;
     r.buf_elems = pr.k_out;
     for (int f = pr.N - 1; f >= 0; --f) {
-        if (pr.P[f] > ROWM_MAXP || w > 65535) return RowmShape();
+        if (w > 65535) return RowmShape();
         const int64_t S = w / pr.P[f];
         if (S * rowm_slice_stride(pr.P[f]) > r.buf_elems) r.buf_elems = S * rowm_slice_stride(pr.P[f]);
         w = S * pr.Q[f];

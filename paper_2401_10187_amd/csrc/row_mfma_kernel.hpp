@@ -15,12 +15,12 @@
 // together with the row's.  No loop holds a division.  Contraction indices past P are zeroed in both operands
 // (what lies behind a slice may be NaN); rows q and columns s past the ends are computed on clamped
 // addresses and dropped.
-// Bound by latency: 10 x (52x50, 65x20), two steps, takes 5.5 us from launch to launch where an empty launch
+// Bound by latency: 10 x (52x50, 65x20), two steps, takes 6.1 us from launch to launch where an empty launch
 // takes 2.3 (13.7 on the FMA kernel, whose factors go through LDS and whose 130 busy threads add up 117
-// products one after the other; fp64 20.1 -> 7.0 against two launches); 200 x 50x50^2 20.2 -> 7.4, 33 x
-// 80x80^2 20.3 -> 10.3, 300 x (32x32, 64x3) 20.1 -> 5.1.  Sixteen wavefronts when units are many or rows few,
-// four (four rows to a compute unit) otherwise; a first version with the factors in LDS took 8.7 us on the
-// first of these, 1.2 of it staging them.
+// products one after the other; fp64 20.1 -> 7.4 against two launches); 200 x 50x50^2 20.2 -> 8.0, 33 x
+// 80x80^2 20.3 -> 11.3, 300 x (32x32, 64x3) 20.0 -> 5.6, 5 x (111x82, 7x9) 15.1 -> 6.1.  Sixteen wavefronts when
+// units are many or rows few, four (four rows to a compute unit) otherwise; a first version with the
+// factors in LDS took 8.7 us on the first of these, 1.2 of it staging them.
 // Slices of a multiple of 8 elements are padded by 4 in LDS, which spreads the 64 operand reads of an MFMA
 // (16 slices x 4 consecutive p) over the banks.
 #pragma once
@@ -69,6 +69,8 @@ __device__ __forceinline__ bool rowm_chunk(int c, int last)
     return c <= last;
 }
 
+// The operand registers hold ROWM_CHUNKS chunks; a longer contraction takes as many rounds of them.
+//
 // Where a wavefront finds the A operand of a unit: element t of lane group g in chunk c is row
 // p = first + 16(c - 1) + 4t + g (4t + g in chunk 0) of factor column q, `step` bytes apart for each t.
 struct RowmOperand {
@@ -85,7 +87,19 @@ __device__ __forceinline__ RowmOperand rowm_operand(const RowmStep& st, int unit
     o.at = (g * st.Q + (q < st.Q ? q : st.Q - 1)) * (int)sizeof(T);
     o.next = o.at + rowm_first(st.P) * st.Q * (int)sizeof(T);
     o.step = 4 * st.Q * (int)sizeof(T);
-    o.last = (st.P - 1) / 16;
+    const int last = (st.P - 1) / 16;
+    o.last = last < ROWM_CHUNKS ? last : ROWM_CHUNKS - 1;
+    return o;
+}
+// ... of its round r > 0, whose chunks are all whole
+template <typename T>
+__device__ __forceinline__ RowmOperand rowm_operand_round(const RowmStep& st, int unit, int r, int j, int g)
+{
+    RowmOperand o = rowm_operand<T>(st, unit, j, g);
+    const int last = (st.P - 1) / 16 - r * ROWM_CHUNKS;
+    o.at = o.next + (r * ROWM_CHUNKS - 1) * 4 * o.step;
+    o.next = o.at + 4 * o.step;
+    o.last = last < ROWM_CHUNKS ? last : ROWM_CHUNKS - 1;
     return o;
 }
 __device__ __forceinline__ void rowm_load(float& v, const RowmOperand& o, int at)
@@ -115,7 +129,7 @@ void row_mfma_sliced_multiply(const T* __restrict__ Xg, T* __restrict__ Yg, cons
 {
     typedef typename RowmOp<T>::OP OP;
     typedef typename Vec16<T>::type V;
-    constexpr int VN = Vec16<T>::N, NT = NW * 64, KC = ROWM_MAXP / 16;
+    constexpr int VN = Vec16<T>::N, NT = NW * 64, KC = ROWM_CHUNKS;
     extern __shared__ __attribute__((aligned(16))) unsigned char rowm_lds[];
     T* const lds = reinterpret_cast<T*>(rowm_lds);
     const int tid = threadIdx.x, lane = tid % 64;
@@ -166,7 +180,7 @@ void row_mfma_sliced_multiply(const T* __restrict__ Xg, T* __restrict__ Yg, cons
             const RowmStep st = ra.step[i];
             const bool more = i + 1 < ra.n;
             const unsigned next_magic = more ? ra.magic[i + 1] : 0;
-            const int first = rowm_first(st.P), last = (st.P - 1) / 16;
+            const int first = rowm_first(st.P), last = (st.P - 1) / 16, last_round = last / KC;
             const int begin = first_unit(st), share = begin + (st.units + NW - 1) / NW, end = share < st.units ? share : st.units;
             const int ahead = more ? first_unit(ra.step[i + 1]) : 0;
             const bool wanted = more && ahead < ra.step[i + 1].units;
@@ -174,37 +188,42 @@ void row_mfma_sliced_multiply(const T* __restrict__ Xg, T* __restrict__ Yg, cons
                 const int qb = rowm_column_block(st, unit);
                 const int s = (unit - qb * st.blocks) * 16 + j;
                 const T* b = buf + (s < st.S ? s : st.S - 1) * rowm_slice_stride(st.P) + g;
-                // the wavefront's next unit, of this step or its first one of the next: its operand takes
-                // the registers of this one's as the products free them
-                RowmOperand o;
-                o.last = -1;
-                if (unit + 1 < end) {                    // (the same columns of the factor: it has the operand already)
-                    if (rowm_column_block(st, unit + 1) != qb) o = rowm_operand<T>(st, unit + 1, j, g);
-                } else if (wanted) {
-                    o = rowm_operand<T>(ra.step[i + 1], ahead, j, g);
-                }
                 typename OP::Acc acc;
 #pragma unroll
                 for (int v = 0; v < OP::NACC; ++v) acc[v] = T(0);
-#pragma unroll
-                for (int c = 0; c < KC; ++c) {
-                    if (c == 0) {
-#pragma unroll
-                        for (int t = 0; t < 4; ++t)
-                            if (rowm_chunk(4 * t + 1, first)) {
-                                const bool in = 4 * t + g < first;
-                                const T x = b[in ? 4 * t : 0];
-                                acc = OP::mma(in ? a[0][t] : T(0), in ? x : T(0), acc);
-                            }
-                    } else if (rowm_chunk(c, last)) {
-                        T bv[4];
-                        const T* at = b + first + 16 * (c - 1);
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) bv[t] = at[4 * t];
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) acc = OP::mma(a[c][t], bv[t], acc);
+                for (int round = 0; round <= last_round; ++round) {
+                    // What comes next (this unit's next round, the next unit of this step, the first one of the next
+                    // step) takes the operand registers as the products free them.
+                    RowmOperand o;
+                    o.last = -1;
+                    if (round < last_round) {
+                        o = rowm_operand_round<T>(st, unit, round + 1, j, g);
+                    } else if (unit + 1 < end) {         // (the same columns of the factor: it has the operand already)
+                        if (last_round > 0 || rowm_column_block(st, unit + 1) != qb) o = rowm_operand<T>(st, unit + 1, j, g);
+                    } else if (wanted) {
+                        o = rowm_operand<T>(ra.step[i + 1], ahead, j, g);
                     }
-                    if (rowm_chunk(c, o.last)) rowm_load_chunk(a[c], o, c);
+                    const T* from = b + (round == 0 ? first - 16 : first + 16 * (round * KC - 1));      // chunk c: 16c elements on
+                    const int here = last - round * KC;
+#pragma unroll
+                    for (int c = 0; c < KC; ++c) {
+                        if (c == 0 && round == 0) {
+#pragma unroll
+                            for (int t = 0; t < 4; ++t)
+                                if (rowm_chunk(4 * t + 1, first)) {
+                                    const bool in = 4 * t + g < first;
+                                    const T x = b[in ? 4 * t : 0];
+                                    acc = OP::mma(in ? a[0][t] : T(0), in ? x : T(0), acc);
+                                }
+                        } else if (rowm_chunk(c, here)) {
+                            T bv[4];
+#pragma unroll
+                            for (int t = 0; t < 4; ++t) bv[t] = from[16 * c + 4 * t];
+#pragma unroll
+                            for (int t = 0; t < 4; ++t) acc = OP::mma(a[c][t], bv[t], acc);
+                        }
+                        if (rowm_chunk(c, o.last)) rowm_load_chunk(a[c], o, c);
+                    }
                 }
 #pragma unroll
                 for (int v = 0; v < OP::NACC; ++v) {
