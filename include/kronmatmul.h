@@ -81,7 +81,8 @@ typedef struct {
     int block;             /* threads per workgroup                                                */
     int lds_bytes;         /* LDS per workgroup                                                    */
     int variant;           /* index of the compiled kernel instance, for reports (-1: the kernel has none;
-                              -2: KM_KERNEL_ROWS in its form for few rows, on the matrix cores)     */
+                              -2: KM_KERNEL_ROWS in its form for few rows, on the matrix cores;
+                              -3: KM_KERNEL_MFMA_ANY with the factor held in registers)             */
     int tiles_per_wg;      /* tiles one workgroup walks over (0: one tile per workgroup)           */
     int tile_order;        /* walk: 0 contiguous range, 1 interleaved pairs, 2 strided by the grid,
                               3 strided inside the XCD's eighth of the tiles                       */

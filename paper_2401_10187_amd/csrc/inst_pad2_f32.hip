@@ -1,0 +1,7 @@
+// Compiled instances: the MFMA kernel with run-time factor shapes and the factor in registers, fp32,
+// contractions of up to 32.
+#include "launch_pad.hpp"
+
+namespace km {
+template hipError_t launch_mfma_pad<float, 2>(const LaunchArgs&);
+}  // namespace km

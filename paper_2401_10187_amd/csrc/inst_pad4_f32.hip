@@ -1,0 +1,7 @@
+// Compiled instances: the MFMA kernel with run-time factor shapes and the factor in registers, fp32,
+// contractions of up to 64.
+#include "launch_pad.hpp"
+
+namespace km {
+template hipError_t launch_mfma_pad<float, 4>(const LaunchArgs&);
+}  // namespace km

@@ -298,6 +298,17 @@ static void cache_plan(const PlannedRef& planned, const Options& opt, bool tuned
     g_plan_cache.insert(g_plan_cache.begin(), CachedPlan{planned, opt, tuned});
 }
 
+template <typename T>
+static hipError_t launch_pad(const LaunchArgs& a)
+{
+    switch (pad_chunks(a.pr->P[a.st->first_factor])) {
+        case 2: return launch_mfma_pad<T, 2>(a);
+        case 4: return launch_mfma_pad<T, 4>(a);
+        case 6: return launch_mfma_pad<T, 6>(a);
+        default: return launch_mfma_pad<T, 8>(a);
+    }
+}
+
 static hipError_t launch_step(const Problem& pr, const km_plan_step& st, const void* src, void* dst,
                               const void* const* F, hipStream_t stream, bool prepare_only = false,
                               bool keep_output = false)
@@ -309,6 +320,8 @@ static hipError_t launch_step(const Problem& pr, const km_plan_step& st, const v
         return pr.dtype == KM_F32 ? launch_rows_mfma<float>(a) : launch_rows_mfma<double>(a);
     if (st.kernel == KM_KERNEL_ROWS)
         return pr.dtype == KM_F32 ? launch_rows<float>(a) : launch_rows<double>(a);
+    if (st.kernel == KM_KERNEL_MFMA_ANY && st.variant == PAD_VARIANT)
+        return pr.dtype == KM_F32 ? launch_pad<float>(a) : launch_pad<double>(a);
     if (st.kernel == KM_KERNEL_MFMA_ANY)
         return pr.dtype == KM_F32 ? launch_mfma_any<float>(a) : launch_mfma_any<double>(a);
     if (st.variant < 0 || st.variant >= g_num_variants) return hipErrorInvalidValue;

@@ -51,5 +51,6 @@ template <int P, int ST, int NW, int PD, int NPASS> hipError_t launch_mfma_pair(
 template <int P, int ST, int NW> hipError_t launch_mfma_pair_rows(const LaunchArgs& a);
 hipError_t launch_shuffle(const LaunchArgs& a);
 template <typename T> hipError_t launch_mfma_any(const LaunchArgs& a);
+template <typename T, int KC> hipError_t launch_mfma_pad(const LaunchArgs& a);      // KC: pad_chunks of the factor
 
 }  // namespace km

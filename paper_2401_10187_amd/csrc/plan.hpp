@@ -212,6 +212,58 @@ KM_HOST_DEVICE inline void unit_of(int64_t b, int64_t tiles, int groups, int64_t
     }
 }
 
+// The run-time-shape MFMA kernel that keeps the factor in registers (mfma_pad_kernel.hpp): factors of up to
+// PAD_MAXP rows and columns, compiled for contractions of 2, 4, 6 and 8 chunks of 16; pad_columns(Q) wavefronts
+// hold 16 columns each, pad_groups of such groups share the slices of a tile, pad_blocks blocks of 16 slices each.
+constexpr int PAD_MAXP = 128, PAD_LDS_LIMIT = 96 * 1024, PAD_VECTORS = 8;
+constexpr int PAD_VARIANT = -3;            // km_plan_step.variant of its launches
+KM_HOST_DEVICE constexpr int pad_chunks(int P) { return P <= 32 ? 2 : P <= 64 ? 4 : P <= 96 ? 6 : 8; }
+KM_HOST_DEVICE constexpr int pad_columns(int Q) { return (Q + 15) / 16; }
+KM_HOST_DEVICE constexpr int pad_groups(int columns) { return columns == 1 ? 4 : columns <= 3 ? 2 : 1; }
+KM_HOST_DEVICE constexpr int pad_blocks(size_t esize, int columns, int chunks) { return (chunks == 2 && columns > 1 ? 8 : 4) * 4 / (int)esize; }
+KM_HOST_DEVICE constexpr int pad_tile_slices(size_t esize, int columns, int chunks) { return 16 * pad_blocks(esize, columns, chunks) * pad_groups(columns); }
+// 16-byte vectors of a tile that one thread fetches, at most PAD_VECTORS
+KM_HOST_DEVICE constexpr int pad_vectors(size_t esize, int columns, int chunks)
+{
+    const int threads = 64 * columns * pad_groups(columns), vectors = pad_tile_slices(esize, columns, chunks) * chunks * (int)esize;
+    return (vectors + threads - 1) / threads < PAD_VECTORS ? (vectors + threads - 1) / threads : PAD_VECTORS;
+}
+// wavefronts per SIMD that registers are limited for
+KM_HOST_DEVICE constexpr int pad_waves(size_t esize, int columns, int chunks)
+{
+    return (chunks == 8 && (esize == 8 || columns <= 4)) || (chunks == 6 && columns <= 4) || (chunks == 2 && columns <= 2) ? 3 : 4;
+}
+// LDS row stride in elements: 4 times an odd number of floats or 2 times an odd number of doubles where slices
+// are whole 16-byte vectors; others stay as they lie in memory
+KM_HOST_DEVICE constexpr int pad_stride(int P, size_t esize)
+{
+    const int u = esize == 4 ? 4 : 2;
+    return P % u ? P : (P / u % 2 ? P : P + u);
+}
+// How the kernel would run a factor on `slices` slices (threads == 0: it cannot).
+struct PadShape {
+    int threads = 0, tile_slices = 0, lds_bytes = 0;
+    int64_t grid = 0;
+};
+inline PadShape pad_shape(int P, int Q, size_t esize, int64_t slices)
+{
+    PadShape r;
+    if (P < 2 || P > PAD_MAXP || Q > PAD_MAXP) return r;
+    const int c = pad_columns(Q), k = pad_chunks(P), threads = 64 * c * pad_groups(c);
+    r.tile_slices = pad_tile_slices(esize, c, k);
+    const int64_t lds = 2 * (int64_t)r.tile_slices * pad_stride(P, esize) * (int64_t)esize + 16;     // (16: a masked read past the last slice)
+    if ((int64_t)r.tile_slices * P * (int64_t)esize > (int64_t)pad_vectors(esize, c, k) * threads * 16 || lds > PAD_LDS_LIMIT) return PadShape();
+    r.threads = threads;
+    r.lds_bytes = (int)lds;
+    // one round of the workgroups the chip holds, each walking over its share; a multiple of 8 for the XCDs
+    const int64_t tiles = (slices + r.tile_slices - 1) / r.tile_slices;
+    int64_t per_cu = 160 * 1024 / lds;
+    if (per_cu > 4 * pad_waves(esize, c, k) * 64 / threads) per_cu = 4 * pad_waves(esize, c, k) * 64 / threads;
+    if (per_cu < 1) per_cu = 1;
+    r.grid = tiles < 256 * per_cu ? (tiles + 7) / 8 * 8 : 256 * per_cu;
+    return r;
+}
+
 // The whole-row MFMA kernel: up to ROWM_MAXF factors; slices of a multiple of 8 elements are padded by 4 in
 // LDS, the operand registers hold ROWM_CHUNKS chunks of 16 rows of a factor (row_mfma_kernel.hpp says why).
 // Rows whose two buffers need more than 60 KB keep their tiled plans: their work takes one compute unit so
@@ -690,6 +742,14 @@ inline km_plan_step build_step(const Problem& pr, const Options& opt, const Vari
         st.variant = -1;
         st.tile_rows = 1;
         st.tile_slices = any_unit_slices(gen, pr.P[f], pr.esize);
+        const PadShape pad = pad_shape(pr.P[f], pr.Q[f], pr.esize, pr.M * (st.k_in / pr.P[f]));
+        if (pad.threads > 0) {                           // the form with the factor in registers
+            st.variant = PAD_VARIANT;
+            st.block = pad.threads;
+            st.lds_bytes = pad.lds_bytes;
+            st.grid = pad.grid;
+            return st;
+        }
         st.block = gen.any_threads;
         st.lds_bytes = any_lds_bytes(gen, pr.P[f], pr.Q[f], pr.esize);
         const int64_t S = st.k_in / pr.P[f];
