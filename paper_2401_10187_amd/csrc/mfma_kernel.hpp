@@ -11,8 +11,13 @@
 // from LDS with 16-byte reads.  LDS rows (one slice each) are padded so that eight consecutive
 // lanes of such a read fall into different banks.
 //
+// With three factors on rows of 32^3 floats (128 KB, one workgroup to a compute unit) both memory and matrix
+// cores need 41-43 us for 1024 rows and the workgroups, in step with each other, use them mostly one after the
+// other: 81 us, matrix cores busy half the time.  What it took to get there, each in us: addresses kept out of the
+// registers (181 -> 94, spills), the next row fetched from the first stage on instead of the last (94 -> 86).
+//
 // A workgroup walks over `tiles_per_wg` consecutive tiles.  A tile is ST*P^NF contiguous elements of
-// one row; NF = 1 or 2 factors are applied with the intermediate kept in LDS (section 4.2) and the
+// one row; NF = 1 to 3 factors are applied with the intermediate kept in LDS (section 4.2) and the
 // result is scattered exactly as in the non-MFMA fused kernel.  The next tile is fetched from
 // global memory into registers while the current one is being multiplied.
 #pragma once
@@ -114,10 +119,24 @@ struct MfmaShape {
     static_assert(TK % (VN * NT) == 0, "tile must be a whole number of vectors per thread");
 };
 
+// factor pieces of this lane: A[i][k] = F[p][q] with q = column block + i, p = k group * PL + t
+template <class OP, int P, int Q, int NF, int ST, int NW, int QSPLIT>
+__device__ __forceinline__ void mfma_load_factor(const typename OP::T* __restrict__ F,
+                                                 typename OP::T (&a)[MfmaShape<OP, P, Q, NF, ST, NW, QSPLIT>::QTW][MfmaShape<OP, P, Q, NF, ST, NW, QSPLIT>::PL])
+{
+    typedef MfmaShape<OP, P, Q, NF, ST, NW, QSPLIT> Sh;
+    const int lane = threadIdx.x % 64, wq = threadIdx.x / 64 % QSPLIT;
+    const int ai = lane % OP::MB, ag = lane / OP::MB;
+#pragma unroll
+    for (int qt = 0; qt < Sh::QTW; ++qt)
+#pragma unroll
+        for (int t = 0; t < Sh::PL; ++t) a[qt][t] = F[(ag * Sh::PL + t) * Q + (wq * Sh::QTW + qt) * OP::MB + ai];
+}
+
 template <class OP, int P, int Q, int NF, int ST, int NW, int QSPLIT, int J, bool KEEP>
 __device__ __forceinline__ void mfma_stage(typename OP::T* __restrict__ tile,
                                            const typename OP::T (&a)[MfmaShape<OP, P, Q, NF, ST, NW, QSPLIT>::QTW][MfmaShape<OP, P, Q, NF, ST, NW, QSPLIT>::PL],
-                                           typename OP::T* __restrict__ Yrow, int64_t s_row, int64_t h)
+                                           typename OP::T* __restrict__ Yrow, int64_t s_row, int64_t h, int tid)
 {
     typedef MfmaShape<OP, P, Q, NF, ST, NW, QSPLIT> Sh;
     typedef typename OP::T T;
@@ -128,7 +147,7 @@ __device__ __forceinline__ void mfma_stage(typename OP::T* __restrict__ tile,
     constexpr int BPW = NBLK / SG;                     // ... per wave group
     static_assert(SJ % OP::NB == 0 && NBLK % SG == 0, "slice blocks must divide among the wave groups");
     constexpr bool LAST = J == NF - 1;
-    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+    const int lane = tid % 64, wave = tid / 64;
     const int j = lane % OP::NB, g = lane / OP::NB;
     const int wq = wave % QSPLIT, ws = wave / QSPLIT;
 
@@ -157,7 +176,7 @@ __device__ __forceinline__ void mfma_stage(typename OP::T* __restrict__ tile,
             // local (q, s), s = qrest*ST + r  ->  column (q*Q^(NF-1) + qrest)*s_row + h*ST + r
             constexpr int QREST = (int)ipow(Q, NF - 1);
             // (in-row offsets fit 32 bits: the planner only picks this kernel for rows below 2^31 bytes)
-            const int sr = (int)s_row;
+            const int sr = ST == 1 ? 1 : (int)s_row;       // (one slice per tile: whole rows only)
             if constexpr (JOIN) {
                 if (bi % 2 == 1) {
                     // blocks s0 - NB and s0 together: 2*NB consecutive slices per half wavefront
@@ -187,14 +206,20 @@ __device__ __forceinline__ void mfma_stage(typename OP::T* __restrict__ tile,
         __syncthreads();                               // the whole tile has been read
 #pragma unroll
         for (int bi = 0; bi < BPW; ++bi) {
-            const int s = (ws + bi * SG) * OP::NB + j;
+            const unsigned s = (ws + bi * SG) * OP::NB + j;
 #pragma unroll
             for (int qt = 0; qt < QTW; ++qt)
 #pragma unroll
                 for (int v = 0; v < OP::NACC; ++v) {
-                    const int q = (wq * QTW + qt) * OP::MB + OP::row_lane(lane) + OP::row_reg(v);
-                    const int c = q * SJ + s;          // position in the next stage's row of the tile
-                    tile[(c / P) * RS + (c % P)] = acc[bi][qt][v];
+                    const unsigned q = (wq * QTW + qt) * OP::MB + OP::row_lane(lane) + OP::row_reg(v);
+                    // position q * SJ + s in the next stage's row of the tile; SJ is whole slices wherever this
+                    // matters, so a lane's addresses are one base and constants
+                    if constexpr (SJ % P == 0) {
+                        tile[(q * (SJ / P) + s / P) * RS + s % P] = acc[bi][qt][v];
+                    } else {
+                        const int c = q * SJ + s;
+                        tile[(c / P) * RS + (c % P)] = acc[bi][qt][v];
+                    }
                 }
         }
         __syncthreads();
@@ -285,6 +310,7 @@ template <class OP, int P, int Q, int NF, int ST, int NW, int QSPLIT, bool KEEP>
 __global__ __launch_bounds__(NW * 64, (NW >= 16 ? 4 : 2))   // second bound: wavefronts per SIMD to fit
 void mfma_sliced_multiply(const typename OP::T* __restrict__ Xg, typename OP::T* __restrict__ Yg,
                           const typename OP::T* __restrict__ F0, const typename OP::T* __restrict__ F1,
+                          const typename OP::T* __restrict__ F2,
                           int64_t k_in, int64_t k_out, int64_t tiles_per_row, int64_t num_tiles,
                           int64_t tiles_per_wg, int tile_order)
 {
@@ -292,24 +318,15 @@ void mfma_sliced_multiply(const typename OP::T* __restrict__ Xg, typename OP::T*
     typedef typename OP::T T;
     typedef typename Vec16<T>::type V;
     constexpr int VN = Sh::VN, PL = Sh::PL, QTW = Sh::QTW, RS = Sh::RS, NT = Sh::NT, RV = Sh::RV;
+    static_assert(NF <= 3, "up to three factors");
     extern __shared__ __attribute__((aligned(16))) unsigned char mfma_lds[];
     T* tile = reinterpret_cast<T*>(mfma_lds);
 
     const int tid = threadIdx.x;
-    const int lane = tid % 64, wave = tid / 64;
-    const int wq = wave % QSPLIT;
-    const int ai = lane % OP::MB, ag = lane / OP::MB;
-
-    // factor pieces of this lane: A[i][k] = F[p][q] with q = column block + ai, p = ag*PL + t
-    T a0[QTW][PL], a1[NF > 1 ? QTW : 1][NF > 1 ? PL : 1];
-#pragma unroll
-    for (int qt = 0; qt < QTW; ++qt)
-#pragma unroll
-        for (int t = 0; t < PL; ++t) {
-            const int q = (wq * QTW + qt) * OP::MB + ai;
-            a0[qt][t] = F0[(ag * PL + t) * Q + q];
-            if constexpr (NF > 1) a1[qt][t] = F1[(ag * PL + t) * Q + q];
-        }
+    T a0[QTW][PL], a1[NF > 1 ? QTW : 1][NF > 1 ? PL : 1], a2[NF > 2 ? QTW : 1][NF > 2 ? PL : 1];
+    mfma_load_factor<OP, P, Q, NF, ST, NW, QSPLIT>(F0, a0);
+    if constexpr (NF > 1) mfma_load_factor<OP, P, Q, NF, ST, NW, QSPLIT>(F1, a1);
+    if constexpr (NF > 2) mfma_load_factor<OP, P, Q, NF, ST, NW, QSPLIT>(F2, a2);
 
     const int64_t s_row = tiles_per_row * ST;
     // Tiles of this workgroup: t_begin, t_begin + t_step, ... below t_end.
@@ -395,10 +412,13 @@ void mfma_sliced_multiply(const typename OP::T* __restrict__ Xg, typename OP::T*
         }
     } else {
         for (int64_t t = t_begin; t < t_end; t += t_step) {
+            int own = tid;
+            // (three factors: no registers to spare for addresses held over the tiles)
+            if constexpr (NF > 2) asm volatile("" : "+v"(own));
             // registers -> LDS rows of P elements with stride RS
 #pragma unroll
             for (int i = 0; i < RV; ++i) {
-                const int e = (tid + i * NT) * VN;
+                const int e = (own + i * NT) * VN;
                 *reinterpret_cast<V*>(tile + (e / P) * RS + (e % P)) = pf[i];
             }
             __syncthreads();
@@ -413,15 +433,20 @@ void mfma_sliced_multiply(const typename OP::T* __restrict__ Xg, typename OP::T*
 #pragma unroll
                     for (int i = 0; i < RV; ++i) pf[i] = stream_load(&src[tid + i * NT]);
                 }
-                mfma_stage<OP, P, Q, NF, ST, NW, QSPLIT, 0, KEEP>(tile, a0, Yrow, s_row, h);
+                mfma_stage<OP, P, Q, NF, ST, NW, QSPLIT, 0, KEEP>(tile, a0, Yrow, s_row, h, own);
             } else {
-                mfma_stage<OP, P, Q, NF, ST, NW, QSPLIT, 0, KEEP>(tile, a0, Yrow, s_row, h);
-                if (t + t_step < t_end) {
-                    const V* src = tile_ptr(t + t_step);
+                auto ahead = [&]() {
+                    if (t + t_step < t_end) {
+                        const V* src = tile_ptr(t + t_step);
 #pragma unroll
-                    for (int i = 0; i < RV; ++i) pf[i] = stream_load(&src[tid + i * NT]);
-                }
-                mfma_stage<OP, P, Q, NF, ST, NW, QSPLIT, 1, KEEP>(tile, a1, Yrow, s_row, h);
+                        for (int i = 0; i < RV; ++i) pf[i] = stream_load(&src[own + i * NT]);
+                    }
+                };
+                if constexpr (NF > 2) ahead();
+                mfma_stage<OP, P, Q, NF, ST, NW, QSPLIT, 0, KEEP>(tile, a0, Yrow, s_row, h, own);
+                if constexpr (NF == 2) ahead();
+                mfma_stage<OP, P, Q, NF, ST, NW, QSPLIT, 1, KEEP>(tile, a1, Yrow, s_row, h, own);
+                if constexpr (NF > 2) mfma_stage<OP, P, Q, NF, ST, NW, QSPLIT, 2, KEEP>(tile, a2, Yrow, s_row, h, own);
             }
             __syncthreads();                           // tile fully consumed before it is overwritten
         }

@@ -521,6 +521,12 @@ inline Choice find_variant(const Variant* table, int count, const Problem& pr, i
         if (c.rows_per_tile > 1 && s_row != c.tile_slices) continue;      // tiles of several rows hold whole rows
         if (c.min_tiles > 0 && !c.flexible && pr.M * (s_row / c.tile_slices) < c.min_tiles && opt.prefer_instance != v + 1)
             continue;                                     // too few tiles for this instance (unless it is asked for)
+        // A whole row that takes more than 64 KB of LDS has a compute unit to itself: only where the last round of
+        // 256 rows is nearly full (300 x 128x128^2 0.038 ms, two tiled launches 0.034, 520 rows 0.060 and 0.052; 700
+        // rows 0.058 and 0.060, 1000 rows 0.076 and 0.084; 32x32^3: 100 rows 0.020 and 0.017, 240 rows 0.024 and 0.032)
+        if (c.max_srow == 1 && !c.flexible && c.lds_bytes > 64 * 1024 && opt.prefer_instance != v + 1 &&
+            (pr.M + 255) / 256 * 256 * 10 > pr.M * 13)
+            continue;
         // slices per tile: fixed, or the best divisor of s_row up to the instance's limit
         int cand[3] = {0, 0, 0};
         int rows = c.rows_per_tile;
@@ -728,6 +734,14 @@ inline km_plan_step build_step(const Problem& pr, const Options& opt, const Vari
             const int64_t num_tiles = st.grid;
             st.tiles_per_wg = (int)tpw;
             st.grid = (num_tiles + tpw - 1) / tpw;
+            // Whole rows: every compute unit, also where the rows are no multiple of them.  (As many workgroups as give
+            // each the same walk leave some compute units out, and cost more than those: 1000 x 32x32^3 in 250 workgroups
+            // 0.108 ms, in 256 0.081; 4000 rows 0.496 and 0.296.)
+            if (var->walk == -1 && var->max_srow == 1 && hint <= 0 && tpw > 1) {
+                st.grid = 256 * resident_per_cu(*var);
+                while (st.grid > num_tiles) st.grid /= 2;
+                st.tiles_per_wg = (int)((num_tiles + st.grid - 1) / st.grid);
+            }
             st.tile_order = ch.tile_order >= 0 ? ch.tile_order : (opt.tile_order >= 0 ? opt.tile_order : (var->xcd_order ? 3 : 2));
             // output runs shorter than a 128-byte line: neighbouring tiles go to a pair of workgroups
             // that run side by side (order 1), when the tiles split evenly that way
@@ -884,7 +898,9 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
             Choice ch = find_variant(table, count, pr, r - 1, nf, width[r], opt);
             if (nf > 1 && !ch.var) continue;             // only single factors fall back to the kernels without compiled shapes
             if (!ch.var) ch.any_mfma = any_mfma_fits(pr, r - 1, opt);
-            const double c = launch_cost(pr, width[r], width[r - nf], ch, pr.P[r - 1]) + best[r - nf];
+            double c = launch_cost(pr, width[r], width[r - nf], ch, pr.P[r - 1]);
+            if (opt.prefer_instance > 0 && opt.prefer_instance <= count && ch.var == &table[opt.prefer_instance - 1]) c *= 0.5;      // (asked for: the grouping should let it in)
+            c += best[r - nf];
             if (best[r] < 0 || c <= best[r] * (1 + 1e-9)) { best[r] = c; take[r] = nf; pick[r] = ch; }
         }
     }

@@ -1,0 +1,46 @@
+"""The MFMA instances whose tile is a whole row (tile_slices 1): every factor of a short row in one launch."""
+import numpy as np
+import pytest
+
+import kron_inputs
+import paper_2401_10187_amd as km
+
+# (dtype, rows, P, N): fewer rows than compute units, more than one round of workgroups, no multiple of them
+CASES = [("float32", 5, 64, 2), ("float32", 1367, 64, 2), ("float32", 256, 32, 3), ("float32", 700, 32, 3),
+         ("float32", 230, 128, 2), ("float32", 700, 128, 2), ("float64", 4, 16, 3), ("float64", 2101, 16, 3),
+         ("float64", 3, 32, 2), ("float64", 4099, 32, 2)]
+
+
+def _plan(dtype, M, P, N):
+    return km.plan(M, [P] * N, [P] * N, dtype)
+
+
+def test_one_launch_without_workspace_that_reaches_every_row():
+    for dtype, M, P, N in CASES:
+        (st,) = _plan(dtype, M, P, N)
+        assert st["kernel"] == km.KM_KERNEL_MFMA and st["num_factors"] == N and st["tile_slices"] == 1
+        assert st["grid"] <= M <= st["grid"] * st["tiles_per_wg"]
+        assert km.workspace_size(M, [P] * N, [P] * N, dtype) == 0
+    # a row that fills a compute unit's LDS: not where the last round of 256 workgroups would be mostly idle
+    for M in (100, 300, 520):
+        assert len(_plan("float32", M, 128, 2)) == 2
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,M,P,N", CASES, ids=str)
+def test_matches_the_reference(dtype, M, P, N):
+    """1e-5 (fp32), 1e-12 (fp64) of the largest value (sums of P terms per factor: at most (P + 1) N u of the
+    product of absolute values), and bit for bit on small integers."""
+    import oracle
+    torch = pytest.importorskip("torch")
+    tol = 1e-5 if dtype == "float32" else 1e-12
+    for kinds, exact in ((dict(x="uniform", f="normal"), False), (dict(x="int2", f="int1"), True)):
+        X, Fs = kron_inputs.make_problem(M, [(P, P)] * N, dtype, seed=65, **kinds)
+        print("mfma_rows %s M=%d %d^%d" % (dtype, M, P, N), flush=True)
+        Y = km.kronmatmul(torch.from_numpy(X).cuda(), [torch.from_numpy(F).cuda() for F in Fs])
+        torch.cuda.synchronize()
+        ref, got = oracle.kron_matmul(X, Fs), Y.cpu().numpy()
+        if exact:
+            assert np.array_equal(got, ref)
+        else:
+            assert np.abs(got - ref).max() <= tol * np.abs(ref).max()
