@@ -5,7 +5,8 @@
 // Fused FMA instances: X(type, dtype code, P, Q, factors per launch, tile_slices, threads).
 // Register-resident MFMA pairs: Z(P, tile_slices, wavefronts, units fetched ahead, output passes) (fp32, Q = 32, two factors).
 // Small-factor instances with several factors per LDS pass and a run-time tile length:
-// W(type, dtype code, P, Q, G0, G1, G2, largest tile_slices, threads).
+// W(type, dtype code, P, Q, G0, G1, G2, largest tile_slices, threads); a row that differs from the one before it
+// in its threads only is taken for tiles that give all of them work (larger_workgroup in plan.hpp).
 // The same with a fourth super-stage (whole rows of P^4 elements in one launch):
 // U(type, dtype code, P, Q, G0, G1, G2, G3, largest tile_slices, threads).
 // The same for rows of exactly P*P elements, ST rows per tile: R(P, rows per tile, wavefronts).
@@ -125,13 +126,16 @@
     W(float, KM_F32, 4, 4, 2, 0, 0, 1024, 256)          \
     W(float, KM_F32, 4, 4, 1, 0, 0, 4096, 256)          \
     W(float, KM_F32, 3, 3, 3, 2, 2, 9, 256)             \
+    W(float, KM_F32, 3, 3, 3, 2, 2, 9, 768)             \
     W(float, KM_F32, 3, 3, 2, 2, 2, 27, 256)            \
+    W(float, KM_F32, 3, 3, 2, 2, 2, 27, 768)            \
     W(float, KM_F32, 3, 3, 2, 2, 1, 81, 256)            \
     W(float, KM_F32, 3, 3, 2, 2, 0, 81, 256)            \
     W(float, KM_F32, 3, 3, 2, 1, 0, 243, 256)           \
     W(float, KM_F32, 3, 3, 2, 0, 0, 729, 256)           \
     W(float, KM_F32, 3, 3, 1, 0, 0, 2187, 256)          \
     W(float, KM_F32, 5, 5, 2, 2, 0, 25, 256)            \
+    W(float, KM_F32, 5, 5, 2, 2, 0, 25, 640)            \
     W(float, KM_F32, 5, 5, 2, 1, 0, 125, 256)           \
     W(float, KM_F32, 5, 5, 2, 0, 0, 625, 256)           \
     W(float, KM_F32, 5, 5, 1, 0, 0, 3125, 256)          \
@@ -162,6 +166,7 @@
     W(double, KM_F64, 8, 8, 1, 0, 0, 1024, 256)         \
     W(double, KM_F64, 3, 3, 3, 2, 2, 3, 256)            \
     W(double, KM_F64, 3, 3, 2, 2, 2, 9, 256)            \
+    W(double, KM_F64, 3, 3, 2, 2, 2, 9, 768)            \
     W(double, KM_F64, 3, 3, 2, 2, 1, 27, 256)           \
     W(double, KM_F64, 3, 3, 2, 2, 0, 81, 256)           \
     W(double, KM_F64, 3, 3, 2, 1, 0, 243, 256)          \

@@ -493,6 +493,27 @@ inline void enumerate_choices(const Variant* table, int count, const Problem& pr
     }
 }
 
+// Flexible instances whose full tile leaves room for only two workgroups on a compute unit are compiled with a
+// larger workgroup too, which is taken when the tile has work for 90 % of its threads (a thread takes
+// thread_elems elements at a time): 1000 x 5x5^8 (62 KB tiles) 2.03 ms with 256 threads, 1.61 with 640; 100 x
+// 3x3^12 0.290 -> 0.219 (768); fp64 1000 x 3x3^10 0.439 -> 0.417 (768).  Short
+// tiles keep the small one (rows of 3^7 use 81 threads), and so do instances with smaller full tiles, which share
+// a compute unit in threes and fours (7^6 0.519 ms with 256 threads, 0.743 with 512; 10^5, 6^7, 4^9 alike).
+inline Choice larger_workgroup(const Variant* table, int count, Choice ch, int64_t pg)
+{
+    if (!ch.var || !ch.var->flexible || ch.var->thread_elems <= 0) return ch;
+    const Variant& c = *ch.var;
+    const int64_t busy = (int64_t)ch.tile_slices * ch.tile_rows * pg / c.thread_elems;
+    for (int v = 0; v < count; ++v) {
+        const Variant& t = table[v];
+        if (t.kernel == c.kernel && t.dtype == c.dtype && t.P == c.P && t.Q == c.Q && t.num_factors == c.num_factors && t.flexible &&
+            t.tile_slices == c.tile_slices && t.lds_per_slice == c.lds_per_slice && t.thread_elems == c.thread_elems &&
+            t.max_srow == c.max_srow && c.mix[2] == 0 && t.mix[2] == 0 && t.threads > ch.var->threads && busy * 10 >= (int64_t)t.threads * 9)
+            ch.var = &t;
+    }
+    return ch;
+}
+
 // Picks the instance for factors [f - nf + 1, f] applied to rows of width k_cur (var == nullptr: none).
 // The table is in order of preference (fastest instance on a full machine first).  The first instance
 // that fits the shape and still gives the chip enough workgroups wins; failing that, the fitting
@@ -630,8 +651,8 @@ inline Choice find_variant(const Variant* table, int count, const Problem& pr, i
     // decent runs finish sooner (16 rows of 6^6: three launches of two factors in 1296 tiles 0.024 ms,
     // two of three factors in 144 tiles of 24 slices 0.013): when the cost estimate rates another
     // tile length of a fitting flexible instance a fifth cheaper than the rules' choice, that one is taken.
-    if (base.var && cheapest.var && cheapest_cost < 0.8 * launch_cost(pr, k_cur, k_out, base, 0)) return cheapest;
-    return base;
+    if (base.var && cheapest.var && cheapest_cost < 0.8 * launch_cost(pr, k_cur, k_out, base, 0)) return larger_workgroup(table, count, cheapest, pg);
+    return larger_workgroup(table, count, base, pg);
 }
 
 // Estimated cost of one launch in "bytes moved at full speed": rows read and written, scaled up for
