@@ -755,14 +755,6 @@ inline km_plan_step build_step(const Problem& pr, const Options& opt, const Vari
             const int64_t num_tiles = st.grid;
             st.tiles_per_wg = (int)tpw;
             st.grid = (num_tiles + tpw - 1) / tpw;
-            // Whole rows: every compute unit, also where the rows are no multiple of them.  (As many workgroups as give
-            // each the same walk leave some compute units out, and cost more than those: 1000 x 32x32^3 in 250 workgroups
-            // 0.108 ms, in 256 0.081; 4000 rows 0.496 and 0.296.)
-            if (var->walk == -1 && var->max_srow == 1 && hint <= 0 && tpw > 1) {
-                st.grid = 256 * resident_per_cu(*var);
-                while (st.grid > num_tiles) st.grid /= 2;
-                st.tiles_per_wg = (int)((num_tiles + st.grid - 1) / st.grid);
-            }
             st.tile_order = ch.tile_order >= 0 ? ch.tile_order : (opt.tile_order >= 0 ? opt.tile_order : (var->xcd_order ? 3 : 2));
             // output runs shorter than a 128-byte line: neighbouring tiles go to a pair of workgroups
             // that run side by side (order 1), when the tiles split evenly that way
@@ -771,6 +763,15 @@ inline km_plan_step build_step(const Problem& pr, const Options& opt, const Vari
                 st.tile_order = 1;
             if (st.tile_order == 1 && (var->persistent != 1 || !pair_order_fits(num_tiles, tpw))) st.tile_order = 0;
             if (st.tile_order == 3 && !xcd_order_fits(num_tiles, st.grid)) st.tile_order = 2;
+            // Whole rows: every compute unit, also where the rows are no multiple of them.  (As many workgroups as give
+            // each the same walk leave some compute units out, and cost more than those: 1000 x 32x32^3 in 250 workgroups
+            // 0.108 ms, in 256 0.081; 4000 rows 0.496 and 0.296.  Tiles strided by the grid only: in the other
+            // orders a workgroup's tiles are a run of tiles_per_wg, so the grid is what that leaves.)
+            if (var->walk == -1 && var->max_srow == 1 && hint <= 0 && tpw > 1 && st.tile_order == 2) {
+                st.grid = 256 * resident_per_cu(*var);
+                while (st.grid > num_tiles) st.grid /= 2;
+                st.tiles_per_wg = (int)((num_tiles + st.grid - 1) / st.grid);
+            }
         }
     } else if (ch.any_mfma) {
         st.kernel = KM_KERNEL_MFMA_ANY;

@@ -3,7 +3,9 @@ import numpy as np
 import pytest
 
 import kron_inputs
-import paper_2401_10187_amd as km
+
+torch = pytest.importorskip("torch")          # before the library is loaded: both then use torch's HIP runtime
+import paper_2401_10187_amd as km  # noqa: E402
 
 # (dtype, rows, P, N): fewer rows than compute units, more than one round of workgroups, no multiple of them
 CASES = [("float32", 5, 64, 2), ("float32", 1367, 64, 2), ("float32", 256, 32, 3), ("float32", 700, 32, 3),
@@ -24,6 +26,46 @@ def test_one_launch_without_workspace_that_reaches_every_row():
     # a row that fills a compute unit's LDS: not where the last round of 256 workgroups would be mostly idle
     for M in (100, 300, 520):
         assert len(_plan("float32", M, 128, 2)) == 2
+
+
+# rows that are several rounds of workgroups, with a walk that leaves a remainder
+ORDERED = [("float32", 1000, 32, 3), ("float32", 4000, 32, 3), ("float32", 5000, 64, 2), ("float32", 700, 128, 2),
+           ("float64", 5000, 16, 3), ("float64", 20000, 32, 2)]
+
+
+@pytest.fixture
+def tile_order(request):
+    old = km.get_option(km.KM_OPT_TILE_ORDER)
+    km.set_option(km.KM_OPT_TILE_ORDER, request.param)
+    yield request.param
+    km.set_option(km.KM_OPT_TILE_ORDER, old)
+
+
+@pytest.mark.parametrize("tile_order", [0, 2, 3], indirect=True)
+def test_the_grid_fits_the_tile_order(tile_order):
+    """Contiguous ranges (order 0) and ranges inside an XCD's eighth (3) are dealt in runs of tiles_per_wg, so
+    the grid has to be the number of such runs; tiles strided by the grid (2) take any grid that reaches them all."""
+    for dtype, M, P, N in ORDERED:
+        (st,) = _plan(dtype, M, P, N)
+        grid, walk = st["grid"], st["tiles_per_wg"]
+        if st["tile_order"] == 2:
+            assert tile_order == 2 or M % 8 or -(-M // walk) % 8, (dtype, M, P, N)
+            assert grid <= M <= grid * walk
+        else:
+            assert st["tile_order"] == tile_order and grid == -(-M // walk), (dtype, M, P, N, grid, walk)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tile_order", [0, 2, 3], indirect=True)
+@pytest.mark.parametrize("dtype,M,P,N", ORDERED, ids=str)
+def test_every_tile_order_gives_the_same_bits(dtype, M, P, N, tile_order):
+    """The order deals out rows, it does not change one: results are those of the planner's own order, bit for bit."""
+    X, Fs = kron_inputs.make_problem(M, [(P, P)] * N, dtype, seed=67)
+    Xd, Fd = torch.from_numpy(X).cuda(), [torch.from_numpy(F).cuda() for F in Fs]
+    print("mfma_rows order %d %s M=%d %d^%d" % (tile_order, dtype, M, P, N), flush=True)
+    got = km.kronmatmul(Xd, Fd)
+    km.set_option(km.KM_OPT_TILE_ORDER, -1)
+    assert torch.equal(got, km.kronmatmul(Xd, Fd))
 
 
 @pytest.mark.gpu
