@@ -119,20 +119,6 @@ struct MfmaShape {
     static_assert(TK % (VN * NT) == 0, "tile must be a whole number of vectors per thread");
 };
 
-// factor pieces of this lane: A[i][k] = F[p][q] with q = column block + i, p = k group * PL + t
-template <class OP, int P, int Q, int NF, int ST, int NW, int QSPLIT>
-__device__ __forceinline__ void mfma_load_factor(const typename OP::T* __restrict__ F,
-                                                 typename OP::T (&a)[MfmaShape<OP, P, Q, NF, ST, NW, QSPLIT>::QTW][MfmaShape<OP, P, Q, NF, ST, NW, QSPLIT>::PL])
-{
-    typedef MfmaShape<OP, P, Q, NF, ST, NW, QSPLIT> Sh;
-    const int lane = threadIdx.x % 64, wq = threadIdx.x / 64 % QSPLIT;
-    const int ai = lane % OP::MB, ag = lane / OP::MB;
-#pragma unroll
-    for (int qt = 0; qt < Sh::QTW; ++qt)
-#pragma unroll
-        for (int t = 0; t < Sh::PL; ++t) a[qt][t] = F[(ag * Sh::PL + t) * Q + (wq * Sh::QTW + qt) * OP::MB + ai];
-}
-
 template <class OP, int P, int Q, int NF, int ST, int NW, int QSPLIT, int J, bool KEEP>
 __device__ __forceinline__ void mfma_stage(typename OP::T* __restrict__ tile,
                                            const typename OP::T (&a)[MfmaShape<OP, P, Q, NF, ST, NW, QSPLIT>::QTW][MfmaShape<OP, P, Q, NF, ST, NW, QSPLIT>::PL],
@@ -308,9 +294,8 @@ template <class OP, int P, int Q, int NF, int ST, int NW, int QSPLIT, bool KEEP>
 __global__ __launch_bounds__(NW * 64, (NW >= 16 ? 4 : 2))   // second bound: wavefronts per SIMD to fit
 void mfma_sliced_multiply(const typename OP::T* __restrict__ Xg, typename OP::T* __restrict__ Yg,
                           const typename OP::T* __restrict__ F0, const typename OP::T* __restrict__ F1,
-                          const typename OP::T* __restrict__ F2,
                           int64_t k_in, int64_t k_out, int64_t tiles_per_row, int64_t num_tiles,
-                          int64_t tiles_per_wg, int tile_order)
+                          int64_t tiles_per_wg, int tile_order, const typename OP::T* __restrict__ F2)
 {
     typedef MfmaShape<OP, P, Q, NF, ST, NW, QSPLIT> Sh;
     typedef typename OP::T T;
@@ -321,10 +306,23 @@ void mfma_sliced_multiply(const typename OP::T* __restrict__ Xg, typename OP::T*
     T* tile = reinterpret_cast<T*>(mfma_lds);
 
     const int tid = threadIdx.x;
+    const int lane = tid % 64, wave = tid / 64;
+    const int wq = wave % QSPLIT;
+    const int ai = lane % OP::MB, ag = lane / OP::MB;
+
+    // factor pieces of this lane: A[i][k] = F[p][q] with q = column block + ai, p = ag*PL + t
+    // (all factors in one loop: with a loop, and a function, for each the single-factor instances held the loads'
+    // addresses and took 4-6 % longer: 3 x 128x128^3 54.0 us, 51.6 this way; 1000 x 64x64^2 fp64 35.1, 33.2)
     T a0[QTW][PL], a1[NF > 1 ? QTW : 1][NF > 1 ? PL : 1], a2[NF > 2 ? QTW : 1][NF > 2 ? PL : 1];
-    mfma_load_factor<OP, P, Q, NF, ST, NW, QSPLIT>(F0, a0);
-    if constexpr (NF > 1) mfma_load_factor<OP, P, Q, NF, ST, NW, QSPLIT>(F1, a1);
-    if constexpr (NF > 2) mfma_load_factor<OP, P, Q, NF, ST, NW, QSPLIT>(F2, a2);
+#pragma unroll
+    for (int qt = 0; qt < QTW; ++qt)
+#pragma unroll
+        for (int t = 0; t < PL; ++t) {
+            const int q = (wq * QTW + qt) * OP::MB + ai;
+            a0[qt][t] = F0[(ag * PL + t) * Q + q];
+            if constexpr (NF > 1) a1[qt][t] = F1[(ag * PL + t) * Q + q];
+            if constexpr (NF > 2) a2[qt][t] = F2[(ag * PL + t) * Q + q];
+        }
 
     const int64_t s_row = tiles_per_row * ST;
     // Tiles of this workgroup: t_begin, t_begin + t_step, ... below t_end.
