@@ -628,26 +628,31 @@ struct TransposeArgs {
 // Workgroup (x, y) copies elements y * TRANSPOSE_SPAN ... of factor x, four per thread with their loads in
 // flight together: bound by the latency of one such trip.  One workgroup per factor walked through all its elements
 // a trip of 256 at a time (whole calls: 4 x 128x128^3 fp64 145 us, 135 now; 2 x 700x700 386, 52 now).
-constexpr int TRANSPOSE_SPAN = 1024;
-template <typename T>
-__global__ __launch_bounds__(256) void transpose_factors(TransposeArgs a)
+// The thread's first element costs a division, the others follow from it (a division each, of 64 bits, took 0.3 us
+// more on small factors).  I: an unsigned type that holds the element count of every factor.
+constexpr int TRANSPOSE_SPAN = 1024, TRANSPOSE_THREADS = 256;
+template <typename T, typename I>
+__global__ __launch_bounds__(TRANSPOSE_THREADS) void transpose_factors(TransposeArgs a)
 {
     const int f = blockIdx.x;
     const T* src = static_cast<const T*>(a.src[f]);
     T* dst = static_cast<T*>(a.dst[f]);
-    const int P = a.p[f], Q = a.q[f];
-    const int64_t n = (int64_t)P * Q;
-    for (int64_t e0 = (int64_t)blockIdx.y * TRANSPOSE_SPAN + threadIdx.x; e0 < n; e0 += (int64_t)gridDim.y * TRANSPOSE_SPAN) {
+    const unsigned P = (unsigned)a.p[f], Q = (unsigned)a.q[f];
+    const unsigned dp = TRANSPOSE_THREADS / Q, dq = TRANSPOSE_THREADS % Q;
+    const I n = (I)P * Q, step = (I)gridDim.y * TRANSPOSE_SPAN;
+    for (I e0 = (I)blockIdx.y * TRANSPOSE_SPAN + threadIdx.x; e0 < n; e0 += step) {
+        I pp = e0 / Q, qq = e0 - pp * Q;                      // element (pp, qq) of the P x Q result
         T v[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int64_t e = e0 + k * 256;
-            const int64_t pp = e / Q, qq = e - pp * Q;        // element (pp, qq) of the P x Q result
-            if (e < n) v[k] = src[qq * P + pp];
+            if (e0 + k * TRANSPOSE_THREADS < n) v[k] = src[qq * P + pp];
+            pp += dp;
+            qq += dq;
+            if (qq >= Q) { qq -= Q; ++pp; }
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            if (e0 + k * 256 < n) dst[e0 + k * 256] = v[k];
+            if (e0 + k * TRANSPOSE_THREADS < n) dst[e0 + k * TRANSPOSE_THREADS] = v[k];
     }
 }
 
@@ -752,10 +757,11 @@ static km_status execute(int M, int N, const int* P, const int* Q, const void* X
     for (int i = 0; i < pr.N; ++i) largest = (int64_t)pr.P[i] * pr.Q[i] > largest ? (int64_t)pr.P[i] * pr.Q[i] : largest;
     int64_t spans = (largest + TRANSPOSE_SPAN - 1) / TRANSPOSE_SPAN;
     if (spans > 1024) spans = 1024;                      // the kernel strides over what is left
-    if (pr.dtype == KM_F32)
-        hipLaunchKernelGGL(transpose_factors<float>, dim3(pr.N, (unsigned)spans), dim3(256), 0, (hipStream_t)stream, ta);
-    else
-        hipLaunchKernelGGL(transpose_factors<double>, dim3(pr.N, (unsigned)spans), dim3(256), 0, (hipStream_t)stream, ta);
+    // (32-bit element numbers wherever a step past the last element still fits them)
+    auto copy = largest < ((int64_t)1 << 31)
+                    ? (pr.dtype == KM_F32 ? transpose_factors<float, uint32_t> : transpose_factors<double, uint32_t>)
+                    : (pr.dtype == KM_F32 ? transpose_factors<float, uint64_t> : transpose_factors<double, uint64_t>);
+    hipLaunchKernelGGL(copy, dim3(pr.N, (unsigned)spans), dim3(TRANSPOSE_THREADS), 0, (hipStream_t)stream, ta);
     if (hipGetLastError() != hipSuccess) return KM_ELAUNCH;
     return run(pr, plan, X, fcopy, Y, ws, (hipStream_t)stream);
 }
