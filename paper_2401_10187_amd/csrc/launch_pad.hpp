@@ -16,7 +16,7 @@ static hipError_t launch_pad_shape(const LaunchArgs& a)
     if (e != hipSuccess || a.prepare_only) return e;
     const int64_t S = st.k_in / P, slices = a.pr->M * S;
     const PadShape sh = pad_shape(P, Q, sizeof(T), slices);
-    if (sh.threads == 0 || st.block != sh.threads || st.grid != sh.grid || st.lds_bytes != sh.lds_bytes) return hipErrorInvalidValue;
+    if (sh.threads == 0 || st.block != sh.threads || st.grid != sh.grid || st.lds_bytes != sh.lds_bytes || st.tile_slices != sh.tile_slices) return hipErrorInvalidValue;
     auto magic = [](int64_t d) { return (unsigned)(((1ull << 32) + (unsigned long long)d - 1) / (unsigned long long)d); };
     // (element numbers of a tile stay below 2^16, slice numbers below S + the tile's.  A row at least as long as a
     // tile is left at most once.)

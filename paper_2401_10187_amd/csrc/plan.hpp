@@ -781,6 +781,7 @@ inline km_plan_step build_step(const Problem& pr, const Options& opt, const Vari
         const PadShape pad = pad_shape(pr.P[f], pr.Q[f], pr.esize, pr.M * (st.k_in / pr.P[f]));
         if (pad.threads > 0) {                           // the form with the factor in registers
             st.variant = PAD_VARIANT;
+            st.tile_slices = pad.tile_slices;
             st.block = pad.threads;
             st.lds_bytes = pad.lds_bytes;
             st.grid = pad.grid;

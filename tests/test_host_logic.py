@@ -187,24 +187,31 @@ def test_tuning_options_round_trip():
 
 def test_padded_shapes_go_to_the_run_time_shape_mfma_kernel_within_its_padding_limits():
     """A padded product of at most 3x the real one, whatever the alignment of the slices; everything else
-    without a compiled instance stays with the generic kernel.  The narrow shape (slices of up to 128
-    bytes) takes 256 slices per unit, the wide one 128."""
+    without a compiled instance stays with the generic kernel.  Factors of up to 128 rows and columns whose
+    tiles fit take the form that holds the factor in registers (variant -3), tiles of 16 slices times the
+    blocks and groups of wavefronts it is compiled for; of the others, which are walked through LDS in chunks
+    (variant -1), the narrow shape (slices of up to 128 bytes) takes 256 slices per unit, the wide one 128."""
     def kernels(dtype, M, shapes):
-        return [(s["kernel"], s["tile_slices"]) for s in km.plan(M, [p for p, _ in shapes], [q for _, q in shapes], dtype)]
+        return [(s["kernel"], s["variant"], s["tile_slices"]) for s in km.plan(M, [p for p, _ in shapes], [q for _, q in shapes], dtype)]
     any_, gen = km.KM_KERNEL_MFMA_ANY, km.KM_KERNEL_GENERIC
-    assert kernels("float32", 4096, [(20, 20)] * 3) == [(any_, 256)] * 3          # 32*32 / 400 = 2.56
-    assert kernels("float32", 4096, [(36, 50)] * 3) == [(any_, 128)] * 3
-    assert kernels("float32", 4096, [(20, 15)] * 3) == [(any_, 256)] * 3          # Q need not be a whole vector
-    assert [k for k, _ in kernels("float32", 4096, [(20, 7)] * 4)] == [gen] * 4    # 32*16 / 140 = 3.7
-    assert kernels("float32", 4096, [(22, 22)] * 4) == [(any_, 256)] * 4          # slices not 16-byte aligned, but one chunk
-    assert kernels("float32", 1024, [(66, 66)] * 3) == [(any_, 128)] * 3          # ... or longer than a chunk (264 bytes)
-    assert kernels("float64", 4096, [(16, 20)] * 4) == [(any_, 256)] * 4          # 16*32 / 320 = 1.6, 128-byte slices
-    assert kernels("float64", 4096, [(26, 26)] * 3) == [(any_, 128)] * 3          # 32*32 / 676 = 1.5
-    assert kernels("float64", 4096, [(40, 40)] * 3) == [(any_, 128)] * 3          # 48*48 / 1600 = 1.44
-    assert kernels("float64", 4096, [(20, 20)] * 3) == [(any_, 128)] * 3          # 32*32 / 400 = 2.56
-    assert [k for k, _ in kernels("float64", 4096, [(6, 50)] * 3)] == [gen] * 3    # 16*64 / 300 = 3.4
-    assert kernels("float64", 4096, [(15, 16)] * 4) == [(any_, 256)] * 4          # odd P, 120-byte slices
-    assert kernels("float64", 4096, [(33, 33)] * 3) == [(any_, 128)] * 3          # odd P, 264-byte slices
+    assert kernels("float32", 4096, [(20, 20)] * 3) == [(any_, -3, 256)] * 3          # 32*32 / 400 = 2.56
+    assert kernels("float32", 4096, [(36, 50)] * 3) == [(any_, -3, 64)] * 3
+    assert kernels("float32", 4096, [(20, 15)] * 3) == [(any_, -3, 256)] * 3          # Q need not be a whole vector
+    assert [k for k, *_ in kernels("float32", 4096, [(20, 7)] * 4)] == [gen] * 4       # 32*16 / 140 = 3.7
+    assert kernels("float32", 4096, [(22, 22)] * 4) == [(any_, -3, 256)] * 4          # slices not 16-byte aligned, but one chunk
+    assert kernels("float32", 1024, [(66, 66)] * 3) == [(any_, -3, 64)] * 3           # ... or longer than a chunk (264 bytes)
+    assert kernels("float64", 4096, [(16, 20)] * 4) == [(any_, -3, 128)] * 4          # 16*32 / 320 = 1.6, 128-byte slices
+    assert kernels("float64", 4096, [(26, 26)] * 3) == [(any_, -3, 128)] * 3          # 32*32 / 676 = 1.5
+    assert kernels("float64", 4096, [(40, 40)] * 3) == [(any_, -3, 64)] * 3           # 48*48 / 1600 = 1.44
+    assert kernels("float64", 4096, [(20, 20)] * 3) == [(any_, -3, 128)] * 3          # 32*32 / 400 = 2.56
+    assert [k for k, *_ in kernels("float64", 4096, [(6, 50)] * 3)] == [gen] * 3       # 16*64 / 300 = 3.4
+    assert kernels("float64", 4096, [(15, 16)] * 4) == [(any_, -3, 128)] * 4          # odd P, 120-byte slices
+    assert kernels("float64", 4096, [(33, 33)] * 3) == [(any_, -3, 64)] * 3           # odd P, 264-byte slices
+    # more than 128 columns or rows, and tall factors whose tile would be too long: the chunked form
+    assert kernels("float32", 4096, [(20, 200)]) == kernels("float32", 4096, [(13, 160)]) == [(any_, -1, 256)]
+    assert kernels("float32", 4096, [(33, 200)]) == kernels("float32", 4096, [(144, 100)]) == [(any_, -1, 128)]
+    assert kernels("float64", 4096, [(13, 160)]) == [(any_, -1, 256)]
+    assert kernels("float64", 4096, [(25, 160)]) == kernels("float64", 4096, [(100, 20)]) == [(any_, -1, 128)]
 
 
 def test_neighbouring_runs_of_different_small_shapes_are_one_launch_where_an_instance_is_compiled():
