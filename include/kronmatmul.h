@@ -188,7 +188,8 @@ km_status kronmatmul_cost(int M, int N, const int* P, const int* Q, km_dtype dty
  * kernels measured faster).  KM_OPT_MAX_FUSE: upper limit on factors per launch (1 to 16, default 16).
  * KM_OPT_PROFILE: when 1, every launch is bracketed by HIP events on the caller's stream.
  * KM_OPT_PREFER_TILE / KM_OPT_PREFER_THREADS: tuning aids; when non-zero the planner prefers compiled
- * instances with that tile_slices / workgroup size where one fits the shape (0 = automatic).
+ * instances, and the form of KM_KERNEL_MFMA_ANY, with that tile_slices / workgroup size where one fits
+ * the shape (0 = automatic).
  * KM_OPT_TILES_PER_WG: tuning aid; consecutive tiles per workgroup of the MFMA kernels (0 = automatic).
  * KM_OPT_PAIR_INTERLEAVE: tuning aid (default 1); MFMA kernels whose output runs are shorter than a
  * cache line give alternate tiles to pairs of workgroups that share an XCD.

@@ -243,7 +243,7 @@ KM_HOST_DEVICE constexpr int pad_stride(int P, size_t esize)
 // How the kernel would run a factor on `slices` slices (threads == 0: it cannot).
 struct PadShape {
     int threads = 0, tile_slices = 0, lds_bytes = 0;
-    int64_t grid = 0;
+    int64_t grid = 0, per_cu = 0;          // per_cu: workgroups a compute unit holds at once
 };
 inline PadShape pad_shape(int P, int Q, size_t esize, int64_t slices)
 {
@@ -260,6 +260,7 @@ inline PadShape pad_shape(int P, int Q, size_t esize, int64_t slices)
     int64_t per_cu = 160 * 1024 / lds;
     if (per_cu > 4 * pad_waves(esize, c, k) * 64 / threads) per_cu = 4 * pad_waves(esize, c, k) * 64 / threads;
     if (per_cu < 1) per_cu = 1;
+    r.per_cu = per_cu;
     r.grid = tiles < 256 * per_cu ? (tiles + 7) / 8 * 8 : 256 * per_cu;
     return r;
 }
@@ -347,8 +348,61 @@ inline int any_lds_bytes(const GenericKernel& gen, int P, int Q, size_t esize)
     return (any_unit_slices(gen, P, esize) + 16 * any_column_blocks(Q)) * (row + 16);
 }
 
+// Tiles (or units) that keep a compute unit busy when `tiles` of them are dealt to workgroups of which it holds
+// per_cu at once: between whole rounds (a workgroup's last tile has nothing left to overlap with) and an even deal.
+inline double tiles_in_turn(int64_t tiles, int64_t per_cu)
+{
+    const int64_t grid = tiles < 256 * per_cu ? tiles : 256 * per_cu, side = (grid + 255) / 256;
+    const int64_t rounds = (tiles + grid - 1) / grid, left = tiles % grid;
+    return 0.7 * (double)(rounds * side) + 0.3 * (double)(tiles / grid * side + (left + 255) / 256);
+}
+
+// Does the form of the run-time-shape MFMA kernel that walks the factor through LDS in chunks beat the one that holds
+// it in registers (`pad`)?  Measured side by side on 900 pairs of equal factors, 1 to 60000 rows: the register form
+// is faster (mostly 1.05 to 3 times) in launches of up to 256 tiles, where slices are no whole 16-byte vectors (the other
+// one deals their elements to LDS one by one) and where its wavefronts, one per 16 columns, fill the four SIMDs
+// of a compute unit evenly.  What is left are, of long contractions, three, five or six column blocks, and
+// slices of up to 32 elements with one or two: there the chunked form, with units of twice the slices and one
+// workgroup more on a compute unit, needs fewer rounds for some row counts (654 x 80x80^2 fp64 57.8 us in registers,
+// 46.9 in chunks, 240 rows 29.0 and 27.8, 1028 rows 79.1 and 82.4; 1586 x 48x48^2 25.4 and 19.9, 2717 rows 30.4 and 38.1).
+// Both are estimated there, in nanoseconds fitted to those measurements (8 to 11 % off either way): a fixed part and,
+// per tile in turn, its bytes at 21 per nanosecond (a compute unit's share of 5.4 TB/s) and its products at the matrix
+// cores' rate.  The chunked form is taken where it promises 5 %: of the 45 among 1021 problems that
+// the register form made more than 3 % slower 24 are left, by 13 % at most but for one, and 4 become slower for it.
+inline bool chunked_form_wins(const GenericKernel& gen, int P, int Q, size_t esize, int64_t S, int64_t slices, const PadShape& pad)
+{
+    const int columns = pad_columns(Q);
+    const int64_t tiles = (slices + pad.tile_slices - 1) / pad.tile_slices;
+    // (rows of a single slice of 32 elements, which fill a chunk: 826 x (32x32) 7.49 us in registers, 7.24 in chunks,
+    // 48694 x (32x24) 9.60 and 9.12, fp64 687 x (32x16) 4.34 and 4.02; level at 28 and 36)
+    if (S == 1 && P == 32 && columns <= 2) return true;
+    if (tiles <= 256 || P * esize % 16 != 0) return false;
+    if (!(columns == 3 ? P > (esize == 4 ? 32 : 64) : P <= 32 ? columns < 3 : P > 64 && (columns == 5 || columns == 6))) return false;
+    const bool f32 = esize == 4;
+    const double mfma = (f32 ? 32.0 : 64.0) / 2.4;       // one 16x16x4 product on one SIMD
+    auto bytes = [&](int64_t n, int q) { return (double)n * (double)(P + q) * (double)esize / 21.0; };
+
+    const int waves = pad.threads / 64, k4 = (P + 3) / 4;
+    const double n = tiles_in_turn(tiles, pad.per_cu), b = n * bytes(pad.tile_slices, Q);
+    const double m = n * (double)(pad_blocks(esize, columns, pad_chunks(P)) * k4 * ((waves + 3) / 4)) * mfma;
+    const double in_registers = f32 ? 2600.0 + 0.83 * b + 0.80 * m + 2.4 * P : 1780.0 + 0.56 * b + 0.82 * m + 166.0 * n + 32.6 * P;
+
+    const int cb = any_column_blocks(Q), ts = any_unit_slices(gen, P, esize);
+    const int64_t units = (slices + ts - 1) / ts * ((Q + 16 * cb - 1) / (16 * cb));
+    int64_t per_cu = 160 * 1024 / any_lds_bytes(gen, P, Q, esize);
+    if (per_cu > 3) per_cu = 3;                          // (the registers it is compiled for)
+    if (per_cu > 2 && (cb >= 5 || (!f32 && cb >= 3 && any_narrow(gen, P, esize)))) per_cu = 2;
+    if (f32 && columns == 3 && units > 256 * per_cu) return false;       // (level or slower from its second round on)
+    const double un = tiles_in_turn(units, per_cu), ub = un * bytes(ts, Q < 16 * cb ? Q : 16 * cb);
+    const double um = (double)(ts / 16 * cb * ((P + 15) / 16 * 4)) * mfma / 4.0;
+    const double in_chunks = f32 ? 1930.0 + 0.48 * ub + (1.16 * un + 1.05) * um + 544.0 * un
+                                 : 2570.0 + 0.38 * ub + (0.95 * un + 0.57) * um + 650.0 * un;
+    return in_chunks < 0.95 * in_registers;
+}
+
 struct Choice {
     bool any_mfma = false;   // with var == nullptr: the run-time-shape MFMA kernel instead of the generic one
+    int any_form = 0;        // ... 0: the form that is estimated faster, PAD_VARIANT: factor in registers, -1: in chunks
     const Variant* var = nullptr;
     int tile_slices = 0;
     int64_t grid = 0;        // tiles (before the persistent-walk division)
@@ -778,8 +832,17 @@ inline km_plan_step build_step(const Problem& pr, const Options& opt, const Vari
         st.variant = -1;
         st.tile_rows = 1;
         st.tile_slices = any_unit_slices(gen, pr.P[f], pr.esize);
-        const PadShape pad = pad_shape(pr.P[f], pr.Q[f], pr.esize, pr.M * (st.k_in / pr.P[f]));
-        if (pad.threads > 0) {                           // the form with the factor in registers
+        const int64_t slices = pr.M * (st.k_in / pr.P[f]);
+        const PadShape pad = pad_shape(pr.P[f], pr.Q[f], pr.esize, slices);
+        bool chunked = pad.threads == 0 || ch.any_form == -1;
+        if (!chunked && ch.any_form == 0) {
+            // the tuning options prefer the form with that tile or workgroup, as they do among compiled instances (the
+            // chunked one where both have it: the other is what the planner mostly takes by itself)
+            auto wish = [&](int tile, int threads) { return (opt.prefer_tile == tile ? 2 : 0) + (opt.prefer_threads == threads ? 1 : 0); };
+            const int a = wish(pad.tile_slices, pad.threads), b = wish(st.tile_slices, gen.any_threads);
+            chunked = a + b > 0 ? b >= a : chunked_form_wins(gen, pr.P[f], pr.Q[f], pr.esize, st.k_in / pr.P[f], slices, pad);
+        }
+        if (!chunked) {                                  // the form with the factor in registers
             st.variant = PAD_VARIANT;
             st.tile_slices = pad.tile_slices;
             st.block = pad.threads;

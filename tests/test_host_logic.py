@@ -200,7 +200,7 @@ def test_padded_shapes_go_to_the_run_time_shape_mfma_kernel_within_its_padding_l
     assert [k for k, *_ in kernels("float32", 4096, [(20, 7)] * 4)] == [gen] * 4       # 32*16 / 140 = 3.7
     assert kernels("float32", 4096, [(22, 22)] * 4) == [(any_, -3, 256)] * 4          # slices not 16-byte aligned, but one chunk
     assert kernels("float32", 1024, [(66, 66)] * 3) == [(any_, -3, 64)] * 3           # ... or longer than a chunk (264 bytes)
-    assert kernels("float64", 4096, [(16, 20)] * 4) == [(any_, -3, 128)] * 4          # 16*32 / 320 = 1.6, 128-byte slices
+    assert kernels("float64", 64, [(16, 20)] * 4) == [(any_, -3, 128)] * 4          # 16*32 / 320 = 1.6, 128-byte slices
     assert kernels("float64", 4096, [(26, 26)] * 3) == [(any_, -3, 128)] * 3          # 32*32 / 676 = 1.5
     assert kernels("float64", 4096, [(40, 40)] * 3) == [(any_, -3, 64)] * 3           # 48*48 / 1600 = 1.44
     assert kernels("float64", 4096, [(20, 20)] * 3) == [(any_, -3, 128)] * 3          # 32*32 / 400 = 2.56
