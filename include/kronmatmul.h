@@ -199,7 +199,8 @@ km_status kronmatmul_cost(int M, int N, const int* P, const int* Q, km_dtype dty
  * and 3 to the compiled instance.
  * KM_OPT_PREFER_INSTANCE: tuning aid; k > 0 makes the planner take compiled instance k - 1 (the
  * `variant` of a plan step) wherever it fits the shape (0 = automatic); k = instance count + 1
- * makes it take the whole-row kernel (KM_KERNEL_ROWS) whenever the rows fit LDS.
+ * makes it take the whole-row kernel (KM_KERNEL_ROWS in its general form, variant -1) whenever the
+ * rows and factors fit LDS.
  * KM_OPT_INSTANCE_COUNT: read-only; the number of compiled instances.
  * KM_OPT_KEEP_MIB: tuning aid (default 320); a launch that is not a call's last and writes between 48
  * and this many MiB (four times as many for the KM_KERNEL_FUSED family) uses ordinary instead of

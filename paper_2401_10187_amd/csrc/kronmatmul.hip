@@ -566,22 +566,32 @@ static km_status tune(const Problem& pr, const Options& opt, hipStream_t stream,
 
     // Launches timed alone can rank differently than in sequence: keep the measured plan only if the
     // whole sequence beats the planner's own.
-    // A third candidate: the whole-row kernel wherever it fits, if the planner did not take it itself.
-    Plan rows;
-    bool have_rows = false;
-    if (deflt.steps.size() != 1 || deflt.steps[0].kernel != KM_KERNEL_ROWS) {
+    // Third and fourth candidates: the whole-row kernels wherever they fit, if the planner did not take them itself.
+    auto is_rows = [](const Plan& p, int variant) {
+        return p.steps.size() == 1 && p.steps[0].kernel == KM_KERNEL_ROWS && p.steps[0].variant == variant;
+    };
+    Plan rows, rows_mfma;
+    bool have_rows = false, have_rows_mfma = false;
+    if (!is_rows(deflt, -1)) {
         Options force = opt;
         force.prefer_instance = g_num_variants + 1;
         have_rows = make_plan(pr, force, g_variants, g_num_variants, generic_kernel(pr.dtype), rows) == KM_OK &&
-                    rows.steps.size() == 1 && rows.steps[0].kernel == KM_KERNEL_ROWS && launchable(rows.steps[0]);
+                    is_rows(rows, -1) && launchable(rows.steps[0]);
+    }
+    RowmShape rs;
+    if (!is_rows(deflt, ROWM_VARIANT) && rowm_fits(pr, opt, rs)) {
+        rows_mfma = deflt;                               // (for its flops)
+        take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, rows_mfma);
+        have_rows_mfma = true;
     }
     const size_t need_d = deflt.ws0_bytes + deflt.ws1_bytes, need_t = tuned.ws0_bytes + tuned.ws1_bytes;
     const size_t need = need_d > need_t ? need_d : need_t;
     if (need > 0 && hipMalloc(&sc.ws, need) != hipSuccess) { (void)hipGetLastError(); return KM_ENOMEM; }
-    const Plan* plans[3] = {&deflt, &tuned, have_rows ? &rows : nullptr};
-    float t[3] = {-1.f, -1.f, -1.f};
+    constexpr int PLANS = 4;
+    const Plan* plans[PLANS] = {&deflt, &tuned, have_rows ? &rows : nullptr, have_rows_mfma ? &rows_mfma : nullptr};
+    float t[PLANS] = {-1.f, -1.f, -1.f, -1.f};
     float quickest = -1.f;
-    for (int k = 0; k < 3; ++k) {
+    for (int k = 0; k < PLANS; ++k) {
         if (!plans[k]) continue;
         auto body = [&]() { return run(pr, *plans[k], sc.a, F.data(), sc.b, sc.ws, stream, false) == KM_OK; };
         t[k] = time_body(sc, stream, 1, body);
@@ -590,7 +600,7 @@ static km_status tune(const Problem& pr, const Options& opt, hipStream_t stream,
     }
     const int reps = reps_for(quickest);
     for (int round = 0; round < 2; ++round)
-        for (int k = 0; k < 3; ++k) {
+        for (int k = 0; k < PLANS; ++k) {
             if (!plans[k]) continue;
             auto body = [&]() { return run(pr, *plans[k], sc.a, F.data(), sc.b, sc.ws, stream, false) == KM_OK; };
             const float ms = time_body(sc, stream, reps, body);
@@ -600,7 +610,7 @@ static km_status tune(const Problem& pr, const Options& opt, hipStream_t stream,
     // The planner's own unless another is 1 % faster and needs no more workspace: a caller that sized
     // its workspace before tuning must not find it too small afterwards.
     int keep = 0;
-    for (int k = 1; k < 3; ++k)
+    for (int k = 1; k < PLANS; ++k)
         if (plans[k] && t[k] < 0.99f * t[0] && t[k] < t[keep] &&
             plans[k]->ws0_bytes + plans[k]->ws1_bytes <= need_d) keep = k;
     chosen = *plans[keep];

@@ -968,6 +968,14 @@ inline void take_rows_plan(const Problem& pr, int variant, int threads, int64_t 
     for (int i = 0; i < pr.N; ++i) plan.bytes += (double)pr.P[i] * pr.Q[i] * pr.esize;
 }
 
+// May the whole-row kernel on the matrix cores take the problem (with the shape it would run in)?
+inline bool rowm_fits(const Problem& pr, const Options& opt, RowmShape& rs)
+{
+    if (!(opt.kernels >> KM_KERNEL_ROWS & 1) || pr.N < 2 || pr.N > opt.max_fuse || pr.M > ROWM_ROWS) return false;
+    rs = rowm_shape(pr);
+    return rs.threads > 0;
+}
+
 inline km_status make_plan(const Problem& pr, const Options& opt, const Variant* table, int count,
                            const GenericKernel& gen, Plan& plan)
 {
@@ -999,7 +1007,7 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
     // fixed cost, plus 35 ns per multiply-add of each of its 256 threads, or 50 ns with the 1024
     // threads taken when rows are few (fp64: 1.5 times that); rows run side by side as far as LDS
     // and 2048 threads per compute unit allow.
-    const bool force_rows = opt.prefer_instance == count + 1;      // tuning aid: whenever it fits
+    const bool force_rows = opt.prefer_instance == count + 1;      // tuning aid: this kernel whenever it fits
     double rows_cost = -1;
     if ((opt.kernels >> KM_KERNEL_ROWS & 1) && N >= 2 && N <= gen.row_max_factors && N <= opt.max_fuse &&
         (plan.steps.size() > 1 || force_rows)) {
@@ -1051,8 +1059,8 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
     // x 50x50^2 20.2 and 7.4; 300 x (32x32, 64x3) on the FMA kernel 20.2 and 5.1).
     bool compiled = true;
     for (const km_plan_step& s1 : plan.steps) compiled = compiled && s1.variant >= 0;
-    if ((opt.kernels >> KM_KERNEL_ROWS & 1) && N >= 2 && N <= opt.max_fuse && pr.M <= ROWM_ROWS && !compiled) {
-        const RowmShape rs = rowm_shape(pr);
+    RowmShape rs;
+    if (!compiled && !(force_rows && rows_cost >= 0) && rowm_fits(pr, opt, rs)) {
         // what the plan at hand takes, a launch's 2.6 us (of the 5 that launch_cost charges) left out for one
         double had = 0;
         if (rows_cost >= 0) {
@@ -1079,7 +1087,7 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
             }
             had -= 2.6e-6;
         }
-        if (rs.threads > 0 && rs.seconds < had) take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, plan);
+        if (rs.seconds < had) take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, plan);
     }
     return KM_OK;
 }

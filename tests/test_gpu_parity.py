@@ -1098,6 +1098,7 @@ def test_whole_row_kernel_matches_the_oracle(dtype, M, shapes):
     with options(instance=km.get_option(km.KM_OPT_INSTANCE_COUNT) + 1):
         steps = km.plan(M, P, Q, dtype)
         assert len(steps) == 1 and steps[0]["kernel"] == km.KM_KERNEL_ROWS and steps[0]["num_factors"] == len(shapes)
+        assert steps[0]["variant"] == -1, "the general form, not the one on the matrix cores"
         assert km.workspace_size(M, P, Q, dtype) == 0
         X, Fs = kron_inputs.make_problem(M, shapes, dtype, seed=41)
         assert_close(run_gpu(X, Fs), X, Fs)

@@ -43,6 +43,21 @@ def test_planned_only_where_its_limits_hold():
     assert seen > 100
 
 
+def test_the_general_form_can_be_asked_for():
+    """The option that takes the whole-row kernel wherever it fits means the general form, also where the planner
+    would take this one."""
+    old = km.get_option(km.KM_OPT_PREFER_INSTANCE)
+    for dtype, M, shapes in (("float32", 10, [(52, 50), (65, 20)]), ("float64", 3, [(9, 1), (4, 6), (1, 5)]),
+                             ("float32", 33, [(32, 32), (64, 3)]), ("float32", 4, [(1, 1), (6, 6), (6, 6)])):
+        assert _plan(dtype, M, shapes)[0]["variant"] == ROW_MFMA
+        km.set_option(km.KM_OPT_PREFER_INSTANCE, km.get_option(km.KM_OPT_INSTANCE_COUNT) + 1)
+        try:
+            (st,) = _plan(dtype, M, shapes)
+            assert st["kernel"] == km.KM_KERNEL_ROWS and st["variant"] == -1
+        finally:
+            km.set_option(km.KM_OPT_PREFER_INSTANCE, old)
+
+
 CASES = [
     ("float32", 10, [(52, 50), (65, 20)]), ("float64", 10, [(52, 50), (65, 20)]),
     ("float32", 3, [(80, 80), (80, 80)]), ("float64", 2, [(40, 33), (79, 48)]),      # contractions of one round of the operand registers
