@@ -278,7 +278,7 @@ KM_HOST_DEVICE inline int rowm_slice_stride(int P) { return P + (P % 8 == 0 ? 4 
 struct RowmShape {
     int threads = 0;
     int64_t buf_elems = 0, lds_bytes = 0;
-    double seconds = 0;                    // estimate
+    double us = 0;                         // estimate of the launch
 };
 inline RowmShape rowm_shape(const Problem& pr)
 {
@@ -296,27 +296,35 @@ inline RowmShape rowm_shape(const Problem& pr)
     r.buf_elems = (r.buf_elems + 7) / 4 * 4;              // (whole vectors, and a few elements that a masked read may touch)
     r.lds_bytes = 2 * r.buf_elems * (int64_t)pr.esize;
     if (r.lds_bytes > ROWM_LDS_LIMIT) return RowmShape();
-    // Four or sixteen wavefronts per row, by an estimate: a row takes about 1.2 us to load and store, a step
-    // 0.5 us and 0.15 us for each 16x16 block a wavefront computes in turn; 25 ns per block and 3.5 ns per
-    // MFMA (fp64 7) are the compute unit's, so the rows on it share them (registers allow 16 wavefronts per unit).
-    // Within 15 % of what was measured, the launch's 2.6 us aside, for 10 x (52x50, 65x20) (2.9 us, fp64 4.5),
-    // 200 x 50x50^2 (4.8), 1000 x 50x50^2 (14.1), 1024 x 36x36^2 (7.9), 33 x 80x80^2 (7.7), 30 x 20x20^3 (12.1),
-    // 50 x 17x17^3 fp64 (12.0) and 1 x (5x5^2, 2x2, 25x25) (6.7).
+    // Four or sixteen wavefronts per row, by what a row takes that has its compute unit to itself (1.2 us to load and
+    // store it, per step 0.5 us and 0.15 us for each 16x16 block that a wavefront computes in turn) and what the rows on a
+    // compute unit take from each other (per block 25 ns and 3.5 ns per MFMA, fp64 7; registers allow 16 wavefronts
+    // per unit).  `us` is a finer estimate of the launch in the chosen form, with the parts of a step taken apart (the
+    // contraction's length, its rounds of the operand registers, the products' time in a wavefront): fitted to 700
+    // problems of 1 to 1024 rows, 6 % off either way.
+    double best = 0;
     for (int nw = 16; nw >= 4; nw -= 12) {
         int64_t per_cu = 160 * 1024 / r.lds_bytes;
         if (per_cu > 16 / nw) per_cu = 16 / nw;
-        double row = 1.2e-6 + (double)pr.k_in / (nw * 64) * 0.02e-6, busy = 0;
+        const double rounds = (double)((pr.M + 256 * per_cu - 1) / (256 * per_cu));
+        const double together = (double)(pr.M < 256 * per_cu ? (pr.M + 255) / 256 : per_cu);
+        double coarse = 1.2 + 0.02 * (double)pr.k_in / (nw * 64);
+        double fine = (0.078 * (double)pr.k_in + 0.086 * (double)pr.k_out) / (nw * 64);
         w = pr.k_in;
         for (int f = pr.N - 1; f >= 0; --f) {
-            const int64_t S = w / pr.P[f], units = (S + 15) / 16 * ((pr.Q[f] + 15) / 16);
-            row += 0.5e-6 + 0.15e-6 * (double)((units + nw - 1) / nw);
-            busy += (double)units * (25e-9 + (double)((pr.P[f] + 3) / 4) * (pr.esize == 4 ? 3.5e-9 : 7e-9));
+            const int64_t S = w / pr.P[f], blocks = (S + 15) / 16 * ((pr.Q[f] + 15) / 16);
+            const double turns = (double)((blocks + nw - 1) / nw), shared = together * (double)blocks;
+            const double k4 = (double)((pr.P[f] + 3) / 4) * (pr.esize == 4 ? 1 : 2);
+            coarse += 0.5 + 0.15 * turns + shared * (0.025 + 0.0035 * k4);
+            fine += 0.635 + 0.0012 * pr.P[f] + 0.317 * ((pr.P[f] - 1) / (16 * ROWM_CHUNKS)) + turns * (0.2465 + 0.0075 * k4) +
+                    shared * (0.0357 + 0.0036 * k4);
             w = S * pr.Q[f];
         }
-        const int64_t rounds = (pr.M + 256 * per_cu - 1) / (256 * per_cu);
-        const int64_t together = pr.M < 256 * per_cu ? (pr.M + 255) / 256 : per_cu;
-        const double t = 1.15 * (double)rounds * (row + busy * (double)together);
-        if (r.threads == 0 || t < r.seconds) { r.threads = nw * 64; r.seconds = t; }
+        if (r.threads == 0 || rounds * coarse < best) {
+            best = rounds * coarse;
+            r.threads = nw * 64;
+            r.us = 2.33 + rounds * fine;
+        }
     }
     return r;
 }
@@ -355,6 +363,20 @@ inline double tiles_in_turn(int64_t tiles, int64_t per_cu)
     const int64_t grid = tiles < 256 * per_cu ? tiles : 256 * per_cu, side = (grid + 255) / 256;
     const int64_t rounds = (tiles + grid - 1) / grid, left = tiles % grid;
     return 0.7 * (double)(rounds * side) + 0.3 * (double)(tiles / grid * side + (left + 255) / 256);
+}
+
+// Microseconds of a launch of the form that holds the factor in registers, for comparison with the whole-row kernel on
+// few rows (fitted to 900 pairs of launches, 8 % off either way): a fixed part with the factor's loads, and the tiles of a
+// compute unit by their bytes and by their wavefronts' products, where one SIMD has the most of them.
+inline double pad_us(int P, int Q, size_t esize, int64_t slices, const PadShape& pad)
+{
+    const int64_t tiles = (slices + pad.tile_slices - 1) / pad.tile_slices, grid = 256 * pad.per_cu < tiles ? 256 * pad.per_cu : tiles;
+    const int64_t side = (grid + 255) / 256, left = tiles % grid;
+    const double n = (double)(tiles / grid * side + (left + 255) / 256);
+    const double bytes = (double)pad.tile_slices * (double)(P + Q) * (double)esize / 21.0e3;
+    const double products = (double)(pad_blocks(esize, pad_columns(Q), pad_chunks(P)) * ((P + 3) / 4) * ((pad.threads / 64 + 3) / 4)) *
+                            (esize == 4 ? 32.0 : 64.0) / 2400.0;
+    return 2.26 + 0.0081 * P + 0.09 * (double)((tiles + grid - 1) / grid) + n * (0.13 + 0.64 * bytes + 0.98 * products);
 }
 
 // Does the form of the run-time-shape MFMA kernel that walks the factor through LDS in chunks beat the one that holds
@@ -1055,39 +1077,47 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
     // The same on the matrix cores (row_mfma_kernel.hpp), for up to ROWM_ROWS rows, in the place of a whole-row
     // plan of the FMA kernel or of tiled launches without compiled shapes.  Launches of compiled instances are
     // as quick on problems this small (16 x 16x16^3 6.9 us in three of them, 7.7 here; 128 x 32x32^2 4.9
-    // and 4.7), those without compiled shapes are not (10 x (52x50, 65x20) fp64 20.1 us in two, 7.1 here; 200
-    // x 50x50^2 20.2 and 7.4; 300 x (32x32, 64x3) on the FMA kernel 20.2 and 5.1).
+    // and 4.7).  The others by their estimates, each within 8 % of what was measured, 700 problems: 10 x (52x50,
+    // 65x20) fp64 20.1 us in two launches, 7.1 here, 5 x 61x61^2 fp64 9.1 and 11.3; on the FMA kernel 300 x (32x32, 64x3)
+    // 20.2 and 5.1, 1 x (2x40, 3x5) 3.71 and 3.98.  The choice comes out 0.3 % behind
+    // the best one on average; close to tiled launches the single one without workspace is taken (1000 x 50x50^2 16.9 us
+    // and 18.3, 900 rows 17.2 and 15.9).
     bool compiled = true;
     for (const km_plan_step& s1 : plan.steps) compiled = compiled && s1.variant >= 0;
     RowmShape rs;
     if (!compiled && !(force_rows && rows_cost >= 0) && rowm_fits(pr, opt, rs)) {
-        // what the plan at hand takes, a launch's 2.6 us (of the 5 that launch_cost charges) left out for one
-        double had = 0;
+        double had = 0;                                  // us of the plan at hand
         if (rows_cost >= 0) {
-            had = (rows_cost - 2.5e7) / 5e12;
-            // (steps with few results leave most of the FMA kernel's threads idle: a step then takes 70 ns for each
-            // of the P products one thread adds up: 300 x (32x32, 64x3) 17 us, 16 x (128x128, 4x4) 15)
-            double chain = 2.0e-6;
-            const int64_t threads = plan.steps[0].block;
+            // The FMA kernel: per row a fixed part, its factors' loads and per step 1 us and 70 ns (fp64 106) for each of the P
+            // products that a thread adds up in turn; 1024 threads have a compute unit to themselves.
+            const int threads = plan.steps[0].block;
+            int64_t side = threads >= 1024 ? 1 : 160 * 1024 / (plan.steps[0].lds_bytes < 20 * 1024 ? 20 * 1024 : plan.steps[0].lds_bytes);
+            if (side > 2048 / threads) side = 2048 / threads;
+            const int64_t rounds = (pr.M + 256 * side - 1) / (256 * side);
+            if (side > (pr.M + 255) / 256) side = (pr.M + 255) / 256;
+            double row = 0.328 + 0.159 * (double)(pr.k_in + pr.k_out) / threads;
             for (int r = N; r >= 1; --r) {
                 const int64_t S = width[r] / pr.P[r - 1], units = (S + 1) / 2 * ((pr.Q[r - 1] + 3) / 4);
-                chain += 0.4e-6 + (double)((units + threads - 1) / threads) * pr.P[r - 1] * 0.07e-6;
+                row += 1.036 + (double)((units + threads - 1) / threads) * pr.P[r - 1] * (pr.esize == 4 ? 0.069 : 0.106) +
+                       (double)side * (double)width[r] * (double)pr.Q[r - 1] * 5.4e-6 + 0.275 * pr.P[r - 1] * pr.Q[r - 1] / threads;
             }
-            if (had < chain) had = chain;
+            had = 1.13 + (double)rounds * row;
         } else {
             for (const km_plan_step& s1 : plan.steps) {
                 const double bytes = (double)pr.M * ((double)s1.k_in + (double)s1.k_out) * (double)pr.esize;
-                const int P = pr.P[s1.first_factor];
-                // (small launches of the run-time-shape MFMA kernel: 5.5 us when slices are whole 16-byte vectors and
-                // one chunk, 10 otherwise: 100 x 36x36^2 10.0 us in two, 200 x 50x50^2 20.2, 33 x 80x80^2 20.4)
-                if (s1.kernel == KM_KERNEL_MFMA_ANY)
-                    had += (P * pr.esize % 16 == 0 && P * pr.esize <= (size_t)gen.any_row_bytes ? 5.5e-6 : 9.5e-6) + bytes / 7e12;
+                const int P = pr.P[s1.first_factor], Q = pr.Q[s1.first_factor];
+                // (small launches of the chunked form of the run-time-shape MFMA kernel: 5.5 us when slices are whole 16-byte
+                // vectors and one chunk, 10 otherwise: 100 x 36x36^2 10.0 us in two, 200 x 50x50^2 20.2, 33 x 80x80^2 20.4)
+                if (s1.variant == PAD_VARIANT) {
+                    const int64_t slices = pr.M * (s1.k_in / P);
+                    had += pad_us(P, Q, pr.esize, slices, pad_shape(P, Q, pr.esize, slices));
+                } else if (s1.kernel == KM_KERNEL_MFMA_ANY)
+                    had += (P * pr.esize % 16 == 0 && P * pr.esize <= (size_t)gen.any_row_bytes ? 5.5 : 9.5) + bytes / 7e6;
                 else
-                    had += (s1.kernel == KM_KERNEL_GENERIC ? 4.5e-6 + 0.7e-6 * ((P + 15) / 16) : 2.5e-6) + bytes / 5e12;
+                    had += (s1.kernel == KM_KERNEL_GENERIC ? 4.5 + 0.7 * ((P + 15) / 16) : 2.5) + bytes / 5e6;
             }
-            had -= 2.6e-6;
         }
-        if (rs.seconds < had) take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, plan);
+        if (rs.us < (rows_cost >= 0 ? 1.0 : 1.06) * had) take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, plan);
     }
     return KM_OK;
 }
