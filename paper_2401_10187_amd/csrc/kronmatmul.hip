@@ -40,8 +40,7 @@ namespace km {
    1.08 -> 1.02, and costs on others: 200000 x 16x16^2 0.148 -> 0.181, 1024 x 64x64^2 fp64 0.038 -> 0.048) */
 #define KM_MFMA_ROW(OP, DT, P, Q, NF, ST, NW, QS) \
     {KM_KERNEL_MFMA, DT, P, Q, NF, ST, NW * 64, MfmaShape<OP, P, Q, NF, ST, NW, QS>::LDS_BYTES, 1, ST == 1 ? 2 : 1, 0, 1.0f, "mfma", \
-     0, 0, ST == 1 ? 1 : 0 /* whole rows only */, \
-     (ST == 1 && P == 16 && DT == KM_F64) ? 4 : 0 /* (3 rows of 16^3 doubles: two launches, with the intermediate that the test of the entry point without allocations wants) */, \
+     0, 0, ST == 1 ? 1 : 0 /* whole rows only */, 0, \
      (ST == 1 || P == 80 || P == 96 || P == 112 || P >= 144 || (P == 64 && Q == 64 && DT == KM_F32) || (P == 48 && DT == KM_F64)) ? -1 : 0 /* walk: one round of resident workgroups */},
 /* One workgroup per compute unit with the whole output tile staged at once (NPASS == 1): 7-12 % faster
    than two 4-wave workgroups where output rows lie up to 8 KB apart and every compute unit gets 8 tiles

@@ -9,7 +9,8 @@ import paper_2401_10187_amd as km  # noqa: E402
 
 # (dtype, rows, P, N): fewer rows than compute units, more than one round of workgroups, no multiple of them
 CASES = [("float32", 5, 64, 2), ("float32", 1367, 64, 2), ("float32", 256, 32, 3), ("float32", 700, 32, 3),
-         ("float32", 230, 128, 2), ("float32", 700, 128, 2), ("float64", 4, 16, 3), ("float64", 2101, 16, 3),
+         ("float32", 230, 128, 2), ("float32", 700, 128, 2), ("float64", 1, 16, 3), ("float64", 3, 16, 3),
+         ("float64", 4, 16, 3), ("float64", 2101, 16, 3),
          ("float64", 3, 32, 2), ("float64", 4099, 32, 2)]
 
 

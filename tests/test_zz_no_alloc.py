@@ -22,7 +22,7 @@ REL_TOL = {np.dtype("float32"): 1e-5, np.dtype("float64"): 1e-12}
 SEQUENCE = [
     ("float32", 16, [(8, 8)] * 5),          # 2 MiB of workspace
     ("float32", 3, [(8, 8)] * 5),           # 384 KiB (a smaller input than the first)
-    ("float64", 3, [(16, 16)] * 3),         # 96 KiB, other kernels
+    ("float64", 3, [(64, 64)] * 2),         # 96 KiB, other kernels
     ("float64", 2, [(70, 30), (110, 50)]),  # 55 KiB, generic kernel
 ]
 
