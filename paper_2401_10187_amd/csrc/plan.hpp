@@ -584,7 +584,8 @@ inline Choice larger_workgroup(const Variant* table, int count, Choice ch, int64
         const Variant& t = table[v];
         if (t.kernel == c.kernel && t.dtype == c.dtype && t.P == c.P && t.Q == c.Q && t.num_factors == c.num_factors && t.flexible &&
             t.tile_slices == c.tile_slices && t.lds_per_slice == c.lds_per_slice && t.thread_elems == c.thread_elems &&
-            t.max_srow == c.max_srow && c.mix[2] == 0 && t.mix[2] == 0 && t.threads > ch.var->threads && busy * 10 >= (int64_t)t.threads * 9)
+            t.max_srow == c.max_srow && c.mix[2] == 0 && t.mix[2] == 0 && t.threads > ch.var->threads && busy * 10 >= (int64_t)t.threads * 9 &&
+            (double)ch.grid * (double)t.threads < 4294967296.0)              // (a launch's limit of work-items)
             ch.var = &t;
     }
     return ch;

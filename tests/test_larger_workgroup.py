@@ -15,6 +15,13 @@ def test_long_tiles_take_the_larger_workgroup_and_short_ones_do_not():
         assert all(s["block"] == 256 for s in km.plan(M, [P] * N, [P] * N, dtype)), (dtype, P, N)
 
 
+def test_a_launch_that_only_the_small_workgroup_can_make_is_still_planned():
+    """A launch holds fewer than 2^32 work-items: 275114 x 5^8 is 6.9 million tiles, too many for 640 threads each."""
+    for dtype, M, P, N in (("float32", 275114, 5, 8), ("float32", 1400112, 5, 7)):
+        steps = km.plan(M, [P] * N, [P] * N, dtype)
+        assert all(s["grid"] * s["block"] < 2 ** 32 for s in steps), (M, P, N)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,M,P,N,threads", CASES, ids=str)
 def test_matches_the_reference(dtype, M, P, N, threads):
