@@ -308,7 +308,8 @@ def _marshal(X, Fs, Y, workspace, transposed=False):
     if K != kin:
         raise ValueError("X has %d columns, the factors need %d" % (K, kin))
     if Y is None:
-        Y = X.new_empty((M, kout))
+        # (new_empty is the quicker one; on a subclass of Tensor it would return that subclass)
+        Y = X.new_empty((M, kout)) if type(X) is torch.Tensor else torch.empty((M, kout), dtype=dtype, device=X.device)
     elif (Y.dtype != dtype or Y.get_device() != index or not Y.is_contiguous() or Y.shape != (M, kout)):
         raise ValueError("Y must be a contiguous CUDA tensor of shape (%d, %d)" % (M, kout))
     code = KM_F32 if dtype is torch.float32 else _dtype_code(dtype)
