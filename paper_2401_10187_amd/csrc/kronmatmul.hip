@@ -41,7 +41,9 @@ namespace km {
 #define KM_MFMA_ROW(OP, DT, P, Q, NF, ST, NW, QS) \
     {KM_KERNEL_MFMA, DT, P, Q, NF, ST, NW * 64, MfmaShape<OP, P, Q, NF, ST, NW, QS>::LDS_BYTES, 1, ST == 1 ? 2 : 1, 0, 1.0f, "mfma", \
      0, 0, ST == 1 ? 1 : 0 /* whole rows only */, 0, \
-     (ST == 1 || P == 80 || P == 96 || P == 112 || P >= 144 || (P == 64 && Q == 64 && DT == KM_F32) || (P == 48 && DT == KM_F64)) ? -1 : 0 /* walk: one round of resident workgroups */},
+     (ST == 1 || P == 80 || P == 96 || P == 112 || P >= 144 || (P == 64 && Q == 64 && DT == KM_F32) || (P == 48 && DT == KM_F64)) ? -1 : 0 /* walk: one round of resident workgroups */, \
+     0, 0, {0, 0, 0, 0, 0, 0, 0, 0, 0}, \
+     ST != 1 || DT != KM_F32 ? 0 : P == 64 ? 4 : P == 128 ? 3 : 0 /* (114 and 156 registers; the other whole-row instances are held to as many workgroups by LDS) */},
 /* One workgroup per compute unit with the whole output tile staged at once (NPASS == 1): 7-12 % faster
    than two 4-wave workgroups where output rows lie up to 8 KB apart and every compute unit gets 8 tiles
    and more (1024 x 32x32^4: 1.75 -> 1.54 ms per launch); 15 % slower on rows of 32^5 elements (128 KB

@@ -35,6 +35,7 @@ struct Variant {
     int lds_slack;     // flexible instances: LDS bytes a launch needs on top of lds_per_slice * tile_slices
     int mix[9];        // instances whose stages have their own factor shapes: (P, Q, factors) of up to three
                        // stages in order of application (P, Q above are the first stage's); all 0 otherwise
+    int simd_waves;    // > 0: wavefronts that the instance's registers leave room for on a SIMD
 };
 
 // Do factors [f - nf + 1, f] (applied from f downwards) have the shapes instance c is compiled for?
@@ -471,12 +472,14 @@ inline bool xcd_order_fits(int64_t num_tiles, int64_t grid)
     return num_tiles % 8 == 0 && grid % 8 == 0 && grid >= 8;
 }
 
-// Workgroups of an instance that one compute unit holds at once (160 KB of LDS, 2048 threads).
+// Workgroups of an instance that one compute unit holds at once (160 KB of LDS, 2048 threads, registers where the
+// table names their limit).
 inline int64_t resident_per_cu(const Variant& c)
 {
     int64_t by_lds = c.lds_bytes > 0 ? (160 * 1024) / c.lds_bytes : 8;
     int64_t by_threads = 2048 / (c.threads > 0 ? c.threads : 256);
     int64_t n = by_lds < by_threads ? by_lds : by_threads;
+    if (c.simd_waves > 0 && n > 4 * 64 * c.simd_waves / c.threads) n = 4 * 64 * c.simd_waves / c.threads;
     return n < 1 ? 1 : (n > 8 ? 8 : n);
 }
 
