@@ -145,7 +145,7 @@ static hipError_t launch_rows_mfma(const LaunchArgs& a)
     const RowmShape rs = rowm_shape(pr);
     const int n = st.num_factors;
     if (st.first_factor != 0 || n != pr.N || rs.threads == 0) return hipErrorInvalidValue;
-    if (st.grid < 1 || st.grid > pr.M || st.block != rs.threads || st.lds_bytes != rs.lds_bytes) return hipErrorInvalidValue;
+    if (st.grid != pr.M || st.block != rs.threads || st.lds_bytes != rs.lds_bytes) return hipErrorInvalidValue;
     auto kern = rs.threads == 1024 ? row_mfma_sliced_multiply<T, 16> : row_mfma_sliced_multiply<T, 4>;
     static unsigned char lds_ok[2][64];
     hipError_t e = allow_lds((const void*)kern, ROWM_LDS_LIMIT, lds_ok[rs.threads == 1024]);
@@ -170,7 +170,7 @@ static hipError_t launch_rows_mfma(const LaunchArgs& a)
     }
     if (w != st.k_out) return hipErrorInvalidValue;
     hipLaunchKernelGGL(kern, dim3((unsigned)st.grid), dim3((unsigned)st.block), (size_t)st.lds_bytes, a.stream,
-                       (const T*)a.src, (T*)a.dst, ra, (int)st.k_in, (int)st.k_out, pr.M);
+                       (const T*)a.src, (T*)a.dst, ra, (int)st.k_in, (int)st.k_out);
     return hipGetLastError();
 }
 

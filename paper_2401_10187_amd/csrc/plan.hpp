@@ -268,9 +268,9 @@ inline PadShape pad_shape(int P, int Q, size_t esize, int64_t slices)
 
 // The whole-row MFMA kernel: up to ROWM_MAXF factors; slices of a multiple of 8 elements are padded by 4 in
 // LDS, the operand registers hold ROWM_CHUNKS chunks of 16 rows of a factor (row_mfma_kernel.hpp says why).
-// Rows whose two buffers need more than 60 KB keep their tiled plans: their work takes one compute unit so
-// long that little is gained (30 x 20x20^3 18.0 us in three launches, 14.6 here; 50 x 17x17^3 fp64 15.6 and
-// 14.5) and lost as soon as there are a few hundred of them (300 x 20x20^3 24.9 and 28.5).
+// Rows whose two buffers need more than 60 KB keep their other plans: their work takes one compute unit so
+// long that nothing is gained (30 x 20x20^3 14.6 us in three launches and 14.6 here, 300 rows 21.2 and 28.5; 50 x 17x17^3
+// fp64 15.6 on the FMA kernel, 14.5 here).
 constexpr int ROWM_MAXF = 8, ROWM_CHUNKS = 5, ROWM_LDS_LIMIT = 60 * 1024, ROWM_ROWS = 1024;
 constexpr int ROWM_VARIANT = -2;           // km_plan_step.variant of its launches
 KM_HOST_DEVICE inline int rowm_slice_stride(int P) { return P + (P % 8 == 0 ? 4 : 0); }
@@ -324,7 +324,7 @@ inline RowmShape rowm_shape(const Problem& pr)
         if (r.threads == 0 || rounds * coarse < best) {
             best = rounds * coarse;
             r.threads = nw * 64;
-            r.us = 2.33 + rounds * fine;
+            r.us = 1.94 + rounds * fine;
         }
     }
     return r;
@@ -985,7 +985,7 @@ inline void take_rows_plan(const Problem& pr, int variant, int threads, int64_t 
     one.k_out = pr.k_out;
     one.src = KM_BUF_X;
     one.dst = KM_BUF_Y;
-    one.grid = pr.M < 65536 ? pr.M : 65536;              // the kernels stride over the rows
+    one.grid = pr.M < 65536 ? pr.M : 65536;              // (the FMA kernel strides over the rows, the other one has at most ROWM_ROWS)
     one.block = threads;
     one.lds_bytes = (int)lds_bytes;
     plan.steps.assign(1, one);
@@ -1081,11 +1081,10 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
     // The same on the matrix cores (row_mfma_kernel.hpp), for up to ROWM_ROWS rows, in the place of a whole-row
     // plan of the FMA kernel or of tiled launches without compiled shapes.  Launches of compiled instances are
     // as quick on problems this small (16 x 16x16^3 6.9 us in three of them, 7.7 here; 128 x 32x32^2 4.9
-    // and 4.7).  The others by their estimates, each within 8 % of what was measured, 700 problems: 10 x (52x50,
-    // 65x20) fp64 20.1 us in two launches, 7.1 here, 5 x 61x61^2 fp64 9.1 and 11.3; on the FMA kernel 300 x (32x32, 64x3)
-    // 20.2 and 5.1, 1 x (2x40, 3x5) 3.71 and 3.98.  The choice comes out 0.3 % behind
-    // the best one on average; close to tiled launches the single one without workspace is taken (1000 x 50x50^2 16.9 us
-    // and 18.3, 900 rows 17.2 and 15.9).
+    // and 4.7).  The others by their estimates, each within 8 % of what was measured on 700 problems: 10 x (52x50,
+    // 65x20) fp64 20.1 us in two launches, 7.0 here, 5 x 61x61^2 fp64 9.1 and 11.0; on the FMA kernel 300 x (32x32, 64x3)
+    // 19.9 and 5.0, 37 x (9x4, 15x14, 4x44) 8.5 and 10.4.  (Level with tiled launches the single one without workspace is
+    // taken: 1000 x 50x50^2 18.3 us and 16.8, 900 rows 15.9 and 16.6.)
     bool compiled = true;
     for (const km_plan_step& s1 : plan.steps) compiled = compiled && s1.variant >= 0;
     RowmShape rs;
@@ -1121,7 +1120,7 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
                     had += (s1.kernel == KM_KERNEL_GENERIC ? 4.5 + 0.7 * ((P + 15) / 16) : 2.5) + bytes / 5e6;
             }
         }
-        if (rs.us < (rows_cost >= 0 ? 1.0 : 1.06) * had) take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, plan);
+        if (rs.us < (rows_cost >= 0 ? 1.0 : 1.02) * had) take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, plan);
     }
     return KM_OK;
 }

@@ -1,7 +1,7 @@
 // Every factor of a Kron-Matmul applied to a short row inside one launch, on the matrix cores, for problems
 // of few rows, which are bound by latency: by how long one workgroup takes from its start to its end.
 //
-// As in row_kernel.hpp the whole row is the tile: a workgroup loads one row of X, applies factor N, N-1,
+// As in row_kernel.hpp the whole row is the tile, one workgroup per row: it loads the row of X, applies factor N, N-1,
 // ..., 1 by the rule of Algorithm 1 (slice s times column q goes to q*(K/P) + s) between two LDS buffers
 // and writes the row of Y; factor shapes are run-time values.  A step is the dense product
 // D[q][s] = sum_p F[p][q] * X[s*P + p] on the 16x16x4 MFMA of the element type: the factor is the A operand
@@ -15,12 +15,13 @@
 // together with the row's.  No loop holds a division.  Contraction indices past P are zeroed in both operands
 // (what lies behind a slice may be NaN); rows q and columns s past the ends are computed on clamped
 // addresses and dropped.
-// Bound by latency: 10 x (52x50, 65x20), two steps, takes 6.1 us from launch to launch where an empty launch
-// takes 2.3 (13.7 on the FMA kernel, whose factors go through LDS and whose 130 busy threads add up 117
-// products one after the other; fp64 20.1 -> 7.4 against two launches); 200 x 50x50^2 20.2 -> 8.0, 33 x
-// 80x80^2 20.3 -> 11.3, 300 x (32x32, 64x3) 20.0 -> 5.6, 5 x (111x82, 7x9) 15.1 -> 6.1.  Sixteen wavefronts when
-// units are many or rows few, four (four rows to a compute unit) otherwise; a first version with the
-// factors in LDS took 8.7 us on the first of these, 1.2 of it staging them.
+// Bound by latency: 10 x (52x50, 65x20), two steps, takes 5.6 us from launch to launch where an empty launch
+// takes 2.3 (13.6 on the FMA kernel, whose factors go through LDS and whose 130 busy threads add up 117
+// products one after the other; fp64 20.1 -> 7.0 against two launches); 200 x 50x50^2 20.0 -> 7.6 (9.3 in two launches
+// of the factor-in-register kernel), 33 x 80x80^2 20.2 -> 10.5, 300 x (32x32, 64x3) 19.9 -> 5.0, 5 x (111x82, 7x9)
+// 14.9 -> 5.4.  Sixteen wavefronts when units are many or rows few, four (four rows to a compute unit) otherwise; a
+// first version with the factors in LDS took 8.7 us on the first of these, 1.2 of it staging them, and a loop over
+// rows around all of it 0.4 us more on every problem, though it ran once.
 // Slices of a multiple of 8 elements are padded by 4 in LDS, which spreads the 64 operand reads of an MFMA
 // (16 slices x 4 consecutive p) over the banks.
 #pragma once
@@ -125,7 +126,7 @@ __device__ __forceinline__ void rowm_load_chunk(T (&a)[4], RowmOperand& o, int c
 template <typename T, int NW>
 __global__ __launch_bounds__(NW * 64, NW / 4)
 void row_mfma_sliced_multiply(const T* __restrict__ Xg, T* __restrict__ Yg, const RowmArgs ra,
-                              int k_in, int k_out, int64_t M)
+                              int k_in, int k_out)
 {
     typedef typename RowmOp<T>::OP OP;
     typedef typename Vec16<T>::type V;
@@ -135,119 +136,115 @@ void row_mfma_sliced_multiply(const T* __restrict__ Xg, T* __restrict__ Yg, cons
     const int tid = threadIdx.x, lane = tid % 64;
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
 
-    for (int64_t row = blockIdx.x; row < M; row += gridDim.x) {
-        int own = lane;
-        asm volatile("" : "+v"(own));                    // (keeps addresses from being held in registers over the rows)
-        const int j = own % 16, g = own / 16;
-        T a[KC][4];                                      // A operand of the wavefront's next unit
-        auto first_unit = [&](const RowmStep& st) { return wave * ((st.units + NW - 1) / NW); };
-        if (first_unit(ra.step[0]) < ra.step[0].units) {
-            RowmOperand o = rowm_operand<T>(ra.step[0], first_unit(ra.step[0]), j, g);
+    const int64_t row = blockIdx.x;
+    const int j = lane % 16, g = lane / 16;
+    T a[KC][4];                                      // A operand of the wavefront's next unit
+    auto first_unit = [&](const RowmStep& st) { return wave * ((st.units + NW - 1) / NW); };
+    if (first_unit(ra.step[0]) < ra.step[0].units) {
+        RowmOperand o = rowm_operand<T>(ra.step[0], first_unit(ra.step[0]), j, g);
+#pragma unroll
+        for (int c = 0; c < KC; ++c)
+            if (rowm_chunk(c, o.last)) rowm_load_chunk(a[c], o, c);
+    }
+    {
+        const T* src = Xg + row * k_in;
+        const unsigned magic = ra.magic[0];
+        if (k_in % VN == 0) {                        // (a padded slice is a multiple of 8 elements: a vector stays inside it)
+            for (int c0 = tid * VN; c0 < k_in; c0 += 4 * NT * VN) {
+                V v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (c0 + i * NT * VN < k_in) v[i] = stream_load(reinterpret_cast<const V*>(src + c0 + i * NT * VN));
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (c0 + i * NT * VN < k_in) *reinterpret_cast<V*>(lds + rowm_at(c0 + i * NT * VN, magic)) = v[i];
+            }
+        } else {
+            for (int c0 = tid; c0 < k_in; c0 += 4 * NT) {
+                T v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (c0 + i * NT < k_in) v[i] = src[c0 + i * NT];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (c0 + i * NT < k_in) lds[rowm_at(c0 + i * NT, magic)] = v[i];
+            }
+        }
+    }
+    __syncthreads();
+
+    T* buf = lds;
+    T* out = lds + ra.buf_elems;
+    for (int i = 0; i < ra.n; ++i) {
+        const RowmStep st = ra.step[i];
+        const bool more = i + 1 < ra.n;
+        const unsigned next_magic = more ? ra.magic[i + 1] : 0;
+        const int first = rowm_first(st.P), last = (st.P - 1) / 16, last_round = last / KC;
+        const int begin = first_unit(st), share = begin + (st.units + NW - 1) / NW, end = share < st.units ? share : st.units;
+        const int ahead = more ? first_unit(ra.step[i + 1]) : 0;
+        const bool wanted = more && ahead < ra.step[i + 1].units;
+        for (int unit = begin; unit < end; ++unit) {
+            const int qb = rowm_column_block(st, unit);
+            const int s = (unit - qb * st.blocks) * 16 + j;
+            const T* b = buf + (s < st.S ? s : st.S - 1) * rowm_slice_stride(st.P) + g;
+            typename OP::Acc acc;
+#pragma unroll
+            for (int v = 0; v < OP::NACC; ++v) acc[v] = T(0);
+            for (int round = 0; round <= last_round; ++round) {
+                // What comes next (this unit's next round, the next unit of this step, the first one of the next
+                // step) takes the operand registers as the products free them.
+                RowmOperand o;
+                o.last = -1;
+                if (round < last_round) {
+                    o = rowm_operand_round<T>(st, unit, round + 1, j, g);
+                } else if (unit + 1 < end) {         // (the same columns of the factor: it has the operand already)
+                    if (last_round > 0 || rowm_column_block(st, unit + 1) != qb) o = rowm_operand<T>(st, unit + 1, j, g);
+                } else if (wanted) {
+                    o = rowm_operand<T>(ra.step[i + 1], ahead, j, g);
+                }
+                const T* from = b + (round == 0 ? first - 16 : first + 16 * (round * KC - 1));      // chunk c: 16c elements on
+                const int here = last - round * KC;
+#pragma unroll
+                for (int c = 0; c < KC; ++c) {
+                    if (c == 0 && round == 0) {
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+                            if (rowm_chunk(4 * t + 1, first)) {
+                                const bool in = 4 * t + g < first;
+                                const T x = b[in ? 4 * t : 0];
+                                acc = OP::mma(in ? a[0][t] : T(0), in ? x : T(0), acc);
+                            }
+                    } else if (rowm_chunk(c, here)) {
+                        T bv[4];
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) bv[t] = from[16 * c + 4 * t];
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) acc = OP::mma(a[c][t], bv[t], acc);
+                    }
+                    if (rowm_chunk(c, o.last)) rowm_load_chunk(a[c], o, c);
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < OP::NACC; ++v) {
+                const int q = qb * 16 + OP::row_lane(lane) + OP::row_reg(v);
+                if (q < st.Q && s < st.S) out[rowm_at(q * st.S + s, next_magic)] = acc[v];
+            }
+        }
+        if (begin >= end && wanted) {                // idle in this step
+            RowmOperand o = rowm_operand<T>(ra.step[i + 1], ahead, j, g);
 #pragma unroll
             for (int c = 0; c < KC; ++c)
                 if (rowm_chunk(c, o.last)) rowm_load_chunk(a[c], o, c);
         }
-        {
-            const T* src = Xg + row * k_in;
-            const unsigned magic = ra.magic[0];
-            if (k_in % VN == 0) {                        // (a padded slice is a multiple of 8 elements: a vector stays inside it)
-                for (int c0 = tid * VN; c0 < k_in; c0 += 4 * NT * VN) {
-                    V v[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (c0 + i * NT * VN < k_in) v[i] = stream_load(reinterpret_cast<const V*>(src + c0 + i * NT * VN));
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (c0 + i * NT * VN < k_in) *reinterpret_cast<V*>(lds + rowm_at(c0 + i * NT * VN, magic)) = v[i];
-                }
-            } else {
-                for (int c0 = tid; c0 < k_in; c0 += 4 * NT) {
-                    T v[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (c0 + i * NT < k_in) v[i] = src[c0 + i * NT];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (c0 + i * NT < k_in) lds[rowm_at(c0 + i * NT, magic)] = v[i];
-                }
-            }
-        }
         __syncthreads();
+        T* other = buf; buf = out; out = other;
+    }
 
-        T* buf = lds;
-        T* out = lds + ra.buf_elems;
-        for (int i = 0; i < ra.n; ++i) {
-            const RowmStep st = ra.step[i];
-            const bool more = i + 1 < ra.n;
-            const unsigned next_magic = more ? ra.magic[i + 1] : 0;
-            const int first = rowm_first(st.P), last = (st.P - 1) / 16, last_round = last / KC;
-            const int begin = first_unit(st), share = begin + (st.units + NW - 1) / NW, end = share < st.units ? share : st.units;
-            const int ahead = more ? first_unit(ra.step[i + 1]) : 0;
-            const bool wanted = more && ahead < ra.step[i + 1].units;
-            for (int unit = begin; unit < end; ++unit) {
-                const int qb = rowm_column_block(st, unit);
-                const int s = (unit - qb * st.blocks) * 16 + j;
-                const T* b = buf + (s < st.S ? s : st.S - 1) * rowm_slice_stride(st.P) + g;
-                typename OP::Acc acc;
-#pragma unroll
-                for (int v = 0; v < OP::NACC; ++v) acc[v] = T(0);
-                for (int round = 0; round <= last_round; ++round) {
-                    // What comes next (this unit's next round, the next unit of this step, the first one of the next
-                    // step) takes the operand registers as the products free them.
-                    RowmOperand o;
-                    o.last = -1;
-                    if (round < last_round) {
-                        o = rowm_operand_round<T>(st, unit, round + 1, j, g);
-                    } else if (unit + 1 < end) {         // (the same columns of the factor: it has the operand already)
-                        if (last_round > 0 || rowm_column_block(st, unit + 1) != qb) o = rowm_operand<T>(st, unit + 1, j, g);
-                    } else if (wanted) {
-                        o = rowm_operand<T>(ra.step[i + 1], ahead, j, g);
-                    }
-                    const T* from = b + (round == 0 ? first - 16 : first + 16 * (round * KC - 1));      // chunk c: 16c elements on
-                    const int here = last - round * KC;
-#pragma unroll
-                    for (int c = 0; c < KC; ++c) {
-                        if (c == 0 && round == 0) {
-#pragma unroll
-                            for (int t = 0; t < 4; ++t)
-                                if (rowm_chunk(4 * t + 1, first)) {
-                                    const bool in = 4 * t + g < first;
-                                    const T x = b[in ? 4 * t : 0];
-                                    acc = OP::mma(in ? a[0][t] : T(0), in ? x : T(0), acc);
-                                }
-                        } else if (rowm_chunk(c, here)) {
-                            T bv[4];
-#pragma unroll
-                            for (int t = 0; t < 4; ++t) bv[t] = from[16 * c + 4 * t];
-#pragma unroll
-                            for (int t = 0; t < 4; ++t) acc = OP::mma(a[c][t], bv[t], acc);
-                        }
-                        if (rowm_chunk(c, o.last)) rowm_load_chunk(a[c], o, c);
-                    }
-                }
-#pragma unroll
-                for (int v = 0; v < OP::NACC; ++v) {
-                    const int q = qb * 16 + OP::row_lane(lane) + OP::row_reg(v);
-                    if (q < st.Q && s < st.S) out[rowm_at(q * st.S + s, next_magic)] = acc[v];
-                }
-            }
-            if (begin >= end && wanted) {                // idle in this step
-                RowmOperand o = rowm_operand<T>(ra.step[i + 1], ahead, j, g);
-#pragma unroll
-                for (int c = 0; c < KC; ++c)
-                    if (rowm_chunk(c, o.last)) rowm_load_chunk(a[c], o, c);
-            }
-            __syncthreads();
-            T* other = buf; buf = out; out = other;
-        }
-
-        T* dst = Yg + row * k_out;
-        if (k_out % VN == 0) {
-            for (int c = tid * VN; c < k_out; c += NT * VN) stream_store(*reinterpret_cast<const V*>(buf + c), reinterpret_cast<V*>(dst + c));
-        } else {
-            for (int c = tid; c < k_out; c += NT) dst[c] = buf[c];
-        }
-        if (row + gridDim.x < M) __syncthreads();        // the result has left LDS
+    T* dst = Yg + row * k_out;
+    if (k_out % VN == 0) {
+        for (int c = tid * VN; c < k_out; c += NT * VN) stream_store(*reinterpret_cast<const V*>(buf + c), reinterpret_cast<V*>(dst + c));
+    } else {
+        for (int c = tid; c < k_out; c += NT) dst[c] = buf[c];
     }
 }
 

@@ -59,11 +59,10 @@ def test_the_general_form_can_be_asked_for():
 
 
 def test_taken_where_it_is_the_faster_one():
-    """On either side of the line, as measured: against the FMA form 5.1 us here and 20.2 there (300 x (32x32, 64x3)), 3.98
-    and 3.71 (1 x (2x40, 3x5)), 4.09 and 3.87 (66 x 2x2^2 fp64); against tiled launches 7.8 and 9.3
-    (200 x 50x50^2), 21.7 and 14.3 (265 x (104x100, 52x40)), 11.3 and 9.1 (5 x 61x61^2 fp64)."""
-    for dtype, M, shapes, taken in (("float32", 300, [(32, 32), (64, 3)], True), ("float32", 1, [(2, 40), (3, 5)], False),
-                                    ("float64", 66, [(2, 2)] * 2, False),
+    """On either side of the line, as measured: against the FMA form 5.0 us here and 19.9 there (300 x (32x32, 64x3)),
+    10.4 and 8.5 (37 x (9x4, 15x14, 4x44)); against tiled launches 7.6 and 9.3 (200 x 50x50^2), 21.3 and 14.1
+    (265 x (104x100, 52x40)), 11.0 and 9.1 (5 x 61x61^2 fp64)."""
+    for dtype, M, shapes, taken in (("float32", 300, [(32, 32), (64, 3)], True), ("float32", 37, [(9, 4), (15, 14), (4, 44)], False),
                                     ("float32", 200, [(50, 50)] * 2, True), ("float32", 265, [(104, 100), (52, 40)], False),
                                     ("float64", 5, [(61, 61)] * 2, False)):
         assert (_plan(dtype, M, shapes)[0]["variant"] == ROW_MFMA) == taken, (dtype, M, shapes)
