@@ -1084,7 +1084,8 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
     // and 4.7).  The others by their estimates, each within 8 % of what was measured on 700 problems: 10 x (52x50,
     // 65x20) fp64 20.1 us in two launches, 7.0 here, 5 x 61x61^2 fp64 9.1 and 11.0; on the FMA kernel 300 x (32x32, 64x3)
     // 19.9 and 5.0, 37 x (9x4, 15x14, 4x44) 8.5 and 10.4.  (Level with tiled launches the single one without workspace is
-    // taken: 1000 x 50x50^2 18.3 us and 16.8, 900 rows 15.9 and 16.6.)
+    // taken: 1000 x 50x50^2 18.3 us and 16.8, 900 rows 15.9 and 16.6; the FMA kernel stays where the two are within 5 %, since
+    // short contractions make this one's estimate too low: 54 x 2x1^6 7.2 us and 7.6.)
     bool compiled = true;
     for (const km_plan_step& s1 : plan.steps) compiled = compiled && s1.variant >= 0;
     RowmShape rs;
@@ -1117,10 +1118,12 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
                 } else if (s1.kernel == KM_KERNEL_MFMA_ANY)
                     had += (P * pr.esize % 16 == 0 && P * pr.esize <= (size_t)gen.any_row_bytes ? 5.5 : 9.5) + bytes / 7e6;
                 else
-                    had += (s1.kernel == KM_KERNEL_GENERIC ? 4.5 + 0.7 * ((P + 15) / 16) : 2.5) + bytes / 5e6;
+                    // (the generic kernel moves its bytes at a third of the rate, as launch_cost has it: 827 x (26x44, 3x4, 7x15)
+                    // fp64 36.9 us, 23.6 here)
+                    had += s1.kernel == KM_KERNEL_GENERIC ? 4.5 + 0.7 * ((P + 15) / 16) + bytes / 1.7e6 : 2.5 + bytes / 5e6;
             }
         }
-        if (rs.us < (rows_cost >= 0 ? 1.0 : 1.02) * had) take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, plan);
+        if (rs.us < (rows_cost >= 0 ? 0.95 : 1.02) * had) take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, plan);
     }
     return KM_OK;
 }
