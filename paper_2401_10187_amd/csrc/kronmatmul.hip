@@ -32,9 +32,9 @@ namespace km {
      NT == 1024 ? 8192 : 0},       /* 1024-thread workgroups only from 8192 tiles up: below, the 256-thread instance of the same tile is \
                                       2-5 % faster (128 x 8x8^6 0.110 vs 0.104 ms), above 1-2 % slower (2048 x 8x8^6 1.426 vs 1.454) */
 /* (ST == 1, a tile is a whole row of P^NF elements: every factor in one launch, X read and Y written once.
-   Measured against two or three tiled launches: 1000 x 64x64^2 0.0196 -> 0.0134 ms, 30000 rows 0.412 -> 0.263, 16 rows
-   0.0093 -> 0.0048; fp64 5000 x 16x16^3 0.106 -> 0.061, 20000 x 32x32^2 0.112 -> 0.064; 1000 x 32x32^3 0.0935 -> 0.0809,
-   4000 rows 0.381 -> 0.296; 1000 x 128x128^2 0.084 -> 0.076.) */
+   Measured against two or three tiled launches: 1000 x 64x64^2 0.0188 -> 0.0112 ms, 30000 rows 0.406 -> 0.272, 29 rows
+   0.0085 -> 0.0044; fp64 5000 x 16x16^3 0.104 -> 0.061, 2 rows 0.0060 -> 0.0046, 20000 x 32x32^2 0.109 -> 0.063; 1000 x
+   32x32^3 0.0896 -> 0.0783, 4000 rows 0.374 -> 0.296; 1000 x 128x128^2 0.082 -> 0.072.) */
 /* (walk -1, one round of resident workgroups: measured for every single-factor instance; it pays for the
    shapes named here, e.g. 4096 x 64x64^2 0.100 -> 0.071 ms, 20000 x 64x64^2 0.327 -> 0.275, 1024 x 48x48^3 fp64
    1.08 -> 1.02, and costs on others: 200000 x 16x16^2 0.148 -> 0.181, 1024 x 64x64^2 fp64 0.038 -> 0.048) */

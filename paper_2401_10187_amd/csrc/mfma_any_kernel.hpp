@@ -1,5 +1,6 @@
-// (Factors of up to 128 rows and columns take the form that keeps the factor in registers, mfma_pad_kernel.hpp,
-// as far as a tile of it fits; this one has the others.)
+// (Factors of up to 128 rows and columns mostly take the form that keeps the factor in registers,
+// mfma_pad_kernel.hpp, as far as a tile of it fits; this one has the others, and those that chunked_form_wins in
+// plan.hpp gives it.)
 // One sliced-multiply iteration on the matrix cores for a factor of any shape whose slices start on
 // 16-byte boundaries (P a multiple of 4 floats or 2 doubles; run-time shapes: 20, 48, 80, 96, 100, ...
 // and rectangles), are at most one chunk long (FLAT == 1 below: 13, 22, 33, 50, ...) or neither

@@ -1,6 +1,7 @@
 // One sliced-multiply iteration on the matrix cores for a factor of run-time shape (P, Q up to 128) that
-// stays in registers: the form of the run-time-shape MFMA family (mfma_any_kernel.hpp) that factors of
-// this size take; larger ones are walked through LDS in chunks by the other.
+// stays in registers: the form of the run-time-shape MFMA family (mfma_any_kernel.hpp) that most factors of
+// this size take; larger ones, tall ones and those that chunked_form_wins in plan.hpp names are walked through
+// LDS in chunks by the other.
 //
 // The contraction of a slice with the factor (Algorithm 1's inner loop) is the dense product
 //     D[q][s] = sum_p F[p][q] * X[s*P + p]
@@ -28,7 +29,9 @@
 // other chunks are four whole steps, and no product is spent on padding P further.  Columns past Q are
 // computed on zeros and dropped.
 // LDS rows (one slice each) have a stride of 4 times an odd number of floats, or 2 times an odd number of
-// doubles, which spreads the 64 operand reads of a step (16 slices x 4 consecutive p) over the banks.  Slices
+// doubles, so that the 64 operand reads of a step (16 slices x 4 consecutive p) start in different banks (counters:
+// 40-46 % of the LDS-active cycles are conflicts all the same, of an LDS that is active 18-32 % of the time).  What
+// keeps 100x100^3 at 58 % busy matrix cores is 112 columns for 100 and seven wavefronts on four SIMDs.  Slices
 // that are not whole 16-byte vectors keep the stride P, so that the tile is copied in vectors all the same (it
 // starts on a 16-byte boundary): most such strides meet a bank twice, those next to a multiple of 64 four
 // times, which costs less than dealing the elements to padded rows one by one (512 x 62x62^3 0.84 ms that
