@@ -764,7 +764,9 @@ inline double launch_cost(const Problem& pr, int64_t k_in, int64_t k_out, const 
     if (!ch.var && !ch.any_mfma) fixed += 1.0e7 + 3.5e6 * (double)((generic_P + 15) / 16);
     // a launch of the run-time-shape MFMA kernel that moves next to nothing takes 6-8 us (measured on the
     // paper's Table 4 sizes: two such launches 12.5 us for 50 x (32x8, 64x128), 15.4 us for 10 x (52x65,
-    // 50x20), where the whole-row kernel takes 17 and 13.4)
+    // 50x20), where the whole-row kernel takes 17 and 13.4).  That was its chunked form; the one with the factor in
+    // registers takes 4-6, and the factor of 1.5 above is the chunked form's too: this price only weighs the groupings
+    // against each other, the whole-row kernel for few rows is compared with finer estimates in make_plan.
     if (ch.any_mfma) fixed += 1.25e7;
     return bytes * slow + fixed;
 }
