@@ -82,10 +82,14 @@ typedef struct {
     int lds_bytes;         /* LDS per workgroup                                                    */
     int variant;           /* index of the compiled kernel instance, for reports (-1: the kernel has none;
                               -2: KM_KERNEL_ROWS in its form for few rows, on the matrix cores;
-                              -3: KM_KERNEL_MFMA_ANY with the factor held in registers)             */
+                              -3: KM_KERNEL_MFMA_ANY with the factor held in registers;
+                              -4, -5: KM_KERNEL_MFMA for two factors and for one that leave their
+                              digits in place)                                                      */
     int tiles_per_wg;      /* tiles one workgroup walks over (0: one tile per workgroup)           */
     int tile_order;        /* walk: 0 contiguous range, 1 interleaved pairs, 2 strided by the grid,
-                              3 strided inside the XCD's eighth of the tiles                       */
+                              3 strided inside the XCD's eighth of the tiles, 4 strided by the grid
+                              with the digits left in place: the rows between the launches of such
+                              a plan keep the order of their digits                                */
     int tile_rows;         /* rows per tile (the T_M of section 4); above 1 only when a tile holds
                               whole rows, tile_slices then being the slices of one row            */
 } km_plan_step;

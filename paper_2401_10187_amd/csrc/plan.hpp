@@ -330,6 +330,13 @@ inline RowmShape rowm_shape(const Problem& pr)
     return r;
 }
 
+// The fp32 kernels that leave digits in place (mfma_inplace_kernel.hpp).  The last two factors, both 48x48 or both
+// 64x64, are one launch with a tile of one matrix per wavefront, each factor before them (multiples of 16 up to 128) one
+// with tiles of DIGIT_COLS columns, in two stretches.
+constexpr int CHAIN_THREADS = 256, DIGIT_THREADS = 256, DIGIT_COLS = 512;
+constexpr int CHAIN_VARIANT = -4, DIGIT_VARIANT = -5;      // km_plan_step.variant of their launches
+constexpr int INPLACE_ORDER = 4;                           // ... and tile_order
+
 // A compiled instance chosen for one group of factors, with the slices per tile it will run with.
 // What the planner needs to know of the generic kernel: a workgroup of `threads` work-items takes
 // `tile_slices` slices and `tile_cols` factor columns at a time.
@@ -930,6 +937,30 @@ inline void row_widths(const Problem& pr, std::vector<int64_t>& width)
     for (int r = pr.N; r >= 1; --r) width[r - 1] = width[r] / pr.P[r - 1] * pr.Q[r - 1];
 }
 
+// Which buffers the launches of a plan read and write, and the workspace that takes.
+inline void assign_buffers(const Problem& pr, Plan& plan)
+{
+    // Buffers, assigned backwards from Y: the last launch writes Y, the one before it writes WS0,
+    // the one before that writes "B", and so on alternately.  B is Y itself when every row written
+    // there fits in a row of Y, otherwise the second workspace.
+    const int n = (int)plan.steps.size();
+    bool b_is_y = true;
+    for (int i = n - 3; i >= 0; i -= 2)
+        if (plan.steps[i].k_out > pr.k_out) b_is_y = false;
+    int64_t w0 = 0, w1 = 0;
+    for (int i = n - 1; i >= 0; --i) {
+        const int back = n - 1 - i;
+        int dst = back == 0 ? KM_BUF_Y : (back % 2 == 1 ? KM_BUF_WS0 : (b_is_y ? KM_BUF_Y : KM_BUF_WS1));
+        plan.steps[i].dst = dst;
+        if (dst == KM_BUF_WS0 && plan.steps[i].k_out > w0) w0 = plan.steps[i].k_out;
+        if (dst == KM_BUF_WS1 && plan.steps[i].k_out > w1) w1 = plan.steps[i].k_out;
+        if (i + 1 < n) plan.steps[i + 1].src = dst;
+    }
+    plan.steps[0].src = KM_BUF_X;
+    plan.ws0_bytes = round_up((size_t)(pr.M * w0) * pr.esize, 256);
+    plan.ws1_bytes = round_up((size_t)(pr.M * w1) * pr.esize, 256);
+}
+
 // Completes a plan from its groups: take[r] factors are applied when r remain, with pick[r].
 inline km_status finish_plan(const Problem& pr, const Options& opt, const Variant* table,
                              const std::vector<int>& take, const std::vector<Choice>& pick,
@@ -951,25 +982,7 @@ inline km_status finish_plan(const Problem& pr, const Options& opt, const Varian
         plan.bytes += (double)pr.M * ((double)st.k_in + (double)st.k_out) * pr.esize;
         plan.steps.push_back(st);
     }
-    // Buffers, assigned backwards from Y: the last launch writes Y, the one before it writes WS0,
-    // the one before that writes "B", and so on alternately.  B is Y itself when every row written
-    // there fits in a row of Y, otherwise the second workspace.
-    const int n = (int)plan.steps.size();
-    bool b_is_y = true;
-    for (int i = n - 3; i >= 0; i -= 2)
-        if (plan.steps[i].k_out > pr.k_out) b_is_y = false;
-    int64_t w0 = 0, w1 = 0;
-    for (int i = n - 1; i >= 0; --i) {
-        const int back = n - 1 - i;
-        int dst = back == 0 ? KM_BUF_Y : (back % 2 == 1 ? KM_BUF_WS0 : (b_is_y ? KM_BUF_Y : KM_BUF_WS1));
-        plan.steps[i].dst = dst;
-        if (dst == KM_BUF_WS0 && plan.steps[i].k_out > w0) w0 = plan.steps[i].k_out;
-        if (dst == KM_BUF_WS1 && plan.steps[i].k_out > w1) w1 = plan.steps[i].k_out;
-        if (i + 1 < n) plan.steps[i + 1].src = dst;
-    }
-    plan.steps[0].src = KM_BUF_X;
-    plan.ws0_bytes = round_up((size_t)(pr.M * w0) * pr.esize, 256);
-    plan.ws1_bytes = round_up((size_t)(pr.M * w1) * pr.esize, 256);
+    assign_buffers(pr, plan);
     return KM_OK;
 }
 
@@ -1002,6 +1015,79 @@ inline bool rowm_fits(const Problem& pr, const Options& opt, RowmShape& rs)
     if (!(opt.kernels >> KM_KERNEL_ROWS & 1) || pr.N < 2 || pr.N > opt.max_fuse || pr.M > ROWM_ROWS) return false;
     rs = rowm_shape(pr);
     return rs.threads > 0;
+}
+
+// Can the kernels that leave digits in place run the whole problem?  (The tuning aids ask for other kernels.)
+inline bool inplace_fits(const Problem& pr, const Options& opt)
+{
+    if (pr.dtype != KM_F32 || pr.N < 2 || opt.max_fuse < 2 || !(opt.kernels >> KM_KERNEL_MFMA & 1)) return false;
+    if (opt.prefer_tile || opt.prefer_threads || opt.prefer_instance || opt.tiles_per_wg || opt.tile_order >= 0) return false;
+    const int P = pr.P[pr.N - 1];
+    if (P != 48 && P != 64) return false;
+    for (int f = pr.N - 2; f < pr.N; ++f)
+        if (pr.P[f] != P || pr.Q[f] != P) return false;
+    int64_t w = pr.k_in;
+    for (int f = pr.N - 1; f >= 0; --f) {
+        if (f < pr.N - 2 && (pr.P[f] % 16 || pr.Q[f] % 16 || pr.P[f] > 128 || pr.Q[f] > 128)) return false;
+        if (w * (int64_t)pr.esize >= (int64_t)1 << 31) return false;     // (in-row offsets are 32 bits)
+        w = w / pr.P[f] * pr.Q[f];
+    }
+    return w * (int64_t)pr.esize < (int64_t)1 << 31;
+}
+
+// ... and are they the faster ones?  From a matrix per wavefront of the first launch on (two workgroups of four on each
+// compute unit): 64 x 64x64^3 88 us as rotating launches, 78 here, 16 rows 28.9 and 36.8; 64 x 48x48^3 43.9 and 35.4, 16 rows 18.6
+// and 18.0, 4 rows 13.3 and 15.6; 1024 rows 1157 and 987, 513 and 359.  Two 64x64 factors alone have a whole-row instance
+// (65536 rows 0.570 ms, 0.594 here); two 48x48 ones were two launches (65536 rows 0.529 ms, 0.264 here, 4096 rows 46.5 us and 23.8).
+inline bool inplace_wins(const Problem& pr)
+{
+    const int P = pr.P[pr.N - 1];
+    if (pr.N == 2 && P == 64) return false;
+    return pr.M * (pr.k_in / (P * P)) >= 512 * (CHAIN_THREADS / 64);
+}
+
+inline void take_inplace_plan(const Problem& pr, Plan& plan)
+{
+    plan.steps.clear();
+    plan.bytes = 0;
+    int64_t w = pr.k_in;
+    for (int left = pr.N; left > 0;) {
+        km_plan_step st{};
+        st.kernel = KM_KERNEL_MFMA;
+        st.num_factors = left == pr.N ? 2 : 1;
+        st.first_factor = left - st.num_factors;
+        st.k_in = w;
+        for (int f = left - 1; f >= st.first_factor; --f) {
+            w = w / pr.P[f] * pr.Q[f];
+            plan.bytes += (double)pr.P[f] * pr.Q[f] * pr.esize;
+        }
+        st.k_out = w;
+        st.tile_order = INPLACE_ORDER;
+        st.tile_rows = 1;
+        const int64_t P = pr.P[st.first_factor], Q = pr.Q[st.first_factor];
+        int64_t tiles, round;
+        if (st.num_factors == 2) {                       // two workgroups per compute unit
+            st.variant = CHAIN_VARIANT;
+            st.tile_slices = CHAIN_THREADS / 64;
+            st.block = CHAIN_THREADS;
+            st.lds_bytes = (int)(2 * P * P * (int64_t)pr.esize);
+            tiles = (pr.M * (st.k_in / (P * P)) + st.tile_slices - 1) / st.tile_slices;
+            round = 512;
+        } else {                                         // one
+            st.variant = DIGIT_VARIANT;
+            st.tile_slices = DIGIT_COLS;
+            st.block = DIGIT_THREADS;
+            st.lds_bytes = (int)(P * Q * (int64_t)pr.esize);
+            tiles = (pr.M * (st.k_in / P) + st.tile_slices - 1) / st.tile_slices;
+            round = 256;
+        }
+        st.grid = tiles < round ? tiles : round;
+        st.tiles_per_wg = (int)((tiles + st.grid - 1) / st.grid);
+        plan.bytes += (double)pr.M * ((double)st.k_in + (double)st.k_out) * pr.esize;
+        plan.steps.push_back(st);
+        left = st.first_factor;
+    }
+    assign_buffers(pr, plan);
 }
 
 inline km_status make_plan(const Problem& pr, const Options& opt, const Variant* table, int count,
@@ -1127,6 +1213,7 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
         }
         if (rs.us < (rows_cost >= 0 ? 0.95 : 1.02) * had) take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, plan);
     }
+    if (inplace_fits(pr, opt) && inplace_wins(pr)) take_inplace_plan(pr, plan);
     return KM_OK;
 }
 
