@@ -11,7 +11,7 @@
 // U(type, dtype code, P, Q, G0, G1, G2, G3, largest tile_slices, threads).
 // The same for rows of exactly P*P elements, ST rows per tile: R(P, rows per tile, wavefronts).
 // MFMA instances: Y(op, dtype code, P, Q, factors per launch, tile_slices, wavefronts, q split); tile_slices 1:
-// whole rows of P^(factors per launch) elements.
+// whole rows of P^(factors per launch) elements (of 32^3 floats: mfma_row32_kernel.hpp).
 // The same with a factor shape per stage, for neighbouring runs of different small shapes, stages in
 // order of application (the group's last factors first):
 // V(type, dtype code, P0, Q0, G0, P1, Q1, G1, P2, Q2, G2, largest tile_slices, threads); the comment
@@ -38,7 +38,7 @@
     R(32, 32, 4)                                        \
     Z(32, 32, 16, 1, 1)                                 \
     Z(32, 32, 4, 1, 2)                                  \
-    Y(MfmaF32x32, KM_F32, 32, 32, 3, 1, 8, 1)           \
+    Y(MfmaF32x32, KM_F32, 32, 32, 3, 1, 16, 1)          \
     Y(MfmaF32x32, KM_F32, 64, 64, 2, 1, 4, 2)           \
     Y(MfmaF32x16, KM_F32, 128, 128, 2, 1, 8, 8)         \
     Y(MfmaF64x16, KM_F64, 16, 16, 3, 1, 4, 1)           \

@@ -34,13 +34,14 @@ namespace km {
 /* (ST == 1, a tile is a whole row of P^NF elements: every factor in one launch, X read and Y written once.
    Measured against two or three tiled launches: 1000 x 64x64^2 0.0188 -> 0.0112 ms, 30000 rows 0.406 -> 0.272, 29 rows
    0.0085 -> 0.0044; fp64 5000 x 16x16^3 0.104 -> 0.061, 2 rows 0.0060 -> 0.0046, 20000 x 32x32^2 0.109 -> 0.063; 1000 x
-   32x32^3 0.0896 -> 0.0783, 4000 rows 0.374 -> 0.296; 1000 x 128x128^2 0.082 -> 0.072.) */
+   128x128^2 0.082 -> 0.072; 1000 x 32x32^3 0.0896 -> 0.0616, 4000 rows 0.374 -> 0.246, 96 rows 0.0172 -> 0.0173, 48 rows
+   0.0136 -> 0.0164, which is why those start at 96.) */
 /* (walk -1, one round of resident workgroups: measured for every single-factor instance; it pays for the
    shapes named here, e.g. 4096 x 64x64^2 0.100 -> 0.071 ms, 20000 x 64x64^2 0.327 -> 0.275, 1024 x 48x48^3 fp64
    1.08 -> 1.02, and costs on others: 200000 x 16x16^2 0.148 -> 0.181, 1024 x 64x64^2 fp64 0.038 -> 0.048) */
 #define KM_MFMA_ROW(OP, DT, P, Q, NF, ST, NW, QS) \
     {KM_KERNEL_MFMA, DT, P, Q, NF, ST, NW * 64, MfmaShape<OP, P, Q, NF, ST, NW, QS>::LDS_BYTES, 1, ST == 1 ? 2 : 1, 0, 1.0f, "mfma", \
-     0, 0, ST == 1 ? 1 : 0 /* whole rows only */, 0, \
+     0, 0, ST == 1 ? 1 : 0 /* whole rows only */, ST == 1 && P == 32 && DT == KM_F32 ? 96 : 0 /* 32^3: a row alone takes longer than three tiled launches */, \
      (ST == 1 || P == 80 || P == 96 || P == 112 || P >= 144 || (P == 64 && Q == 64 && DT == KM_F32) || (P == 48 && DT == KM_F64)) ? -1 : 0 /* walk: one round of resident workgroups */, \
      0, 0, {0, 0, 0, 0, 0, 0, 0, 0, 0}, \
      ST != 1 || DT != KM_F32 ? 0 : P == 64 ? 4 : P == 128 ? 3 : 0 /* (114 and 156 registers; the other whole-row instances are held to as many workgroups by LDS) */},

@@ -11,11 +11,6 @@
 // from LDS with 16-byte reads.  LDS rows (one slice each) are padded so that eight consecutive
 // lanes of such a read fall into different banks.
 //
-// With three factors on rows of 32^3 floats (128 KB, one workgroup to a compute unit) both memory and matrix
-// cores need 41-43 us for 1024 rows and the workgroups, in step with each other, use them mostly one after the
-// other: 81 us, matrix cores busy half the time.  What it took to get there, each in us: addresses kept out of the
-// registers (181 -> 94, spills), the next row fetched from the first stage on instead of the last (94 -> 86).
-//
 // A workgroup walks over `tiles_per_wg` consecutive tiles.  A tile is ST*P^NF contiguous elements of
 // one row; NF = 1 to 3 factors are applied with the intermediate kept in LDS (section 4.2) and the
 // result is scattered exactly as in the non-MFMA fused kernel.  The next tile is fetched from
@@ -200,7 +195,7 @@ __device__ __forceinline__ void mfma_stage(typename OP::T* __restrict__ tile,
                     const int q = (wq * QTW + qt) * OP::MB + OP::row_lane(lane) + OP::row_reg(v);
                     const int c = q * SJ + s;          // position in the next stage's row of the tile
                     // Whole rows: the same position as one base and a constant per register, which spares the
-                    // registers that its division takes (1024 x 32x32^3 fp32: 181 us where they spilled); longer tiles lose 2 % by it
+                    // registers that its division takes (rows of 32^3 floats took twice as long where they spilled); longer tiles lose 2 % by it
                     // (16x16^6 fp64, 16 rows: 2.46 -> 2.50 ms).
                     if constexpr (ST == 1 && SJ % P == 0) tile[((unsigned)q * (SJ / P) + (unsigned)s / P) * RS + (unsigned)s % P] = acc[bi][qt][v];
                     else tile[(c / P) * RS + (c % P)] = acc[bi][qt][v];

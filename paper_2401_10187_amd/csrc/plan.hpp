@@ -629,10 +629,10 @@ inline Choice find_variant(const Variant* table, int count, const Problem& pr, i
         if (c.rows_per_tile > 1 && s_row != c.tile_slices) continue;      // tiles of several rows hold whole rows
         if (c.min_tiles > 0 && !c.flexible && pr.M * (s_row / c.tile_slices) < c.min_tiles && opt.prefer_instance != v + 1)
             continue;                                     // too few tiles for this instance (unless it is asked for)
-        // A whole row that takes more than 64 KB of LDS has a compute unit to itself: only where the last round of
-        // 256 rows is nearly full (300 x 128x128^2 0.038 ms, two tiled launches 0.034, 520 rows 0.054 and 0.052; 700
-        // rows 0.054 and 0.060, 1000 rows 0.072 and 0.082; 32x32^3: 100 rows 0.020 and 0.017, 240 rows 0.024 and 0.032)
-        if (c.max_srow == 1 && !c.flexible && c.lds_bytes > 64 * 1024 && opt.prefer_instance != v + 1 &&
+        // Rows of 128x128, which take more than 64 KB of LDS and have a compute unit to themselves: only where the last
+        // round of 256 rows is nearly full (300 x 128x128^2 0.038 ms, two tiled launches 0.034, 520 rows 0.054 and 0.052; 700
+        // rows 0.054 and 0.060, 1000 rows 0.072 and 0.082; rows of 32^3 always: 300 rows 0.037 and 0.043)
+        if (c.max_srow == 1 && nf == 2 && !c.flexible && c.lds_bytes > 64 * 1024 && opt.prefer_instance != v + 1 &&
             (pr.M + 255) / 256 * 256 * 10 > pr.M * 13)
             continue;
         // slices per tile: fixed, or the best divisor of s_row up to the instance's limit

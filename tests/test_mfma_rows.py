@@ -87,3 +87,36 @@ def test_matches_the_reference(dtype, M, P, N):
             assert np.array_equal(got, ref)
         else:
             assert np.abs(got - ref).max() <= tol * np.abs(ref).max()
+
+
+# rows of 32^3 floats, which have a kernel of their own: the fewest that take it, a row more than compute units, walks of several
+ROW32 = [96, 257, 1030]
+
+
+def test_rows_of_32_cubed_are_one_launch_from_96_on():
+    for M in ROW32:
+        (st,) = _plan("float32", M, 32, 3)
+        assert st["block"] == 1024 and st["tile_slices"] == 1 and st["grid"] <= M <= st["grid"] * st["tiles_per_wg"]
+    assert len(_plan("float32", 95, 32, 3)) > 1
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M", ROW32)
+def test_rows_of_32_cubed_match_and_keep_apart(M):
+    """1e-5 of the largest value (sums of 32 terms per factor, three of them: at most 99 u of the product of absolute
+    values), bit for bit on small integers; what is not finite stays in its row."""
+    import oracle
+    for kinds, exact in ((dict(x="uniform", f="normal"), False), (dict(x="int2", f="int1"), True)):
+        X, Fs = kron_inputs.make_problem(M, [(32, 32)] * 3, "float32", seed=83, **kinds)
+        print("rows of 32^3, M=%d" % M, flush=True)
+        Fd = [torch.from_numpy(F).cuda() for F in Fs]
+        got = km.kronmatmul(torch.from_numpy(X).cuda(), Fd)
+        ref = oracle.kron_matmul(X, Fs)
+        if exact:
+            assert np.array_equal(got.cpu().numpy(), ref)
+        else:
+            assert np.abs(got.cpu().numpy() - ref).max() <= 1e-5 * np.abs(ref).max()
+            X[5, 77] = X[M - 1, 0] = np.inf
+            bad = km.kronmatmul(torch.from_numpy(X).cuda(), Fd)
+            rest = [r for r in range(M) if r not in (5, M - 1)]
+            assert torch.equal(bad[rest], got[rest]) and not torch.isfinite(bad[[5, M - 1]]).any()
