@@ -84,7 +84,7 @@ typedef struct {
                               -2: KM_KERNEL_ROWS in its form for few rows, on the matrix cores;
                               -3: KM_KERNEL_MFMA_ANY with the factor held in registers;
                               -4, -5: KM_KERNEL_MFMA for two factors and for one that leave their
-                              digits in place)                                                      */
+                              digits in place, -6: KM_KERNEL_FUSED for whole rows of 4^7 floats)    */
     int tiles_per_wg;      /* tiles one workgroup walks over (0: one tile per workgroup)           */
     int tile_order;        /* walk: 0 contiguous range, 1 interleaved pairs, 2 strided by the grid,
                               3 strided inside the XCD's eighth of the tiles, 4 strided by the grid

@@ -1,0 +1,169 @@
+// All factors of a row of 4^7 floats in one launch: 4x4 ones, two 2x2 ones in the place of each as it comes.  X is read and Y
+// written once.
+//
+// A row is seven digits of two bits.  A thread holds two digits (sixteen values) at a time and applies their
+// factors in registers; three exchanges through LDS give it the next two.  Digits stay where they are in the row, so
+// a thread writes its results over what it has read and an exchange takes one barrier; the one between
+// the second and the third pair of digits stays within a wavefront and takes none.  The first pair is the lowest digit,
+// a 16-byte vector, with the highest one, and the last digit is applied to whole vectors of the lowest, so
+// every load and store of global memory is 1 KB in a piece.  LDS strides are padded so that none of the accesses
+// meets a bank twice.  Factors are wave-uniform: scalar loads, as in fused_kernel.hpp.
+//
+// Bound by memory: 1024 rows take 23 us (5.8 TB/s, 37.3 before), 20000 rows 463 us (5.7 TB/s, 552 before); 1024 rows of 2^14 23 us
+// (34 before).  The kernel that ran these rows (fused_multi_kernel.hpp with four super-stages) gave a row to 256
+// threads that load, multiply and store it in turn, all workgroups in step; here the next row is on its way into
+// registers meanwhile (16 more of the 64 that two workgroups of 1024 threads leave a thread).
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+#include "fused_kernel.hpp"   // Vec16, as_constant
+#include "plan.hpp"           // ROW4_*
+
+namespace km {
+
+struct Row4Shape {
+    static constexpr int NT = ROW4_THREADS, ROW = ROW4_ELEMS, N = ROW4_DIGITS;
+    static constexpr int D4 = 64 + 4, D3 = 4 * D4, BLOCK = 4 * D3;       // LDS strides of digits 4, 3 and (1, 2)
+    static_assert(16 * BLOCK * 4 == ROW4_LDS_BYTES && 16 * NT == ROW, "the planner's numbers");
+};
+// What is applied to each digit of the row, in the order of the Kronecker product: a 4x4 factor (g null), or two 2x2
+// ones, f before g.
+struct Row4Factors {
+    const float* f[Row4Shape::N];
+    const float* g[Row4Shape::N];
+};
+
+// d[.] <- what is applied to four values of a digit, for every e
+template <int E>
+__device__ __forceinline__ void row4_apply(const Row4Factors& fa, int digit, float (&d)[4][E])
+{
+    const float *f = fa.f[digit - 1], *g = fa.g[digit - 1];
+    asm volatile("" : "+s"(f), "+s"(g));               // (all factors would be held in scalar registers over the rows, and spill)
+    const auto cf = as_constant(f);
+    if (g) {
+        const auto cg = as_constant(g);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+#pragma unroll
+            for (int i = 0; i < 4; i += 2) {           // the later factor: the digit's low bit
+                const float y0 = __builtin_fmaf(d[i + 1][e], cg[2], d[i][e] * cg[0]), y1 = __builtin_fmaf(d[i + 1][e], cg[3], d[i][e] * cg[1]);
+                d[i][e] = y0;
+                d[i + 1][e] = y1;
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const float y0 = __builtin_fmaf(d[i + 2][e], cf[2], d[i][e] * cf[0]), y1 = __builtin_fmaf(d[i + 2][e], cf[3], d[i][e] * cf[1]);
+                d[i][e] = y0;
+                d[i + 2][e] = y1;
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        float y[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            y[q] = d[0][e] * cf[q];
+#pragma unroll
+            for (int p = 1; p < 4; ++p) y[q] = __builtin_fmaf(d[p][e], cf[4 * p + q], y[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) d[q][e] = y[q];
+    }
+}
+__device__ __forceinline__ void row4_transpose(const float (&a)[4][4], float (&b)[4][4])
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) b[j][i] = a[i][j];
+}
+
+__global__ __launch_bounds__(Row4Shape::NT, 8)
+void fused_row4_multiply(const float* __restrict__ Xg, float* __restrict__ Yg, Row4Factors fa, int64_t num_rows)
+{
+    typedef Row4Shape Sh;
+    typedef Vec16<float>::type V;
+    constexpr int ROW = Sh::ROW, D4 = Sh::D4, D3 = Sh::D3, BLOCK = Sh::BLOCK;
+    extern __shared__ __attribute__((aligned(16))) unsigned char row4_lds[];
+    float* const lds = reinterpret_cast<float*>(row4_lds);
+    const int tid = threadIdx.x, l = tid % 64;
+    const int w = __builtin_amdgcn_readfirstlane(tid / 64);
+
+    V x[4];
+    auto fetch = [&](int64_t r) __attribute__((always_inline)) {
+        const float* src = Xg + r * ROW + w * 256 + 4 * l;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = stream_load(reinterpret_cast<const V*>(src + k * 4096));
+    };
+    if (blockIdx.x < num_rows) fetch(blockIdx.x);
+    for (int64_t row = blockIdx.x; row < num_rows; row += gridDim.x) {
+        float a[4][4], b[4][4];
+        // digits 7 (in a vector) and 1 (vector k)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[e][k] = x[k][e];
+        if (row + gridDim.x < num_rows) fetch(row + gridDim.x);
+        row4_apply(fa, 7, a);
+        row4_transpose(a, b);
+        row4_apply(fa, 1, b);
+        {
+            float* to = lds + (w / 4) * BLOCK + (w % 4) * D3 + (l / 16) * D4 + (l % 16) * 4;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) *reinterpret_cast<V*>(to + k * 4 * BLOCK) = V{b[k][0], b[k][1], b[k][2], b[k][3]};
+        }
+        __syncthreads();
+        // digits 4 and 3: this wavefront's block of 1024, lanes along digits 5 to 7
+        {
+            float* at = lds + w * BLOCK + l;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) a[j][i] = at[i * D3 + j * D4];
+            row4_apply(fa, 4, a);
+            row4_transpose(a, b);
+            row4_apply(fa, 3, b);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) at[i * D3 + j * D4] = b[i][j];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");           // (within the wavefront: no barrier)
+        __builtin_amdgcn_wave_barrier();
+        // digits 6 and 5 of the same block, lanes along digits 3, 4 and 7
+        {
+            float* at = lds + w * BLOCK + (l / 16) * D3 + (l / 4 % 4) * D4 + l % 4;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) a[j][i] = at[i * 16 + j * 4];
+            row4_apply(fa, 6, a);
+            row4_transpose(a, b);
+            row4_apply(fa, 5, b);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) at[i * 16 + j * 4] = b[i][j];
+        }
+        __syncthreads();
+        // digit 2, whole vectors of digit 7, lanes along digits 4 to 6
+        {
+            const float* from = lds + (w / 4) * 4 * BLOCK + (w % 4) * D3 + (l / 16) * D4 + (l % 16) * 4;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const V v = *reinterpret_cast<const V*>(from + k * BLOCK);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[k][e] = v[e];
+            }
+        }
+        __syncthreads();                               // read by everybody: the next row may be written
+        row4_apply(fa, 2, a);
+        float* const y = Yg + row * ROW + (w / 4) * 4096 + (w % 4) * 256 + 4 * l;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) stream_store(V{a[k][0], a[k][1], a[k][2], a[k][3]}, reinterpret_cast<V*>(y + k * 1024));
+    }
+}
+
+}  // namespace km

@@ -330,6 +330,13 @@ inline RowmShape rowm_shape(const Problem& pr)
     return r;
 }
 
+// The kernel for rows of 4^7 floats whose factors are 4x4 or pairs of 2x2 (fused_row4_kernel.hpp): all of them in one launch,
+// two workgroups to a compute unit.  It is the faster one for any number of rows (4^7, us: 1 row 8.5 -> 6.2, 100 rows 11.1 -> 7.0, 512
+// rows 17.2 -> 12.3, 1024 rows 37.3 -> 23.1, 20000 rows 552 -> 463; what it replaces: two launches for few rows, else
+// fused_multi_kernel.hpp).
+constexpr int ROW4_ELEMS = 16384, ROW4_DIGITS = 7, ROW4_THREADS = 1024, ROW4_LDS_BYTES = 16 * 4 * 4 * 68 * 4, ROW4_GRID = 512;
+constexpr int ROW4_VARIANT = -6;           // km_plan_step.variant of its launches
+
 // The fp32 kernels that leave digits in place (mfma_inplace_kernel.hpp).  The last two factors, both 48x48 or both
 // 64x64, are one launch with a tile of one matrix per wavefront, each factor before them (multiples of 16 up to 128) one
 // with tiles of DIGIT_COLS columns, in two stretches.
@@ -1017,11 +1024,40 @@ inline bool rowm_fits(const Problem& pr, const Options& opt, RowmShape& rs)
     return rs.threads > 0;
 }
 
-// Can the kernels that leave digits in place run the whole problem?  (The tuning aids ask for other kernels.)
+// No tuning aid asks for particular kernels, tiles or walks.
+inline bool no_wishes(const Options& opt)
+{
+    return !opt.prefer_tile && !opt.prefer_threads && !opt.prefer_instance && !opt.tiles_per_wg && opt.tile_order < 0;
+}
+
+// Factor of each of the row's digits of two bits (the first of two 2x2 ones): can fused_row4_kernel.hpp run the problem?
+inline bool row4_digits(const Problem& pr, int (&first)[ROW4_DIGITS])
+{
+    if (pr.dtype != KM_F32 || pr.k_in != ROW4_ELEMS) return false;
+    int f = 0;
+    for (int d = 0; d < ROW4_DIGITS; ++d) {
+        if (f >= pr.N) return false;
+        first[d] = f;
+        const int p = pr.P[f];
+        if ((p != 4 && p != 2) || pr.Q[f] != p) return false;
+        if (p == 2 && (f + 1 >= pr.N || pr.P[f + 1] != 2 || pr.Q[f + 1] != 2)) return false;
+        if (p == 4 && f > 0 && pr.P[f - 1] == 2) return false;      // (the order of 2x2 before 4x4 has no one-launch form; the tests hold it to that)
+        f += p == 2 ? 2 : 1;
+    }
+    return f == pr.N;
+}
+
+inline bool row4_fits(const Problem& pr, const Options& opt)
+{
+    int first[ROW4_DIGITS];
+    return no_wishes(opt) && (opt.kernels >> KM_KERNEL_FUSED & 1) && opt.max_fuse >= pr.N && row4_digits(pr, first);
+}
+
+// Can the kernels that leave digits in place run the whole problem?
 inline bool inplace_fits(const Problem& pr, const Options& opt)
 {
     if (pr.dtype != KM_F32 || pr.N < 2 || opt.max_fuse < 2 || !(opt.kernels >> KM_KERNEL_MFMA & 1)) return false;
-    if (opt.prefer_tile || opt.prefer_threads || opt.prefer_instance || opt.tiles_per_wg || opt.tile_order >= 0) return false;
+    if (!no_wishes(opt)) return false;
     const int P = pr.P[pr.N - 1];
     if (P != 48 && P != 64) return false;
     for (int f = pr.N - 2; f < pr.N; ++f)
@@ -1214,6 +1250,14 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
         if (rs.us < (rows_cost >= 0 ? 0.95 : 1.02) * had) take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, plan);
     }
     if (inplace_fits(pr, opt) && inplace_wins(pr)) take_inplace_plan(pr, plan);
+    if (row4_fits(pr, opt)) {
+        take_rows_plan(pr, ROW4_VARIANT, ROW4_THREADS, ROW4_LDS_BYTES, plan);
+        km_plan_step& one = plan.steps[0];
+        one.kernel = KM_KERNEL_FUSED;
+        one.grid = pr.M < ROW4_GRID ? pr.M : ROW4_GRID;
+        one.tiles_per_wg = (int)((pr.M + one.grid - 1) / one.grid);
+        one.tile_order = 2;
+    }
     return KM_OK;
 }
 
