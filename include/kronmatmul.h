@@ -70,7 +70,8 @@ typedef enum { KM_BUF_X = 0, KM_BUF_Y = 1, KM_BUF_WS0 = 2, KM_BUF_WS1 = 3 } km_b
  * F, applied last to first) map rows of width k_in to rows of width k_out. */
 typedef struct {
     int kernel;            /* km_kernel                                                            */
-    int first_factor;      /* lowest factor index in this step                                     */
+    int first_factor;      /* lowest factor index in this step (with variant -7 and two steps, the
+                              second one has the factors at both ends)                             */
     int num_factors;       /* factors fused in this launch (N_fused of section 4.2)                */
     int tile_slices;       /* contiguous output run per tile and fused column (T_K / prod P)       */
     long long k_in;        /* row width read                                                       */
@@ -84,7 +85,8 @@ typedef struct {
                               -2: KM_KERNEL_ROWS in its form for few rows, on the matrix cores;
                               -3: KM_KERNEL_MFMA_ANY with the factor held in registers;
                               -4, -5: KM_KERNEL_MFMA for two factors and for one that leave their
-                              digits in place, -6: KM_KERNEL_FUSED for whole rows of 4^7 floats)    */
+                              digits in place, -6: KM_KERNEL_FUSED for whole rows of 4^7 floats,
+                              -7: for rows of 5^6, 5^8, 3^9 and 3^12 floats)                       */
     int tiles_per_wg;      /* tiles one workgroup walks over (0: one tile per workgroup)           */
     int tile_order;        /* walk: 0 contiguous range, 1 interleaved pairs, 2 strided by the grid,
                               3 strided inside the XCD's eighth of the tiles, 4 strided by the grid

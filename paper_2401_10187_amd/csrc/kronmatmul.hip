@@ -332,6 +332,7 @@ static hipError_t launch_step(const Problem& pr, const km_plan_step& st, const v
         return pr.dtype == KM_F32 ? launch_pad<float>(a) : launch_pad<double>(a);
     if (st.kernel == KM_KERNEL_MFMA_ANY)
         return pr.dtype == KM_F32 ? launch_mfma_any<float>(a) : launch_mfma_any<double>(a);
+    if (st.kernel == KM_KERNEL_FUSED && st.variant == CUBE_VARIANT) return launch_cube(a);
     if (st.kernel == KM_KERNEL_FUSED && st.variant == ROW4_VARIANT) return launch_row4(a);
     if (st.kernel == KM_KERNEL_MFMA && st.variant == CHAIN_VARIANT) return launch_chain(a);
     if (st.kernel == KM_KERNEL_MFMA && st.variant == DIGIT_VARIANT) return launch_digit(a);

@@ -337,6 +337,10 @@ inline RowmShape rowm_shape(const Problem& pr)
 constexpr int ROW4_ELEMS = 16384, ROW4_DIGITS = 7, ROW4_THREADS = 1024, ROW4_LDS_BYTES = 16 * 4 * 4 * 68 * 4, ROW4_GRID = 512;
 constexpr int ROW4_VARIANT = -6;           // km_plan_step.variant of its launches
 
+// The kernel for rows of P^(3G) and P^(4G) floats, square factors of size 5 (G = 2) and 3 (G = 3) (fused_cube_kernel.hpp).
+constexpr int CUBE_VARIANT = -7;           // km_plan_step.variant of its launches
+KM_HOST_DEVICE constexpr int cube_stride(int E) { return E * E + (E + 64 - E * E % 64) % 64; }       // the same modulo 64 as E
+
 // The fp32 kernels that leave digits in place (mfma_inplace_kernel.hpp).  The last two factors, both 48x48 or both
 // 64x64, are one launch with a tile of one matrix per wavefront, each factor before them (multiples of 16 up to 128) one
 // with tiles of DIGIT_COLS columns, in two stretches.
@@ -1053,6 +1057,52 @@ inline bool row4_fits(const Problem& pr, const Options& opt)
     return no_wishes(opt) && (opt.kernels >> KM_KERNEL_FUSED & 1) && opt.max_fuse >= pr.N && row4_digits(pr, first);
 }
 
+// Digits per group if fused_cube_kernel.hpp can run the problem, else 0.
+inline int cube_group(const Problem& pr)
+{
+    const int P = pr.P[0], G = P == 5 ? 2 : P == 3 ? 3 : 0;
+    if (pr.dtype != KM_F32 || G == 0 || (pr.N != 3 * G && pr.N != 4 * G)) return 0;
+    for (int i = 0; i < pr.N; ++i)
+        if (pr.P[i] != P || pr.Q[i] != P) return 0;
+    return G;
+}
+
+// (one row of 4G digits is 25 or 27 tiles, and stays with launches of smaller ones: 5^8 12.9 us there, 13.5 here, two rows 17.8
+// and 14.5)
+inline bool cube_fits(const Problem& pr, const Options& opt)
+{
+    return no_wishes(opt) && (opt.kernels >> KM_KERNEL_FUSED & 1) && opt.max_fuse >= pr.N && cube_group(pr) > 0 && !(pr.M == 1 && pr.N == 4 * cube_group(pr));
+}
+
+inline void take_cube_plan(const Problem& pr, Plan& plan)
+{
+    const int G = cube_group(pr), launches = pr.N / G - 2;
+    int64_t E = 1;
+    for (int i = 0; i < G; ++i) E *= pr.P[0];
+    plan.steps.clear();
+    plan.bytes = 0;
+    for (int i = 0; i < launches; ++i) {
+        km_plan_step st{};
+        st.kernel = KM_KERNEL_FUSED;
+        st.variant = CUBE_VARIANT;
+        // (two launches: the factors in the middle, then those at both ends)
+        st.num_factors = pr.N / launches;
+        st.first_factor = launches == 2 && i == 0 ? G : 0;
+        st.tile_slices = launches == 2 ? (int)E : 1;
+        st.tile_rows = 1;
+        st.k_in = st.k_out = pr.k_in;
+        st.block = (int)((E * E + 63) / 64 * 64);
+        st.lds_bytes = (int)(E * cube_stride((int)E) * (int64_t)pr.esize);
+        st.tile_order = INPLACE_ORDER;
+        const int64_t tiles = pr.M * (pr.k_in / (E * E * E)), most = launches == 2 && tiles >= 4096 ? 256 : 512;
+        st.grid = tiles < most ? tiles : most;
+        st.tiles_per_wg = (int)((tiles + st.grid - 1) / st.grid);
+        plan.bytes += (double)pr.M * 2.0 * (double)pr.k_in * pr.esize + (double)st.num_factors * pr.P[0] * pr.P[0] * pr.esize;
+        plan.steps.push_back(st);
+    }
+    assign_buffers(pr, plan);
+}
+
 // Can the kernels that leave digits in place run the whole problem?
 inline bool inplace_fits(const Problem& pr, const Options& opt)
 {
@@ -1250,6 +1300,7 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
         if (rs.us < (rows_cost >= 0 ? 0.95 : 1.02) * had) take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, plan);
     }
     if (inplace_fits(pr, opt) && inplace_wins(pr)) take_inplace_plan(pr, plan);
+    if (cube_fits(pr, opt)) take_cube_plan(pr, plan);
     if (row4_fits(pr, opt)) {
         take_rows_plan(pr, ROW4_VARIANT, ROW4_THREADS, ROW4_LDS_BYTES, plan);
         km_plan_step& one = plan.steps[0];
