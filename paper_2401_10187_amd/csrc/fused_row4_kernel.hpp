@@ -97,7 +97,10 @@ void fused_row4_multiply(const float* __restrict__ Xg, float* __restrict__ Yg, R
 #pragma unroll
         for (int k = 0; k < 4; ++k) x[k] = stream_load(reinterpret_cast<const V*>(src + k * 4096));
     };
-    if (blockIdx.x < num_rows) fetch(blockIdx.x);
+    if (blockIdx.x >= num_rows) return;
+    fetch(blockIdx.x);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(x[k]));      // (waited for here: in the loop the compiler would wait for the stores behind them too)
     for (int64_t row = blockIdx.x; row < num_rows; row += gridDim.x) {
         float a[4][4], b[4][4];
         // digits 7 (in a vector) and 1 (vector k)

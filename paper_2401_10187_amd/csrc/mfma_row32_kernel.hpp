@@ -8,7 +8,7 @@
 // multiplied and stored by some wavefronts, others are already at the next row, whose loads are issued as
 // soon as the operand registers are free.
 //
-// 1024 rows take 62 us (77 before, with the row in LDS between all three products and two more barriers), 4000 rows 246
+// 1024 rows take 62 us (77 before, with the row in LDS between all three products and two more barriers), 4000 rows 238
 // (297).  A row costs its compute unit 15 us, of which the products are 10.2 at the matrix cores' full rate; with memory
 // at 4.3 TB/s beside them the chip's power allows them no more than about 110 TFLOP/s, 12 us.  One row alone takes
 // 14 us, four wavefronts on a SIMD in turn.
@@ -33,7 +33,7 @@ void mfma_row32_multiply(const float* __restrict__ Xg, float* __restrict__ Yg, c
 {
     typedef Row32Shape Sh;
     typedef Vec16<float>::type V;
-    constexpr int P = Sh::P, NW = Sh::NW, NT = Sh::NT, ROW = Sh::ROW, APW = Sh::APW;
+    constexpr int P = Sh::P, NW = Sh::NW, ROW = Sh::ROW, APW = Sh::APW;
     extern __shared__ __attribute__((aligned(16))) unsigned char row32_lds[];
     float* const z = reinterpret_cast<float*>(row32_lds);
     float* const f0 = z + ROW;
@@ -76,6 +76,10 @@ void mfma_row32_multiply(const float* __restrict__ Xg, float* __restrict__ Yg, c
         for (int a = 0; a < APW; ++a) fetch(row, a);
     const int turn = (wave / 2) % 2 * 32;              // this wavefront's window of the intermediate has its halves swapped
     __syncthreads();
+#pragma unroll
+    for (int a = 0; a < APW; ++a)
+#pragma unroll
+        for (int j = 0; j < P / 8; ++j) asm volatile("" : "+v"(x[a][j]));       // (waited for here: in the loop the compiler would wait for the stores behind them too)
     for (; row < end; row += step) {
         int at = lane * 4;
         asm volatile("" : "+v"(at));                   // (the factors would be held in registers over the rows)
