@@ -1,4 +1,5 @@
-"""ctypes binding of the C-ABI in include/kronmatmul.h.  Argument marshalling only: every step of
+"""Binding of the C-ABI in include/kronmatmul.h, by ctypes and, for calls of plain tensors, by a native part
+(csrc/marshal.cpp).  Argument marshalling only: every step of
 the computation runs in the HIP library.  There is no fallback: a missing library is an error."""
 import ctypes
 import os
@@ -227,20 +228,25 @@ def release():
     _check(lib().kronmatmul_release(), "kronmatmul_release")
 
 
+_native = None              # the binding's native part, once started (csrc/marshal.cpp)
 _raw_stream = None          # torch's (device index) -> hipStream_t of its current stream
 _entries = {}               # entry point name -> function of the library
 _int_arrays, _ptr_arrays = {}, {}      # ctypes array types by length
 
 
-def _current_stream(index):
-    """The raw handle of torch's current stream on a device.  torch has a call for just that, which takes 0.07 us
+def _stream_getter():
+    """What gives the raw handle of torch's current stream on a device.  torch has a call for just that, which takes 0.07 us
     where building the Stream object takes 1.9; where a torch lacks it, the object is built."""
     global _raw_stream
     if _raw_stream is None:
         import torch
         _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
             lambda i: torch.cuda.current_stream(i).cuda_stream)
-    return _raw_stream(index)
+    return _raw_stream
+
+
+def _current_stream(index):
+    return (_raw_stream or _stream_getter())(index)
 
 
 def _entry(name):
@@ -248,6 +254,25 @@ def _entry(name):
     if fn is None:
         fn = _entries[name] = getattr(lib(), name)
     return fn
+
+
+def _raise_status(status, transposed, with_ws):
+    raise KronMatmulError(status, _entry_name(with_ws, transposed))
+
+
+def _start_native():
+    """Loads the native part and hands it the library's entry points.  It takes calls of plain tensors; what it declines goes
+    through _marshal below, which also says what is wrong with it."""
+    global _native
+    import torch  # noqa: F401 - the native part is linked against torch's libraries, which this loads
+    L = lib()
+    if not os.path.exists(os.path.join(HERE, "_marshal.so")):
+        raise RuntimeError("the binding's native part _marshal.so is missing: run `python -c 'import __graft_entry__ as g; g.build()'`")
+    from . import _marshal as native
+    address = [ctypes.cast(getattr(L, _entry_name(ws, t)), ctypes.c_void_p).value for ws in (False, True) for t in (False, True)]
+    native.start(*address, _stream_getter(), _raise_status)
+    _native = native
+    return native
 
 
 class Prepared:
@@ -261,15 +286,17 @@ class Prepared:
         self._device = X.get_device()
         self._what = _entry_name(self._ws_call, transposed)
         self._fn = getattr(lib(), self._what)
+        M, n, P, Q, x, F, y, code, ws, nbytes = (self._args + (0, 0))[:10]
+        self._bound = (_native or _start_native()).bind(M, n, ctypes.addressof(P), ctypes.addressof(Q), x, ctypes.addressof(F), y, code,
+                                                        ws, nbytes, self._ws_call, transposed, self._device)
 
     def __call__(self, stream=None):
         """Enqueue on `stream` (a raw hipStream_t value; default: torch's current stream).  The
         tensors' device must be the current device."""
-        if stream is None:
-            stream = _current_stream(self._device)
-        st = self._fn(*self._args, stream)
-        if st != KM_OK:
-            raise KronMatmulError(st, self._what)
+        if stream is None or type(stream) is int:
+            self._bound(stream)
+        else:
+            _check(self._fn(*self._args, stream), self._what)
         return self.Y
 
 
@@ -329,6 +356,10 @@ def kronmatmul(X, Fs, Y=None, workspace=None, stream=None, transposed=False, sta
     With static=True the call goes to kronmatmul_static (no allocation; Y must then be given, or the
     binding's own torch.empty allocates it).
     Returns Y.  The call is asynchronous on `stream` (default: torch's current stream)."""
+    if stream is None and not static:
+        got = (_native or _start_native()).call(X, Fs, Y, workspace, transposed)
+        if got is not NotImplemented:
+            return got
     import torch
     if static and (workspace is not None or transposed):
         raise ValueError("static=True takes neither a workspace nor transposed factors")

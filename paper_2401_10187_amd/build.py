@@ -1,11 +1,13 @@
-"""Compile the HIP library for gfx950 into paper_2401_10187_amd/libkronmatmul.so (in-tree).
+"""Compile the HIP library for gfx950 into paper_2401_10187_amd/libkronmatmul.so (in-tree), and the binding's native part for this Python and torch into paper_2401_10187_amd/_marshal.so.
 
 The kernel instances are spread over one translation unit per kernel family (csrc/inst_*.hip) so that
 they compile side by side; csrc/kronmatmul.hip holds the C-ABI, the planner and the two kernels
 without compile-time shapes."""
 import glob
+import importlib.util
 import os
 import subprocess
+import sysconfig
 import time
 from concurrent.futures import ThreadPoolExecutor
 
@@ -13,6 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libkronmatmul.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -50,6 +53,15 @@ def _stale(obj):
     return any(not os.path.exists(n) or os.path.getmtime(n) > t for n in names)
 
 
+def build_marshal(verbose=False):
+    """Host code only: the headers of Python and torch, linked against the torch libraries that `import torch` loads."""
+    torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"],
+          "-isystem", os.path.join(torch_dir, "include"), "-isystem", os.path.join(torch_dir, "include/torch/csrc/api/include"),
+          "-o", MARSHAL, os.path.join(CSRC, "marshal.cpp"), "-L" + os.path.join(torch_dir, "lib"), "-lc10", "-ltorch_cpu",
+          "-ltorch_python"], verbose)
+
+
 def build(verbose=False, jobs=None, incremental=False):
     """Recompiles every translation unit (with incremental=True only those whose sources changed, a
     convenience while working on one kernel); returns the path of the shared library."""
@@ -59,9 +71,15 @@ def build(verbose=False, jobs=None, incremental=False):
     objs = [os.path.join(OBJ, os.path.basename(s)[:-4] + ".o") for s in srcs]
     todo = [(s, o) for s, o in zip(srcs, objs) if not incremental or _stale(o)]
     jobs = jobs or min(max(len(todo), 1), os.cpu_count() or 1, 16)
+    source = os.path.join(CSRC, "marshal.cpp")
     with ThreadPoolExecutor(max_workers=jobs) as pool:
+        marshal = None
+        if not incremental or not os.path.exists(MARSHAL) or os.path.getmtime(MARSHAL) < os.path.getmtime(source):
+            marshal = pool.submit(build_marshal, verbose)
         list(pool.map(lambda so: _run([hipcc] + HIPCC_FLAGS + ["-MD", "-MF", so[1][:-2] + ".d", "-c", "-o", so[1], so[0]],
                                       verbose), todo))
+        if marshal:
+            marshal.result()
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs, verbose)
     return LIB
 
