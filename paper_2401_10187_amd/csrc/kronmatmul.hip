@@ -12,6 +12,7 @@
 #include "launch.hpp"
 #include "instances.hpp"
 #include "generic_kernel.hpp"
+#include "generic_small_kernel.hpp"
 #include "row_kernel.hpp"
 #include "row_mfma_kernel.hpp"
 #include "fused_kernel.hpp"          // the kernel headers below are only needed for their shape structs
@@ -87,6 +88,22 @@ static const LaunchFn g_launchers[] = {
     KM_INSTANCES(KM_FUSED_FN, KM_MFMA_FN, KM_PAIR_FN, KM_MULTI_FN, KM_ROWS_FN, KM_MIXED_FN, KM_MULTI4_FN) };
 static const int g_num_variants = (int)(sizeof(g_variants) / sizeof(g_variants[0]));
 
+template <typename T, int NC>
+static hipError_t launch_small(const LaunchArgs& a, int64_t S, int64_t slices, int64_t units)
+{
+    const int P = a.pr->P[a.st->first_factor], Q = a.pr->Q[a.st->first_factor];
+    const bool few = P <= GEN_FEW;
+    auto kern = few ? sliced_multiply_small<T, NC, true> : sliced_multiply_small<T, NC, false>;
+    static unsigned char lds_ok[64];
+    hipError_t e = few ? hipSuccess : allow_lds((const void*)kern, GEN_SMALL_LDS, lds_ok);
+    if (e != hipSuccess || a.prepare_only) return e;
+    // (element numbers of a unit stay below 2^15, so 32 bits of magic are exact)
+    hipLaunchKernelGGL(kern, dim3((unsigned)a.st->grid), dim3(GEN_THREADS), few ? 0 : (size_t)gen_small_lds(P, sizeof(T)),
+                       a.stream, (const T*)a.src, (const T*)a.factors[a.st->first_factor], (T*)a.dst, S, P, Q, slices, units,
+                       (unsigned)(((1ull << 32) + (unsigned)P - 1) / (unsigned)P));
+    return hipGetLastError();
+}
+
 template <typename T>
 static hipError_t launch_generic(const LaunchArgs& a)
 {
@@ -97,6 +114,17 @@ static hipError_t launch_generic(const LaunchArgs& a)
     const int64_t slices = a.pr->M * S;                  // counted through all rows
     const int64_t units = ((slices + GEN_TS - 1) / GEN_TS) * ((Q + GEN_TQ - 1) / GEN_TQ);
     if (st.grid < 1 || st.grid > units) return hipErrorInvalidValue;
+    // (a few slices per row and many columns, results 8 to 28 bytes apart: 150000 x (2x2, 5x40) 71 us in the other form, 73 in this one;
+    // with one slice 300000 x 5x40 71 and 29)
+    if (gen_small_lds(P, sizeof(T)) <= GEN_SMALL_LDS && !(S > 1 && S < 8 && Q > 16)) {
+        switch (gen_small_columns(Q)) {
+            case 1: return launch_small<T, 1>(a, S, slices, units);
+            case 2: return launch_small<T, 2>(a, S, slices, units);
+            case 4: return launch_small<T, 4>(a, S, slices, units);
+            case 8: return launch_small<T, 8>(a, S, slices, units);
+            default: return launch_small<T, 16>(a, S, slices, units);
+        }
+    }
     if (a.prepare_only) return hipSuccess;
     hipLaunchKernelGGL((sliced_multiply_generic<T>), dim3((unsigned)st.grid), dim3(GEN_THREADS), 0, a.stream,
                        (const T*)a.src, (const T*)a.factors[f], (T*)a.dst, st.k_in, P, Q, slices, units);
