@@ -20,10 +20,6 @@
 
 namespace km {
 
-constexpr int GEN_SMALL_LDS = 66 * 1024 + 64;
-// LDS row of a slice: an odd number of elements
-KM_HOST_DEVICE constexpr int gen_small_stride(int P) { return P | 1; }
-KM_HOST_DEVICE constexpr int64_t gen_small_lds(int64_t P, int64_t esize) { return GEN_TS * (P | 1) * esize; }
 // slices that a thread reads by itself: what 64 lanes read one after the other is one run, and no barrier is needed
 constexpr int GEN_FEW = 8;
 // columns per thread: a power of two that covers half a unit's columns
@@ -61,7 +57,7 @@ void sliced_multiply_small(const T* __restrict__ Xg, const T* __restrict__ Fg, T
 {
     typedef typename Vec16<T>::type V;
     constexpr int VN = Vec16<T>::N, AHEAD = 8;         // vectors in flight per thread
-    static_assert(GEN_THREADS == 2 * GEN_TS, "two groups of columns per slice");
+    static_assert(GEN_THREADS == 2 * GEN_TS && GEN_TS == GEN_SLICES, "two groups of columns per slice");
     extern __shared__ __attribute__((aligned(16))) unsigned char small_lds[];
     T* const lds = reinterpret_cast<T*>(small_lds);
     const int tid = threadIdx.x, rs = gen_small_stride(P);

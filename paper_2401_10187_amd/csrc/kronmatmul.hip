@@ -114,9 +114,7 @@ static hipError_t launch_generic(const LaunchArgs& a)
     const int64_t slices = a.pr->M * S;                  // counted through all rows
     const int64_t units = ((slices + GEN_TS - 1) / GEN_TS) * ((Q + GEN_TQ - 1) / GEN_TQ);
     if (st.grid < 1 || st.grid > units) return hipErrorInvalidValue;
-    // (a few slices per row and many columns, results 8 to 28 bytes apart: 150000 x (2x2, 5x40) 71 us in the other form, 73 in this one;
-    // with one slice 300000 x 5x40 71 and 29)
-    if (gen_small_lds(P, sizeof(T)) <= GEN_SMALL_LDS && !(S > 1 && S < 8 && Q > 16)) {
+    if (gen_small_form(P, Q, S, (int64_t)sizeof(T))) {
         switch (gen_small_columns(Q)) {
             case 1: return launch_small<T, 1>(a, S, slices, units);
             case 2: return launch_small<T, 2>(a, S, slices, units);

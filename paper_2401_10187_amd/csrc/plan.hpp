@@ -398,6 +398,17 @@ inline double pad_us(int P, int Q, size_t esize, int64_t slices, const PadShape&
     return 2.26 + 0.0081 * P + 0.09 * (double)((tiles + grid - 1) / grid) + n * (0.13 + 0.64 * bytes + 0.98 * products);
 }
 
+// The generic kernel's form for small factors (generic_small_kernel.hpp): units of GEN_SLICES slices, held in LDS whole with an odd
+// stride.  (A few slices per row and many columns, results 8 to 28 bytes apart: 150000 x (2x2, 5x40) 71 us in the other
+// form, 73 in this one; with one slice 300000 x 5x40 71 and 29.)
+constexpr int GEN_SLICES = 128, GEN_SMALL_LDS = 66 * 1024 + 64;
+KM_HOST_DEVICE constexpr int gen_small_stride(int P) { return P | 1; }
+KM_HOST_DEVICE constexpr int64_t gen_small_lds(int64_t P, int64_t esize) { return GEN_SLICES * (P | 1) * esize; }
+KM_HOST_DEVICE constexpr bool gen_small_form(int P, int Q, int64_t S, int64_t esize)
+{
+    return gen_small_lds(P, esize) <= GEN_SMALL_LDS && !(S > 1 && S < 8 && Q > 16);
+}
+
 // Does the form of the run-time-shape MFMA kernel that walks the factor through LDS in chunks beat the one that holds
 // it in registers (`pad`)?  Measured side by side on 900 pairs of equal factors, 1 to 60000 rows: the register form
 // is faster (mostly 1.05 to 3 times) in launches of up to 256 tiles, where slices are no whole 16-byte vectors (the other
@@ -1176,6 +1187,48 @@ inline void take_inplace_plan(const Problem& pr, Plan& plan)
     assign_buffers(pr, plan);
 }
 
+// Microseconds of the whole-row FMA kernel: per row a fixed part, its factors' loads and per step 1 us and 70 ns (fp64 106) for each of
+// the P products that a thread adds up in turn; 1024 threads have a compute unit to themselves.
+inline double fma_rows_us(const Problem& pr, int threads, int64_t lds_bytes, const std::vector<int64_t>& width)
+{
+    int64_t side = threads >= 1024 ? 1 : 160 * 1024 / (lds_bytes < 20 * 1024 ? 20 * 1024 : lds_bytes);
+    if (side > 2048 / threads) side = 2048 / threads;
+    const int64_t rounds = (pr.M + 256 * side - 1) / (256 * side);
+    if (side > (pr.M + 255) / 256) side = (pr.M + 255) / 256;
+    double row = 0.328 + 0.159 * (double)(pr.k_in + pr.k_out) / threads;
+    for (int r = pr.N; r >= 1; --r) {
+        const int64_t S = width[r] / pr.P[r - 1], units = (S + 1) / 2 * ((pr.Q[r - 1] + 3) / 4);
+        row += 1.036 + (double)((units + threads - 1) / threads) * pr.P[r - 1] * (pr.esize == 4 ? 0.069 : 0.106) +
+               (double)side * (double)width[r] * (double)pr.Q[r - 1] * 5.4e-6 + 0.275 * pr.P[r - 1] * pr.Q[r - 1] / threads;
+    }
+    return 1.13 + (double)rounds * row;
+}
+
+// Microseconds of tiled launches, for comparison with the whole-row kernels.
+inline double tiled_us(const Problem& pr, const std::vector<km_plan_step>& steps, const GenericKernel& gen)
+{
+    double us = 0;
+    for (const km_plan_step& st : steps) {
+        const double bytes = (double)pr.M * ((double)st.k_in + (double)st.k_out) * (double)pr.esize;
+        const int P = pr.P[st.first_factor], Q = pr.Q[st.first_factor];
+        // (small launches of the chunked form of the run-time-shape MFMA kernel: 5.5 us when slices are whole 16-byte
+        // vectors and one chunk, 10 otherwise: 100 x 36x36^2 10.0 us in two, 200 x 50x50^2 20.2, 33 x 80x80^2 20.4)
+        if (st.variant == PAD_VARIANT) {
+            const int64_t slices = pr.M * (st.k_in / P);
+            us += pad_us(P, Q, pr.esize, slices, pad_shape(P, Q, pr.esize, slices));
+        } else if (st.kernel == KM_KERNEL_MFMA_ANY)
+            us += (P * pr.esize % 16 == 0 && P * pr.esize <= (size_t)gen.any_row_bytes ? 5.5 : 9.5) + bytes / 7e6;
+        else if (st.kernel == KM_KERNEL_GENERIC) {
+            // (the form without padding: its pass over a tall slice takes its time too; the other one moves its bytes at a
+            // third of the rate, as launch_cost has it)
+            const bool small = gen_small_form(P, Q, st.k_in / P, (int64_t)pr.esize);
+            us += small ? 2.7 + (P > 16 ? 0.06 * (P - 16) : 0.0) + bytes / 3e6 : 4.5 + 0.7 * ((P + 15) / 16) + bytes / 1.7e6;
+        } else
+            us += 2.5 + bytes / 5e6;
+    }
+    return us;
+}
+
 inline km_status make_plan(const Problem& pr, const Options& opt, const Variant* table, int count,
                            const GenericKernel& gen, Plan& plan)
 {
@@ -1246,7 +1299,12 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
             // plan 0.090; 116508 x (16x13, 36x4) fp64 0.628 against 0.228)
             if (c < 4.5 * bytes) c = 4.5 * bytes;
             c += 2.5e7;
-            if (c < best[N] || force_rows) {
+            // (tiled launches by the finer estimates, where they promise a tenth and their workspace fits the static array, as the row
+            // kernel's did: 9363 x (74x14, 18x5) 79 us in rows, 31 in two launches, 5058 x (18x4, 39x3) 27 and 10, 1254 x (7x2, 51x23)
+            // 11.6 and 7.6; of 35 such problems 21 are faster tiled, by up to 2.7 times, since the generic kernel has its form for small factors)
+            const bool tiled = !force_rows && plan.ws0_bytes + plan.ws1_bytes <= KM_STATIC_SCRATCH_BYTES &&
+                               tiled_us(pr, plan.steps, gen) < 0.9 * fma_rows_us(pr, threads, lds, width);
+            if ((c < best[N] && !tiled) || force_rows) {
                 take_rows_plan(pr, -1, threads, lds, plan);
                 rows_cost = c;
             }
@@ -1264,39 +1322,7 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
     for (const km_plan_step& s1 : plan.steps) compiled = compiled && s1.variant >= 0;
     RowmShape rs;
     if (!compiled && !(force_rows && rows_cost >= 0) && rowm_fits(pr, opt, rs)) {
-        double had = 0;                                  // us of the plan at hand
-        if (rows_cost >= 0) {
-            // The FMA kernel: per row a fixed part, its factors' loads and per step 1 us and 70 ns (fp64 106) for each of the P
-            // products that a thread adds up in turn; 1024 threads have a compute unit to themselves.
-            const int threads = plan.steps[0].block;
-            int64_t side = threads >= 1024 ? 1 : 160 * 1024 / (plan.steps[0].lds_bytes < 20 * 1024 ? 20 * 1024 : plan.steps[0].lds_bytes);
-            if (side > 2048 / threads) side = 2048 / threads;
-            const int64_t rounds = (pr.M + 256 * side - 1) / (256 * side);
-            if (side > (pr.M + 255) / 256) side = (pr.M + 255) / 256;
-            double row = 0.328 + 0.159 * (double)(pr.k_in + pr.k_out) / threads;
-            for (int r = N; r >= 1; --r) {
-                const int64_t S = width[r] / pr.P[r - 1], units = (S + 1) / 2 * ((pr.Q[r - 1] + 3) / 4);
-                row += 1.036 + (double)((units + threads - 1) / threads) * pr.P[r - 1] * (pr.esize == 4 ? 0.069 : 0.106) +
-                       (double)side * (double)width[r] * (double)pr.Q[r - 1] * 5.4e-6 + 0.275 * pr.P[r - 1] * pr.Q[r - 1] / threads;
-            }
-            had = 1.13 + (double)rounds * row;
-        } else {
-            for (const km_plan_step& s1 : plan.steps) {
-                const double bytes = (double)pr.M * ((double)s1.k_in + (double)s1.k_out) * (double)pr.esize;
-                const int P = pr.P[s1.first_factor], Q = pr.Q[s1.first_factor];
-                // (small launches of the chunked form of the run-time-shape MFMA kernel: 5.5 us when slices are whole 16-byte
-                // vectors and one chunk, 10 otherwise: 100 x 36x36^2 10.0 us in two, 200 x 50x50^2 20.2, 33 x 80x80^2 20.4)
-                if (s1.variant == PAD_VARIANT) {
-                    const int64_t slices = pr.M * (s1.k_in / P);
-                    had += pad_us(P, Q, pr.esize, slices, pad_shape(P, Q, pr.esize, slices));
-                } else if (s1.kernel == KM_KERNEL_MFMA_ANY)
-                    had += (P * pr.esize % 16 == 0 && P * pr.esize <= (size_t)gen.any_row_bytes ? 5.5 : 9.5) + bytes / 7e6;
-                else
-                    // (the generic kernel moves its bytes at a third of the rate, as launch_cost has it: 827 x (26x44, 3x4, 7x15)
-                    // fp64 36.9 us, 23.6 here)
-                    had += s1.kernel == KM_KERNEL_GENERIC ? 4.5 + 0.7 * ((P + 15) / 16) + bytes / 1.7e6 : 2.5 + bytes / 5e6;
-            }
-        }
+        const double had = rows_cost >= 0 ? fma_rows_us(pr, plan.steps[0].block, plan.steps[0].lds_bytes, width) : tiled_us(pr, plan.steps, gen);
         if (rs.us < (rows_cost >= 0 ? 0.95 : 1.02) * had) take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, plan);
     }
     if (inplace_fits(pr, opt) && inplace_wins(pr)) take_inplace_plan(pr, plan);
