@@ -20,8 +20,6 @@
 
 namespace km {
 
-// slices that a thread reads by itself: what 64 lanes read one after the other is one run, and no barrier is needed
-constexpr int GEN_FEW = 8;
 // columns per thread: a power of two that covers half a unit's columns
 KM_HOST_DEVICE constexpr int gen_small_columns(int Q) { return Q <= 2 ? 1 : Q <= 4 ? 2 : Q <= 8 ? 4 : Q <= 16 ? 8 : 16; }
 
@@ -49,7 +47,8 @@ __device__ __forceinline__ void small_multiply(T (&acc)[NC], const T* __restrict
     }
 }
 
-// FEW: P is at most GEN_FEW, and a thread reads its slice by itself.
+// FEW: P is at most GEN_FEW, and a thread reads its slice by itself: what 64 lanes read one after the other is one run, and no
+// barrier is needed.
 template <typename T, int NC, bool FEW>
 __global__ __launch_bounds__(GEN_THREADS)
 void sliced_multiply_small(const T* __restrict__ Xg, const T* __restrict__ Fg, T* __restrict__ Yg, int64_t S, int P, int Q,

@@ -401,7 +401,8 @@ inline double pad_us(int P, int Q, size_t esize, int64_t slices, const PadShape&
 // The generic kernel's form for small factors (generic_small_kernel.hpp): units of GEN_SLICES slices, held in LDS whole with an odd
 // stride.  (A few slices per row and many columns, results 8 to 28 bytes apart: 150000 x (2x2, 5x40) 71 us in the other
 // form, 73 in this one; with one slice 300000 x 5x40 71 and 29.)
-constexpr int GEN_SLICES = 128, GEN_SMALL_LDS = 66 * 1024 + 64;
+// Slices of up to GEN_FEW elements are read by a thread each, without LDS.
+constexpr int GEN_SLICES = 128, GEN_SMALL_LDS = 66 * 1024 + 64, GEN_FEW = 8;
 KM_HOST_DEVICE constexpr int gen_small_stride(int P) { return P | 1; }
 KM_HOST_DEVICE constexpr int64_t gen_small_lds(int64_t P, int64_t esize) { return GEN_SLICES * (P | 1) * esize; }
 KM_HOST_DEVICE constexpr bool gen_small_form(int P, int Q, int64_t S, int64_t esize)
@@ -925,8 +926,8 @@ inline km_plan_step build_step(const Problem& pr, const Options& opt, const Vari
         st.tile_rows = 1;
         st.tile_slices = gen.tile_slices;
         st.block = gen.threads;
-        st.lds_bytes = gen.lds_bytes;
         const int64_t S = st.k_in / pr.P[f];
+        st.lds_bytes = !gen_small_form(pr.P[f], pr.Q[f], S, (int64_t)pr.esize) ? gen.lds_bytes : pr.P[f] <= GEN_FEW ? 0 : (int)gen_small_lds(pr.P[f], (int64_t)pr.esize);
         // one workgroup per (tile of slices, group of factor columns); tiles may span rows
         st.grid = ((pr.M * S + gen.tile_slices - 1) / gen.tile_slices) * ((pr.Q[f] + gen.tile_cols - 1) / gen.tile_cols);
         // the generic kernel strides over its work, so its grid can stay below the launch limit
