@@ -1302,8 +1302,9 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
             c += 2.5e7;
             // (tiled launches by the finer estimates, where they promise a tenth and their workspace fits the static array, as the row
             // kernel's did: 9363 x (74x14, 18x5) 79 us in rows, 31 in two launches, 5058 x (18x4, 39x3) 27 and 10, 1254 x (7x2, 51x23)
-            // 11.6 and 7.6; of 35 such problems 21 are faster tiled, by up to 2.7 times, since the generic kernel has its form for small factors)
-            const bool tiled = !force_rows && plan.ws0_bytes + plan.ws1_bytes <= KM_STATIC_SCRATCH_BYTES &&
+            // 11.6 and 7.6; of 35 such problems 21 are faster tiled, by up to 2.7 times, since the generic kernel has its form for small factors.
+            // Up to a row per compute unit the fixed costs decide, which these estimates do not know that well: one launch there.)
+            const bool tiled = !force_rows && pr.M > 256 && plan.ws0_bytes + plan.ws1_bytes <= KM_STATIC_SCRATCH_BYTES &&
                                tiled_us(pr, plan.steps, gen) < 0.9 * fma_rows_us(pr, threads, lds, width);
             if ((c < best[N] && !tiled) || force_rows) {
                 take_rows_plan(pr, -1, threads, lds, plan);
