@@ -70,3 +70,15 @@ def test_what_is_not_finite_stays_in_its_slice(generic_only, dtype, P):
     got = km.kronmatmul(torch.from_numpy(X).cuda(), F)
     rest = [r for r in range(M) if r not in (0, 130, M - 1)]
     assert torch.equal(got[rest], clean[rest]) and not torch.isfinite(got[[0, 130, M - 1]]).any()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,shapes,tiled", [(9363, [(74, 14), (18, 5)], True), (1254, [(7, 2), (51, 23)], True),
+                                            (1, [(5, 5), (5, 5), (5, 5), (2, 2)], False), (256, [(7, 2), (51, 23)], False)], ids=str)
+def test_small_mixed_problems_of_many_rows_are_tiled(M, shapes, tiled):
+    """Where whole rows on the FMA kernel are the slower plan, its launches' intermediates fit the static array all the same."""
+    P, Q = [s[0] for s in shapes], [s[1] for s in shapes]
+    rows = [s["kernel"] for s in km.plan(M, P, Q, "float32")] == [km.KM_KERNEL_ROWS]
+    assert rows != tiled
+    assert km.workspace_size(M, P, Q, "float32") <= (km.KM_STATIC_SCRATCH_BYTES if tiled else 0)
+    _check("float32", M, shapes)
