@@ -1205,8 +1205,9 @@ inline double fma_rows_us(const Problem& pr, int threads, int64_t lds_bytes, con
     return 1.13 + (double)rounds * row;
 }
 
-// Microseconds of tiled launches, for comparison with the whole-row kernels.
-inline double tiled_us(const Problem& pr, const std::vector<km_plan_step>& steps, const GenericKernel& gen)
+// Microseconds of tiled launches, for comparison with the whole-row kernels.  Generic launches in the form that they take, or
+// (by_form false) all at the padded form's rate, which is what decides whether a problem has a whole-row plan at all.
+inline double tiled_us(const Problem& pr, const std::vector<km_plan_step>& steps, const GenericKernel& gen, bool by_form)
 {
     double us = 0;
     for (const km_plan_step& st : steps) {
@@ -1222,7 +1223,7 @@ inline double tiled_us(const Problem& pr, const std::vector<km_plan_step>& steps
         else if (st.kernel == KM_KERNEL_GENERIC) {
             // (the form without padding: its pass over a tall slice takes its time too; the other one moves its bytes at a
             // third of the rate, as launch_cost has it)
-            const bool small = gen_small_form(P, Q, st.k_in / P, (int64_t)pr.esize);
+            const bool small = by_form && gen_small_form(P, Q, st.k_in / P, (int64_t)pr.esize);
             us += small ? 2.7 + (P > 16 ? 0.06 * (P - 16) : 0.0) + bytes / 3e6 : 4.5 + 0.7 * ((P + 15) / 16) + bytes / 1.7e6;
         } else
             us += 2.5 + bytes / 5e6;
@@ -1262,7 +1263,8 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
     // threads taken when rows are few (fp64: 1.5 times that); rows run side by side as far as LDS
     // and 2048 threads per compute unit allow.
     const bool force_rows = opt.prefer_instance == count + 1;      // tuning aid: this kernel whenever it fits
-    double rows_cost = -1;
+    Plan rows = plan;                                    // (for its flops)
+    double rows_us = -1;
     if ((opt.kernels >> KM_KERNEL_ROWS & 1) && N >= 2 && N <= gen.row_max_factors && N <= opt.max_fuse &&
         (plan.steps.size() > 1 || force_rows)) {
         int64_t maxw = 0;
@@ -1300,15 +1302,9 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
             // plan 0.090; 116508 x (16x13, 36x4) fp64 0.628 against 0.228)
             if (c < 4.5 * bytes) c = 4.5 * bytes;
             c += 2.5e7;
-            // (tiled launches by the finer estimates, where they promise a tenth and their workspace fits the static array, as the row
-            // kernel's did: 9363 x (74x14, 18x5) 79 us in rows, 31 in two launches, 5058 x (18x4, 39x3) 27 and 10, 1254 x (7x2, 51x23)
-            // 11.6 and 7.6; of 35 such problems 21 are faster tiled, by up to 2.7 times, since the generic kernel has its form for small factors.
-            // Up to a row per compute unit the fixed costs decide, which these estimates do not know that well: one launch there.)
-            const bool tiled = !force_rows && pr.M > 256 && plan.ws0_bytes + plan.ws1_bytes <= KM_STATIC_SCRATCH_BYTES &&
-                               tiled_us(pr, plan.steps, gen) < 0.9 * fma_rows_us(pr, threads, lds, width);
-            if ((c < best[N] && !tiled) || force_rows) {
-                take_rows_plan(pr, -1, threads, lds, plan);
-                rows_cost = c;
+            if (c < best[N] || force_rows) {
+                take_rows_plan(pr, -1, threads, lds, rows);
+                rows_us = fma_rows_us(pr, threads, lds, width);
             }
         }
     }
@@ -1323,9 +1319,23 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
     bool compiled = true;
     for (const km_plan_step& s1 : plan.steps) compiled = compiled && s1.variant >= 0;
     RowmShape rs;
-    if (!compiled && !(force_rows && rows_cost >= 0) && rowm_fits(pr, opt, rs)) {
-        const double had = rows_cost >= 0 ? fma_rows_us(pr, plan.steps[0].block, plan.steps[0].lds_bytes, width) : tiled_us(pr, plan.steps, gen);
-        if (rs.us < (rows_cost >= 0 ? 0.95 : 1.02) * had) take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, plan);
+    if ((rows_us >= 0 || !compiled) && !(force_rows && rows_us >= 0) && rowm_fits(pr, opt, rs)) {
+        const double had = rows_us >= 0 ? rows_us : tiled_us(pr, plan.steps, gen, false);
+        if (rs.us < (rows_us >= 0 ? 0.95 : 1.02) * had) {
+            take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, rows);
+            rows_us = rs.us;
+        }
+    }
+    // The whole-row plan, whichever kernel it is on, unless the finer estimates promise a tenth from tiled launches whose
+    // workspace fits the static array, as the whole-row plan's did: 9363 x (74x14, 18x5) 79 us in rows, 31 in two launches, 5058 x (18x4,
+    // 39x3) 27 and 10; of 110 such problems 105 are faster tiled, by up to 5 times, since the generic kernel has its form for small
+    // factors.  (Not so small compiled launches against the matrix-core rows: 300 x 2x2^2 fp64 3.9 us in rows, 6.6 tiled, 500 x 4x4^3 fp64
+    // 4.7 and 6.3; 500 x 16x16^2 takes 4.2 and 3.8, but two launches of the host's.  Up to a row per compute unit the fixed costs
+    // decide, which these estimates do not know that well: one launch there.)
+    if (rows_us >= 0) {
+        const bool tiled = !force_rows && pr.M > 256 && plan.ws0_bytes + plan.ws1_bytes <= KM_STATIC_SCRATCH_BYTES &&
+                           tiled_us(pr, plan.steps, gen, true) < 0.9 * rows_us;
+        if (!tiled) plan = rows;
     }
     if (inplace_fits(pr, opt) && inplace_wins(pr)) take_inplace_plan(pr, plan);
     if (cube_fits(pr, opt)) take_cube_plan(pr, plan);

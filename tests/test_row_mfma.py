@@ -43,6 +43,20 @@ def test_planned_only_where_its_limits_hold():
     assert seen > 100
 
 
+@pytest.mark.parametrize("dtype,M,shapes", [("float32", 257, [(16, 16)] * 2), ("float32", 487, [(16, 16)] * 2), ("float32", 1024, [(16, 16)] * 2),
+                                            ("float64", 793, [(16, 16)] * 2), ("float64", 1000, [(16, 16)] * 2), ("float64", 257, [(2, 2)] * 2),
+                                            ("float64", 512, [(2, 2)] * 2), ("float64", 400, [(4, 4)] * 3), ("float64", 300, [(2, 4)] * 3),
+                                            ("float64", 300, [(4, 2)] * 3),
+                                            # tiled launches would need more than the static array, or have up to 256 rows
+                                            ("float64", 793, [(37, 5), (76, 81)]), ("float64", 850, [(37, 5), (76, 81)]),
+                                            ("float32", 6, [(52, 122), (6, 3), (2, 18)]), ("float32", 2, [(85, 124), (5, 54)])], ids=str)
+def test_tiled_launches_are_weighed_against_the_whole_row_plan_that_they_stand_in_for(dtype, M, shapes):
+    """The general whole-row kernel loses to tiled launches here, or generic launches are cheap; the one on the matrix cores
+    is the plan all the same: one launch, no workspace."""
+    assert [s["variant"] for s in _plan(dtype, M, shapes)] == [ROW_MFMA]
+    assert km.workspace_size(M, [p for p, _ in shapes], [q for _, q in shapes], dtype) == 0
+
+
 def test_the_general_form_can_be_asked_for():
     """The option that takes the whole-row kernel wherever it fits means the general form, also where the planner
     would take this one."""
