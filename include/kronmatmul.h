@@ -97,6 +97,9 @@ typedef struct {
 } km_plan_step;
 
 /* Bytes of device workspace kronmatmul_ws needs for this problem (0 when one launch suffices).
+ * Small problems of many rows may have two plans: launches that share a workspace, which are the faster ones, and one launch
+ * without any.  This size, kronmatmul_plan and kronmatmul_cost are then the faster plan's; kronmatmul, kronmatmul_static and
+ * kronmatmul_ws with a smaller workspace run the one launch.
  * Follows Algorithm 1's two swapped intermediates, except that Y stands in for one of them when it
  * is wide enough and X is read in place.  Pure host computation. */
 km_status kronmatmul_workspace_size(int M, int N, const int* P, const int* Q, km_dtype dtype,

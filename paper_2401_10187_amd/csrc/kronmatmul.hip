@@ -247,6 +247,7 @@ static GenericKernel generic_kernel(int dtype)
 struct Planned {
     Problem pr;
     Plan plan;
+    Plan spare;          // what calls without the plan's workspace run instead (no steps: nothing)
 };
 typedef std::shared_ptr<const Planned> PlannedRef;
 struct CachedPlan {
@@ -301,7 +302,7 @@ static km_status plan_for(int M, int N, const int* P, const int* Q, int dtype, P
     auto made = std::make_shared<Planned>();
     km_status s = make_problem(M, N, P, Q, dtype, made->pr);
     if (s != KM_OK) return s;
-    s = make_plan(made->pr, opt, g_variants, g_num_variants, generic_kernel(dtype), made->plan);
+    s = make_plan(made->pr, opt, g_variants, g_num_variants, generic_kernel(dtype), made->plan, made->spare);
     if (s != KM_OK) return s;
     for (const km_plan_step& st : made->plan.steps)
         if (!launchable(st)) return KM_EUNSUPPORTED;
@@ -523,7 +524,7 @@ static int reps_for(float ms_once)
     return reps < 2 ? 2 : (reps > 20 ? 20 : reps);
 }
 
-static km_status tune(const Problem& pr, const Options& opt, hipStream_t stream, Plan& chosen,
+static km_status tune(const Problem& pr, const Options& opt, hipStream_t stream, Plan& chosen, Plan& spare,
                       float* tuned_ms, float* default_ms)
 {
     const int N = pr.N;
@@ -534,7 +535,7 @@ static km_status tune(const Problem& pr, const Options& opt, hipStream_t stream,
     for (int i = 0; i < N; ++i) fmax = (int64_t)pr.P[i] * pr.Q[i] > fmax ? (int64_t)pr.P[i] * pr.Q[i] : fmax;
 
     Plan deflt;
-    km_status s = make_plan(pr, opt, g_variants, g_num_variants, generic_kernel(pr.dtype), deflt);
+    km_status s = make_plan(pr, opt, g_variants, g_num_variants, generic_kernel(pr.dtype), deflt, spare);
     if (s != KM_OK) return s;
 
     TuneScratch sc;
@@ -607,7 +608,8 @@ static km_status tune(const Problem& pr, const Options& opt, hipStream_t stream,
     if (!is_rows(deflt, -1)) {
         Options force = opt;
         force.prefer_instance = g_num_variants + 1;
-        have_rows = make_plan(pr, force, g_variants, g_num_variants, generic_kernel(pr.dtype), rows) == KM_OK &&
+        Plan none;
+        have_rows = make_plan(pr, force, g_variants, g_num_variants, generic_kernel(pr.dtype), rows, none) == KM_OK &&
                     is_rows(rows, -1) && launchable(rows.steps[0]);
     }
     RowmShape rs;
@@ -646,6 +648,7 @@ static km_status tune(const Problem& pr, const Options& opt, hipStream_t stream,
         if (plans[k] && t[k] < 0.99f * t[0] && t[k] < t[keep] &&
             plans[k]->ws0_bytes + plans[k]->ws1_bytes <= need_d) keep = k;
     chosen = *plans[keep];
+    if (chosen.ws0_bytes + chosen.ws1_bytes == 0) spare = Plan();
     if (tuned_ms) *tuned_ms = t[keep];
     if (default_ms) *default_ms = t[0];
     if (hipStreamSynchronize(stream) != hipSuccess) return KM_ELAUNCH;
@@ -765,11 +768,20 @@ static km_status execute(int M, int N, const int* P, const int* Q, const void* X
         return p != KM_OK ? p : s;
     }
     const Problem& pr = planned->pr;
-    const Plan& plan = planned->plan;
     s = check_pointers(pr, X, F, Y);
     if (s != KM_OK) return s;
+    auto needs = [&](const Plan& p) {
+        return transposed ? round_up(p.ws0_bytes + p.ws1_bytes, 256) + factor_copy_bytes(pr) : p.ws0_bytes + p.ws1_bytes;
+    };
+    // (where there is a spare plan, the other one takes a workspace of the caller's that is fit for it, or transposed factors,
+    // whose copies are in a workspace anyhow)
+    const size_t most = needs(planned->plan);
+    const bool spared = !planned->spare.steps.empty() &&
+                        !(kind == WS_CALLER ? workspace && workspace_bytes >= most && aligned(workspace, 16) && check_workspace(pr, X, Y, workspace, most) == KM_OK
+                                            : transposed);
+    const Plan& plan = spared ? planned->spare : planned->plan;
     const size_t plan_need = round_up(plan.ws0_bytes + plan.ws1_bytes, 256);
-    const size_t need = transposed ? plan_need + factor_copy_bytes(pr) : plan.ws0_bytes + plan.ws1_bytes;
+    const size_t need = needs(plan);
     void* ws = workspace;
     if (kind == WS_CALLER) {
         if (need > 0 && (!workspace || workspace_bytes < need)) return KM_ENOMEM;
@@ -897,7 +909,7 @@ km_status kronmatmul_tune(int M, int N, const int* P, const int* Q, km_dtype dty
     }
     auto made = std::make_shared<Planned>();
     made->pr = pr;
-    s = tune(pr, opt, (hipStream_t)stream, made->plan, tuned_ms, default_ms);
+    s = tune(pr, opt, (hipStream_t)stream, made->plan, made->spare, tuned_ms, default_ms);
     if (s != KM_OK) return s;
     for (const km_plan_step& st : made->plan.steps)
         if (!launchable(st)) return KM_EUNSUPPORTED;
@@ -917,8 +929,9 @@ km_status kronmatmul_prepare(int M, int N, const int* P, const int* Q, km_dtype 
     if (s != KM_OK) return s;
     const Plan& plan = planned->plan;
     std::vector<const void*> none(pr.N, nullptr);
-    for (const km_plan_step& st : plan.steps)
-        if (launch_step(pr, st, nullptr, nullptr, none.data(), nullptr, true) != hipSuccess) return KM_ELAUNCH;
+    for (const Plan* p : {&plan, &planned->spare})
+        for (const km_plan_step& st : p->steps)
+            if (launch_step(pr, st, nullptr, nullptr, none.data(), nullptr, true) != hipSuccess) return KM_ELAUNCH;
     void* unused;
     return static_scratch(&unused);          // kronmatmul_static finds its array's address resolved
 }

@@ -1231,10 +1231,12 @@ inline double tiled_us(const Problem& pr, const std::vector<km_plan_step>& steps
     return us;
 }
 
+// `spare`: where `plan` needs a workspace and stands in for a whole-row plan, that one; else without steps.
 inline km_status make_plan(const Problem& pr, const Options& opt, const Variant* table, int count,
-                           const GenericKernel& gen, Plan& plan)
+                           const GenericKernel& gen, Plan& plan, Plan& spare)
 {
     const int N = pr.N;
+    spare = Plan();
     std::vector<int64_t> width;
     row_widths(pr, width);
     // Grouping by dynamic programming over r: best[r] = cheapest way to apply factors 0..r-1.
@@ -1327,15 +1329,16 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
         }
     }
     // The whole-row plan, whichever kernel it is on, unless the finer estimates promise a tenth from tiled launches whose
-    // workspace fits the static array, as the whole-row plan's did: 9363 x (74x14, 18x5) 79 us in rows, 31 in two launches, 5058 x (18x4,
+    // workspace fits the static array: 9363 x (74x14, 18x5) 79 us in rows, 31 in two launches, 5058 x (18x4,
     // 39x3) 27 and 10; of 110 such problems 105 are faster tiled, by up to 5 times, since the generic kernel has its form for small
     // factors.  (Not so small compiled launches against the matrix-core rows: 300 x 2x2^2 fp64 3.9 us in rows, 6.6 tiled, 500 x 4x4^3 fp64
     // 4.7 and 6.3; 500 x 16x16^2 takes 4.2 and 3.8, but two launches of the host's.  Up to a row per compute unit the fixed costs
-    // decide, which these estimates do not know that well: one launch there.)
+    // decide, which these estimates do not know that well: one launch there.)  Calls that bring no such workspace keep the
+    // whole-row plan: they may run side by side on several streams, which calls that share one workspace may not.
     if (rows_us >= 0) {
         const bool tiled = !force_rows && pr.M > 256 && plan.ws0_bytes + plan.ws1_bytes <= KM_STATIC_SCRATCH_BYTES &&
                            tiled_us(pr, plan.steps, gen, true) < 0.9 * rows_us;
-        if (!tiled) plan = rows;
+        (tiled ? spare : plan) = rows;
     }
     if (inplace_fits(pr, opt) && inplace_wins(pr)) take_inplace_plan(pr, plan);
     if (cube_fits(pr, opt)) take_cube_plan(pr, plan);
@@ -1347,6 +1350,7 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
         one.tiles_per_wg = (int)((pr.M + one.grid - 1) / one.grid);
         one.tile_order = 2;
     }
+    if (plan.ws0_bytes + plan.ws1_bytes == 0) spare = Plan();
     return KM_OK;
 }
 
