@@ -344,7 +344,7 @@ KM_HOST_DEVICE constexpr int cube_stride(int E) { return E * E + (E + 64 - E * E
 // The fp32 kernels that leave digits in place (mfma_inplace_kernel.hpp).  The last two factors, both 48x48 or both
 // 64x64, are one launch with a tile of one matrix per wavefront, each factor before them (multiples of 16 up to 128) one
 // with tiles of DIGIT_COLS columns, in two stretches.
-constexpr int CHAIN_THREADS = 256, DIGIT_THREADS = 256, DIGIT_COLS = 512;
+constexpr int CHAIN_THREADS = 256, DIGIT_THREADS = 256, DIGIT_COLS = 512, DIGIT_STRETCH = DIGIT_COLS / 2;
 constexpr int CHAIN_VARIANT = -4, DIGIT_VARIANT = -5;      // km_plan_step.variant of their launches
 constexpr int INPLACE_ORDER = 4;                           // ... and tile_order
 
@@ -1133,6 +1133,17 @@ inline bool inplace_fits(const Problem& pr, const Options& opt)
     return w * (int64_t)pr.esize < (int64_t)1 << 31;
 }
 
+// Workgroups of a launch on a digit, at most one per compute unit: one for each stretch of columns while there are no more of
+// them than compute units, then one for two.  (A workgroup for two from the start left half the chip idle: 20 x (128x128,
+// 48x48^2) 65.6 us, 50.8 now, 26 x (96x96, 48x48^2) 47.3 and 38.3.  32 x (112x112, 48x48^2), 288 stretches: 63.4 us in 144
+// workgroups, 65.9 in 256.)
+inline int64_t digit_stretches(int64_t columns) { return (columns + DIGIT_STRETCH - 1) / DIGIT_STRETCH; }
+inline int64_t digit_grid(int64_t columns)
+{
+    const int64_t stretches = digit_stretches(columns), grid = stretches <= 256 ? stretches : (stretches + 1) / 2;
+    return grid < 256 ? grid : 256;
+}
+
 // ... and are they the faster ones?  From a matrix per wavefront of the first launch on (two workgroups of four on each
 // compute unit): 64 x 64x64^3 88 us as rotating launches, 78 here, 16 rows 28.9 and 36.8; 64 x 48x48^3 43.9 and 35.4, 16 rows 18.6
 // and 18.0, 4 rows 13.3 and 15.6; 1024 rows 1157 and 987, 513 and 359.  Two 64x64 factors alone have a whole-row instance
@@ -1163,23 +1174,22 @@ inline void take_inplace_plan(const Problem& pr, Plan& plan)
         st.tile_order = INPLACE_ORDER;
         st.tile_rows = 1;
         const int64_t P = pr.P[st.first_factor], Q = pr.Q[st.first_factor];
-        int64_t tiles, round;
+        int64_t tiles;
         if (st.num_factors == 2) {                       // two workgroups per compute unit
             st.variant = CHAIN_VARIANT;
             st.tile_slices = CHAIN_THREADS / 64;
             st.block = CHAIN_THREADS;
             st.lds_bytes = (int)(2 * P * P * (int64_t)pr.esize);
             tiles = (pr.M * (st.k_in / (P * P)) + st.tile_slices - 1) / st.tile_slices;
-            round = 512;
+            st.grid = tiles < 512 ? tiles : 512;
         } else {                                         // one
             st.variant = DIGIT_VARIANT;
             st.tile_slices = DIGIT_COLS;
             st.block = DIGIT_THREADS;
             st.lds_bytes = (int)(P * Q * (int64_t)pr.esize);
             tiles = (pr.M * (st.k_in / P) + st.tile_slices - 1) / st.tile_slices;
-            round = 256;
+            st.grid = digit_grid(pr.M * (st.k_in / P));
         }
-        st.grid = tiles < round ? tiles : round;
         st.tiles_per_wg = (int)((tiles + st.grid - 1) / st.grid);
         plan.bytes += (double)pr.M * ((double)st.k_in + (double)st.k_out) * pr.esize;
         plan.steps.push_back(st);

@@ -39,6 +39,13 @@ def test_plans_leave_every_digit_in_place_or_none():
         assert all(s["variant"] not in (CHAIN, DIGIT) for s in _plan(M, shapes, dtype)), (M, shapes, dtype)
 
 
+def test_a_digit_with_few_columns_has_a_workgroup_for_each_stretch_of_them():
+    for M, P, grid in ((24, 112, 216), (28, 96, 252), (57, 80, 256), (40, 96, 180)):
+        (_, st) = _plan(M, [(P, P)] + [(48, 48)] * 2)
+        assert st["variant"] == DIGIT and st["tile_slices"] == 512 and st["grid"] == grid
+        assert st["tiles_per_wg"] == -(-(-(-M * 2304 // 512)) // grid)
+
+
 @pytest.mark.parametrize("option,value", [("MAX_FUSE", 1), ("KERNELS", 51), ("TILE_ORDER", 2), ("TILES_PER_WG", 8), ("PREFER_TILE", 32)])
 def test_options_that_ask_for_other_kernels_get_them(option, value):
     key = getattr(km, "KM_OPT_" + option)
