@@ -1144,15 +1144,52 @@ inline int64_t digit_grid(int64_t columns)
     return grid < 256 ? grid : 256;
 }
 
+// Microseconds of the launches that leave digits in place, and of the rotating launches that they stand in for, fitted to 511
+// problems (5 and 6 % off): the first kernel by its matrices per wavefront, the others by their bytes or, where there are few
+// columns, by a wavefront's runs.
+inline double inplace_us(const Problem& pr)
+{
+    const int64_t last = pr.P[pr.N - 1];
+    int64_t w = pr.k_in;
+    double us = 13.7 + 18.2 * (double)(pr.M * (w / (last * last))) / 2048 * (double)(last * last * last) / (64 * 64 * 64);
+    for (int f = pr.N - 3; f >= 0; --f) {
+        const int64_t stretches = digit_stretches(pr.M * (w / pr.P[f])), to = w / pr.P[f] * pr.Q[f];
+        const double move = (double)pr.M * (double)(w + to) * (double)pr.esize / 5.85e6;
+        const double runs = (double)((stretches + 255) / 256) * (0.9 + 22.0 * pr.P[f] * pr.Q[f] / (128 * 128));
+        us += 2.7 + (move > runs ? move : runs);
+        w = to;
+    }
+    return us;
+}
+inline double rotating_us(const Problem& pr, const std::vector<km_plan_step>& steps)
+{
+    double us = 0;
+    for (const km_plan_step& st : steps) {
+        double flops = 0;
+        int64_t w = st.k_in;
+        for (int f = st.first_factor + st.num_factors - 1; f >= st.first_factor; --f) {
+            flops += 2.0 * (double)pr.M * (double)w * pr.Q[f];
+            w = w / pr.P[f] * pr.Q[f];
+        }
+        const double bytes = (double)pr.M * (double)(st.k_in + st.k_out) * (double)pr.esize;
+        const bool any = st.kernel != KM_KERNEL_MFMA, pair = !any && st.num_factors > 1;
+        const double move = bytes / (any ? 5.15e6 : pair ? 5.2e6 : 5.95e6), products = flops / (any ? 93e6 : pair ? 64.6e6 : 91e6);
+        us += (any ? 8.9 : pair ? 0.7 : 5.8) + (move > products ? move : products);
+    }
+    return us;
+}
+
 // ... and are they the faster ones?  From a matrix per wavefront of the first launch on (two workgroups of four on each
-// compute unit): 64 x 64x64^3 88 us as rotating launches, 78 here, 16 rows 28.9 and 36.8; 64 x 48x48^3 43.9 and 35.4, 16 rows 18.6
-// and 18.0, 4 rows 13.3 and 15.6; 1024 rows 1157 and 987, 513 and 359.  Two 64x64 factors alone have a whole-row instance
-// (65536 rows 0.570 ms, 0.594 here); two 48x48 ones were two launches (65536 rows 0.529 ms, 0.264 here, 4096 rows 46.5 us and 23.8).
-inline bool inplace_wins(const Problem& pr)
+// compute unit), and then by the estimates.  Two 64x64 factors alone have a whole-row instance (65536 rows 0.570 ms, 0.594 here); two
+// 48x48 ones were two launches (65536 rows 0.529 ms, 0.264 here, 4096 rows 46.5 us and 23.8).  With factors before them, rotating launches and these,
+// us: 1024 x 64x64^3 1157 and 987, 64 rows 88 and 79, 64 x 48x48^3 44 and 35, 256 x (96x96, 48x48^2) 308 and 223.  Rotating launches are
+// the faster ones where they take two leading factors at a time and where wide factors have few columns: 128 x (16x16^2, 64x64^2)
+// 569 and 669, 1 x (16x16^4, 48x48^2) 956 and 1134, 20 x (128x128, 48x48^2) 45 and 51, 1 x (128x128, 16x16, 48x48^2) 47 and 58.
+inline bool inplace_wins(const Problem& pr, const std::vector<km_plan_step>& steps)
 {
     const int P = pr.P[pr.N - 1];
-    if (pr.N == 2 && P == 64) return false;
-    return pr.M * (pr.k_in / (P * P)) >= 512 * (CHAIN_THREADS / 64);
+    if (pr.M * (pr.k_in / (P * P)) < 512 * (CHAIN_THREADS / 64)) return false;
+    return pr.N == 2 ? P == 48 : inplace_us(pr) < 0.97 * rotating_us(pr, steps);
 }
 
 inline void take_inplace_plan(const Problem& pr, Plan& plan)
@@ -1350,7 +1387,7 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
                            tiled_us(pr, plan.steps, gen, true) < 0.9 * rows_us;
         (tiled ? spare : plan) = rows;
     }
-    if (inplace_fits(pr, opt) && inplace_wins(pr)) take_inplace_plan(pr, plan);
+    if (inplace_fits(pr, opt) && inplace_wins(pr, plan.steps)) take_inplace_plan(pr, plan);
     if (cube_fits(pr, opt)) take_cube_plan(pr, plan);
     if (row4_fits(pr, opt)) {
         take_rows_plan(pr, ROW4_VARIANT, ROW4_THREADS, ROW4_LDS_BYTES, plan);

@@ -10,11 +10,12 @@ import paper_2401_10187_amd as km  # noqa: E402
 CHAIN, DIGIT = -4, -5
 
 # (rows, factors): as many matrices as wavefronts and one more; columns (Q) of every compiled count of blocks, contractions
-# of 16 to 128; fewer runs of columns than wavefronts and more, runs whose next one lies in another block; two leading digits
+# of 16 to 128; fewer runs of columns than wavefronts and more, runs whose next one lies in another block; two leading digits.  (54 rows of
+# (64x128, 48x48^2): 33 take 45.3 us with digits in place and 44.5 as rotating launches, which they are.)
 CASES = [(2048, [(48, 48)] * 2), (2051, [(48, 48)] * 2), (32, [(64, 64)] * 3), (43, [(48, 48)] * 3),
          (128, [(16, 16)] + [(48, 48)] * 2), (131, [(16, 32)] + [(64, 64)] * 2), (16, [(128, 16)] + [(64, 64)] * 2),
          (22, [(96, 96)] + [(48, 48)] * 2), (32, [(64, 112)] + [(64, 64)] * 2), (19, [(112, 80)] + [(48, 48)] * 2),
-         (33, [(64, 128)] + [(48, 48)] * 2), (8, [(16, 16), (16, 48)] + [(48, 48)] * 2), (5, [(32, 16), (16, 64)] + [(64, 64)] * 2)]
+         (54, [(64, 128)] + [(48, 48)] * 2), (8, [(16, 16), (16, 48)] + [(48, 48)] * 2), (5, [(32, 16), (16, 64)] + [(64, 64)] * 2)]
 
 
 def _plan(M, shapes, dtype="float32"):
@@ -37,6 +38,15 @@ def test_plans_leave_every_digit_in_place_or_none():
                              (64, [(48, 48)] * 3, "float64"), (64, [(64, 64)] * 2 + [(48, 48)], "float32"),
                              (64, [(24, 32)] + [(64, 64)] * 2, "float32"), (64, [(144, 16)] + [(48, 48)] * 2, "float32")):
         assert all(s["variant"] not in (CHAIN, DIGIT) for s in _plan(M, shapes, dtype)), (M, shapes, dtype)
+
+
+@pytest.mark.parametrize("M,shapes", [(128, [(16, 16)] * 2 + [(64, 64)] * 2), (8, [(16, 16)] * 3 + [(64, 64)] * 2), (1, [(16, 16)] * 4 + [(48, 48)] * 2),
+                                      (16, [(32, 32)] * 2 + [(64, 64)] * 2), (20, [(128, 128)] + [(48, 48)] * 2), (30, [(128, 128)] + [(48, 48)] * 2),
+                                      (19, [(128, 128)] + [(64, 64)] * 2), (1, [(32, 32), (128, 128)] + [(48, 48)] * 2),
+                                      (33, [(64, 128)] + [(48, 48)] * 2)], ids=str)
+def test_rotating_launches_stay_where_they_are_the_faster_ones(M, shapes):
+    """Leading factors that rotating launches take two at a time, and wide ones with few columns."""
+    assert all(s["variant"] not in (CHAIN, DIGIT) for s in _plan(M, shapes))
 
 
 def test_a_digit_with_few_columns_has_a_workgroup_for_each_stretch_of_them():
