@@ -1,18 +1,20 @@
 // All factors of a row of 4^7 floats in one launch: 4x4 ones, two 2x2 ones in the place of each as it comes.  X is read and Y
 // written once.
 //
-// A row is seven digits of two bits.  A thread holds two digits (sixteen values) at a time and applies their
-// factors in registers; three exchanges through LDS give it the next two.  Digits stay where they are in the row, so
-// a thread writes its results over what it has read and an exchange takes one barrier; the one between
-// the second and the third pair of digits stays within a wavefront and takes none.  The first pair is the lowest digit,
-// a 16-byte vector, with the highest one, and the last digit is applied to whole vectors of the lowest, so
-// every load and store of global memory is 1 KB in a piece.  LDS strides are padded against bank conflicts
-// (8 % of the cycles in which LDS is busy, which are 17 % of all).  Factors are wave-uniform: scalar loads, as in fused_kernel.hpp.
+// A row is seven digits of two bits.  A thread holds one or two digits (sixteen values) at a time and applies their
+// factors in registers, the last digit first, as Algorithm 1 does; four exchanges through LDS give it the next ones.  Digits
+// stay where they are in the row, so a thread writes its results over what it has read and an exchange takes one barrier;
+// those between digits 6 and 5 and digits 4 and 3, and between the first two digits, stay within a wavefront and take none.
+// The last digit is a 16-byte vector and the first two are applied to whole vectors of it, so every load and store of global memory is
+// 256 bytes or more in a piece.  LDS strides are padded against bank conflicts.  Factors are wave-uniform: scalar loads,
+// as in fused_kernel.hpp.
 //
-// Bound by memory: 1024 rows take 23 us (5.8 TB/s, 37.3 before), 20000 rows 463 us (5.7 TB/s, 552 before); 1024 rows of 2^14 23 us
-// (34 before).  The kernel that ran these rows (fused_multi_kernel.hpp with four super-stages) gave a row to 256
+// Bound by memory: 1024 rows take 23 us (5.8 TB/s; 37.7 before), 20000 rows 449 us (5.8 TB/s; 569 before); 1024 rows of 2^14 23 us
+// (35 before).  The kernel that ran these rows (fused_multi_kernel.hpp with four super-stages) gave a row to 256
 // threads that load, multiply and store it in turn, all workgroups in step; here the next row is on its way into
-// registers meanwhile (16 more of the 64 that two workgroups of 1024 threads leave a thread).
+// registers meanwhile (16 more of the 64 that two workgroups of 1024 threads leave a thread).  (The first two digits in
+// one stage, sixteen values, results stored 4 bytes a lane: one exchange less, 24.2 us.  Digits in the order 7, 1, 4, 3, 6, 5, 2, three
+// exchanges: 21.9 us, but intermediates overflow that do not in Algorithm 1's order.)
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -103,39 +105,20 @@ void fused_row4_multiply(const float* __restrict__ Xg, float* __restrict__ Yg, R
     for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(x[k]));      // (waited for here: in the loop the compiler would wait for the stores behind them too)
     for (int64_t row = blockIdx.x; row < num_rows; row += gridDim.x) {
         float a[4][4], b[4][4];
-        // digits 7 (in a vector) and 1 (vector k)
+        // digit 7, in a vector; vector k is digit 1
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
             for (int e = 0; e < 4; ++e) a[e][k] = x[k][e];
         if (row + gridDim.x < num_rows) fetch(row + gridDim.x);
         row4_apply(fa, 7, a);
-        row4_transpose(a, b);
-        row4_apply(fa, 1, b);
         {
             float* to = lds + (w / 4) * BLOCK + (w % 4) * D3 + (l / 16) * D4 + (l % 16) * 4;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) *reinterpret_cast<V*>(to + k * 4 * BLOCK) = V{b[k][0], b[k][1], b[k][2], b[k][3]};
+            for (int k = 0; k < 4; ++k) *reinterpret_cast<V*>(to + k * 4 * BLOCK) = V{a[0][k], a[1][k], a[2][k], a[3][k]};
         }
         __syncthreads();
-        // digits 4 and 3: this wavefront's block of 1024, lanes along digits 5 to 7
-        {
-            float* at = lds + w * BLOCK + l;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) a[j][i] = at[i * D3 + j * D4];
-            row4_apply(fa, 4, a);
-            row4_transpose(a, b);
-            row4_apply(fa, 3, b);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) at[i * D3 + j * D4] = b[i][j];
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");           // (within the wavefront: no barrier)
-        __builtin_amdgcn_wave_barrier();
-        // digits 6 and 5 of the same block, lanes along digits 3, 4 and 7
+        // digits 6 and 5: this wavefront's block of 1024, lanes along digits 3, 4 and 7
         {
             float* at = lds + w * BLOCK + (l / 16) * D3 + (l / 4 % 4) * D4 + l % 4;
 #pragma unroll
@@ -150,22 +133,52 @@ void fused_row4_multiply(const float* __restrict__ Xg, float* __restrict__ Yg, R
 #pragma unroll
                 for (int j = 0; j < 4; ++j) at[i * 16 + j * 4] = b[i][j];
         }
-        __syncthreads();
-        // digit 2, whole vectors of digit 7, lanes along digits 4 to 6
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");           // (within the wavefront: no barrier)
+        __builtin_amdgcn_wave_barrier();
+        // digits 4 and 3 of the same block, lanes along digits 5 to 7
         {
-            const float* from = lds + (w / 4) * 4 * BLOCK + (w % 4) * D3 + (l / 16) * D4 + (l % 16) * 4;
+            float* at = lds + w * BLOCK + l;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) a[j][i] = at[i * D3 + j * D4];
+            row4_apply(fa, 4, a);
+            row4_transpose(a, b);
+            row4_apply(fa, 3, b);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) at[i * D3 + j * D4] = b[i][j];
+        }
+        __syncthreads();
+        // digit 2, whole vectors of digit 7, wavefronts along digits 3 and 4, lanes along digits 1, 5 and 6
+        float* const to = lds + (w / 4) * D3 + (w % 4) * D4 + (l % 16) * 4;
+        {
+            float* at = to + (l / 16) * 4 * BLOCK;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const V v = *reinterpret_cast<const V*>(from + k * BLOCK);
+                const V v = *reinterpret_cast<const V*>(at + k * BLOCK);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) a[k][e] = v[e];
             }
+            row4_apply(fa, 2, a);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) *reinterpret_cast<V*>(at + k * BLOCK) = V{a[k][0], a[k][1], a[k][2], a[k][3]};
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        // digit 1, lanes along digits 2, 5 and 6
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const V v = *reinterpret_cast<const V*>(to + ((l / 16) + 4 * k) * BLOCK);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[k][e] = v[e];
         }
         __syncthreads();                               // read by everybody: the next row may be written
-        row4_apply(fa, 2, a);
-        float* const y = Yg + row * ROW + (w / 4) * 4096 + (w % 4) * 256 + 4 * l;
+        row4_apply(fa, 1, a);
+        float* const y = Yg + row * ROW + (l / 16) * 1024 + w * 64 + (l % 16) * 4;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) stream_store(V{a[k][0], a[k][1], a[k][2], a[k][3]}, reinterpret_cast<V*>(y + k * 1024));
+        for (int k = 0; k < 4; ++k) stream_store(V{a[k][0], a[k][1], a[k][2], a[k][3]}, reinterpret_cast<V*>(y + k * 4096));
     }
 }
 
