@@ -70,8 +70,7 @@ typedef enum { KM_BUF_X = 0, KM_BUF_Y = 1, KM_BUF_WS0 = 2, KM_BUF_WS1 = 3 } km_b
  * F, applied last to first) map rows of width k_in to rows of width k_out. */
 typedef struct {
     int kernel;            /* km_kernel                                                            */
-    int first_factor;      /* lowest factor index in this step (with variant -7 and two steps, the
-                              second one has the factors at both ends)                             */
+    int first_factor;      /* lowest factor index in this step                                     */
     int num_factors;       /* factors fused in this launch (N_fused of section 4.2)                */
     int tile_slices;       /* contiguous output run per tile and fused column (T_K / prod P)       */
     long long k_in;        /* row width read                                                       */
@@ -90,8 +89,10 @@ typedef struct {
     int tiles_per_wg;      /* tiles one workgroup walks over (0: one tile per workgroup)           */
     int tile_order;        /* walk: 0 contiguous range, 1 interleaved pairs, 2 strided by the grid,
                               3 strided inside the XCD's eighth of the tiles, 4 strided by the grid
-                              with the digits left in place: the rows between the launches of such
-                              a plan keep the order of their digits                                */
+                              (variant -7: inside the XCD's eighth), the rows between the launches of
+                              such a plan not being in Algorithm 1's order: variants -4 and -5 leave
+                              the digits in place, the first of two steps with variant -7 puts the
+                              third quarter of the digits in front                                 */
     int tile_rows;         /* rows per tile (the T_M of section 4); above 1 only when a tile holds
                               whole rows, tile_slices then being the slices of one row            */
 } km_plan_step;

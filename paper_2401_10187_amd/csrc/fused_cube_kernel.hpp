@@ -1,24 +1,22 @@
 // Rows of P^(3G) floats in one launch and of P^(4G) floats in two, square factors of an odd size P (fp32; P = 5 with G = 2 and
 // P = 3 with G = 3).
 //
-// A tile is a cube: three groups of G digits, E = P^G values each (5^6 = 25^3, 3^9 = 27^3 elements).  A thread holds the E values
-// of one group in registers, applies the group's factors to them and changes to the next group through LDS.  Digits stay
-// where they are, so a thread writes its values over those it has read, and an exchange takes one barrier.  A row of 3G
-// digits is one tile.  A row of 4G digits takes two launches, and since digits stay in place each may have the groups
-// that lie best for it: the first one applies groups 2 and 3 to contiguous tiles of groups 2 to 4, the second one
-// groups 1 and 4 to tiles of E runs of E^2 elements, one for each value of group 1.  Rotating digits, as Algorithm 1
-// does, leave a launch of such a row with output runs of E elements (100 bytes) in the way of whole lines.
-// Lanes run along the two groups behind the one in registers, so global loads and stores are runs of E^2 elements, 4 bytes a
-// lane (rows of odd length start on no boundary); the LDS stride of the first group is congruent to E modulo the 64
-// banks, so an access meets a bank twice only at the ends of runs (19 % of the cycles in which LDS is busy, which are 17 % of all).
-// The next tile's loads are issued before the current one is multiplied.
+// A tile is a cube: three groups of G digits, E = P^G values each (5^6 = 25^3, 3^9 = 27^3 elements), contiguous where it is
+// read.  A thread holds the E values of one group in registers, applies the group's factors to them and changes to the group before it
+// through LDS; the last group comes first, as in Algorithm 1.  Digits stay where they are, so a thread writes its values over
+// those it has read, and an exchange takes one barrier.  A row of 3G digits is one tile.  A row of 4G digits takes two launches of two
+// groups each.  The first one leaves the row in an order that makes the second one's tiles contiguous too, and writes it in runs of
+// E^2 elements; the second one's results are runs of E elements (100 and 108 bytes), which cost it a quarter of its rate.  (The two middle groups
+// first, then the two outer ones, reads and writes all runs of E^2, 1000 x 5x5^8 1.26 ms, but intermediates overflow that do
+// not in Algorithm 1's order.  Three groups and one, 1.32.)
+// Lanes run along the two groups behind the one in registers, 4 bytes a lane (rows of odd length start on no boundary); the LDS
+// stride of the first group is congruent to E modulo the 64 banks, so an access meets a bank twice only at the ends of
+// runs.  The next tile's loads are issued before the current one is multiplied.
 //
-// Bound by memory.  1000 x 5x5^8 1.61 -> 1.25 ms (two launches of 0.61 and 0.63, 5.1 TB/s; a plain copy of X takes 0.58), 40 rows
-// 0.076 -> 0.053; 1000 x 3x3^12 2.00 -> 1.69; 1024 x 5x5^6 42 -> 32 us, 1024 x 3x3^9 46 -> 34.  (What ran these rows,
+// Bound by memory.  1000 x 5x5^8 1.61 -> 1.34 ms (two launches of 0.60 and 0.74; a plain copy of X takes 0.58), 40 rows
+// 75 -> 56 us; 1000 x 3x3^12 1.99 -> 1.83; 1024 x 5x5^6 42 -> 31 us, 4096 rows 142 -> 121; 1024 x 3x3^9 46 -> 34.  (What ran these rows,
 // fused_multi_kernel.hpp, loads, multiplies and stores a tile in turn and stores element-sized pieces of 100 and 108 bytes.)
-// For the two launches one workgroup per compute unit is faster than two from a few thousand tiles on (1000 x 5x5^8 1.24 ms and 1.31, 40
-// rows 0.063 and 0.053), with three groups two are (4096 x 5x5^6 131 us and 117).  Loads are ordinary ones: at the ends of a
-// wavefront's 256 bytes its neighbour reads the same lines (non-temporal 0.64 and 0.66 ms, stores too 0.67 and 0.68).
+// Loads are ordinary ones: at the ends of a wavefront's 256 bytes its neighbour reads the same lines.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -36,7 +34,7 @@ struct CubeShape {
     static constexpr int LDS_BYTES = E * S1 * 4;
     static constexpr int WAVES = 2 * (NT / 64) / 4;    // two workgroups per compute unit, per SIMD
 };
-// The factors of a group in the order of the Kronecker product; f[0] null: the group is left as it is.
+// The factors of each group in the order of the Kronecker product.
 struct CubeFactors {
     const float* f[3][3];
 };
@@ -68,19 +66,20 @@ __device__ __forceinline__ void cube_apply(const float* const (&f)[3], float (&d
     }
 }
 
-// Tile t = (m, h): E runs of EE elements, `run` apart, from m * group + h * EE on.
-template <int P, int G>
+// PART 0: rows of three groups, all factors.  Rows of four groups g1 ... g4: PART 1 applies the last two to tiles (row, g1) of
+// X and leaves the row in the order g3, g1, g2, g4, which makes tiles (row, g3) contiguous too; PART 2 applies the first two to those.
+template <int P, int G, int PART>
 __global__ __launch_bounds__((CubeShape<P, G>::NT), (CubeShape<P, G>::WAVES))
-void fused_cube_multiply(const float* __restrict__ Xg, float* __restrict__ Yg, CubeFactors fa, int64_t tiles, int64_t tiles_per_group,
-                         int64_t group, int64_t run)
+void fused_cube_multiply(const float* __restrict__ Xg, float* __restrict__ Yg, CubeFactors fa, int64_t tiles)
 {
     typedef CubeShape<P, G> Sh;
     constexpr int E = Sh::E, EE = Sh::EE, S1 = Sh::S1;
+    constexpr int64_t EEE = (int64_t)E * EE;
     extern __shared__ __attribute__((aligned(16))) unsigned char cube_lds[];
     float* const lds = reinterpret_cast<float*>(cube_lds);
     const int u = (int)threadIdx.x < EE ? (int)threadIdx.x : EE - 1;     // (what is left of the last wavefront does the last one's work again: no access hangs on a condition)
     const int ua = u / E, ub = u % E;
-    const uint32_t u4 = (uint32_t)u * 4u;
+    const uint32_t in4 = (uint32_t)u * 4u, out4 = PART == 2 ? (uint32_t)(ua * EE + ub) * 4u : in4;
 
     // each XCD (workgroup b runs on XCD b % 8) walks its own part of the tiles; grids that do not split by 8: one tile each
     int64_t first = blockIdx.x, step = gridDim.x, end = tiles;
@@ -92,14 +91,13 @@ void fused_cube_multiply(const float* __restrict__ Xg, float* __restrict__ Yg, C
     }
 
     float x[E];
-    auto base = [&](int64_t t) __attribute__((always_inline)) { return t / tiles_per_group * group + t % tiles_per_group * EE; };
     auto fetch = [&](int64_t t) __attribute__((always_inline)) {
-        const char* src = reinterpret_cast<const char*>(Xg + base(t));
-        int64_t go = run * 4;
+        const char* src = reinterpret_cast<const char*>(Xg + t * EEE);
+        int64_t go = EE * 4;
         asm volatile("" : "+s"(go));                   // (multiples of it would be held in scalar registers, and spill)
 #pragma unroll
         for (int k = 0; k < E; ++k) {
-            x[k] = *reinterpret_cast<const float*>(src + u4);
+            x[k] = *reinterpret_cast<const float*>(src + in4);
             src += go;
         }
     };
@@ -112,44 +110,40 @@ void fused_cube_multiply(const float* __restrict__ Xg, float* __restrict__ Yg, C
     for (int64_t t = first; t < end; t += step) {
         float d[E];
 #pragma unroll
-        for (int k = 0; k < E; ++k) d[k] = x[k];
-        if (t + step < end) fetch(t + step);
-        if (fa.f[0][0]) cube_apply<P, G>(fa.f[0], d);
-#pragma unroll
-        for (int k = 0; k < E; ++k) lds[k * S1 + u] = d[k];
+        for (int k = 0; k < E; ++k) lds[k * S1 + u] = x[k];
         __syncthreads();
-        if (fa.f[1][0]) {
-            {
-                float* at = lds + ua * S1 + ub;
+        if (t + step < end) fetch(t + step);
+        if constexpr (PART != 2) {                     // the tile's third group
+            float* at = lds + ua * S1 + ub * E;
 #pragma unroll
-                for (int k = 0; k < E; ++k) d[k] = at[k * E];
+            for (int k = 0; k < E; ++k) d[k] = at[k];
+            cube_apply<P, G>(fa.f[2], d);
+#pragma unroll
+            for (int k = 0; k < E; ++k) at[k] = d[k];
+            __syncthreads();
+        }
+        {                                              // the second
+            float* at = lds + ua * S1 + ub;
+#pragma unroll
+            for (int k = 0; k < E; ++k) d[k] = at[k * E];
+            if constexpr (PART != 1) {
                 cube_apply<P, G>(fa.f[1], d);
 #pragma unroll
                 for (int k = 0; k < E; ++k) at[k * E] = d[k];
+                __syncthreads();
+#pragma unroll
+                for (int k = 0; k < E; ++k) d[k] = lds[k * S1 + u];
             }
-            __syncthreads();
         }
-        if (fa.f[2][0]) {
-            {
-                float* at = lds + ua * S1 + ub * E;
-#pragma unroll
-                for (int k = 0; k < E; ++k) d[k] = at[k];
-                cube_apply<P, G>(fa.f[2], d);
-#pragma unroll
-                for (int k = 0; k < E; ++k) at[k] = d[k];
-            }
-            __syncthreads();
-        }
-#pragma unroll
-        for (int k = 0; k < E; ++k) d[k] = lds[k * S1 + u];
         __syncthreads();                               // read by everybody: the next tile may be written
+        cube_apply<P, G>(fa.f[PART == 1 ? 1 : 0], d);
         {
-            char* dst = reinterpret_cast<char*>(Yg + base(t));
-            int64_t go = run * 4;
+            char* dst = reinterpret_cast<char*>(Yg + (PART == 0 ? t * EEE : t / E * (EEE * E) + t % E * (PART == 1 ? EE : E)));
+            int64_t go = (PART == 0 ? EE : EEE) * 4;
             asm volatile("" : "+s"(go));
 #pragma unroll
             for (int k = 0; k < E; ++k) {
-                *reinterpret_cast<float*>(dst + u4) = d[k];
+                *reinterpret_cast<float*>(dst + out4) = d[k];
                 dst += go;
             }
         }

@@ -1097,17 +1097,21 @@ inline void take_cube_plan(const Problem& pr, Plan& plan)
         km_plan_step st{};
         st.kernel = KM_KERNEL_FUSED;
         st.variant = CUBE_VARIANT;
-        // (two launches: the factors in the middle, then those at both ends)
         st.num_factors = pr.N / launches;
-        st.first_factor = launches == 2 && i == 0 ? G : 0;
+        st.first_factor = launches == 2 && i == 0 ? 2 * G : 0;
         st.tile_slices = launches == 2 ? (int)E : 1;
         st.tile_rows = 1;
         st.k_in = st.k_out = pr.k_in;
         st.block = (int)((E * E + 63) / 64 * 64);
         st.lds_bytes = (int)(E * cube_stride((int)E) * (int64_t)pr.esize);
         st.tile_order = INPLACE_ORDER;
-        const int64_t tiles = pr.M * (pr.k_in / (E * E * E)), most = launches == 2 && tiles >= 4096 ? 256 : 512;
-        st.grid = tiles < most ? tiles : most;
+        const int64_t tiles = pr.M * (pr.k_in / (E * E * E));
+        // (Two workgroups to a compute unit that walk; with two launches and thousands of tiles a workgroup for each, in multiples of 8 for
+        // the order of the tiles, us in both launches: 100 x 5x5^8 162 and 155, 250 rows 442 and 355, 1000 rows 1783 and 1343, but 40
+        // rows 56 and 63.  Walking workgroups drift apart, and lines that neighbouring tiles share are moved twice; the
+        // limit keeps a launch below 2^32 work-items.)
+        const int64_t limit = (int64_t)1 << 20;
+        st.grid = launches == 2 && tiles >= 2500 ? (tiles < limit ? tiles : limit) / 8 * 8 : tiles < 512 ? tiles : 512;
         st.tiles_per_wg = (int)((tiles + st.grid - 1) / st.grid);
         plan.bytes += (double)pr.M * 2.0 * (double)pr.k_in * pr.esize + (double)st.num_factors * pr.P[0] * pr.P[0] * pr.esize;
         plan.steps.push_back(st);

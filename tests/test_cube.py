@@ -70,3 +70,18 @@ def test_matches_the_reference(M, P, N):
             bad = km.kronmatmul(torch.from_numpy(X).cuda(), Fd)
             rest = [r for r in range(M) if r not in (1, M - 1)]
             assert torch.equal(bad[rest], Y[rest]) and not torch.isfinite(bad[[1, M - 1]]).any()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,P,N", [(3, 5, 6), (3, 5, 8), (3, 3, 9), (2, 3, 12)], ids=str)
+def test_factors_are_applied_last_to_first(M, P, N):
+    """Scaling by powers of two changes no rounding as long as nothing overflows: of two neighbours the later one makes values small
+    and the earlier one large again, so any other order of the two is infinite."""
+    X, Fs = kron_inputs.make_problem(M, [(P, P)] * N, "float32", "uniform", "normal", seed=92)
+    Xd, Fd = torch.from_numpy(X).cuda(), [torch.from_numpy(F).cuda() for F in Fs]
+    assert {s["variant"] for s in _plan(M, [(P, P)] * N)} == {CUBE}
+    want = km.kronmatmul(Xd, Fd) * 2.0 ** 60
+    for i in range(N - 1):
+        scaled = list(Fd)
+        scaled[i], scaled[i + 1] = Fd[i] * 2.0 ** 80, Fd[i + 1] * 2.0 ** -80
+        assert torch.equal(km.kronmatmul(Xd * 2.0 ** 60, scaled), want), i

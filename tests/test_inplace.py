@@ -107,3 +107,17 @@ def test_what_is_not_finite_stays_in_its_row_and_stores_keep_to_y(M, shapes):
     assert torch.equal(got[rest], clean[rest])
     assert not torch.isfinite(got[[3, 7, M - 1]]).any()
     assert (frame[:1024] == -7).all() and (frame[1024 + n:] == -7).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,shapes", [(2048, [(48, 48)] * 2), (32, [(64, 64)] * 3), (8, [(16, 16), (16, 48)] + [(48, 48)] * 2)], ids=str)
+def test_factors_are_applied_last_to_first(M, shapes):
+    """Scaling by powers of two changes no rounding as long as nothing overflows: of two neighbours the later one makes values small
+    and the earlier one large again, so any other order of the two is infinite."""
+    X, Fs = kron_inputs.make_problem(M, shapes, "float32", "uniform", "normal", seed=93)
+    Xd, Fd = torch.from_numpy(X).cuda(), [torch.from_numpy(F).cuda() for F in Fs]
+    want = km.kronmatmul(Xd, Fd) * 2.0 ** 60
+    for i in range(len(Fd) - 1):
+        scaled = list(Fd)
+        scaled[i], scaled[i + 1] = Fd[i] * 2.0 ** 80, Fd[i + 1] * 2.0 ** -80
+        assert torch.equal(km.kronmatmul(Xd * 2.0 ** 60, scaled), want), i
