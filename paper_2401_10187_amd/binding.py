@@ -1,8 +1,10 @@
 """Binding of the C-ABI in include/kronmatmul.h, by ctypes and, for calls of plain tensors, by a native part
 (csrc/marshal.cpp).  Argument marshalling only: every step of
-the computation runs in the HIP library.  There is no fallback: a missing library is an error."""
+the computation runs in the HIP library.  There is no fallback for it: a missing library is an error.  Without the native part,
+which is built for one Python and one torch, all calls go by ctypes."""
 import ctypes
 import os
+import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libkronmatmul.so")
@@ -260,17 +262,36 @@ def _raise_status(status, transposed, with_ws):
     raise KronMatmulError(status, _entry_name(with_ws, transposed))
 
 
+class _ByCtypes:
+    """In the place of a native part that cannot be loaded: takes no call."""
+
+    @staticmethod
+    def call(*args):
+        return NotImplemented
+
+    @staticmethod
+    def bind(*args):
+        return None
+
+
 def _start_native():
     """Loads the native part and hands it the library's entry points.  It takes calls of plain tensors; what it declines goes
     through _marshal below, which also says what is wrong with it."""
     global _native
-    import torch  # noqa: F401 - the native part is linked against torch's libraries, which this loads
+    import torch      # the native part is linked against torch's libraries, which this loads
     L = lib()
-    if not os.path.exists(os.path.join(HERE, "_marshal.so")):
-        raise RuntimeError("the binding's native part _marshal.so is missing: run `python -c 'import __graft_entry__ as g; g.build()'`")
-    from . import _marshal as native
-    address = [ctypes.cast(getattr(L, _entry_name(ws, t)), ctypes.c_void_p).value for ws in (False, True) for t in (False, True)]
-    native.start(*address, _stream_getter(), _raise_status)
+    try:
+        from . import _marshal as native
+        built_for = getattr(native, "built_for", None)
+        if built_for != torch.__version__:
+            raise ImportError("built for torch %s, this is %s" % (built_for, torch.__version__))
+    except ImportError as e:
+        warnings.warn("the binding's native part cannot be used, calls take 2 to 4 us longer (`python -c 'import __graft_entry__ "
+                      "as g; g.build()'` builds it): %s" % e, RuntimeWarning, stacklevel=3)
+        native = _ByCtypes
+    else:
+        address = [ctypes.cast(getattr(L, _entry_name(ws, t)), ctypes.c_void_p).value for ws in (False, True) for t in (False, True)]
+        native.start(*address, _stream_getter(), _raise_status)
     _native = native
     return native
 
@@ -293,10 +314,10 @@ class Prepared:
     def __call__(self, stream=None):
         """Enqueue on `stream` (a raw hipStream_t value; default: torch's current stream).  The
         tensors' device must be the current device."""
-        if stream is None or type(stream) is int:
+        if self._bound is not None and (stream is None or type(stream) is int):
             self._bound(stream)
         else:
-            _check(self._fn(*self._args, stream), self._what)
+            _check(self._fn(*self._args, _current_stream(self._device) if stream is None else stream), self._what)
         return self.Y
 
 

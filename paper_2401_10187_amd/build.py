@@ -1,4 +1,6 @@
-"""Compile the HIP library for gfx950 into paper_2401_10187_amd/libkronmatmul.so (in-tree), and the binding's native part for this Python and torch into paper_2401_10187_amd/_marshal.so.
+"""Compile the HIP library for gfx950 into paper_2401_10187_amd/libkronmatmul.so (in-tree), and the binding's native part for
+this Python and torch into paper_2401_10187_amd/_marshal.<this Python's suffix>.so.  The library is needed; without the native part
+the binding marshals by ctypes.
 
 The kernel instances are spread over one translation unit per kernel family (csrc/inst_*.hip) so that
 they compile side by side; csrc/kronmatmul.hip holds the C-ABI, the planner and the two kernels
@@ -6,6 +8,7 @@ without compile-time shapes."""
 import glob
 import importlib.util
 import os
+import re
 import subprocess
 import sysconfig
 import time
@@ -15,7 +18,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libkronmatmul.so")
-MARSHAL = os.path.join(HERE, "_marshal.so")
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
+MARSHAL_SOURCE = os.path.join(CSRC, "marshal.cpp")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -34,7 +38,7 @@ def _run(cmd, verbose):
         print("%.0f s: %s" % (time.time() - t0, os.path.basename(cmd[-1])), flush=True)
     out = "\n".join(l for l in proc.stdout.splitlines() if "packed-fp32-ops" not in l)
     if proc.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError("%s failed:\n%s" % (os.path.basename(cmd[0]), out))
     if verbose and out.strip():
         print(out, flush=True)
 
@@ -53,13 +57,41 @@ def _stale(obj):
     return any(not os.path.exists(n) or os.path.getmtime(n) > t for n in names)
 
 
+def _torch_version(torch_dir):
+    """torch.__version__, without the import."""
+    return re.search(r"^__version__ = '(.*)'", open(os.path.join(torch_dir, "version.py")).read(), re.M).group(1)
+
+
+def _marshal_stale():
+    """True unless the native part is newer than its source and built for the torch at hand (whose version is kept beside the objects)."""
+    try:
+        torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
+        return (os.path.getmtime(MARSHAL) < os.path.getmtime(MARSHAL_SOURCE) or
+                open(os.path.join(OBJ, "marshal.torch")).read() != _torch_version(torch_dir))
+    except (OSError, AttributeError):
+        return True
+
+
 def build_marshal(verbose=False):
-    """Host code only: the headers of Python and torch, linked against the torch libraries that `import torch` loads."""
-    torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
-    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"],
-          "-isystem", os.path.join(torch_dir, "include"), "-isystem", os.path.join(torch_dir, "include/torch/csrc/api/include"),
-          "-o", MARSHAL, os.path.join(CSRC, "marshal.cpp"), "-L" + os.path.join(torch_dir, "lib"), "-lc10", "-ltorch_cpu",
-          "-ltorch_python"], verbose)
+    """Host code only: the headers of Python and torch, linked against the torch libraries that `import torch` loads.  Returns
+    whether that worked: a machine without a C++ compiler or these headers has the library all the same."""
+    for old in {MARSHAL, os.path.join(HERE, "_marshal.so")}:       # (nothing older is left to be loaded in its place)
+        if os.path.exists(old):
+            os.remove(old)
+    try:
+        torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
+        version = _torch_version(torch_dir)
+        _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"],
+              "-isystem", os.path.join(torch_dir, "include"), "-isystem", os.path.join(torch_dir, "include/torch/csrc/api/include"),
+              '-DKM_BUILT_FOR="%s"' % version,
+              "-o", MARSHAL, MARSHAL_SOURCE, "-L" + os.path.join(torch_dir, "lib"), "-lc10", "-ltorch_cpu",
+              "-ltorch_python"], verbose)
+        with open(os.path.join(OBJ, "marshal.torch"), "w") as f:
+            f.write(version)
+    except (OSError, AttributeError, RuntimeError) as e:
+        print("the binding's native part was not built, calls are marshalled by ctypes: %s" % e, flush=True)
+        return False
+    return True
 
 
 def build(verbose=False, jobs=None, incremental=False):
@@ -71,10 +103,9 @@ def build(verbose=False, jobs=None, incremental=False):
     objs = [os.path.join(OBJ, os.path.basename(s)[:-4] + ".o") for s in srcs]
     todo = [(s, o) for s, o in zip(srcs, objs) if not incremental or _stale(o)]
     jobs = jobs or min(max(len(todo), 1), os.cpu_count() or 1, 16)
-    source = os.path.join(CSRC, "marshal.cpp")
     with ThreadPoolExecutor(max_workers=jobs) as pool:
         marshal = None
-        if not incremental or not os.path.exists(MARSHAL) or os.path.getmtime(MARSHAL) < os.path.getmtime(source):
+        if not incremental or _marshal_stale():
             marshal = pool.submit(build_marshal, verbose)
         list(pool.map(lambda so: _run([hipcc] + HIPCC_FLAGS + ["-MD", "-MF", so[1][:-2] + ".d", "-c", "-o", so[1], so[0]],
                                       verbose), todo))

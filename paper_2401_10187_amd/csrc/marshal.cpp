@@ -235,5 +235,7 @@ PyMODINIT_FUNC PyInit__marshal(void)
     BoundType.tp_call = PyVectorcall_Call;
     BoundType.tp_dealloc = bound_dealloc;
     if (PyType_Ready(&BoundType) < 0) return nullptr;
-    return PyModule_Create(&module);
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", KM_BUILT_FOR) < 0) Py_CLEAR(m);      // the torch whose headers these are
+    return m;
 }

@@ -1,6 +1,9 @@
 """The binding's native part (csrc/marshal.cpp): what it takes gives what the long way gives, and what it declines, or refuses,
 is what the long way takes or refuses."""
 import ctypes
+import os
+import sys
+import warnings
 
 import pytest
 
@@ -20,6 +23,47 @@ def test_mistakes_are_named_without_a_gpu():
     assert native.call(torch.zeros(2, 4), iter(()), None, None, 0) is NotImplemented
     with pytest.raises(TypeError):
         native.call(1, 2)
+
+
+@pytest.fixture
+def no_native(monkeypatch):
+    """The binding as it is where the native part cannot be imported."""
+    monkeypatch.setattr(B, "_native", None)
+    monkeypatch.delattr(km, "_marshal", raising=False)
+    monkeypatch.setitem(sys.modules, km.__name__ + "._marshal", None)
+
+
+def test_without_the_native_part_calls_go_by_ctypes(no_native):
+    with pytest.warns(RuntimeWarning, match="native part"), pytest.raises(ValueError, match="contiguous 2-D CUDA tensor"):
+        km.kronmatmul(torch.zeros(2, 4), [torch.zeros(2, 2)] * 2)
+    with warnings.catch_warnings():                      # said once
+        warnings.simplefilter("error")
+        with pytest.raises(ValueError, match="contiguous 2-D CUDA tensor"):
+            km.kronmatmul(torch.zeros(2, 4), [torch.zeros(2, 2)] * 2)
+
+
+def test_a_native_part_of_another_torch_is_not_used(monkeypatch):
+    native = B._start_native()
+    monkeypatch.setattr(B, "_native", None)
+    monkeypatch.setattr(native, "built_for", "1.0")
+    with pytest.warns(RuntimeWarning, match="built for torch 1.0"):
+        assert B._start_native() is not native
+
+
+def test_the_library_builds_without_the_native_part(monkeypatch, tmp_path, capsys):
+    from paper_2401_10187_amd import build
+    monkeypatch.setattr(build, "HERE", str(tmp_path))
+    monkeypatch.setattr(build, "OBJ", str(tmp_path))
+    monkeypatch.setattr(build, "MARSHAL", str(tmp_path / "_marshal.so"))
+    (tmp_path / "_marshal.so").write_text("")
+    (tmp_path / "marshal.torch").write_text("1.0")
+    os.utime(tmp_path / "_marshal.so", (2 ** 32, 2 ** 32))
+    assert build._marshal_stale()                        # newer than its source, but of another torch
+    (tmp_path / "marshal.torch").write_text(torch.__version__)
+    assert not build._marshal_stale()
+    monkeypatch.setenv("CXX", str(tmp_path / "no-such-compiler"))
+    assert build.build_marshal() is False and "not built" in capsys.readouterr().out
+    assert not (tmp_path / "_marshal.so").exists()       # an old one is not left behind
 
 
 class Sub(torch.Tensor):
@@ -96,3 +140,17 @@ def test_what_is_declined_goes_the_long_way_and_what_is_wrong_is_named():
         assert torch.equal(km.kronmatmul(X, Fs), want)
     with pytest.raises(RuntimeError):                    # a batched tensor of vmap has no memory to point at
         torch.func.vmap(lambda x: km.kronmatmul(x, Fs))(X.view(5, 1, 18))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("transposed", [False, True])
+def test_the_same_bits_without_the_native_part(no_native, transposed):
+    X, Fs = _problem()
+    given = [F.t().contiguous() for F in Fs] if transposed else Fs
+    want = _long_way(X, given, transposed=transposed)
+    with pytest.warns(RuntimeWarning, match="native part"):
+        assert torch.equal(km.kronmatmul(X, given, transposed=transposed), want)
+    prepared = km.Prepared(X, given, transposed=transposed)
+    for stream in (None, torch.cuda.current_stream().cuda_stream):
+        prepared.Y.zero_()
+        assert torch.equal(prepared(stream), want)
