@@ -25,6 +25,12 @@ WorkspaceFn g_workspace[2];
 PyObject* g_raw_stream;          // device index -> handle of torch's current stream
 PyObject* g_fail;                // (status, transposed, with workspace): raises
 
+// The interpreter is left to other threads meanwhile, and taken back however the block ends.
+struct WithoutGil {
+    PyThreadState* state = PyEval_SaveThread();
+    ~WithoutGil() { PyEval_RestoreThread(state); }
+};
+
 // Handle of torch's current stream on a device; false with a Python error set.
 bool current_stream(PyObject* index, void** stream)
 {
@@ -110,11 +116,12 @@ PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t nargs)
         Py_XDECREF(index);
         if (!ok) return nullptr;
         int status;
-        Py_BEGIN_ALLOW_THREADS
-        const int code = type == at::kFloat ? 0 : 1;
-        status = w ? g_workspace[transposed]((int)M, (int)n, P, Q, in, ptr, out, code, const_cast<void*>(ws), ws_bytes, stream)
-                   : g_plain[transposed]((int)M, (int)n, P, Q, in, ptr, out, code, stream);
-        Py_END_ALLOW_THREADS
+        {
+            WithoutGil other_threads;
+            const int code = type == at::kFloat ? 0 : 1;
+            status = w ? g_workspace[transposed]((int)M, (int)n, P, Q, in, ptr, out, code, const_cast<void*>(ws), ws_bytes, stream)
+                       : g_plain[transposed]((int)M, (int)n, P, Q, in, ptr, out, code, stream);
+        }
         if (status != 0) return fail(status, transposed, w != nullptr);
         if (yo != Py_None) {
             Py_INCREF(yo);
@@ -154,13 +161,16 @@ PyObject* bound_call(PyObject* self, PyObject* const* args, size_t nargsf, PyObj
         stream = PyLong_AsVoidPtr(args[0]);
         if (PyErr_Occurred()) return nullptr;
     }
+    HANDLE_TH_ERRORS
     int status;
-    Py_BEGIN_ALLOW_THREADS
-    status = b->with_ws ? g_workspace[b->transposed](b->M, b->n, b->P, b->Q, b->X, b->F, b->Y, b->code, const_cast<void*>(b->ws), b->ws_bytes, stream)
-                        : g_plain[b->transposed](b->M, b->n, b->P, b->Q, b->X, b->F, b->Y, b->code, stream);
-    Py_END_ALLOW_THREADS
+    {
+        WithoutGil other_threads;
+        status = b->with_ws ? g_workspace[b->transposed](b->M, b->n, b->P, b->Q, b->X, b->F, b->Y, b->code, const_cast<void*>(b->ws), b->ws_bytes, stream)
+                            : g_plain[b->transposed](b->M, b->n, b->P, b->Q, b->X, b->F, b->Y, b->code, stream);
+    }
     if (status != 0) return fail(status, b->transposed, b->with_ws);
     Py_RETURN_NONE;
+    END_HANDLE_TH_ERRORS
 }
 
 void bound_dealloc(PyObject* self)

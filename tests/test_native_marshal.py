@@ -2,6 +2,8 @@
 is what the long way takes or refuses."""
 import ctypes
 import os
+import shutil
+import subprocess
 import sys
 import warnings
 
@@ -64,6 +66,32 @@ def test_the_library_builds_without_the_native_part(monkeypatch, tmp_path, capsy
     monkeypatch.setenv("CXX", str(tmp_path / "no-such-compiler"))
     assert build.build_marshal() is False and "not built" in capsys.readouterr().out
     assert not (tmp_path / "_marshal.so").exists()       # an old one is not left behind
+
+
+THROWS = """
+import ctypes, sys
+import torch
+import paper_2401_10187_amd as km
+from paper_2401_10187_amd import binding as B
+entry = ctypes.cast(ctypes.CDLL(sys.argv[1]).entry, ctypes.c_void_p).value
+native = B._start_native()
+native.start(entry, entry, entry, entry, lambda index: 0, B._raise_status)
+try:
+    native.bind(1, 1, 0, 0, 0, 0, 0, 0, 0, 0, False, False, 0)(0)
+except RuntimeError as e:
+    print("raised", e)
+"""
+
+
+def test_an_exception_of_the_library_is_raised(tmp_path):
+    """Out of host memory in the planner, for instance: an error like any other, with the interpreter as it was."""
+    if not shutil.which("g++"):
+        pytest.skip("needs a C++ compiler")
+    (tmp_path / "t.cpp").write_text('#include <stdexcept>\nextern "C" int entry(int) { throw std::runtime_error("no memory left"); }\n')
+    subprocess.run(["g++", "-shared", "-fPIC", "-o", str(tmp_path / "t.so"), str(tmp_path / "t.cpp")], check=True)
+    r = subprocess.run([sys.executable, "-c", THROWS, str(tmp_path / "t.so")], capture_output=True, text=True, timeout=300,
+                       cwd=os.path.dirname(B.HERE))
+    assert r.returncode == 0 and "raised no memory left" in r.stdout, r.stderr[-2000:]
 
 
 class Sub(torch.Tensor):
