@@ -696,11 +696,12 @@ def test_full_size_every_element(name):
 
 @pytest.mark.parametrize("dtype,M,shapes", [
     ("float32", 64, [(8, 8)] * 6),          # small-factor kernel, 64 MiB intermediate
-    ("float32", 64, [(64, 64)] * 3),        # single-factor fp32 MFMA instances, 64 MiB
+    ("float32", 64, [(64, 64)] * 3),        # fp32 MFMA launches that leave digits in place, 64 MiB
     ("float64", 4, [(128, 128)] * 3),       # fp64 MFMA instances, 64 MiB
     ("float32", 16, [(32, 32)] * 4),        # pair kernel, 64 MiB
-    ("float32", 64, [(80, 80)] * 3),        # run-time-shape MFMA kernel, 125 MiB
-    ("float64", 128, [(40, 40)] * 3),       # the same, padded shape, 62 MiB
+    ("float32", 64, [(80, 80)] * 3),        # single-factor fp32 MFMA instances, 125 MiB
+    ("float32", 32, [(100, 100)] * 3),      # run-time-shape MFMA kernel, 122 MiB
+    ("float64", 128, [(40, 40)] * 3),       # the same, 62 MiB
     ("float32", 64, [(4, 4)] * 9),          # several small factors per LDS pass, 64 MiB
     ("float64", 48, [(3, 3)] * 11),         # the same on rows of odd length (element-sized stores), 65 MiB
 ], ids=lambda v: str(v).replace(" ", ""))

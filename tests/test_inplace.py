@@ -121,3 +121,53 @@ def test_factors_are_applied_last_to_first(M, shapes):
         scaled = list(Fd)
         scaled[i], scaled[i + 1] = Fd[i] * 2.0 ** 80, Fd[i + 1] * 2.0 ** -80
         assert torch.equal(km.kronmatmul(Xd * 2.0 ** 60, scaled), want), i
+
+
+# both forms of the first kernel, and the second one for every count of blocks of columns: a launch before the last one
+# writes 48 MiB and more
+KEPT = [(128, [(48, 48)] * 3), (64, [(64, 64)] * 3), (8, [(48, 48)] * 4), (11, [(32, 16), (16, 16)] + [(48, 48)] * 2),
+        (11, [(16, 16), (16, 32)] + [(48, 48)] * 2), (8, [(16, 16), (16, 48)] + [(48, 48)] * 2), (6, [(16, 16), (32, 64)] + [(48, 48)] * 2),
+        (5, [(16, 16), (32, 80)] + [(48, 48)] * 2), (4, [(16, 16), (32, 96)] + [(48, 48)] * 2),
+        (2, [(16, 16), (64, 112)] + [(64, 64)] * 2), (3, [(16, 16), (48, 128)] + [(48, 48)] * 2)]
+
+
+def _kept(M, shapes):
+    """Which launches write an intermediate that stays in the last-level cache."""
+    return [(s["variant"], s["k_out"] // s["k_in"] if s["variant"] == CHAIN else shapes[s["first_factor"]][1] // 16)
+            for s in _plan(M, shapes)[:-1] if 48 << 20 <= M * s["k_out"] * 4 <= 320 << 20]
+
+
+def test_the_cases_reach_every_form_that_keeps_its_results():
+    for M, shapes in KEPT:
+        assert [s["variant"] for s in _plan(M, shapes)] == [CHAIN] + [DIGIT] * (len(shapes) - 2), (M, shapes)
+    assert {mb for c in KEPT for v, mb in _kept(*c) if v == DIGIT} == set(range(1, 9))
+    assert {c[1][-1][0] for c in KEPT if any(v == CHAIN for v, _ in _kept(*c))} == {48, 64}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,shapes", KEPT, ids=lambda v: str(v).replace(" ", ""))
+def test_kept_intermediates_change_no_bit_and_stores_keep_to_the_workspace(M, shapes):
+    """With ordinary and with non-temporal stores the same bits; sampled rows match the reference (1e-5 of the largest value, as
+    above); nothing is written behind the workspace or around Y."""
+    import oracle
+    X, Fs = kron_inputs.make_problem(M, shapes, "float32", "uniform", "normal", seed=94)
+    print("in place, kept, M=%d %s" % (M, shapes), flush=True)
+    Xd, Fd = torch.from_numpy(X).cuda(), [torch.from_numpy(F).cuda() for F in Fs]
+    P, Q = [p for p, _ in shapes], [q for _, q in shapes]
+    need, n = km.workspace_size(M, P, Q, "float32"), M * int(np.prod(Q))
+    ws = torch.full((need + 4096,), 7, dtype=torch.uint8, device="cuda")
+    frame = torch.full((n + 2048,), -7.0, device="cuda")
+    Y = frame[1024:1024 + n].view(M, -1)
+    got, old = [], km.get_option(km.KM_OPT_KEEP_MIB)
+    try:
+        for keep in (old, 0, 1 << 20):
+            km.set_option(km.KM_OPT_KEEP_MIB, keep)
+            km.kronmatmul(Xd, Fd, Y=Y, workspace=ws[:need])
+            got.append(Y.clone())
+    finally:
+        km.set_option(km.KM_OPT_KEEP_MIB, old)
+    assert (ws[need:] == 7).all() and (frame[:1024] == -7).all() and (frame[1024 + n:] == -7).all()
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+    rows = sorted({0, M // 2, M - 1})
+    ref = oracle.kron_matmul(X[rows], Fs)
+    assert np.abs(got[0][rows].cpu().numpy() - ref).max() <= 1e-5 * np.abs(ref).max()
