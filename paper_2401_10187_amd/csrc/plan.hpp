@@ -331,10 +331,10 @@ inline RowmShape rowm_shape(const Problem& pr)
 }
 
 // The kernel for rows of 4^7 floats whose factors are 4x4 or pairs of 2x2 (fused_row4_kernel.hpp): all of them in one launch,
-// two workgroups to a compute unit.  It is the faster one for any number of rows (4^7, us: 1 row 8.5 -> 6.2, 100 rows 11.0 -> 7.5, 512
-// rows 17.2 -> 13.3, 1024 rows 37.7 -> 23.0, 20000 rows 569 -> 449; what it replaces: two launches for few rows, else
+// two workgroups to a compute unit.  It is the faster one for any number of rows (4^7, us: 1 row 8.5 -> 5.8, 100 rows 11.0 -> 6.8, 512
+// rows 17.2 -> 11.7, 1024 rows 37.7 -> 22.3, 20000 rows 569 -> 451; what it replaces: two launches for few rows, else
 // fused_multi_kernel.hpp).
-constexpr int ROW4_ELEMS = 16384, ROW4_DIGITS = 7, ROW4_THREADS = 1024, ROW4_LDS_BYTES = 16 * 4 * 4 * 68 * 4, ROW4_GRID = 512;
+constexpr int ROW4_ELEMS = 16384, ROW4_DIGITS = 7, ROW4_THREADS = 1024, ROW4_LDS_BYTES = 16 * (4 * 4 * 68 + 16) * 4, ROW4_GRID = 512;
 constexpr int ROW4_VARIANT = -6;           // km_plan_step.variant of its launches
 
 // The kernel for rows of P^(3G) and P^(4G) floats, square factors of size 5 (G = 2) and 3 (G = 3) (fused_cube_kernel.hpp).
