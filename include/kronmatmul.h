@@ -165,7 +165,8 @@ km_status kronmatmul_plan(int M, int N, const int* P, const int* Q, km_dtype dty
 
 /* Autotuning (the search over tile sizes of section 4.3, done at run time on the device that will
  * run the problem): times every compiled instance, tile length and tile walk that fits each group
- * of consecutive factors on synthetic rows of the problem's size, plans on the measured times, and
+ * of consecutive factors (the kernels of steps with variants -4 to -7 only as part of the cost-model plan, where that has
+ * them) on synthetic rows of the problem's size, plans on the measured times, and
  * keeps that plan for later kronmatmul / kronmatmul_ws / kronmatmul_plan calls with this problem and
  * the options in force now, if its launches in sequence beat the cost-model plan and need no more
  * workspace than that plan (otherwise that one is kept: a workspace sized with

@@ -18,6 +18,9 @@
 // behind a row gives the factors in the order of the Kronecker product.  A curated list (neighbouring
 // runs of 2x2, 4x4 and 8x8, 5x5 beside 2x2, 3x3 beside 2x2): a further combination is one more row.
 // Order = preference among instances that fit a shape.
+// (Rows of 5^6, 3^9, 2^14 and 4^7 floats with nothing but their own factors have kernels of their own, fused_cube_kernel.hpp and
+// fused_row4_kernel.hpp; the one-launch instances below for those lengths are planned for rows that come to them before or behind
+// another factor, such as 2000 x (5x5^6, 2x1).)
 #define KM_INSTANCES(X, Y, Z, W, R, V, U)                    \
     X(float, KM_F32, 8, 8, 3, 32, 1024)                 \
     X(float, KM_F32, 8, 8, 3, 32, 256)                  \
