@@ -296,6 +296,12 @@ def _start_native():
     return native
 
 
+def _bound_by_ctypes(fn, what, args, device):
+    def bound(stream):
+        _check(fn(*args, _current_stream(device) if stream is None else stream), what)
+    return bound
+
+
 class Prepared:
     """A Kron-Matmul call with its arguments already checked and marshalled: calling it only crosses
     the C-ABI (for iterative callers that repeat one small problem, where marshalling would cost
@@ -310,14 +316,16 @@ class Prepared:
         M, n, P, Q, x, F, y, code, ws, nbytes = (self._args + (0, 0))[:10]
         self._bound = (_native or _start_native()).bind(M, n, ctypes.addressof(P), ctypes.addressof(Q), x, ctypes.addressof(F), y, code,
                                                         ws, nbytes, self._ws_call, transposed, self._device)
+        if self._bound is None:
+            self._bound = _bound_by_ctypes(self._fn, self._what, self._args, self._device)
 
     def __call__(self, stream=None):
         """Enqueue on `stream` (a raw hipStream_t value; default: torch's current stream).  The
         tensors' device must be the current device."""
-        if self._bound is not None and (stream is None or type(stream) is int):
+        if stream is None or type(stream) is int:
             self._bound(stream)
         else:
-            _check(self._fn(*self._args, _current_stream(self._device) if stream is None else stream), self._what)
+            _check(self._fn(*self._args, stream), self._what)
         return self.Y
 
 
