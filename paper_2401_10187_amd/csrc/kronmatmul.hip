@@ -35,7 +35,7 @@ namespace km {
 /* (ST == 1, a tile is a whole row of P^NF elements: every factor in one launch, X read and Y written once.
    Measured against two or three tiled launches: 1000 x 64x64^2 0.0188 -> 0.0112 ms, 30000 rows 0.406 -> 0.272, 29 rows
    0.0085 -> 0.0044; fp64 5000 x 16x16^3 0.104 -> 0.061, 2 rows 0.0060 -> 0.0046, 20000 x 32x32^2 0.109 -> 0.063; 1000 x
-   128x128^2 0.082 -> 0.072; 1000 x 32x32^3 0.0896 -> 0.0616, 4000 rows 0.374 -> 0.246, 96 rows 0.0172 -> 0.0173, 48 rows
+   128x128^2 0.082 -> 0.072; 1000 x 32x32^3 0.0896 -> 0.0616, 4000 rows 0.374 -> 0.246, 96 rows 0.0172 -> 0.0176, 48 rows
    0.0136 -> 0.0164, which is why those start at 96.) */
 /* (walk -1, one round of resident workgroups: measured for every single-factor instance; it pays for the
    shapes named here, e.g. 4096 x 64x64^2 0.100 -> 0.071 ms, 20000 x 64x64^2 0.327 -> 0.275, 1024 x 48x48^3 fp64

@@ -8,8 +8,8 @@
 // multiplied and stored by some wavefronts, others are already at the next row, whose loads are issued as
 // soon as the operand registers are free.
 //
-// 1024 rows take 62 us (77 before, with the row in LDS between all three products and two more barriers), 4000 rows 238
-// (297).  A row costs its compute unit 15 us, of which the products are 10.2 at the matrix cores' full rate; with memory
+// 1024 rows take 61 us back to back in a graph and 66 as separate calls (77 and 78 before, with the row in LDS between all
+// three products and two more barriers), 4000 rows 238 (299).  A row costs its compute unit 15 us, of which the products are 10.2 at the matrix cores' full rate; with memory
 // at 4.3 TB/s beside them the chip's power allows them no more than about 110 TFLOP/s, 12 us.  One row alone takes
 // 14 us, four wavefronts on a SIMD in turn.
 #pragma once

@@ -1381,7 +1381,7 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
     }
     // The whole-row plan, whichever kernel it is on, unless the finer estimates promise a tenth from tiled launches whose
     // workspace fits the static array: 9363 x (74x14, 18x5) 79 us in rows, 31 in two launches, 5058 x (18x4,
-    // 39x3) 27 and 10; of 110 such problems 105 are faster tiled, by up to 5 times, since the generic kernel has its form for small
+    // 39x3) 27 and 10; of 91 such problems 90 are faster tiled, 2.1 times on average, since the generic kernel has its form for small
     // factors.  (Not so small compiled launches against the matrix-core rows: 300 x 2x2^2 fp64 3.9 us in rows, 6.6 tiled, 500 x 4x4^3 fp64
     // 4.7 and 6.3; 500 x 16x16^2 takes 4.2 and 3.8, but two launches of the host's.  Up to a row per compute unit the fixed costs
     // decide, which these estimates do not know that well: one launch there.)  Calls that bring no such workspace keep the
