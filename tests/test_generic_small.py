@@ -23,7 +23,7 @@ SHAPES = [(P, Q) for P in (1, 2, 3, 4, 5, 7, 8, 9, 12) for Q in (1, 2, 3, 5, 8, 
          [(64, 3), (65, 7), (127, 2), (128, 17), (129, 5), (31, 70), (100, 1)]
 
 
-def _check(dtype, M, shapes):
+def _check(dtype, M, shapes, workspace=False):
     import oracle
     tol = 1e-5 if dtype == "float32" else 1e-12
     for kinds, exact in ((dict(x="uniform", f="normal"), False), (dict(x="int2", f="int1"), True)):
@@ -32,7 +32,9 @@ def _check(dtype, M, shapes):
         n = M * int(np.prod([q for _, q in shapes]))
         frame = torch.full((n + 64,), -7.0, dtype=torch.float32 if dtype == "float32" else torch.float64, device="cuda")
         Y = frame[32:32 + n].view(M, -1)
-        km.kronmatmul(torch.from_numpy(X).cuda(), [torch.from_numpy(F).cuda() for F in Fs], Y=Y)
+        need = km.workspace_size(M, [p for p, _ in shapes], [q for _, q in shapes], dtype)
+        ws = torch.empty(max(need, 1), dtype=torch.uint8, device="cuda") if workspace else None
+        km.kronmatmul(torch.from_numpy(X).cuda(), [torch.from_numpy(F).cuda() for F in Fs], Y=Y, workspace=ws)
         ref, got = oracle.kron_matmul(X, Fs), Y.cpu().numpy()
         assert (frame[:32] == -7).all() and (frame[32 + n:] == -7).all()
         if exact:
@@ -76,9 +78,10 @@ def test_what_is_not_finite_stays_in_its_slice(generic_only, dtype, P):
 @pytest.mark.parametrize("M,shapes,tiled", [(9363, [(74, 14), (18, 5)], True), (1254, [(7, 2), (51, 23)], True),
                                             (1, [(5, 5), (5, 5), (5, 5), (2, 2)], False), (256, [(7, 2), (51, 23)], False)], ids=str)
 def test_small_mixed_problems_of_many_rows_are_tiled(M, shapes, tiled):
-    """Where whole rows on the FMA kernel are the slower plan, its launches' intermediates fit the static array all the same."""
+    """Where whole rows on the FMA kernel are the slower plan, the intermediates of the tiled launches fit the static array all the
+    same.  (Those launches run in calls that bring the workspace.)"""
     P, Q = [s[0] for s in shapes], [s[1] for s in shapes]
     rows = [s["kernel"] for s in km.plan(M, P, Q, "float32")] == [km.KM_KERNEL_ROWS]
     assert rows != tiled
     assert km.workspace_size(M, P, Q, "float32") <= (km.KM_STATIC_SCRATCH_BYTES if tiled else 0)
-    _check("float32", M, shapes)
+    _check("float32", M, shapes, workspace=True)
