@@ -22,7 +22,7 @@ EXPORTS = [
     "kronmatmul_last_profile", "kronmatmul_mean_profile", "kronmatmul_release", "kronmatmul_status_string",
     "kronmatmul_kernel_name", "kronmatmul_tune",
     "kronmatmul_transposed_workspace_size", "kronmatmul_transposed", "kronmatmul_transposed_ws",
-    "kronmatmul_clock_probe", "kronmatmul_prepare", "kronmatmul_static",
+    "kronmatmul_clock_probe", "kronmatmul_prepare", "kronmatmul_static", "kronmatmul_launches",
 ]
 KM_STATIC_SCRATCH_BYTES = 16 << 20
 
@@ -75,6 +75,8 @@ def lib():
         L.kronmatmul_transposed_ws.argtypes = [ci, ci, ip, ip, vp, vp, vp, ci, vp, ctypes.c_size_t, vp]
         L.kronmatmul_plan.restype = ci
         L.kronmatmul_plan.argtypes = [ci, ci, ip, ip, ci, ctypes.POINTER(PlanStep), ci, ip]
+        L.kronmatmul_launches.restype = ci
+        L.kronmatmul_launches.argtypes = L.kronmatmul_plan.argtypes
         L.kronmatmul_tune.restype = ci
         L.kronmatmul_tune.argtypes = [ci, ci, ip, ip, ci, vp, ctypes.POINTER(ctypes.c_float),
                                       ctypes.POINTER(ctypes.c_float)]
@@ -149,15 +151,24 @@ def prepare(M, P, Q, dtype):
     _check(lib().kronmatmul_prepare(int(M), n, p, q, _dtype_code(dtype)), "kronmatmul_prepare")
 
 
-def plan(M, P, Q, dtype):
-    """List of dicts, one per kernel launch, in launch order."""
+def _steps(name, M, P, Q, dtype):
     n, p, q = _shapes(P, Q)
     cap = 64
     steps = (PlanStep * cap)()
     cnt = ctypes.c_int(0)
-    _check(lib().kronmatmul_plan(int(M), n, p, q, _dtype_code(dtype), steps, cap, ctypes.byref(cnt)),
-           "kronmatmul_plan")
+    _check(getattr(lib(), name)(int(M), n, p, q, _dtype_code(dtype), steps, cap, ctypes.byref(cnt)), name)
     return [steps[i].as_dict() for i in range(min(cnt.value, cap))]
+
+
+def plan(M, P, Q, dtype):
+    """List of dicts, one per kernel launch, in launch order."""
+    return _steps("kronmatmul_plan", M, P, Q, dtype)
+
+
+def launches(M, P, Q, dtype):
+    """The same launches in the form they run in: steps of the generic and the run-time-shape MFMA kernel that
+    have many slices run as variant -8."""
+    return _steps("kronmatmul_launches", M, P, Q, dtype)
 
 
 def tune(M, P, Q, dtype, stream=None):

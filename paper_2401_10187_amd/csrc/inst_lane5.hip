@@ -1,0 +1,6 @@
+// Compiled instances: the MFMA kernel with run-time factor shapes and a slice per lane, fp32, chunks of 5 vectors.
+#include "launch_lane.hpp"
+
+namespace km {
+template hipError_t launch_mfma_lane<5>(const LaunchArgs&);
+}  // namespace km

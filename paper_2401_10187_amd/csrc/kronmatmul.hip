@@ -344,6 +344,21 @@ static hipError_t launch_pad(const LaunchArgs& a)
     }
 }
 
+static hipError_t launch_lane(const LaunchArgs& a)
+{
+    switch (lane_units(a.pr->P[a.st->first_factor])) {
+        case 2: return launch_mfma_lane<2>(a);
+        case 3: return launch_mfma_lane<3>(a);
+        case 4: return launch_mfma_lane<4>(a);
+        case 5: return launch_mfma_lane<5>(a);
+        case 6: return launch_mfma_lane<6>(a);
+        case 7: return launch_mfma_lane<7>(a);
+        case 9: return launch_mfma_lane<9>(a);
+        case 13: return launch_mfma_lane<13>(a);
+    }
+    return hipErrorInvalidValue;
+}
+
 static hipError_t launch_step(const Problem& pr, const km_plan_step& st, const void* src, void* dst,
                               const void* const* F, hipStream_t stream, bool prepare_only = false,
                               bool keep_output = false)
@@ -357,6 +372,7 @@ static hipError_t launch_step(const Problem& pr, const km_plan_step& st, const v
         return pr.dtype == KM_F32 ? launch_rows<float>(a) : launch_rows<double>(a);
     if (st.kernel == KM_KERNEL_MFMA_ANY && st.variant == PAD_VARIANT)
         return pr.dtype == KM_F32 ? launch_pad<float>(a) : launch_pad<double>(a);
+    if (st.kernel == KM_KERNEL_MFMA_ANY && st.variant == LANE_VARIANT) return launch_lane(a);
     if (st.kernel == KM_KERNEL_MFMA_ANY)
         return pr.dtype == KM_F32 ? launch_mfma_any<float>(a) : launch_mfma_any<double>(a);
     if (st.kernel == KM_KERNEL_FUSED && st.variant == CUBE_VARIANT) return launch_cube(a);
@@ -372,7 +388,8 @@ static km_status run(const Problem& pr, const Plan& plan, const void* X, const v
 {
     char* ws0 = (char*)ws;
     char* ws1 = ws0 + plan.ws0_bytes;
-    const int n = (int)plan.steps.size();
+    const std::vector<km_plan_step>& steps = plan.launches();
+    const int n = (int)steps.size();
     DeviceState* ds = nullptr;       // set when the call is profiled
     int ev0 = 0;
     std::vector<hipEvent_t> ev;      // this call's events, copied while the lock is held: another thread may grow ds->events
@@ -395,7 +412,7 @@ static km_status run(const Problem& pr, const Plan& plan, const void* X, const v
     const bool profile = ds != nullptr;
     if (profile && hipEventRecord(ev[0], stream) != hipSuccess) return KM_ELAUNCH;
     for (int i = 0; i < n; ++i) {
-        const km_plan_step& st = plan.steps[i];
+        const km_plan_step& st = steps[i];
         auto buf = [&](int b) -> void* {
             switch (b) {
                 case KM_BUF_X: return (void*)X;
@@ -409,7 +426,8 @@ static km_status run(const Problem& pr, const Plan& plan, const void* X, const v
         // (the small-factor kernel still gains 1-2 % at 1 GiB, where a quarter of the intermediate stays on
         // chip: 1024 x 8x8^6 0.724 -> 0.715 ms, 16 x 8x8^8 1.255 -> 1.225, 65536 x 8x8^4 0.714 -> 0.697; level at
         // 2 GiB, 1.6 % slower at 4 GiB; the MFMA kernels lose from 400 MB on)
-        const double keep_max = (double)g_keep_mib * (st.kernel == KM_KERNEL_FUSED ? 4.0 : 1.0);
+        // (one slice per lane: 2427 x 24x24^3, 128 MiB, 150 -> 128 us, but 8388 x 20x20^3, 256 MiB, 286 -> 300)
+        const double keep_max = (double)g_keep_mib * (st.kernel == KM_KERNEL_FUSED ? 4.0 : st.variant == LANE_VARIANT ? 0.5 : 1.0);
         const bool keep = i + 1 < n && out_mib >= KEEP_MIN_MIB && out_mib <= keep_max;
         if (launch_step(pr, st, buf(st.src), buf(st.dst), F, stream, false, keep) != hipSuccess) return KM_ELAUNCH;
         if (profile && hipEventRecord(ev[i + 1], stream) != hipSuccess) return KM_ELAUNCH;
@@ -930,14 +948,13 @@ km_status kronmatmul_prepare(int M, int N, const int* P, const int* Q, km_dtype 
     const Plan& plan = planned->plan;
     std::vector<const void*> none(pr.N, nullptr);
     for (const Plan* p : {&plan, &planned->spare})
-        for (const km_plan_step& st : p->steps)
+        for (const km_plan_step& st : p->launches())
             if (launch_step(pr, st, nullptr, nullptr, none.data(), nullptr, true) != hipSuccess) return KM_ELAUNCH;
     void* unused;
     return static_scratch(&unused);          // kronmatmul_static finds its array's address resolved
 }
 
-km_status kronmatmul_plan(int M, int N, const int* P, const int* Q, km_dtype dtype,
-                          km_plan_step* steps, int cap, int* nsteps)
+static km_status report(int M, int N, const int* P, const int* Q, km_dtype dtype, km_plan_step* steps, int cap, int* nsteps, bool launches)
 {
     if (!nsteps || cap < 0 || (cap > 0 && !steps)) return KM_EINVAL;
     Problem pr;
@@ -948,10 +965,22 @@ km_status kronmatmul_plan(int M, int N, const int* P, const int* Q, km_dtype dty
     PlannedRef planned;
     s = plan_for(M, N, P, Q, (int)dtype, planned);
     if (s != KM_OK) return s;
-    const Plan& plan = planned->plan;
-    *nsteps = (int)plan.steps.size();
-    for (int i = 0; i < *nsteps && i < cap; ++i) steps[i] = plan.steps[i];
+    const std::vector<km_plan_step>& list = launches ? planned->plan.launches() : planned->plan.steps;
+    *nsteps = (int)list.size();
+    for (int i = 0; i < *nsteps && i < cap; ++i) steps[i] = list[i];
     return KM_OK;
+}
+
+km_status kronmatmul_plan(int M, int N, const int* P, const int* Q, km_dtype dtype,
+                          km_plan_step* steps, int cap, int* nsteps)
+{
+    return report(M, N, P, Q, dtype, steps, cap, nsteps, false);
+}
+
+km_status kronmatmul_launches(int M, int N, const int* P, const int* Q, km_dtype dtype,
+                              km_plan_step* steps, int cap, int* nsteps)
+{
+    return report(M, N, P, Q, dtype, steps, cap, nsteps, true);
 }
 
 long long kronmatmul_store_column(long long k_in, long long p_group, long long tile_k,

@@ -52,6 +52,7 @@ template <int P, int ST, int NW> hipError_t launch_mfma_pair_rows(const LaunchAr
 hipError_t launch_shuffle(const LaunchArgs& a);
 template <typename T> hipError_t launch_mfma_any(const LaunchArgs& a);
 template <typename T, int KC> hipError_t launch_mfma_pad(const LaunchArgs& a);      // KC: pad_chunks of the factor
+template <int U> hipError_t launch_mfma_lane(const LaunchArgs& a);      // U: lane_units of the factor
 hipError_t launch_cube(const LaunchArgs& a);
 hipError_t launch_row4(const LaunchArgs& a);
 hipError_t launch_chain(const LaunchArgs& a);

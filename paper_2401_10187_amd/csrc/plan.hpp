@@ -103,7 +103,9 @@ struct Problem {
 };
 
 struct Plan {
-    std::vector<km_plan_step> steps;
+    std::vector<km_plan_step> steps;       // as kronmatmul_plan reports them
+    std::vector<km_plan_step> lane_steps;  // the same with those that run with a slice per lane in that form's launches (none: empty)
+    const std::vector<km_plan_step>& launches() const { return lane_steps.empty() ? steps : lane_steps; }
     size_t ws0_bytes = 0, ws1_bytes = 0;   // the two intermediates (ws1 unused when Y can serve)
     double flops = 0, bytes = 0;
 };
@@ -263,6 +265,55 @@ inline PadShape pad_shape(int P, int Q, size_t esize, int64_t slices)
     if (per_cu < 1) per_cu = 1;
     r.per_cu = per_cu;
     r.grid = tiles < 256 * per_cu ? (tiles + 7) / 8 * 8 : 256 * per_cu;
+    return r;
+}
+
+// The run-time-shape MFMA kernel with a slice per lane (mfma_lane_kernel.hpp): fp32, tiles of LANE_SLICES slices per
+// wavefront, factors of LANE_MINP to LANE_MAXP rows and up to LANE_MAXP columns.
+constexpr int LANE_VARIANT = -8;           // km_plan_step.variant of its launches
+constexpr int LANE_THREADS = 256, LANE_SLICES = 64, LANE_MINP = 5, LANE_MAXP = 128;
+// Vectors of a slice that are moved at a time: the compiled length that leaves the fewest to move twice (each chunk counting as
+// one more; the longest only where it is the whole slice, since longer chunks are fewer workgroups per compute unit: 64 x
+// 100x100^3 in chunks of 7, 9 and 13 vectors 147, 142 and 157 us a launch, 1024 x 50x50^3 in 7 and 13 251 and 225).
+KM_HOST_DEVICE constexpr int lane_units(int P)
+{
+    const int units = (P + 3) / 4;
+    if (units == 13) return 13;
+    int best = 2, cost = 1 << 30;
+    for (int u : {2, 3, 4, 5, 6, 7, 9}) {
+        const int chunks = (units + u - 1) / u, c = chunks * (u + 1);
+        if (u <= units && c <= cost) { best = u; cost = c; }
+    }
+    return best;
+}
+// wavefronts per SIMD that registers are limited for: 4G accumulators, 5U of the next chunk and its addresses, two sets of operands, the rest
+KM_HOST_DEVICE constexpr int lane_waves(int G, int U)
+{
+    const int registers = 4 * G + 5 * U + 8 * (1 + (G + 15) / 16) + 55;
+    return registers <= 122 ? 4 : registers <= 163 ? 3 : 2;
+}
+KM_HOST_DEVICE constexpr int lane_lds_bytes(int P, int Q, int U)
+{
+    return 16 * ((P + 3) / 4 * ((Q + 3) / 4 * 4) + LANE_THREADS * (U | 1));
+}
+// How the kernel would run a factor on `slices` slices (lds_bytes == 0: it cannot).
+struct LaneShape {
+    int lds_bytes = 0;
+    int64_t grid = 0, per_cu = 0;          // per_cu: workgroups a compute unit holds at once
+};
+inline LaneShape lane_shape(int P, int Q, int64_t slices)
+{
+    LaneShape r;
+    if (P < LANE_MINP || P > LANE_MAXP || Q < 1 || Q > LANE_MAXP || slices >= (int64_t)1 << 40) return r;
+    const int U = lane_units(P), G = (Q + 3) / 4;
+    r.lds_bytes = lane_lds_bytes(P, Q, U);
+    r.per_cu = 160 * 1024 / r.lds_bytes < lane_waves(G, U) ? 160 * 1024 / r.lds_bytes : lane_waves(G, U);
+    // One tile per wavefront, two where the factor's way into LDS takes long beside a tile's work; a multiple of 8 for the XCDs.
+    const int64_t groups = (slices + 4 * LANE_SLICES - 1) / (4 * LANE_SLICES);
+    int64_t walk = Q > 32 && groups > 512 * r.per_cu ? 2 : 1;
+    const int64_t most = (int64_t)1 << 23;               // (a launch has fewer than 2^32 work-items)
+    if (groups > most * walk) walk = (groups + most - 1) / most;
+    r.grid = ((groups + walk - 1) / walk + 7) / 8 * 8;
     return r;
 }
 
@@ -1239,6 +1290,57 @@ inline void take_inplace_plan(const Problem& pr, Plan& plan)
     assign_buffers(pr, plan);
 }
 
+// Does the slice-per-lane kernel beat the one that a step was given to?  Measured launch by launch on 800 of random sizes and on
+// whole calls of equal factors:
+// - the generic kernel and the chunked form, from 64 workgroups on: 1.3 times as fast on average (6 x 10x5 of 10^7 128 -> 53 us, 1780
+//   groups of 6x14 13.5 -> 9.1, 4794 of 50x8 89 -> 46, 2572 of 72x72 157 -> 116), at worst 0.8; fewer workgroups
+//   (128 in the chunked form's place) leave it a single tile's latency, which grows with P times Q (42 groups of 39x107 8.1 -> 12.0, 76
+//   of 60x11 5.2 -> 6.4).  Not the generic kernel's tall slices with few columns, 33 to 64 elements, nor what the chunked form
+//   takes of up to 32 (0.8 to 1.1), nor rows of a few slices, whose tiles go on in the next row and are stored element by element
+//   (1067 x (8x65, 6x49, 5x12) with its launch of 96 slices a row here 52 -> 68 us).
+// - the form with the factor in registers where that computes many columns for few, from 96 MB moved on (below, the one tile that a
+//   wavefront gets here takes longer than what registers save): up to 36 x 40 1.1 to 1.4 times as fast (calls of 1213 x 24x24^3 86 -> 67
+//   us, 466 x 33x33^3 116 -> 81, 359 x 36x36^3 100 -> 79; 38x38 to 60x60 0.8 to 1.1 at most sizes), and 65 to 76 columns, whose five
+//   wavefronts there share four SIMDs (122 x 65x65^3 321 -> 218, 89 x 72x72^3 257 -> 223; 81x81 to 100x100 0.87 to 1.0).  Aligned results
+//   of 160 to 320 MiB stay with that form, which leaves them in the last-level cache (8388 x 20x20^3 276 and 286 us; with
+//   ordinary stores 300).
+inline bool lane_wins(const Problem& pr, const km_plan_step& st)
+{
+    const int P = pr.P[st.first_factor], Q = pr.Q[st.first_factor];
+    const int64_t S = st.k_in / P, groups = (pr.M * S + 4 * LANE_SLICES - 1) / (4 * LANE_SLICES);
+    if (st.variant == PAD_VARIANT) {
+        const double out = (double)pr.M * (double)st.k_out * (double)pr.esize;
+        if ((double)pr.M * (double)st.k_in * (double)pr.esize + out < 96e6) return false;
+        if (P <= 36 && Q <= 40) return S * (int64_t)pr.esize % 64 != 0 || out <= 160.0 * 1048576 || out > 320.0 * 1048576;
+        return P > 32 && P <= 80 && Q > 64 && Q <= 76;
+    }
+    if (groups < 64 || S < 16 || (S < 256 && Q > 32)) return false;
+    return st.kernel == KM_KERNEL_GENERIC ? P <= 32 || P > 64 || Q > 8 : P > 32 && groups >= 128;
+}
+
+// The steps that the slice-per-lane kernel runs faster go to it when they are launched.  The plan itself keeps naming the kernel
+// they were planned for, which is what groups factors and weighs plans against each other (its prices know nothing of this form).
+inline void take_lane_steps(const Problem& pr, const Options& opt, Plan& plan)
+{
+    plan.lane_steps.clear();
+    if (pr.dtype != KM_F32 || !(opt.kernels >> KM_KERNEL_MFMA_ANY & 1) || !no_wishes(opt)) return;
+    for (size_t i = 0; i < plan.steps.size(); ++i) {
+        const km_plan_step& had = plan.steps[i];
+        if (had.kernel != KM_KERNEL_GENERIC && had.kernel != KM_KERNEL_MFMA_ANY) continue;
+        const int P = pr.P[had.first_factor], Q = pr.Q[had.first_factor];
+        const LaneShape sh = lane_shape(P, Q, pr.M * (had.k_in / P));
+        if (sh.lds_bytes == 0 || !lane_wins(pr, had)) continue;
+        if (plan.lane_steps.empty()) plan.lane_steps = plan.steps;
+        km_plan_step& st = plan.lane_steps[i];
+        st.kernel = KM_KERNEL_MFMA_ANY;
+        st.variant = LANE_VARIANT;
+        st.tile_slices = LANE_SLICES;
+        st.block = LANE_THREADS;
+        st.lds_bytes = sh.lds_bytes;
+        st.grid = sh.grid;
+    }
+}
+
 // Microseconds of the whole-row FMA kernel: per row a fixed part, its factors' loads and per step 1 us and 70 ns (fp64 106) for each of
 // the P products that a thread adds up in turn; 1024 threads have a compute unit to themselves.
 inline double fma_rows_us(const Problem& pr, int threads, int64_t lds_bytes, const std::vector<int64_t>& width)
@@ -1402,6 +1504,7 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
         one.tile_order = 2;
     }
     if (plan.ws0_bytes + plan.ws1_bytes == 0) spare = Plan();
+    take_lane_steps(pr, opt, plan);
     return KM_OK;
 }
 
