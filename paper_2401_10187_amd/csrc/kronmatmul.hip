@@ -183,7 +183,7 @@ static hipError_t launch_rows_mfma(const LaunchArgs& a)
     auto magic = [](int d) { return d > 1 ? (unsigned)(((1ull << 32) + (unsigned)d - 1) / (unsigned)d) : 0u; };
     int64_t w = st.k_in;
     for (int i = 0; i < n; ++i) {                        // order of application: last factor first
-        const int f = n - 1 - i;
+        const int f = n - 1 - i, waves = rs.threads / 64;
         RowmStep& s = ra.step[i];
         s.f = a.factors[f];
         s.P = pr.P[f];
@@ -191,13 +191,18 @@ static hipError_t launch_rows_mfma(const LaunchArgs& a)
         s.S = (int)(w / s.P);
         s.blocks = (s.S + 15) / 16;
         s.units = s.blocks * ((s.Q + 15) / 16);
+        s.share = (s.units + waves - 1) / waves;
         s.blocks_magic = magic(s.blocks);
-        ra.magic[i] = rowm_slice_stride(s.P) != s.P ? magic(s.P) : 0;
+        s.first = (s.P - 1) % 16 + 1;
+        s.last = (s.P - 1) / 16;
+        s.last_round = s.last / ROWM_CHUNKS;
+        s.stride = rowm_slice_stride(s.P);
+        (i ? ra.step[i - 1].out_magic : ra.in_magic) = s.stride != s.P ? magic(s.P) : 0;
         w = (int64_t)s.S * s.Q;
     }
     if (w != st.k_out) return hipErrorInvalidValue;
     hipLaunchKernelGGL(kern, dim3((unsigned)st.grid), dim3((unsigned)st.block), (size_t)st.lds_bytes, a.stream,
-                       (const T*)a.src, (T*)a.dst, ra, (int)st.k_in, (int)st.k_out);
+                       (const T*)a.src, (T*)a.dst, (int)st.k_in, (int)st.k_out, ra);
     return hipGetLastError();
 }
 

@@ -10,16 +10,20 @@
 // takes a run of them, so that it seldom changes its columns of the factor.
 //
 // What keeps the chain of latencies short: the A operand of a unit is read straight from global memory
-// into registers, and the loads of the next step's first unit are issued before this step's products, so a
+// into registers, and the loads of the next step's first unit are issued among this step's products, so a
 // factor costs neither a pass through LDS nor a memory latency of its own; the first step's are in flight
-// together with the row's.  No loop holds a division.  Contraction indices past P are zeroed in both operands
-// (what lies behind a slice may be NaN); rows q and columns s past the ends are computed on clamped
+// together with the row's.  Where rows are few the B operands of a unit are all read before its first product, and the
+// last step's results go straight to Y instead of through LDS, a barrier and a read.  What remains of a step, some 2000 cycles for a unit
+// whose products take 500, is instructions one after the other: the host works out all that depends on the shapes alone, a
+// step's numbers are one cache line of the arguments.  No loop holds a division.  Contraction indices past P are zeroed in both
+// operands (what lies behind a slice may be NaN); rows q and columns s past the ends are computed on clamped
 // addresses and dropped.
-// Bound by latency: 10 x (52x50, 65x20), two steps, takes 5.6 us from launch to launch where an empty launch
-// takes 2.3 (13.6 on the FMA kernel, whose factors go through LDS and whose 130 busy threads add up 117
-// products one after the other; fp64 20.1 -> 7.0 against two launches); 200 x 50x50^2 20.0 -> 7.6 (9.3 in two launches
-// of the factor-in-register kernel), 33 x 80x80^2 20.2 -> 10.5, 300 x (32x32, 64x3) 19.9 -> 5.0, 5 x (111x82, 7x9)
-// 14.9 -> 5.4.  Sixteen wavefronts when units are many or rows few, four (four rows to a compute unit) otherwise; a
+// Bound by latency: 10 x (52x50, 65x20), two steps, takes 4.9 us from launch to launch where an empty launch
+// takes 1.6 (5.6 before the three things above: 11 x 50x50^2 6.9 -> 6.2, 2 x 80x80^2 10.2 -> 9.3, 6 x 32x32^2 fp64 4.8 -> 4.2, 280 x (5x4, 4x17)
+// 4.5 -> 3.8; 13.6 on the FMA kernel, whose factors go through LDS and whose 130 busy threads add up 117
+// products one after the other; fp64 20.1 -> 7.0 against two launches); 200 x 50x50^2 20.0 -> 6.9 (9.3 in two launches
+// of the factor-in-register kernel), 33 x 80x80^2 20.2 -> 9.5, 300 x (32x32, 64x3) 19.9 -> 5.0, 5 x (111x82, 7x9)
+// 14.9 -> 4.9.  Sixteen wavefronts when units are many or rows few, four (four rows to a compute unit) otherwise; a
 // first version with the factors in LDS took 8.7 us on the first of these, 1.2 of it staging them, and a loop over
 // rows around all of it 0.4 us more on every problem, though it ran once.
 // Slices of a multiple of 8 elements are padded by 4 in LDS, which spreads the 64 operand reads of an MFMA
@@ -36,17 +40,20 @@ template <typename T> struct RowmOp;
 template <> struct RowmOp<float> { typedef MfmaF32x16 OP; };
 template <> struct RowmOp<double> { typedef MfmaF64x16 OP; };
 
-// One factor's step, in order of application (last factor of the product first).
-struct RowmStep {
+// One factor's step, in order of application (last factor of the product first), with what the host can work out of it.
+struct alignas(64) RowmStep {
     const void* f;
     int P, Q, S;                           // S: slices of the row the step reads
-    int units;                             // 16x16 blocks of its result
+    int units, share;                      // 16x16 blocks of its result; those of a wavefront
     unsigned blocks_magic;                 // unit / slice blocks = (unit * blocks_magic) >> 32
     int blocks;                            // slice blocks
+    int first, last, last_round;           // contraction indices of chunk 0, 1 to 16; the last chunk; the last round
+    int stride;                            // of the slices in LDS
+    unsigned out_magic;                    // c / P of the next step if its slices are padded (0: they are not): (c * out_magic) >> 32
 };
 struct RowmArgs {
     RowmStep step[ROWM_MAXF];
-    unsigned magic[ROWM_MAXF];             // c / P of a step whose slices are padded (0: they are not): (c * magic) >> 32
+    unsigned in_magic;                     // out_magic for the row of X
     int n;
     int buf_elems;                         // elements of one row buffer; the second one follows it
 };
@@ -60,9 +67,7 @@ __device__ __forceinline__ int rowm_column_block(const RowmStep& st, int unit)
 // position in LDS of element c of a row that is read in slices of P elements
 __device__ __forceinline__ int rowm_at(int c, unsigned magic) { return magic ? c + 4 * (int)__umulhi((unsigned)c, magic) : c; }
 
-// Contraction indices are taken in chunks of 16, the first one holding what P leaves over (1 to 16 of them).
-__device__ __forceinline__ int rowm_first(int P) { return (P - 1) % 16 + 1; }
-// Is there a chunk c (of chunks 0 to `last`)?  The empty asm keeps the eight answers from being held in
+// Is there a chunk c (of chunks 0 to `last`)?  The empty asm keeps the answers from being held in
 // scalar registers over a loop: asking costs one instruction.
 __device__ __forceinline__ bool rowm_chunk(int c, int last)
 {
@@ -70,36 +75,27 @@ __device__ __forceinline__ bool rowm_chunk(int c, int last)
     return c <= last;
 }
 
+// Contraction indices are taken in chunks of 16, the first one holding what P leaves over (1 to 16 of them).
 // The operand registers hold ROWM_CHUNKS chunks; a longer contraction takes as many rounds of them.
 //
 // Where a wavefront finds the A operand of a unit: element t of lane group g in chunk c is row
 // p = first + 16(c - 1) + 4t + g (4t + g in chunk 0) of factor column q, `step` bytes apart for each t.
 struct RowmOperand {
     __amdgpu_buffer_rsrc_t rsrc;
-    int at, next, step, last;              // byte offsets in chunk 0 and chunk 1; the last chunk (-1: no unit)
+    int at, next, step, last;              // byte offsets in the round's first chunk and in the second one; the last chunk (-1: no unit)
 };
 template <typename T>
-__device__ __forceinline__ RowmOperand rowm_operand(const RowmStep& st, int unit, int j, int g)
+__device__ __forceinline__ RowmOperand rowm_operand(const RowmStep& st, int unit, int round, int j, int g)
 {
-    const int q = rowm_column_block(st, unit) * 16 + j;
+    const int q = rowm_column_block(st, unit) * 16 + j, row = st.Q * (int)sizeof(T);
     RowmOperand o;
     // (elements past the factor's last row, which chunk 0 may ask for, are past the end of the resource and read as zero)
-    o.rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(st.f), 0, st.P * st.Q * (int)sizeof(T), 0x00020000);
-    o.at = (g * st.Q + (q < st.Q ? q : st.Q - 1)) * (int)sizeof(T);
-    o.next = o.at + rowm_first(st.P) * st.Q * (int)sizeof(T);
-    o.step = 4 * st.Q * (int)sizeof(T);
-    const int last = (st.P - 1) / 16;
-    o.last = last < ROWM_CHUNKS ? last : ROWM_CHUNKS - 1;
-    return o;
-}
-// ... of its round r > 0, whose chunks are all whole
-template <typename T>
-__device__ __forceinline__ RowmOperand rowm_operand_round(const RowmStep& st, int unit, int r, int j, int g)
-{
-    RowmOperand o = rowm_operand<T>(st, unit, j, g);
-    const int last = (st.P - 1) / 16 - r * ROWM_CHUNKS;
-    o.at = o.next + (r * ROWM_CHUNKS - 1) * 4 * o.step;
-    o.next = o.at + 4 * o.step;
+    o.rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(st.f), 0, st.P * row, 0x00020000);
+    o.at = g * row + (q < st.Q ? q : st.Q - 1) * (int)sizeof(T);
+    o.step = 4 * row;
+    o.next = o.at + (st.first + round * ROWM_CHUNKS * 16) * row;
+    if (round > 0) o.at = o.next - 16 * row;
+    const int last = st.last - round * ROWM_CHUNKS;
     o.last = last < ROWM_CHUNKS ? last : ROWM_CHUNKS - 1;
     return o;
 }
@@ -125,8 +121,7 @@ __device__ __forceinline__ void rowm_load_chunk(T (&a)[4], RowmOperand& o, int c
 
 template <typename T, int NW>
 __global__ __launch_bounds__(NW * 64, NW / 4)
-void row_mfma_sliced_multiply(const T* __restrict__ Xg, T* __restrict__ Yg, const RowmArgs ra,
-                              int k_in, int k_out)
+void row_mfma_sliced_multiply(const T* __restrict__ Xg, T* __restrict__ Yg, int k_in, int k_out, const RowmArgs ra)
 {
     typedef typename RowmOp<T>::OP OP;
     typedef typename Vec16<T>::type V;
@@ -139,16 +134,15 @@ void row_mfma_sliced_multiply(const T* __restrict__ Xg, T* __restrict__ Yg, cons
     const int64_t row = blockIdx.x;
     const int j = lane % 16, g = lane / 16;
     T a[KC][4];                                      // A operand of the wavefront's next unit
-    auto first_unit = [&](const RowmStep& st) { return wave * ((st.units + NW - 1) / NW); };
-    if (first_unit(ra.step[0]) < ra.step[0].units) {
-        RowmOperand o = rowm_operand<T>(ra.step[0], first_unit(ra.step[0]), j, g);
+    if (wave * ra.step[0].share < ra.step[0].units) {
+        RowmOperand o = rowm_operand<T>(ra.step[0], wave * ra.step[0].share, 0, j, g);
 #pragma unroll
         for (int c = 0; c < KC; ++c)
             if (rowm_chunk(c, o.last)) rowm_load_chunk(a[c], o, c);
     }
     {
         const T* src = Xg + row * k_in;
-        const unsigned magic = ra.magic[0];
+        const unsigned magic = ra.in_magic;
         if (k_in % VN == 0) {                        // (a padded slice is a multiple of 8 elements: a vector stays inside it)
             for (int c0 = tid * VN; c0 < k_in; c0 += 4 * NT * VN) {
                 V v[4];
@@ -175,63 +169,94 @@ void row_mfma_sliced_multiply(const T* __restrict__ Xg, T* __restrict__ Yg, cons
 
     T* buf = lds;
     T* out = lds + ra.buf_elems;
+    // The last step's results go straight to Y with sixteen wavefronts or a short row, else through LDS in whole vectors (922 x
+    // 50x50^2 fp64 24.7 us straight, 23.7 through LDS; 280 x (5x4, 4x17) 4.3 and 4.6; sixteen wavefronts with both ways compiled in
+    // 2 % slower throughout).
+    const bool straight = NW == 16 || k_out * (int)sizeof(T) <= 8192;
     for (int i = 0; i < ra.n; ++i) {
         const RowmStep st = ra.step[i];
         const bool more = i + 1 < ra.n;
-        const unsigned next_magic = more ? ra.magic[i + 1] : 0;
-        const int first = rowm_first(st.P), last = (st.P - 1) / 16, last_round = last / KC;
-        const int begin = first_unit(st), share = begin + (st.units + NW - 1) / NW, end = share < st.units ? share : st.units;
-        const int ahead = more ? first_unit(ra.step[i + 1]) : 0;
-        const bool wanted = more && ahead < ra.step[i + 1].units;
+        const RowmStep& nx = ra.step[more ? i + 1 : i];
+        const int begin = wave * st.share, share = begin + st.share, end = share < st.units ? share : st.units;
         for (int unit = begin; unit < end; ++unit) {
             const int qb = rowm_column_block(st, unit);
             const int s = (unit - qb * st.blocks) * 16 + j;
-            const T* b = buf + (s < st.S ? s : st.S - 1) * rowm_slice_stride(st.P) + g;
+            const T* b = buf + (s < st.S ? s : st.S - 1) * st.stride + g;
             typename OP::Acc acc;
 #pragma unroll
             for (int v = 0; v < OP::NACC; ++v) acc[v] = T(0);
-            for (int round = 0; round <= last_round; ++round) {
+            for (int round = 0; round <= st.last_round; ++round) {
+                // Rows that have their compute unit to themselves: the round's B operands are all asked for before the first product,
+                // one LDS latency (four rows to a unit hide it from each other, and it would cost them registers).
+                constexpr bool AHEAD = NW == 16;
+                const T* from = b + (st.first + 16 * (round * KC - 1));      // chunk c: 16c elements on
+                const int here = st.last - round * KC;
+                T bv[KC][4];
+                if (round == 0) {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) bv[0][t] = b[4 * t + g < st.first ? 4 * t : 0];
+                } else {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) bv[0][t] = from[4 * t];
+                }
+#pragma unroll
+                for (int c = 1; c < KC; ++c)
+                    if (AHEAD && rowm_chunk(c, here))
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) bv[c][t] = from[16 * c + 4 * t];
+                if (round == 0) {
+                    // (the empty asm keeps the reads out of branches of their own)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        asm volatile("" : "+v"(bv[0][t]));
+                        if (4 * t + g >= st.first) { bv[0][t] = T(0); a[0][t] = T(0); }
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (t == 0 || round > 0 || rowm_chunk(4 * t + 1, st.first)) acc = OP::mma(a[0][t], bv[0][t], acc);
                 // What comes next (this unit's next round, the next unit of this step, the first one of the next
                 // step) takes the operand registers as the products free them.
                 RowmOperand o;
                 o.last = -1;
-                if (round < last_round) {
-                    o = rowm_operand_round<T>(st, unit, round + 1, j, g);
+                if (round < st.last_round) {
+                    o = rowm_operand<T>(st, unit, round + 1, j, g);
                 } else if (unit + 1 < end) {         // (the same columns of the factor: it has the operand already)
-                    if (last_round > 0 || rowm_column_block(st, unit + 1) != qb) o = rowm_operand<T>(st, unit + 1, j, g);
-                } else if (wanted) {
-                    o = rowm_operand<T>(ra.step[i + 1], ahead, j, g);
+                    if (st.last_round > 0 || rowm_column_block(st, unit + 1) != qb) o = rowm_operand<T>(st, unit + 1, 0, j, g);
+                } else if (more && wave * nx.share < nx.units) {
+                    o = rowm_operand<T>(nx, wave * nx.share, 0, j, g);
                 }
-                const T* from = b + (round == 0 ? first - 16 : first + 16 * (round * KC - 1));      // chunk c: 16c elements on
-                const int here = last - round * KC;
+                if (rowm_chunk(0, o.last)) rowm_load_chunk(a[0], o, 0);
 #pragma unroll
-                for (int c = 0; c < KC; ++c) {
-                    if (c == 0 && round == 0) {
+                for (int c = 1; c < KC; ++c) {
+                    if (rowm_chunk(c, here)) {
+                        if (!AHEAD)
 #pragma unroll
-                        for (int t = 0; t < 4; ++t)
-                            if (rowm_chunk(4 * t + 1, first)) {
-                                const bool in = 4 * t + g < first;
-                                const T x = b[in ? 4 * t : 0];
-                                acc = OP::mma(in ? a[0][t] : T(0), in ? x : T(0), acc);
-                            }
-                    } else if (rowm_chunk(c, here)) {
-                        T bv[4];
+                            for (int t = 0; t < 4; ++t) bv[c][t] = from[16 * c + 4 * t];
 #pragma unroll
-                        for (int t = 0; t < 4; ++t) bv[t] = from[16 * c + 4 * t];
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) acc = OP::mma(a[c][t], bv[t], acc);
+                        for (int t = 0; t < 4; ++t) acc = OP::mma(a[c][t], bv[c][t], acc);
                     }
                     if (rowm_chunk(c, o.last)) rowm_load_chunk(a[c], o, c);
                 }
             }
+            if (more || !straight) {
 #pragma unroll
-            for (int v = 0; v < OP::NACC; ++v) {
-                const int q = qb * 16 + OP::row_lane(lane) + OP::row_reg(v);
-                if (q < st.Q && s < st.S) out[rowm_at(q * st.S + s, next_magic)] = acc[v];
+                for (int v = 0; v < OP::NACC; ++v) {
+                    const int q = qb * 16 + OP::row_lane(lane) + OP::row_reg(v);
+                    if (q < st.Q && s < st.S) out[rowm_at(q * st.S + s, st.out_magic)] = acc[v];
+                }
+            } else {
+                T* y = Yg + row * k_out + s;
+#pragma unroll
+                for (int v = 0; v < OP::NACC; ++v) {
+                    const int q = qb * 16 + OP::row_lane(lane) + OP::row_reg(v);
+                    if (q < st.Q && s < st.S) y[q * st.S] = acc[v];
+                }
             }
         }
-        if (begin >= end && wanted) {                // idle in this step
-            RowmOperand o = rowm_operand<T>(ra.step[i + 1], ahead, j, g);
+        if (!more && straight) return;
+        if (more && begin >= end && wave * nx.share < nx.units) {        // idle in this step
+            RowmOperand o = rowm_operand<T>(nx, wave * nx.share, 0, j, g);
 #pragma unroll
             for (int c = 0; c < KC; ++c)
                 if (rowm_chunk(c, o.last)) rowm_load_chunk(a[c], o, c);
