@@ -12,13 +12,13 @@
 // slices, numbered through all rows, so one contiguous run of X: nothing is assumed of the row length, the
 // last tile may be ragged.  Workgroups are resident and walk over their share of the tiles; the next
 // tile is on its way into registers while the current one is multiplied, and moves to the other LDS buffer
-// before the results are stored, so waiting for it never means waiting for stores.
+// before the results are stored, so waiting for it never means waiting for this tile's stores.
 //
 // Bound by the matrix cores for large factors and by memory for small ones.  Whole calls, the chunked form ->
-// this one, ms: 64 x 100x100^3 0.785 -> 0.457 (84 TFLOP/s, 55 % of what a large fp32 product reaches), 64 x
-// 99x99^3 0.866 -> 0.450, 64 x 127x127^3 1.61 -> 1.02, 512 x 20x20^4 0.637 -> 0.477 (5.5 TB/s), 2048 x 36x36^3 0.559
-// -> 0.495, 1024 x 50x50^3 0.947 -> 0.734, 512 x 60x60^3 0.661 -> 0.606, 256 x 65x65^3 0.778 -> 0.679; fp64 32 x
-// 100x100^3 0.730 -> 0.492, 64 x 84x84^3 0.639 -> 0.521, 1024 x 33x33^3 0.544 -> 0.400, 1024 x 30x30^3 0.323 -> 0.227.  What
+// this one, ms: 64 x 100x100^3 0.785 -> 0.451 (85 TFLOP/s, 56 % of what a large fp32 product reaches), 64 x
+// 99x99^3 0.866 -> 0.450, 64 x 127x127^3 1.61 -> 1.02, 512 x 20x20^4 0.637 -> 0.477 (5.5 TB/s), 1024
+// x 50x50^3 0.947 -> 0.730, 512 x 60x60^3 0.661 -> 0.591, 256 x 65x65^3 0.778 -> 0.679; fp64 32 x 100x100^3 0.730 ->
+// 0.459, 64 x 84x84^3 0.639 -> 0.521, 1024 x 33x33^3 0.544 -> 0.400, 1024 x 30x30^3 0.323 -> 0.227.  What
 // the chunked form spends and this one does not: a second pass over LDS for the factor with every unit, two
 // barriers per chunk with no load in flight behind them, and products on P padded to 16.
 // Registers decide how many workgroups share a compute unit, so the kernel is compiled for four lengths of
@@ -55,8 +55,22 @@ __device__ __forceinline__ bool pad_has(int i, int last)
     return i <= last;
 }
 
-// WHOLE: slices are whole 16-byte vectors, so X does not end inside one (the test for it in every form of the
-// kernel made 1024 x 24x24^4 2.66 instead of 2.01 ms).
+constexpr int PAD_STREAM = 2;              // non-temporal, as stream_load
+__device__ __forceinline__ void pad_load(float& v, __amdgpu_buffer_rsrc_t rsrc, int at) { v = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, at, 0, 0)); }
+__device__ __forceinline__ void pad_load(double& v, __amdgpu_buffer_rsrc_t rsrc, int at) { v = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rsrc, at, 0, 0)); }
+
+// WHOLE: slices are whole 16-byte vectors.  Both operands are then read by buffer loads whose resource ends where
+// the operand does: what is past it comes as zero, no lane branches, and all loads of a tile go out together.  The
+// first tile is asked for before the factor (in the other order its way to memory came after the factor's: 2 x
+// 48x96^2 10.0 -> 9.2 us, 2064 x 64x32^2 29.4 -> 21.2, 60 x 60x60^3 82 -> 75, 32 x 100x100^3 fp64 490 -> 459).
+// Slices that are not whole vectors keep the branches: without them, large problems were slower (1024 x 50x50^3
+// 0.730 -> 0.810 ms, 1024 x 33x33^3 fp64 0.398 -> 0.455).  (Of the 11 % the fetch
+// without branches costs most, the order and the factor's loads 2 %; on 33x33 these are the 12 %.)
+// drain: wait for the next tile before the results of this one are stored, which keeps reads and writes apart in
+// time; other workgroups of the compute unit use it meanwhile (us without -> with: 1000 x 44x44^3 454 -> 430, 512 x
+// 60x60^3 602 -> 591, fp64 2000 x 30x30^3 556 -> 534, 1000 x 36x36^3 426 -> 418).  The long fp64 classes run one
+// workgroup per compute unit or two, where hardly anybody does: 32 x 100x100^3 457 -> 509.
+// (The test for the end of X inside a vector in every form of the kernel made 1024 x 24x24^4 2.66 instead of 2.01 ms.)
 template <typename T, int QB, int KC, bool KEEP, bool WHOLE>
 __global__ __launch_bounds__(64 * QB * pad_groups(QB), pad_waves(sizeof(T), QB, KC))
 void mfma_pad_sliced_multiply(const T* __restrict__ Xg, const T* __restrict__ Fg, T* __restrict__ Yg,
@@ -67,6 +81,7 @@ void mfma_pad_sliced_multiply(const T* __restrict__ Xg, const T* __restrict__ Fg
     typedef typename Vec16<T>::type V;
     constexpr int VN = Vec16<T>::N, SG = pad_groups(QB), NT = 64 * QB * SG, BPW = pad_blocks(sizeof(T), QB, KC);
     constexpr int TS = 16 * BPW * SG, RV = pad_vectors(sizeof(T), QB, KC);
+    constexpr bool drain = WHOLE && (sizeof(T) == 4 || KC <= 4);
     extern __shared__ __attribute__((aligned(16))) unsigned char pad_lds[];
     T* const lds = reinterpret_cast<T*>(pad_lds);
     const int tid = threadIdx.x, lane = tid % 64, j = lane % 16, g = lane / 16;
@@ -75,25 +90,53 @@ void mfma_pad_sliced_multiply(const T* __restrict__ Xg, const T* __restrict__ Fg
     const int steps = (P + 3) / 4, left = (P - 1) % 4 + 1;          // indices of step 0
     const int head = (steps - 1) % 4 + 1, last = (steps - 1) / 4;   // steps of chunk 0; the last chunk
 
+    // this workgroup's tiles: the XCD (workgroup b runs on XCD b % 8) owns a contiguous part of them
+    const int64_t base = num_tiles / 8, rem = num_tiles % 8, xcd = blockIdx.x % 8;
+    const int64_t t_end = (xcd + 1) * base + (xcd + 1 < rem ? xcd + 1 : rem), t_step = gridDim.x / 8;
+    int64_t tile = xcd * base + (xcd < rem ? xcd : rem) + blockIdx.x / 8;
+
+    V pf[RV];
+    const int tile_elems = TS * P;
+    const int rounds = (tile_elems - wave * 64 * VN + NT * VN - 1) / (NT * VN);      // vectors of this wavefront's threads
+    auto fetch = [&](int64_t t) {
+        const T* src = Xg + t * tile_elems;
+        const int64_t rest = (num_slices - t * TS) * P;
+        const int valid = rest < tile_elems ? (int)rest : tile_elems;
+        if constexpr (WHOLE) {
+            auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(src), 0, valid * (int)sizeof(T), 0x00020000);
+#pragma unroll
+            for (int i = 0; i < RV; ++i)
+                if (i == 0 || i < rounds)
+                    pf[i] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (tid + i * NT) * 16, 0, PAD_STREAM));
+        } else {
+#pragma unroll
+            for (int i = 0; i < RV; ++i) {
+                const int e0 = (tid + i * NT) * VN;
+                if (e0 + VN <= valid) pf[i] = stream_load(reinterpret_cast<const V*>(src + e0));
+                else if (e0 < valid)                     // the end of X inside a vector
+#pragma unroll
+                    for (int k = 0; k < VN; ++k) pf[i][k] = e0 + k < valid ? src[e0 + k] : T(0);
+            }
+        }
+    };
+    if (tile >= t_end) return;
+    if constexpr (WHOLE) fetch(tile);                    // (on its way while the factor is asked for)
     // chunk c >= 1 starts at index first + 16 * (c - 1)
     const int first = left + 4 * (head - 1);
     T a[KC][4];
     {
         const int q = wq * 16 + j;
+        [[maybe_unused]] auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(Fg), 0, P * Q * (int)sizeof(T), 0x00020000);
 #pragma unroll
         for (int c = 0; c < KC; ++c)
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const int p = (c > 0 ? first + 16 * (c - 1) + 4 * t : t > 0 ? left + 4 * (t - 1) : 0) + g;
                 const bool in = q < Q && (c > 0 ? c <= last : t > 0 ? t < head : g < left);
-                a[c][t] = in ? Fg[p * Q + q] : T(0);
+                if constexpr (WHOLE) pad_load(a[c][t], rsrc, in ? (p * Q + q) * (int)sizeof(T) : 0x7ffffff0);    // (past the end: zero)
+                else a[c][t] = in ? Fg[p * Q + q] : T(0);
             }
     }
-
-    // this workgroup's tiles: the XCD (workgroup b runs on XCD b % 8) owns a contiguous part of them
-    const int64_t base = num_tiles / 8, rem = num_tiles % 8, xcd = blockIdx.x % 8;
-    const int64_t t_end = (xcd + 1) * base + (xcd + 1 < rem ? xcd + 1 : rem), t_step = gridDim.x / 8;
-    int64_t tile = xcd * base + (xcd < rem ? xcd : rem) + blockIdx.x / 8;
 
     // vector i of a thread: element e0 of the tile, and where it goes in LDS
     int at[RV];
@@ -102,21 +145,6 @@ void mfma_pad_sliced_multiply(const T* __restrict__ Xg, const T* __restrict__ Fg
         const int e0 = (tid + i * NT) * VN, row = (int)__umulhi((unsigned)e0, p_magic);
         at[i] = e0 + row * (rs - P);
     }
-    V pf[RV];
-    const int tile_elems = TS * P;
-    auto fetch = [&](int64_t t) {
-        const T* src = Xg + t * tile_elems;
-        const int64_t rest = (num_slices - t * TS) * P;
-        const int valid = rest < tile_elems ? (int)rest : tile_elems;
-#pragma unroll
-        for (int i = 0; i < RV; ++i) {
-            const int e0 = (tid + i * NT) * VN;
-            if (e0 + VN <= valid) pf[i] = stream_load(reinterpret_cast<const V*>(src + e0));
-            else if (!WHOLE && e0 < valid)               // the end of X inside a vector
-#pragma unroll
-                for (int k = 0; k < VN; ++k) pf[i][k] = e0 + k < valid ? src[e0 + k] : T(0);
-        }
-    };
     auto place = [&](T* buf) {
 #pragma unroll
         for (int i = 0; i < RV; ++i) {
@@ -124,9 +152,7 @@ void mfma_pad_sliced_multiply(const T* __restrict__ Xg, const T* __restrict__ Fg
             if (e0 < tile_elems) *reinterpret_cast<V*>(buf + at[i]) = pf[i];
         }
     };
-
-    if (tile >= t_end) return;
-    fetch(tile);
+    if constexpr (!WHOLE) fetch(tile);
     place(lds);
     if (tile + t_step < t_end) fetch(tile + t_step);
     __syncthreads();
@@ -167,6 +193,7 @@ void mfma_pad_sliced_multiply(const T* __restrict__ Xg, const T* __restrict__ Fg
         if (tile + t_step < t_end) {
             place(lds + (cur ^ 1) * TS * rs);
             if (tile + 2 * t_step < t_end) fetch(tile + 2 * t_step);
+            if constexpr (drain) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
 
         // permuted store: (slice s of row r, column q) -> Y[r*(S*Q) + q*S + s]
