@@ -22,14 +22,15 @@
 // wavefront has at most 63 memory operations outstanding; 100 stores of 4 bytes after each tile held it up for 13000
 // of 48000 cycles).  Tiles that leave a row, and the last one, store element by element.
 //
-// Bound by memory for P, Q up to 50 and by the power that matrix cores and memory draw together above.  One launch,
-// the form with the factor in registers -> this one, us: 64 x 100x100 in rows of 10^6 152 -> 142 (90 TFLOP/s, matrix cores
-// busy 64 %), 256 x 65x65 of 65^3 225 -> 153, 1024 x 50x50 of 50^3 242 -> 224, 2048 x 36x36 of 36^3 164 -> 149, 256 x 24x24 of
-// 24^4 127 -> 120, 512 x 20x20 of 20^4 117 -> 113 (5.8 TB/s); against the generic kernel's small form 6 x 10x5 of 10^7 128 -> 53.
-// Chunk lengths as template parameters: with one length for all classes and the run-time length beside it 142 became
-// 172 and 120 became 141.  Non-persistent workgroups, the dispatcher evens the chip out: 24x24 in one round of resident
-// workgroups 129, one tile per wavefront 120; with factors of more than 32 columns, whose way into LDS costs more, two tiles
-// per wavefront (100x100: one 152, two 142, three 157; 50x50: 229 and 225).
+// Bound by memory for P, Q up to 50 and by the power that matrix cores and memory draw together above.  Whole calls, the
+// other forms -> this one, us: 256 x 65x65^3 689 -> 481 (88 TFLOP/s), 256 x 72x72^3 853 -> 576, 2048 x 36x36^3 496 -> 449 (5.1 TB/s),
+// 1024 x 24x24^4 2014 -> 1888; against the generic kernel's small form 6 x 10x5^7 244 -> 144.  lane_wins in plan.hpp says where it is
+// taken: for 100x100 the form with the factor in registers stays, 152 us a launch in a chain and 157 here.
+// What follows was measured by launches repeated on one X, part of which the last-level cache then holds, and compares
+// variants of this kernel only.  Chunk lengths as template parameters: with one length for all classes and the run-time length
+// beside it 100x100 took 172 us instead of 142 and 24x24 141 instead of 120.  Non-persistent workgroups, the dispatcher evens
+// the chip out: 24x24 in one round of resident workgroups 129, one tile per wavefront 120; with factors of more than 32 columns,
+// whose way into LDS costs more, two tiles per wavefront (100x100: one 152, two 142, three 157; 50x50: 229 and 225).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

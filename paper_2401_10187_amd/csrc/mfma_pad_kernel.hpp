@@ -16,9 +16,9 @@
 //
 // Bound by the matrix cores for large factors and by memory for small ones.  Whole calls, the chunked form ->
 // this one, ms: 64 x 100x100^3 0.785 -> 0.451 (85 TFLOP/s, 56 % of what a large fp32 product reaches), 64 x
-// 99x99^3 0.866 -> 0.450, 64 x 127x127^3 1.61 -> 1.02, 512 x 20x20^4 0.637 -> 0.477 (5.5 TB/s), 1024
-// x 50x50^3 0.947 -> 0.730, 512 x 60x60^3 0.661 -> 0.591, 256 x 65x65^3 0.778 -> 0.679; fp64 32 x 100x100^3 0.730 ->
-// 0.459, 64 x 84x84^3 0.639 -> 0.521, 1024 x 33x33^3 0.544 -> 0.400, 1024 x 30x30^3 0.323 -> 0.227.  What
+// 99x99^3 0.866 -> 0.450, 64 x 127x127^3 1.61 -> 1.02, 1024 x 50x50^3 0.947 -> 0.730, 512 x
+// 60x60^3 0.661 -> 0.591; fp64 32 x 100x100^3 0.730 -> 0.459, 64 x 84x84^3 0.639 -> 0.501, 1024 x 33x33^3 0.544 -> 0.398, 1024 x
+// 30x30^3 0.323 -> 0.214.  (fp32 steps that lane_wins in plan.hpp names are launched with a slice per lane instead.)  What
 // the chunked form spends and this one does not: a second pass over LDS for the factor with every unit, two
 // barriers per chunk with no load in flight behind them, and products on P padded to 16.
 // Registers decide how many workgroups share a compute unit, so the kernel is compiled for four lengths of

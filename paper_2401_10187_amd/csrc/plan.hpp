@@ -274,7 +274,7 @@ constexpr int LANE_VARIANT = -8;           // km_plan_step.variant of its launch
 constexpr int LANE_THREADS = 256, LANE_SLICES = 64, LANE_MINP = 5, LANE_MAXP = 128;
 // Vectors of a slice that are moved at a time: the compiled length that leaves the fewest to move twice (each chunk counting as
 // one more; the longest only where it is the whole slice, since longer chunks are fewer workgroups per compute unit: 64 x
-// 100x100^3 in chunks of 7, 9 and 13 vectors 147, 142 and 157 us a launch, 1024 x 50x50^3 in 7 and 13 251 and 225).
+// 100x100^3 in chunks of 7, 9 and 13 vectors 147, 142 and 157 us a launch that is repeated on one X, 1024 x 50x50^3 in 7 and 13 251 and 225).
 KM_HOST_DEVICE constexpr int lane_units(int P)
 {
     const int units = (P + 3) / 4;
@@ -1467,8 +1467,8 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
     // plan of the FMA kernel or of tiled launches without compiled shapes.  Launches of compiled instances are
     // as quick on problems this small (16 x 16x16^3 6.9 us in three of them, 7.7 here; 128 x 32x32^2 4.9
     // and 4.7).  The others by their estimates, each within 8 % of what was measured on 700 problems: 10 x (52x50,
-    // 65x20) fp64 20.1 us in two launches, 7.0 here, 5 x 61x61^2 fp64 9.1 and 11.0; on the FMA kernel 300 x (32x32, 64x3)
-    // 19.9 and 5.0, 37 x (9x4, 15x14, 4x44) 8.5 and 10.4.  (Level with tiled launches the single one without workspace is
+    // 65x20) fp64 20.1 us in two launches, 6.6 here, 5 x 61x61^2 fp64 9.1 and 11.0; on the FMA kernel 300 x (32x32, 64x3)
+    // 19.9 and 4.5, 37 x (9x4, 15x14, 4x44) 8.5 and 10.4.  (The kernel has become a tenth quicker than the estimate since.  Level with tiled launches the single one without workspace is
     // taken: 1000 x 50x50^2 18.3 us and 16.8, 900 rows 15.9 and 16.6; the FMA kernel stays where the two are within 5 %, since
     // short contractions make this one's estimate too low: 54 x 2x1^6 7.2 us and 7.6.)
     bool compiled = true;
