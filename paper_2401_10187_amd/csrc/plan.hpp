@@ -1303,15 +1303,23 @@ inline void take_inplace_plan(const Problem& pr, Plan& plan)
 //   us, 466 x 33x33^3 116 -> 81, 359 x 36x36^3 100 -> 79; 38x38 to 60x60 0.8 to 1.1 at most sizes), and 65 to 76 columns, whose five
 //   wavefronts there share four SIMDs (122 x 65x65^3 321 -> 218, 89 x 72x72^3 257 -> 223; 81x81 to 100x100 0.87 to 1.0).  Aligned results
 //   of 160 to 320 MiB stay with that form, which leaves them in the last-level cache (8388 x 20x20^3 276 and 286 us; with
-//   ordinary stores 300).
-inline bool lane_wins(const Problem& pr, const km_plan_step& st)
+//   ordinary stores 300), and where a problem has such a step its others of that size stay too: what they left in memory the next
+//   one would read from there (1790 x 31x32^3, one step of three here, 267 -> 311 us; 2545 x 36x25^3 313 -> 347).
+inline double lane_out(const Problem& pr, const km_plan_step& st) { return (double)pr.M * (double)st.k_out * (double)pr.esize; }
+inline bool lane_cached(const Problem& pr, const km_plan_step& st) { return lane_out(pr, st) > 160.0 * 1048576 && lane_out(pr, st) <= 320.0 * 1048576; }
+inline bool lane_stays(const Problem& pr, const km_plan_step& st)
+{
+    const int P = pr.P[st.first_factor];
+    return st.variant == PAD_VARIANT && P <= 36 && pr.Q[st.first_factor] <= 40 && lane_cached(pr, st) && st.k_in / P * (int64_t)pr.esize % 64 == 0;
+}
+// any_stays: lane_stays() is true of a step of this problem
+inline bool lane_wins(const Problem& pr, const km_plan_step& st, bool any_stays)
 {
     const int P = pr.P[st.first_factor], Q = pr.Q[st.first_factor];
     const int64_t S = st.k_in / P, groups = (pr.M * S + 4 * LANE_SLICES - 1) / (4 * LANE_SLICES);
     if (st.variant == PAD_VARIANT) {
-        const double out = (double)pr.M * (double)st.k_out * (double)pr.esize;
-        if ((double)pr.M * (double)st.k_in * (double)pr.esize + out < 96e6) return false;
-        if (P <= 36 && Q <= 40) return S * (int64_t)pr.esize % 64 != 0 || out <= 160.0 * 1048576 || out > 320.0 * 1048576;
+        if ((double)pr.M * (double)st.k_in * (double)pr.esize + lane_out(pr, st) < 96e6) return false;
+        if (P <= 36 && Q <= 40) return !any_stays || !lane_cached(pr, st);
         return P > 32 && P <= 80 && Q > 64 && Q <= 76;
     }
     if (groups < 64 || S < 16 || (S < 256 && Q > 32)) return false;
@@ -1324,12 +1332,14 @@ inline void take_lane_steps(const Problem& pr, const Options& opt, Plan& plan)
 {
     plan.lane_steps.clear();
     if (pr.dtype != KM_F32 || !(opt.kernels >> KM_KERNEL_MFMA_ANY & 1) || !no_wishes(opt)) return;
+    bool any_stays = false;
+    for (const km_plan_step& st : plan.steps) any_stays = any_stays || lane_stays(pr, st);
     for (size_t i = 0; i < plan.steps.size(); ++i) {
         const km_plan_step& had = plan.steps[i];
         if (had.kernel != KM_KERNEL_GENERIC && had.kernel != KM_KERNEL_MFMA_ANY) continue;
         const int P = pr.P[had.first_factor], Q = pr.Q[had.first_factor];
         const LaneShape sh = lane_shape(P, Q, pr.M * (had.k_in / P));
-        if (sh.lds_bytes == 0 || !lane_wins(pr, had)) continue;
+        if (sh.lds_bytes == 0 || !lane_wins(pr, had, any_stays)) continue;
         if (plan.lane_steps.empty()) plan.lane_steps = plan.steps;
         km_plan_step& st = plan.lane_steps[i];
         st.kernel = KM_KERNEL_MFMA_ANY;
