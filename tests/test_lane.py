@@ -68,6 +68,14 @@ def test_where_the_line_lies():
         km.set_option(km.KM_OPT_PREFER_THREADS, old)
 
 
+def test_launches_are_not_mixed_around_the_last_level_cache():
+    """Results of 160 to 320 MiB: with a step of aligned ones in the problem, which stays, the others of that size stay too."""
+    forms = lambda M, P, Q: [s["variant"] for s in km.launches(M, [P] * 3, [Q] * 3, "float32")]
+    assert forms(1790, 31, 32) == forms(2000, 30, 32) == [PAD] * 3
+    assert forms(5488, 22, 22) == [LANE] * 3                   # none is aligned
+    assert forms(682, 36, 36) == [LANE] * 3                    # 121 MiB
+
+
 def test_every_other_step_is_launched_as_planned():
     rng, lane = np.random.default_rng(3), 0
     for _ in range(3000):
