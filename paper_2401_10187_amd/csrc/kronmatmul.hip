@@ -286,6 +286,13 @@ static bool launchable(const km_plan_step& st)
 {
     return st.grid > 0 && st.block > 0 && (double)st.grid * (double)st.block < 4294967296.0;
 }
+// All that a plan would launch, and there is something.
+static bool launchable(const Plan& plan)
+{
+    for (const Step& st : plan.steps)
+        if (!launchable(st.launch())) return false;
+    return !plan.steps.empty();
+}
 
 // The plan of a problem with M > 0 rows, from the cache or made.
 static km_status plan_for(int M, int N, const int* P, const int* Q, int dtype, PlannedRef& out)
@@ -309,8 +316,7 @@ static km_status plan_for(int M, int N, const int* P, const int* Q, int dtype, P
     if (s != KM_OK) return s;
     s = make_plan(made->pr, opt, g_variants, g_num_variants, generic_kernel(dtype), made->plan, made->spare);
     if (s != KM_OK) return s;
-    for (const km_plan_step& st : made->plan.steps)
-        if (!launchable(st)) return KM_EUNSUPPORTED;
+    if (!launchable(made->plan)) return KM_EUNSUPPORTED;
     out = made;
     std::lock_guard<std::mutex> lock(g_mutex);
     cache_plan(out, opt, false);
@@ -393,8 +399,7 @@ static km_status run(const Problem& pr, const Plan& plan, const void* X, const v
 {
     char* ws0 = (char*)ws;
     char* ws1 = ws0 + plan.ws0_bytes;
-    const std::vector<km_plan_step>& steps = plan.launches();
-    const int n = (int)steps.size();
+    const int n = (int)plan.steps.size();
     DeviceState* ds = nullptr;       // set when the call is profiled
     int ev0 = 0;
     std::vector<hipEvent_t> ev;      // this call's events, copied while the lock is held: another thread may grow ds->events
@@ -417,7 +422,7 @@ static km_status run(const Problem& pr, const Plan& plan, const void* X, const v
     const bool profile = ds != nullptr;
     if (profile && hipEventRecord(ev[0], stream) != hipSuccess) return KM_ELAUNCH;
     for (int i = 0; i < n; ++i) {
-        const km_plan_step& st = steps[i];
+        const km_plan_step st = plan.steps[i].launch();
         auto buf = [&](int b) -> void* {
             switch (b) {
                 case KM_BUF_X: return (void*)X;
@@ -622,30 +627,14 @@ static km_status tune(const Problem& pr, const Options& opt, hipStream_t stream,
 
     // Launches timed alone can rank differently than in sequence: keep the measured plan only if the
     // whole sequence beats the planner's own.
-    // Third and fourth candidates: the whole-row kernels wherever they fit, if the planner did not take them itself.
-    auto is_rows = [](const Plan& p, int variant) {
-        return p.steps.size() == 1 && p.steps[0].kernel == KM_KERNEL_ROWS && p.steps[0].variant == variant;
-    };
+    // Third and fourth candidates: the whole-row kernels.
     Plan rows, rows_mfma;
-    bool have_rows = false, have_rows_mfma = false;
-    if (!is_rows(deflt, -1)) {
-        Options force = opt;
-        force.prefer_instance = g_num_variants + 1;
-        Plan none;
-        have_rows = make_plan(pr, force, g_variants, g_num_variants, generic_kernel(pr.dtype), rows, none) == KM_OK &&
-                    is_rows(rows, -1) && launchable(rows.steps[0]);
-    }
-    RowmShape rs;
-    if (!is_rows(deflt, ROWM_VARIANT) && rowm_fits(pr, opt, rs)) {
-        rows_mfma = deflt;                               // (for its flops)
-        take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, rows_mfma);
-        have_rows_mfma = true;
-    }
+    whole_row_candidates(pr, opt, g_variants, g_num_variants, generic_kernel(pr.dtype), deflt, rows, rows_mfma);
     const size_t need_d = deflt.ws0_bytes + deflt.ws1_bytes, need_t = tuned.ws0_bytes + tuned.ws1_bytes;
     const size_t need = need_d > need_t ? need_d : need_t;
     if (need > 0 && hipMalloc(&sc.ws, need) != hipSuccess) { (void)hipGetLastError(); return KM_ENOMEM; }
     constexpr int PLANS = 4;
-    const Plan* plans[PLANS] = {&deflt, &tuned, have_rows ? &rows : nullptr, have_rows_mfma ? &rows_mfma : nullptr};
+    const Plan* plans[PLANS] = {&deflt, &tuned, launchable(rows) ? &rows : nullptr, launchable(rows_mfma) ? &rows_mfma : nullptr};
     float t[PLANS] = {-1.f, -1.f, -1.f, -1.f};
     float quickest = -1.f;
     for (int k = 0; k < PLANS; ++k) {
@@ -934,8 +923,7 @@ km_status kronmatmul_tune(int M, int N, const int* P, const int* Q, km_dtype dty
     made->pr = pr;
     s = tune(pr, opt, (hipStream_t)stream, made->plan, made->spare, tuned_ms, default_ms);
     if (s != KM_OK) return s;
-    for (const km_plan_step& st : made->plan.steps)
-        if (!launchable(st)) return KM_EUNSUPPORTED;
+    if (!launchable(made->plan)) return KM_EUNSUPPORTED;
     std::lock_guard<std::mutex> lock(g_mutex);
     cache_plan(made, opt, true);
     return KM_OK;
@@ -953,8 +941,8 @@ km_status kronmatmul_prepare(int M, int N, const int* P, const int* Q, km_dtype 
     const Plan& plan = planned->plan;
     std::vector<const void*> none(pr.N, nullptr);
     for (const Plan* p : {&plan, &planned->spare})
-        for (const km_plan_step& st : p->launches())
-            if (launch_step(pr, st, nullptr, nullptr, none.data(), nullptr, true) != hipSuccess) return KM_ELAUNCH;
+        for (const Step& st : p->steps)
+            if (launch_step(pr, st.launch(), nullptr, nullptr, none.data(), nullptr, true) != hipSuccess) return KM_ELAUNCH;
     void* unused;
     return static_scratch(&unused);          // kronmatmul_static finds its array's address resolved
 }
@@ -970,9 +958,9 @@ static km_status report(int M, int N, const int* P, const int* Q, km_dtype dtype
     PlannedRef planned;
     s = plan_for(M, N, P, Q, (int)dtype, planned);
     if (s != KM_OK) return s;
-    const std::vector<km_plan_step>& list = launches ? planned->plan.launches() : planned->plan.steps;
+    const std::vector<Step>& list = planned->plan.steps;
     *nsteps = (int)list.size();
-    for (int i = 0; i < *nsteps && i < cap; ++i) steps[i] = list[i];
+    for (int i = 0; i < *nsteps && i < cap; ++i) steps[i] = launches ? list[i].launch() : static_cast<const km_plan_step&>(list[i]);
     return KM_OK;
 }
 

@@ -102,10 +102,18 @@ struct Problem {
     size_t esize = 4;
 };
 
+// A step of a plan as kronmatmul_plan reports it, and whether it is launched with a slice per lane instead.  Both are one object,
+// so that whoever replaces a plan's steps replaces what is launched.
+struct Step : km_plan_step {
+    int64_t lane_grid = 0;                 // > 0: launched with a slice per lane, in so many workgroups
+    int lane_lds_bytes = 0;
+    Step() : km_plan_step() {}
+    Step(const km_plan_step& planned) : km_plan_step(planned) {}
+    km_plan_step launch() const;           // what runs, as kronmatmul_launches reports it
+};
+
 struct Plan {
-    std::vector<km_plan_step> steps;       // as kronmatmul_plan reports them
-    std::vector<km_plan_step> lane_steps;  // the same with those that run with a slice per lane in that form's launches (none: empty)
-    const std::vector<km_plan_step>& launches() const { return lane_steps.empty() ? steps : lane_steps; }
+    std::vector<Step> steps;
     size_t ws0_bytes = 0, ws1_bytes = 0;   // the two intermediates (ws1 unused when Y can serve)
     double flops = 0, bytes = 0;
 };
@@ -295,6 +303,19 @@ KM_HOST_DEVICE constexpr int lane_waves(int G, int U)
 KM_HOST_DEVICE constexpr int lane_lds_bytes(int P, int Q, int U)
 {
     return 16 * ((P + 3) / 4 * ((Q + 3) / 4 * 4) + LANE_THREADS * (U | 1));
+}
+inline km_plan_step Step::launch() const
+{
+    km_plan_step st = *this;
+    if (lane_grid > 0) {
+        st.kernel = KM_KERNEL_MFMA_ANY;
+        st.variant = LANE_VARIANT;
+        st.tile_slices = LANE_SLICES;
+        st.block = LANE_THREADS;
+        st.lds_bytes = lane_lds_bytes;
+        st.grid = lane_grid;
+    }
+    return st;
 }
 // How the kernel would run a factor on `slices` slices (lds_bytes == 0: it cannot).
 struct LaneShape {
@@ -1216,7 +1237,7 @@ inline double inplace_us(const Problem& pr)
     }
     return us;
 }
-inline double rotating_us(const Problem& pr, const std::vector<km_plan_step>& steps)
+inline double rotating_us(const Problem& pr, const std::vector<Step>& steps)
 {
     double us = 0;
     for (const km_plan_step& st : steps) {
@@ -1240,7 +1261,7 @@ inline double rotating_us(const Problem& pr, const std::vector<km_plan_step>& st
 // us: 1024 x 64x64^3 1157 and 987, 64 rows 88 and 79, 64 x 48x48^3 44 and 35, 256 x (96x96, 48x48^2) 308 and 223.  Rotating launches are
 // the faster ones where they take two leading factors at a time and where wide factors have few columns: 128 x (16x16^2, 64x64^2)
 // 569 and 669, 1 x (16x16^4, 48x48^2) 956 and 1134, 20 x (128x128, 48x48^2) 45 and 51, 1 x (128x128, 16x16, 48x48^2) 47 and 58.
-inline bool inplace_wins(const Problem& pr, const std::vector<km_plan_step>& steps)
+inline bool inplace_wins(const Problem& pr, const std::vector<Step>& steps)
 {
     const int P = pr.P[pr.N - 1];
     if (pr.M * (pr.k_in / (P * P)) < 512 * (CHAIN_THREADS / 64)) return false;
@@ -1330,24 +1351,16 @@ inline bool lane_wins(const Problem& pr, const km_plan_step& st, bool any_stays)
 // they were planned for, which is what groups factors and weighs plans against each other (its prices know nothing of this form).
 inline void take_lane_steps(const Problem& pr, const Options& opt, Plan& plan)
 {
-    plan.lane_steps.clear();
     if (pr.dtype != KM_F32 || !(opt.kernels >> KM_KERNEL_MFMA_ANY & 1) || !no_wishes(opt)) return;
     bool any_stays = false;
-    for (const km_plan_step& st : plan.steps) any_stays = any_stays || lane_stays(pr, st);
-    for (size_t i = 0; i < plan.steps.size(); ++i) {
-        const km_plan_step& had = plan.steps[i];
-        if (had.kernel != KM_KERNEL_GENERIC && had.kernel != KM_KERNEL_MFMA_ANY) continue;
-        const int P = pr.P[had.first_factor], Q = pr.Q[had.first_factor];
-        const LaneShape sh = lane_shape(P, Q, pr.M * (had.k_in / P));
-        if (sh.lds_bytes == 0 || !lane_wins(pr, had, any_stays)) continue;
-        if (plan.lane_steps.empty()) plan.lane_steps = plan.steps;
-        km_plan_step& st = plan.lane_steps[i];
-        st.kernel = KM_KERNEL_MFMA_ANY;
-        st.variant = LANE_VARIANT;
-        st.tile_slices = LANE_SLICES;
-        st.block = LANE_THREADS;
-        st.lds_bytes = sh.lds_bytes;
-        st.grid = sh.grid;
+    for (const Step& st : plan.steps) any_stays = any_stays || lane_stays(pr, st);
+    for (Step& st : plan.steps) {
+        if (st.kernel != KM_KERNEL_GENERIC && st.kernel != KM_KERNEL_MFMA_ANY) continue;
+        const int P = pr.P[st.first_factor], Q = pr.Q[st.first_factor];
+        const LaneShape sh = lane_shape(P, Q, pr.M * (st.k_in / P));
+        if (sh.lds_bytes == 0 || !lane_wins(pr, st, any_stays)) continue;
+        st.lane_lds_bytes = sh.lds_bytes;
+        st.lane_grid = sh.grid;
     }
 }
 
@@ -1370,7 +1383,7 @@ inline double fma_rows_us(const Problem& pr, int threads, int64_t lds_bytes, con
 
 // Microseconds of tiled launches, for comparison with the whole-row kernels.  Generic launches in the form that they take, or
 // (by_form false) all at the padded form's rate, which is what decides whether a problem has a whole-row plan at all.
-inline double tiled_us(const Problem& pr, const std::vector<km_plan_step>& steps, const GenericKernel& gen, bool by_form)
+inline double tiled_us(const Problem& pr, const std::vector<Step>& steps, const GenericKernel& gen, bool by_form)
 {
     double us = 0;
     for (const km_plan_step& st : steps) {
@@ -1516,6 +1529,28 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
     if (plan.ws0_bytes + plan.ws1_bytes == 0) spare = Plan();
     take_lane_steps(pr, opt, plan);
     return KM_OK;
+}
+
+// The tuner's candidates besides the planner's own plan and the one it measured: the whole-row kernels wherever they fit, if the
+// planner did not take them itself (no steps: not a candidate).  They need no workspace.
+inline void whole_row_candidates(const Problem& pr, const Options& opt, const Variant* table, int count, const GenericKernel& gen,
+                                 const Plan& deflt, Plan& fma, Plan& mfma)
+{
+    auto is_rows = [](const Plan& p, int variant) {
+        return p.steps.size() == 1 && p.steps[0].kernel == KM_KERNEL_ROWS && p.steps[0].variant == variant;
+    };
+    fma = mfma = Plan();
+    if (!is_rows(deflt, -1)) {
+        Options force = opt;
+        force.prefer_instance = count + 1;
+        Plan none;
+        if (make_plan(pr, force, table, count, gen, fma, none) != KM_OK || !is_rows(fma, -1)) fma = Plan();
+    }
+    RowmShape rs;
+    if (!is_rows(deflt, ROWM_VARIANT) && rowm_fits(pr, opt, rs)) {
+        mfma = deflt;                                    // (for its flops)
+        take_rows_plan(pr, ROWM_VARIANT, rs.threads, rs.lds_bytes, mfma);
+    }
 }
 
 }  // namespace km
