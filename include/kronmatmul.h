@@ -86,8 +86,7 @@ typedef struct {
                               -4, -5: KM_KERNEL_MFMA for two factors and for one that leave their
                               digits in place, -6: KM_KERNEL_FUSED for whole rows of 4^7 floats,
                               -7: for rows of 5^6, 5^8, 3^9 and 3^12 floats,
-                              -8, in kronmatmul_launches only: KM_KERNEL_MFMA_ANY with a slice per
-                              lane)                                                                */
+                              -8: KM_KERNEL_MFMA_ANY with a slice per lane)                        */
     int tiles_per_wg;      /* tiles one workgroup walks over (0: one tile per workgroup)           */
     int tile_order;        /* walk: 0 contiguous range, 1 interleaved pairs, 2 strided by the grid,
                               3 strided inside the XCD's eighth of the tiles, 4 strided by the grid
@@ -160,14 +159,12 @@ km_status kronmatmul_transposed_ws(int M, int N, const int* P, const int* Q,
                                    const void* X, const void* const* Ft, void* Y,
                                    km_dtype dtype, void* workspace, size_t workspace_bytes, void* stream);
 
-/* The launches kronmatmul would issue for this problem, in order, by the kernels they are planned for.  Writes at most `cap` steps and
+/* The launches kronmatmul would issue for this problem, in order.  Writes at most `cap` steps and
  * the total count to *nsteps.  Pure host computation (no device needed). */
 km_status kronmatmul_plan(int M, int N, const int* P, const int* Q, km_dtype dtype,
                           km_plan_step* steps, int cap, int* nsteps);
 
-/* The same launches in the form they run in: of the fp32 steps that kronmatmul_plan gives to KM_KERNEL_GENERIC or KM_KERNEL_MFMA_ANY,
- * those with many slices run as variant -8, with its grid, workgroup and LDS (same factors, rows and buffers).  Every other step
- * is as in kronmatmul_plan. */
+/* The same (an earlier version listed here what kronmatmul_plan left out: steps of variant -8). */
 km_status kronmatmul_launches(int M, int N, const int* P, const int* Q, km_dtype dtype,
                               km_plan_step* steps, int cap, int* nsteps);
 

@@ -166,8 +166,7 @@ def plan(M, P, Q, dtype):
 
 
 def launches(M, P, Q, dtype):
-    """The same launches in the form they run in: steps of the generic and the run-time-shape MFMA kernel that
-    have many slices run as variant -8."""
+    """The same list, by the name that an earlier version gave it."""
     return _steps("kronmatmul_launches", M, P, Q, dtype)
 
 

@@ -289,8 +289,8 @@ static bool launchable(const km_plan_step& st)
 // All that a plan would launch, and there is something.
 static bool launchable(const Plan& plan)
 {
-    for (const Step& st : plan.steps)
-        if (!launchable(st.launch())) return false;
+    for (const km_plan_step& st : plan.steps)
+        if (!launchable(st)) return false;
     return !plan.steps.empty();
 }
 
@@ -422,7 +422,7 @@ static km_status run(const Problem& pr, const Plan& plan, const void* X, const v
     const bool profile = ds != nullptr;
     if (profile && hipEventRecord(ev[0], stream) != hipSuccess) return KM_ELAUNCH;
     for (int i = 0; i < n; ++i) {
-        const km_plan_step st = plan.steps[i].launch();
+        const km_plan_step& st = plan.steps[i];
         auto buf = [&](int b) -> void* {
             switch (b) {
                 case KM_BUF_X: return (void*)X;
@@ -941,13 +941,14 @@ km_status kronmatmul_prepare(int M, int N, const int* P, const int* Q, km_dtype 
     const Plan& plan = planned->plan;
     std::vector<const void*> none(pr.N, nullptr);
     for (const Plan* p : {&plan, &planned->spare})
-        for (const Step& st : p->steps)
-            if (launch_step(pr, st.launch(), nullptr, nullptr, none.data(), nullptr, true) != hipSuccess) return KM_ELAUNCH;
+        for (const km_plan_step& st : p->steps)
+            if (launch_step(pr, st, nullptr, nullptr, none.data(), nullptr, true) != hipSuccess) return KM_ELAUNCH;
     void* unused;
     return static_scratch(&unused);          // kronmatmul_static finds its array's address resolved
 }
 
-static km_status report(int M, int N, const int* P, const int* Q, km_dtype dtype, km_plan_step* steps, int cap, int* nsteps, bool launches)
+km_status kronmatmul_plan(int M, int N, const int* P, const int* Q, km_dtype dtype,
+                          km_plan_step* steps, int cap, int* nsteps)
 {
     if (!nsteps || cap < 0 || (cap > 0 && !steps)) return KM_EINVAL;
     Problem pr;
@@ -958,22 +959,16 @@ static km_status report(int M, int N, const int* P, const int* Q, km_dtype dtype
     PlannedRef planned;
     s = plan_for(M, N, P, Q, (int)dtype, planned);
     if (s != KM_OK) return s;
-    const std::vector<Step>& list = planned->plan.steps;
-    *nsteps = (int)list.size();
-    for (int i = 0; i < *nsteps && i < cap; ++i) steps[i] = launches ? list[i].launch() : static_cast<const km_plan_step&>(list[i]);
+    const Plan& plan = planned->plan;
+    *nsteps = (int)plan.steps.size();
+    for (int i = 0; i < *nsteps && i < cap; ++i) steps[i] = plan.steps[i];
     return KM_OK;
-}
-
-km_status kronmatmul_plan(int M, int N, const int* P, const int* Q, km_dtype dtype,
-                          km_plan_step* steps, int cap, int* nsteps)
-{
-    return report(M, N, P, Q, dtype, steps, cap, nsteps, false);
 }
 
 km_status kronmatmul_launches(int M, int N, const int* P, const int* Q, km_dtype dtype,
                               km_plan_step* steps, int cap, int* nsteps)
 {
-    return report(M, N, P, Q, dtype, steps, cap, nsteps, true);
+    return kronmatmul_plan(M, N, P, Q, dtype, steps, cap, nsteps);
 }
 
 long long kronmatmul_store_column(long long k_in, long long p_group, long long tile_k,

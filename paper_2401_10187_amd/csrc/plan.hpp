@@ -102,18 +102,8 @@ struct Problem {
     size_t esize = 4;
 };
 
-// A step of a plan as kronmatmul_plan reports it, and whether it is launched with a slice per lane instead.  Both are one object,
-// so that whoever replaces a plan's steps replaces what is launched.
-struct Step : km_plan_step {
-    int64_t lane_grid = 0;                 // > 0: launched with a slice per lane, in so many workgroups
-    int lane_lds_bytes = 0;
-    Step() : km_plan_step() {}
-    Step(const km_plan_step& planned) : km_plan_step(planned) {}
-    km_plan_step launch() const;           // what runs, as kronmatmul_launches reports it
-};
-
 struct Plan {
-    std::vector<Step> steps;
+    std::vector<km_plan_step> steps;
     size_t ws0_bytes = 0, ws1_bytes = 0;   // the two intermediates (ws1 unused when Y can serve)
     double flops = 0, bytes = 0;
 };
@@ -303,19 +293,6 @@ KM_HOST_DEVICE constexpr int lane_waves(int G, int U)
 KM_HOST_DEVICE constexpr int lane_lds_bytes(int P, int Q, int U)
 {
     return 16 * ((P + 3) / 4 * ((Q + 3) / 4 * 4) + LANE_THREADS * (U | 1));
-}
-inline km_plan_step Step::launch() const
-{
-    km_plan_step st = *this;
-    if (lane_grid > 0) {
-        st.kernel = KM_KERNEL_MFMA_ANY;
-        st.variant = LANE_VARIANT;
-        st.tile_slices = LANE_SLICES;
-        st.block = LANE_THREADS;
-        st.lds_bytes = lane_lds_bytes;
-        st.grid = lane_grid;
-    }
-    return st;
 }
 // How the kernel would run a factor on `slices` slices (lds_bytes == 0: it cannot).
 struct LaneShape {
@@ -1237,7 +1214,7 @@ inline double inplace_us(const Problem& pr)
     }
     return us;
 }
-inline double rotating_us(const Problem& pr, const std::vector<Step>& steps)
+inline double rotating_us(const Problem& pr, const std::vector<km_plan_step>& steps)
 {
     double us = 0;
     for (const km_plan_step& st : steps) {
@@ -1261,7 +1238,7 @@ inline double rotating_us(const Problem& pr, const std::vector<Step>& steps)
 // us: 1024 x 64x64^3 1157 and 987, 64 rows 88 and 79, 64 x 48x48^3 44 and 35, 256 x (96x96, 48x48^2) 308 and 223.  Rotating launches are
 // the faster ones where they take two leading factors at a time and where wide factors have few columns: 128 x (16x16^2, 64x64^2)
 // 569 and 669, 1 x (16x16^4, 48x48^2) 956 and 1134, 20 x (128x128, 48x48^2) 45 and 51, 1 x (128x128, 16x16, 48x48^2) 47 and 58.
-inline bool inplace_wins(const Problem& pr, const std::vector<Step>& steps)
+inline bool inplace_wins(const Problem& pr, const std::vector<km_plan_step>& steps)
 {
     const int P = pr.P[pr.N - 1];
     if (pr.M * (pr.k_in / (P * P)) < 512 * (CHAIN_THREADS / 64)) return false;
@@ -1347,20 +1324,24 @@ inline bool lane_wins(const Problem& pr, const km_plan_step& st, bool any_stays)
     return st.kernel == KM_KERNEL_GENERIC ? P <= 32 || P > 64 || Q > 8 : P > 32 && groups >= 128;
 }
 
-// The steps that the slice-per-lane kernel runs faster go to it when they are launched.  The plan itself keeps naming the kernel
-// they were planned for, which is what groups factors and weighs plans against each other (its prices know nothing of this form).
+// The steps that the slice-per-lane kernel runs faster go to it, once the plan is made: the prices that group factors and weigh
+// plans against each other are those of the kernels it takes the steps from.
 inline void take_lane_steps(const Problem& pr, const Options& opt, Plan& plan)
 {
     if (pr.dtype != KM_F32 || !(opt.kernels >> KM_KERNEL_MFMA_ANY & 1) || !no_wishes(opt)) return;
     bool any_stays = false;
-    for (const Step& st : plan.steps) any_stays = any_stays || lane_stays(pr, st);
-    for (Step& st : plan.steps) {
+    for (const km_plan_step& st : plan.steps) any_stays = any_stays || lane_stays(pr, st);
+    for (km_plan_step& st : plan.steps) {
         if (st.kernel != KM_KERNEL_GENERIC && st.kernel != KM_KERNEL_MFMA_ANY) continue;
         const int P = pr.P[st.first_factor], Q = pr.Q[st.first_factor];
         const LaneShape sh = lane_shape(P, Q, pr.M * (st.k_in / P));
         if (sh.lds_bytes == 0 || !lane_wins(pr, st, any_stays)) continue;
-        st.lane_lds_bytes = sh.lds_bytes;
-        st.lane_grid = sh.grid;
+        st.kernel = KM_KERNEL_MFMA_ANY;
+        st.variant = LANE_VARIANT;
+        st.tile_slices = LANE_SLICES;
+        st.block = LANE_THREADS;
+        st.lds_bytes = sh.lds_bytes;
+        st.grid = sh.grid;
     }
 }
 
@@ -1383,7 +1364,7 @@ inline double fma_rows_us(const Problem& pr, int threads, int64_t lds_bytes, con
 
 // Microseconds of tiled launches, for comparison with the whole-row kernels.  Generic launches in the form that they take, or
 // (by_form false) all at the padded form's rate, which is what decides whether a problem has a whole-row plan at all.
-inline double tiled_us(const Problem& pr, const std::vector<Step>& steps, const GenericKernel& gen, bool by_form)
+inline double tiled_us(const Problem& pr, const std::vector<km_plan_step>& steps, const GenericKernel& gen, bool by_form)
 {
     double us = 0;
     for (const km_plan_step& st : steps) {

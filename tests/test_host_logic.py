@@ -190,16 +190,17 @@ def test_padded_shapes_go_to_the_run_time_shape_mfma_kernel_within_its_padding_l
     without a compiled instance stays with the generic kernel.  Factors of up to 128 rows and columns whose
     tiles fit take the form that holds the factor in registers (variant -3), tiles of 16 slices times the
     blocks and groups of wavefronts it is compiled for; of the others, which are walked through LDS in chunks
-    (variant -1), the narrow shape (slices of up to 128 bytes) takes 256 slices per unit, the wide one 128."""
+    (variant -1), the narrow shape (slices of up to 128 bytes) takes 256 slices per unit, the wide one 128.
+    (fp32 problems below the sizes from which a slice goes to each lane.)"""
     def kernels(dtype, M, shapes):
         return [(s["kernel"], s["variant"], s["tile_slices"]) for s in km.plan(M, [p for p, _ in shapes], [q for _, q in shapes], dtype)]
     any_, gen = km.KM_KERNEL_MFMA_ANY, km.KM_KERNEL_GENERIC
-    assert kernels("float32", 4096, [(20, 20)] * 3) == [(any_, -3, 256)] * 3          # 32*32 / 400 = 2.56
+    assert kernels("float32", 1024, [(20, 20)] * 3) == [(any_, -3, 256)] * 3          # 32*32 / 400 = 2.56
     assert kernels("float32", 4096, [(36, 50)] * 3) == [(any_, -3, 64)] * 3
-    assert kernels("float32", 4096, [(20, 15)] * 3) == [(any_, -3, 256)] * 3          # Q need not be a whole vector
-    assert [k for k, *_ in kernels("float32", 4096, [(20, 7)] * 4)] == [gen] * 4       # 32*16 / 140 = 3.7
-    assert kernels("float32", 4096, [(22, 22)] * 4) == [(any_, -3, 256)] * 4          # slices not 16-byte aligned, but one chunk
-    assert kernels("float32", 1024, [(66, 66)] * 3) == [(any_, -3, 64)] * 3           # ... or longer than a chunk (264 bytes)
+    assert kernels("float32", 1024, [(20, 15)] * 3) == [(any_, -3, 256)] * 3          # Q need not be a whole vector
+    assert [k for k, *_ in kernels("float32", 2, [(20, 7)] * 4)] == [gen] * 4       # 32*16 / 140 = 3.7
+    assert kernels("float32", 40, [(22, 22)] * 4) == [(any_, -3, 256)] * 4          # slices not 16-byte aligned, but one chunk
+    assert kernels("float32", 32, [(66, 66)] * 3) == [(any_, -3, 64)] * 3           # ... or longer than a chunk (264 bytes)
     assert kernels("float64", 64, [(16, 20)] * 4) == [(any_, -3, 128)] * 4          # 16*32 / 320 = 1.6, 128-byte slices
     assert kernels("float64", 4096, [(26, 26)] * 3) == [(any_, -3, 128)] * 3          # 32*32 / 676 = 1.5
     assert kernels("float64", 4096, [(40, 40)] * 3) == [(any_, -3, 64)] * 3           # 48*48 / 1600 = 1.44
@@ -356,9 +357,10 @@ def test_launches_stay_below_the_work_item_limit():
 
 
 def test_tile_instances_are_skipped_for_rows_beyond_32_bit_offsets():
-    # 2^31 bytes per row and more: only the generic kernel addresses such rows
+    # 2^31 bytes per row and more: only the generic kernel addresses such rows, and the one with a slice per lane (variant -8)
     steps = km.plan(1, [8] * 10, [8] * 10, "float32")
-    assert all(st["kernel"] == km.KM_KERNEL_GENERIC for st in steps)
+    assert all(st["kernel"] == km.KM_KERNEL_GENERIC or st["variant"] == -8 for st in steps)
+    assert all(st["kernel"] == km.KM_KERNEL_GENERIC for st in km.plan(1, [8] * 10, [8] * 10, "float64"))
 
 
 def test_options_round_trip():

@@ -1,4 +1,4 @@
-"""The run-time-shape MFMA kernel with a slice per lane (variant -8 of kronmatmul_launches)."""
+"""The run-time-shape MFMA kernel with a slice per lane (variant -8 of kronmatmul_plan)."""
 import numpy as np
 import pytest
 
@@ -25,7 +25,7 @@ def _shapes(S, P, Q):
 
 
 def _first(M, shapes, dtype="float32"):
-    return km.launches(M, [p for p, _ in shapes], [q for _, q in shapes], dtype)[0]
+    return km.plan(M, [p for p, _ in shapes], [q for _, q in shapes], dtype)[0]
 
 
 # (rows, slices of a row, P, Q): every compiled chunk length (2 to 7, 9 and 13 vectors), one chunk, several and overlapping ones, 0 to 3
@@ -43,12 +43,10 @@ CASES = [
 
 @pytest.mark.parametrize("M,S,P,Q", CASES)
 def test_the_list_takes_the_kernel_and_its_launches_fit(M, S, P, Q):
-    st, planned = _first(M, _shapes(S, P, Q)), km.plan(M, [S, P], [1, Q], "float32")[0]
+    st = _first(M, _shapes(S, P, Q))
     assert st["variant"] == LANE and st["kernel"] == km.KM_KERNEL_MFMA_ANY
     assert st["block"] == 256 and st["grid"] % 8 == 0 and st["lds_bytes"] <= 160 * 1024
     assert 256 * (st["grid"] - 8) < M * S <= 2 * 256 * st["grid"]           # four tiles of 64 slices, once or twice
-    same = ("first_factor", "num_factors", "k_in", "k_out", "src", "dst", "tile_rows")
-    assert planned["variant"] in (-1, PAD) and all(st[k] == planned[k] for k in same)
 
 
 def test_where_the_line_lies():
@@ -70,25 +68,40 @@ def test_where_the_line_lies():
 
 def test_launches_are_not_mixed_around_the_last_level_cache():
     """Results of 160 to 320 MiB: with a step of aligned ones in the problem, which stays, the others of that size stay too."""
-    forms = lambda M, P, Q: [s["variant"] for s in km.launches(M, [P] * 3, [Q] * 3, "float32")]
+    forms = lambda M, P, Q: [s["variant"] for s in km.plan(M, [P] * 3, [Q] * 3, "float32")]
     assert forms(1790, 31, 32) == forms(2000, 30, 32) == [PAD] * 3
     assert forms(5488, 22, 22) == [LANE] * 3                   # none is aligned
     assert forms(682, 36, 36) == [LANE] * 3                    # 121 MiB
 
 
-def test_every_other_step_is_launched_as_planned():
+def test_the_plan_names_what_runs_and_other_steps_stay_as_they_are():
+    """Beside the plan without this kernel (an option that asks for a workgroup size no kernel has): its steps replace generic ones and
+    ones of its family, factors, rows and buffers stay.  kronmatmul_launches gives the same list."""
     rng, lane = np.random.default_rng(3), 0
+    old = km.get_option(km.KM_OPT_PREFER_THREADS)
     for _ in range(3000):
         dtype = "float32" if rng.random() < 0.7 else "float64"
         n = int(rng.integers(1, 5))
         P, Q = [[int(2 ** rng.uniform(1, 7.2)) for _ in range(n)] for _ in range(2)]
         M = int(10 ** rng.uniform(0, 7))
-        for st, had in zip(km.launches(M, P, Q, dtype), km.plan(M, P, Q, dtype)):
-            assert st == had or st["variant"] == LANE
-            if st["variant"] == LANE:
-                lane += 1
-                assert dtype == "float32" and had["variant"] in (-1, PAD) and had["kernel"] in (km.KM_KERNEL_GENERIC, km.KM_KERNEL_MFMA_ANY)
-                assert 0 < st["grid"] * st["block"] < 2 ** 32
+        steps = km.plan(M, P, Q, dtype)
+        assert km.launches(M, P, Q, dtype) == steps
+        if LANE not in [st["variant"] for st in steps]:
+            continue
+        try:
+            km.set_option(km.KM_OPT_PREFER_THREADS, 1)
+            without = km.plan(M, P, Q, dtype)
+        finally:
+            km.set_option(km.KM_OPT_PREFER_THREADS, old)
+        assert len(without) == len(steps) and dtype == "float32"
+        for st, had in zip(steps, without):
+            if st["variant"] != LANE:
+                assert st == had
+                continue
+            lane += 1
+            assert had["variant"] in (-1, PAD) and had["kernel"] in (km.KM_KERNEL_GENERIC, km.KM_KERNEL_MFMA_ANY)
+            assert all(st[k] == had[k] for k in ("first_factor", "num_factors", "k_in", "k_out", "src", "dst", "tile_rows"))
+            assert 0 < st["grid"] * st["block"] < 2 ** 32
     assert lane > 300
 
 
@@ -132,7 +145,7 @@ def test_replays_from_a_graph_and_both_store_forms():
     """24x24^3, 1300 rows: an intermediate of 69 MiB, stored so that it stays in the last-level cache, and the last one not; every
     replay is compared, with eager work between them."""
     M, shapes = 1300, [(24, 24)] * 3
-    assert [s["variant"] for s in km.launches(M, [24] * 3, [24] * 3, "float32")] == [LANE] * 3
+    assert [s["variant"] for s in km.plan(M, [24] * 3, [24] * 3, "float32")] == [LANE] * 3
     X = torch.randn(M, 24 ** 3, device="cuda")
     F = [torch.randn(24, 24, device="cuda") / 24 ** 0.5 for _ in range(3)]
     want = km.kronmatmul(X, F)

@@ -40,11 +40,10 @@ int main()
         opt.kernels = 0x27;                              // (tiled launches, as where the whole-row kernels do not win)
         if (make_plan(pr, opt, nullptr, 0, gen, deflt, spare) != KM_OK) return printf("unplanned\\n"), 1;
         bool lane = false;
-        for (const Step& st : deflt.steps) {
-            const km_plan_step l = st.launch();
+        for (const km_plan_step& l : deflt.steps) {
             lane = lane || l.variant == LANE_VARIANT;
             const size_t out = (size_t)(pr.M * l.k_out) * pr.esize;
-            if (l.src == l.dst || l.first_factor != st.first_factor || l.k_out != st.k_out || l.dst != st.dst || l.src != st.src) return printf("buffers\\n"), 1;
+            if (l.src == l.dst) return printf("buffers\\n"), 1;
             if ((l.dst == KM_BUF_WS0 && deflt.ws0_bytes < out) || (l.dst == KM_BUF_WS1 && deflt.ws1_bytes < out)) return printf("no room\\n"), 1;
         }
         if (!lane) continue;
@@ -56,7 +55,7 @@ int main()
             const Plan& p = *rows[which];
             if (p.steps.empty()) continue;
             ++(which ? mfma_rows : fma_rows);
-            const km_plan_step l = p.steps[0].launch();
+            const km_plan_step& l = p.steps[0];
             if (p.steps.size() != 1 || l.kernel != KM_KERNEL_ROWS || l.variant != (which ? ROWM_VARIANT : -1) || l.num_factors != n) return printf("other launches\\n"), 1;
             if (l.src != KM_BUF_X || l.dst != KM_BUF_Y || p.ws0_bytes + p.ws1_bytes != 0) return printf("workspace\\n"), 1;
         }
@@ -72,7 +71,7 @@ int main()
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,shapes", [(644, [(40, 118), (6, 23)]), (719, [(2, 1), (13, 3), (90, 76), (2, 1)]), (1024, [(24, 1), (60, 23), (5, 9)])], ids=str)
 def test_tuned_plans_launch_what_they_have_room_for(M, shapes):
-    """Whatever the tuner keeps: kronmatmul_launches names the planned steps, every workspace they use has a size, and the
+    """Whatever the tuner keeps: every workspace that the planned steps use has a size, and the
     calls with and without a workspace of the caller's agree with the reference (bit for bit on small integers)."""
     import oracle
     P, Q = [p for p, _ in shapes], [q for _, q in shapes]
@@ -82,17 +81,17 @@ def test_tuned_plans_launch_what_they_have_room_for(M, shapes):
     old = km.get_option(km.KM_OPT_KERNELS)
     try:
         km.set_option(km.KM_OPT_KERNELS, 39)             # the planner's own plan in tiled launches
-        assert LANE in [s["variant"] for s in km.launches(M, P, Q, "float32")]
+        assert LANE in [s["variant"] for s in km.plan(M, P, Q, "float32")]
         for kernels in (39, 55):
             km.set_option(km.KM_OPT_KERNELS, kernels)
             before = km.workspace_size(M, P, Q, "float32")
             print("tune M=%d %s kernels %d" % (M, shapes, kernels), flush=True)
             km.tune(M, P, Q, "float32")
-            planned, launched = km.plan(M, P, Q, "float32"), km.launches(M, P, Q, "float32")
+            steps = km.plan(M, P, Q, "float32")
             need = km.workspace_size(M, P, Q, "float32")
-            assert len(planned) == len(launched) and need <= before
-            assert (need > 0) == any(s["dst"] in (km.KM_BUF_WS0, km.KM_BUF_WS1) for s in launched)
-            assert all(s["src"] != s["dst"] for s in launched)
+            assert need <= before
+            assert (need > 0) == any(s["dst"] in (km.KM_BUF_WS0, km.KM_BUF_WS1) for s in steps)
+            assert all(s["src"] != s["dst"] for s in steps)
             assert np.array_equal(km.kronmatmul(Xd, Fd).cpu().numpy(), ref)
             ws = torch.empty(max(need, 1), dtype=torch.uint8, device="cuda")
             Y = torch.empty(ref.shape, device="cuda")
