@@ -20,7 +20,7 @@ static hipError_t launch_lane_shape(const LaunchArgs& a)
     // (output runs that do not start on 64-byte boundaries: ordinary stores, as in launch_any.hpp)
     const bool keep = a.keep_output || S * (int64_t)sizeof(float) % 64 != 0;
     hipLaunchKernelGGL(kern, dim3((unsigned)st.grid), dim3((unsigned)st.block), (size_t)st.lds_bytes, a.stream, (const float*)a.src,
-                       (const float*)a.factors[f], (float*)a.dst, S, P, Q, ((P + 3) / 4 + U - 1) / U, S > 1 ? ~(uint64_t)0 / (uint64_t)S + 1 : 0,
+                       (const float*)a.factors[f], (float*)a.dst, S, P, Q, ((P + 3) / 4 + U - 1) / U, lane_row_magic(S),
                        S >= LANE_SLICES || S == 1 ? 0u : (unsigned)(((1ull << 32) + (unsigned long long)S - 1) / (unsigned long long)S),
                        slices, (slices + LANE_SLICES - 1) / LANE_SLICES, keep ? 1 : 0);
     return hipGetLastError();

@@ -70,7 +70,7 @@ __device__ __forceinline__ lane_vec lane_transpose(lane_vec d)
     return lane_vec{d0, d1, d2, d3};
 }
 
-// S_magic: 2^64 / S rounded up (S > 1); s_magic: 2^32 / S rounded up where a tile holds several rows (1 < S < 64), else 0.
+// S_magic: lane_row_magic(S); s_magic: 2^32 / S rounded up where a tile holds several rows (1 < S < 64), else 0.
 template <int G, int U>
 __global__ __launch_bounds__(LANE_THREADS, lane_waves(G, U))
 void mfma_lane_sliced_multiply(const float* __restrict__ Xg, const float* __restrict__ Fg, float* __restrict__ Yg, int64_t S, int P,

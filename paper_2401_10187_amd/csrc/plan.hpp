@@ -270,6 +270,10 @@ inline PadShape pad_shape(int P, int Q, size_t esize, int64_t slices)
 // wavefront, factors of LANE_MINP to LANE_MAXP rows and up to LANE_MAXP columns.
 constexpr int LANE_VARIANT = -8;           // km_plan_step.variant of its launches
 constexpr int LANE_THREADS = 256, LANE_SLICES = 64, LANE_MINP = 5, LANE_MAXP = 128;
+// A slice's row is found as the high half of (slice * lane_row_magic(slices of a row)): exact while their number times that of
+// a row's stays below 2^64 (1 x (5x1)^15, 2^32.5 slices in one row, finds the last one in a second row).
+constexpr int64_t LANE_MAX_SLICES = (int64_t)1 << 32;
+KM_HOST_DEVICE constexpr uint64_t lane_row_magic(int64_t S) { return S > 1 ? ~(uint64_t)0 / (uint64_t)S + 1 : 0; }      // 2^64 / S rounded up
 // Vectors of a slice that are moved at a time: the compiled length that leaves the fewest to move twice (each chunk counting as
 // one more; the longest only where it is the whole slice, since longer chunks are fewer workgroups per compute unit: 64 x
 // 100x100^3 in chunks of 7, 9 and 13 vectors 147, 142 and 157 us a launch that is repeated on one X, 1024 x 50x50^3 in 7 and 13 251 and 225).
@@ -302,7 +306,7 @@ struct LaneShape {
 inline LaneShape lane_shape(int P, int Q, int64_t slices)
 {
     LaneShape r;
-    if (P < LANE_MINP || P > LANE_MAXP || Q < 1 || Q > LANE_MAXP || slices >= (int64_t)1 << 40) return r;
+    if (P < LANE_MINP || P > LANE_MAXP || Q < 1 || Q > LANE_MAXP || slices > LANE_MAX_SLICES) return r;
     const int U = lane_units(P), G = (Q + 3) / 4;
     r.lds_bytes = lane_lds_bytes(P, Q, U);
     r.per_cu = 160 * 1024 / r.lds_bytes < lane_waves(G, U) ? 160 * 1024 / r.lds_bytes : lane_waves(G, U);

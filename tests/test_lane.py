@@ -1,4 +1,7 @@
 """The run-time-shape MFMA kernel with a slice per lane (variant -8 of kronmatmul_plan)."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 
@@ -7,6 +10,7 @@ import kron_inputs
 torch = pytest.importorskip("torch")          # before the library is loaded: both then use torch's HIP runtime
 import paper_2401_10187_amd as km  # noqa: E402
 
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 LANE, PAD = -8, -3
 
 
@@ -64,6 +68,37 @@ def test_where_the_line_lies():
         assert _first(4000, _shapes(320, 10, 3))["variant"] == -1
     finally:
         km.set_option(km.KM_OPT_PREFER_THREADS, old)
+
+
+def test_rows_of_slices_are_found_exactly_up_to_the_most_slices(tmp_path):
+    """The kernel's division by the slices of a row, for the first and the last slices of rows and of all: exact for as many slices as a
+    launch may have, and problems of more are left to the generic kernel.  (The last slice of 1 x (5x1)^15, 2^32.5 slices, is one that it
+    would put into a second row.)"""
+    src = tmp_path / "rows.cpp"
+    src.write_text("""
+#include "paper_2401_10187_amd/csrc/plan.hpp"
+#include <cstdio>
+#include <random>
+using namespace km;
+static int64_t found(int64_t g, int64_t S) { return S == 1 ? g : (int64_t)(((unsigned __int128)(uint64_t)g * lane_row_magic(S)) >> 64); }
+int main()
+{
+    std::mt19937_64 rng(9);
+    for (int k = 0; k < 200000; ++k) {
+        const int64_t S = k < 64 ? LANE_MAX_SLICES - k : 1 + ((int64_t)(rng() % (uint64_t)LANE_MAX_SLICES) >> rng() % 32);
+        const int64_t rows = LANE_MAX_SLICES / S, r = rng() % (uint64_t)rows;
+        for (int64_t g : {r * S, r * S + S - 1, (rows - 1) * S, rows * S - 1, r * S + (int64_t)(rng() % (uint64_t)S)})
+            if (found(g, S) != g / S) return printf("slice %lld of %lld a row\\n", (long long)g, (long long)S), 1;
+        if (lane_shape(5, 1, rows * S).lds_bytes == 0) return printf("refused\\n"), 1;
+    }
+    const int64_t S = 6103515625;                        // 5^14
+    printf("%d %d %d\\n", found(S - 1, S) == 0, lane_shape(5, 1, S).lds_bytes, lane_shape(5, 1, LANE_MAX_SLICES + 1).lds_bytes);
+}
+""")
+    exe = tmp_path / "rows"
+    subprocess.run(["g++", "-std=c++17", "-I", ROOT, "-o", str(exe), str(src)], check=True)
+    assert subprocess.run([str(exe)], capture_output=True, text=True).stdout.strip() == "0 0 0"
+    assert [st["variant"] for st in km.plan(1, [5] * 15, [1] * 15, "float32")][:3] == [-1, LANE, LANE]
 
 
 def test_launches_are_not_mixed_around_the_last_level_cache():
