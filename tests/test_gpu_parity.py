@@ -809,14 +809,26 @@ def test_full_size_permutation_factors_move_columns_bit_exact(name):
     torch.cuda.empty_cache()
 
 
-def test_rows_beyond_32_bit_offsets_use_the_generic_kernel_and_stay_exact():
+@pytest.mark.parametrize("kernels,variant", [(1, -1), (None, -8)])
+def test_rows_beyond_32_bit_offsets_use_the_generic_kernel_and_stay_exact(kernels, variant):
     """Maximum sizes: one row of 8^10 floats (4 GiB) is past the 32-bit in-row offsets of the tiled
-    kernels, so every factor takes the generic kernel with 64-bit indexing.  Cyclic-shift factors
+    kernels, so every factor takes the generic kernel with 64-bit indexing or, by default, the one with a
+    slice per lane (variant -8).  Cyclic-shift factors
     (F[p][(p+1) % 8] = 1) make Y an exactly known column permutation of X, checked bit for bit on
     sampled columns: output digits (q_1..q_10) come from input digits ((q_i - 1) % 8)."""
     n, P = 10, 8
+    old = km.get_option(km.KM_OPT_KERNELS)
+    try:
+        if kernels is not None:
+            km.set_option(km.KM_OPT_KERNELS, kernels)
+        _cyclic_shifts_of_one_row(n, P, variant)
+    finally:
+        km.set_option(km.KM_OPT_KERNELS, old)
+
+
+def _cyclic_shifts_of_one_row(n, P, variant):
     steps = km.plan(1, [P] * n, [P] * n, "float32")
-    assert all(st["kernel"] == km.KM_KERNEL_GENERIC for st in steps)
+    assert all(st["variant"] == variant for st in steps)
     K = P ** n
     gen = torch.Generator(device="cuda")
     gen.manual_seed(1234)
