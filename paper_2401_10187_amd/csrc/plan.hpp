@@ -1292,40 +1292,55 @@ inline void take_inplace_plan(const Problem& pr, Plan& plan)
     assign_buffers(pr, plan);
 }
 
-// Does the slice-per-lane kernel beat the one that a step was given to?  Measured launch by launch on 800 of random sizes and on
-// whole calls of equal factors:
-// - the generic kernel and the chunked form, from 64 workgroups on: 1.3 times as fast on average (6 x 10x5 of 10^7 128 -> 53 us, 1780
-//   groups of 6x14 13.5 -> 9.1, 4794 of 50x8 89 -> 46, 2572 of 72x72 157 -> 116), at worst 0.8; fewer workgroups
-//   (128 in the chunked form's place) leave it a single tile's latency, which grows with P times Q (42 groups of 39x107 8.1 -> 12.0, 76
-//   of 60x11 5.2 -> 6.4).  Not the generic kernel's tall slices with few columns, 33 to 64 elements, nor what the chunked form
-//   takes of up to 32 (0.8 to 1.1), nor rows of a few slices, whose tiles go on in the next row and are stored element by element
-//   (1067 x (8x65, 6x49, 5x12) with its launch of 96 slices a row here 52 -> 68 us).
-// - the form with the factor in registers where that computes many columns for few, from 96 MB moved on (below, the one tile that a
-//   wavefront gets here takes longer than what registers save): up to 36 x 40 1.1 to 1.4 times as fast (calls of 1213 x 24x24^3 86 -> 67
-//   us, 466 x 33x33^3 116 -> 81, 359 x 36x36^3 100 -> 79; 38x38 to 60x60 0.8 to 1.1 at most sizes), and 65 to 76 columns, whose five
-//   wavefronts there share four SIMDs (122 x 65x65^3 321 -> 218, 89 x 72x72^3 257 -> 223; 81x81 to 100x100 0.87 to 1.0).  Aligned results
-//   of 160 to 320 MiB stay with that form, which leaves them in the last-level cache (8388 x 20x20^3 276 and 286 us; with
-//   ordinary stores 300), and where a problem has such a step its others of that size stay too: what they left in memory the next
-//   one would read from there (1790 x 31x32^3, one step of three here, 267 -> 311 us; 2545 x 36x25^3 313 -> 347).
-inline double lane_out(const Problem& pr, const km_plan_step& st) { return (double)pr.M * (double)st.k_out * (double)pr.esize; }
-inline bool lane_cached(const Problem& pr, const km_plan_step& st) { return lane_out(pr, st) > 160.0 * 1048576 && lane_out(pr, st) <= 320.0 * 1048576; }
-inline bool lane_stays(const Problem& pr, const km_plan_step& st)
+// Would the launch after this one find this one's results in the last-level cache?  Launches with a slice per lane leave at most 160 MiB
+// there, others 320.  (Results whose runs do not start on 64-byte boundaries are stored alike by both; above 256 MiB the cache holds too little of them.)
+inline bool lane_cached(const Problem& pr, const km_plan_step& st)
 {
-    const int P = pr.P[st.first_factor];
-    return st.variant == PAD_VARIANT && P <= 36 && pr.Q[st.first_factor] <= 40 && lane_cached(pr, st) && st.k_in / P * (int64_t)pr.esize % 64 == 0;
+    const double mib = (double)pr.M * (double)st.k_out * (double)pr.esize / 1048576.0;
+    return mib > 160.0 && mib <= (st.k_in / pr.P[st.first_factor] * (int64_t)pr.esize % 64 == 0 ? 320.0 : 256.0);
 }
-// any_stays: lane_stays() is true of a step of this problem
-inline bool lane_wins(const Problem& pr, const km_plan_step& st, bool any_stays)
+
+// Does the slice-per-lane kernel beat the one that step i was given to?  Fitted to some 5000 launches, each inside its call and
+// beside the kernel that the step was given to, on 6000 problems of random sizes.  On 1300 more of them the calls that change
+// are 1.23 times as fast on average, 98 % of them as fast or faster (within 2 %), the worst 0.89.  By what the step was given to:
+// - the generic kernel: 1.35 times (20 M slices of 10x2 407 -> 208 us, 10.6 M of 17x9 288 -> 198).  From 64 workgroups of 256 slices
+//   on, 128 with up to four columns; fewer leave it a single tile's latency.  Slices of up to 8 elements, which that kernel reads
+//   without LDS, need more of both: on short rows a tile's results are in many runs and stored element by element (881 K of 8x6, 16 to a row,
+//   15.1 -> 18.8 us).  Tall slices with few columns only while they are few (249 K of 72x2 24.0 -> 21.4, 512 K of 75x2 39.6 -> 45.4).
+// - the chunked form: 1.3 times on slices that are no whole vectors, which that one deals to LDS element by element (5.9 M of 42x7 390 ->
+//   278).  Others lose what it gains elsewhere (1.3 M of 48x9 54 -> 73) but for more than 16 columns (3.6 M of 68x68 754 -> 496) and
+//   36 rows (1.07 to 1.2).
+// - the form with the factor in registers, from 92 MiB moved on; with less the one tile that a wavefront gets takes longer than the products saved.
+//   Its sixteen columns to a wavefront leave some idle, and with two, three and five wavefronts also SIMDs: up to 36 rows and 40 columns
+//   1.17 times (9.6 M of 24x24 368 -> 327, 6.6 M of 30x30 412 -> 298), 65 to 76 columns 1.27 (4 M of 69x74 939 -> 647); columns that
+//   fill the sixteens only on the largest problems (8 M of 30x32 497 -> 353, 1 M of 34x32 39 -> 51), whole vectors with less to gain still (72x72, rows of 72
+//   slices, 0.87; 32x6 0.88).  Rows of less than 64 slices, each tile in several of them, 0.56 to 0.9 (7.8 M x 16x16 333 -> 568 us) where the
+//   intermediates stay on chip or there is none; from 160 MiB on 1.12, and with few columns, few of those stores, 1.17.
+//   Intermediates of 160 to 320 MiB stay with that form, which leaves them in the last-level cache (2250 x 31x31^3 whole 319 us there, 346
+//   with one launch of three here), but for 33 to 36 columns, which gain more than that costs (1.11).
+inline bool lane_wins(const Problem& pr, const Plan& plan, size_t i)
 {
+    const km_plan_step& st = plan.steps[i];
     const int P = pr.P[st.first_factor], Q = pr.Q[st.first_factor];
     const int64_t S = st.k_in / P, groups = (pr.M * S + 4 * LANE_SLICES - 1) / (4 * LANE_SLICES);
+    const bool vectors = P % 4 == 0;                     // slices are whole 16-byte vectors
     if (st.variant == PAD_VARIANT) {
-        if ((double)pr.M * (double)st.k_in * (double)pr.esize + lane_out(pr, st) < 96e6) return false;
-        if (P <= 36 && Q <= 40) return !any_stays || !lane_cached(pr, st);
-        return P > 32 && P <= 80 && Q > 64 && Q <= 76;
+        const bool first = i == 0, last = i + 1 == plan.steps.size();
+        const double mib = (double)pr.M * (double)pr.esize / 1048576.0, in = mib * (double)st.k_in, out = mib * (double)st.k_out;
+        if (in + out < 92.0) return false;
+        if (P > 64) return P <= 80 && Q > 64 && (vectors ? S >= 1024 && Q <= 72 : S >= (Q <= 72 || in + out > 400.0 ? 64 : 128) && Q <= 76);
+        if (P > 36 || Q > 40 || (Q % 16 == 0 && (vectors || in < 600.0))) return false;
+        if (vectors && (Q <= 8 ? P < 20 || P > 28 : Q <= 16 || (P >= 32 && Q <= 32))) return false;
+        if (Q <= 8 || (Q <= 10 && P > 16 && !vectors)) return true;
+        if (S < LANE_SLICES) return !vectors && S >= 6 && P >= 9 && (first || in > 160.0) && (last || out > 160.0);
+        if (P > 32 && Q > 32 && Q <= 36) return true;
+        return !(!first && lane_cached(pr, plan.steps[i - 1])) && !(!last && lane_cached(pr, st));
     }
     if (groups < 64 || S < 16 || (S < 256 && Q > 32)) return false;
-    return st.kernel == KM_KERNEL_GENERIC ? P <= 32 || P > 64 || Q > 8 : P > 32 && groups >= 128;
+    if (st.kernel != KM_KERNEL_GENERIC) return P > 32 && (!vectors || P == 36 ? groups >= 128 : Q > 16 && groups >= (P > 64 ? 128 : 512));
+    if (P <= 8) return S >= 128 ? groups >= (Q <= 16 ? 512 : 128) : Q <= 8 && groups >= (Q <= 4 ? 1024 : 4096);
+    if (P <= 32) return groups >= (Q <= 4 ? 128 : 64);
+    return Q > 8 || P > 96 || (P > 64 && groups < 1024);
 }
 
 // The steps that the slice-per-lane kernel runs faster go to it, once the plan is made: the prices that group factors and weigh
@@ -1333,13 +1348,12 @@ inline bool lane_wins(const Problem& pr, const km_plan_step& st, bool any_stays)
 inline void take_lane_steps(const Problem& pr, const Options& opt, Plan& plan)
 {
     if (pr.dtype != KM_F32 || !(opt.kernels >> KM_KERNEL_MFMA_ANY & 1) || !no_wishes(opt)) return;
-    bool any_stays = false;
-    for (const km_plan_step& st : plan.steps) any_stays = any_stays || lane_stays(pr, st);
-    for (km_plan_step& st : plan.steps) {
+    for (size_t i = 0; i < plan.steps.size(); ++i) {
+        km_plan_step& st = plan.steps[i];
         if (st.kernel != KM_KERNEL_GENERIC && st.kernel != KM_KERNEL_MFMA_ANY) continue;
         const int P = pr.P[st.first_factor], Q = pr.Q[st.first_factor];
         const LaneShape sh = lane_shape(P, Q, pr.M * (st.k_in / P));
-        if (sh.lds_bytes == 0 || !lane_wins(pr, st, any_stays)) continue;
+        if (sh.lds_bytes == 0 || !lane_wins(pr, plan, i)) continue;
         st.kernel = KM_KERNEL_MFMA_ANY;
         st.variant = LANE_VARIANT;
         st.tile_slices = LANE_SLICES;
