@@ -33,7 +33,7 @@ hipError_t launch_mfma_lane(const LaunchArgs& a)
     const int P = a.pr->P[st.first_factor], Q = a.pr->Q[st.first_factor];
     if (a.pr->dtype != KM_F32 || st.num_factors != 1 || st.k_in % P || lane_units(P) != U) return hipErrorInvalidValue;
     switch ((Q + 3) / 4) {
-#define KM_LANE(n) case n: return launch_lane_shape<n, U>(a);
+#define KM_LANE(n) case n: if constexpr (lane_compiled(n, U)) return launch_lane_shape<n, U>(a); break;
         KM_LANE(1) KM_LANE(2) KM_LANE(3) KM_LANE(4) KM_LANE(5) KM_LANE(6) KM_LANE(7) KM_LANE(8)
         KM_LANE(9) KM_LANE(10) KM_LANE(11) KM_LANE(12) KM_LANE(13) KM_LANE(14) KM_LANE(15) KM_LANE(16)
         KM_LANE(17) KM_LANE(18) KM_LANE(19) KM_LANE(20) KM_LANE(21) KM_LANE(22) KM_LANE(23) KM_LANE(24)

@@ -183,17 +183,29 @@ inline int64_t store_column(int64_t k_in, int64_t p_group, int64_t tile_k, int64
 // Column blocks (of 16) per unit of the run-time-shape MFMA kernel for a factor with Q columns: one or
 // two for factors that narrow, else the width among 4, 5 and 3 that leaves the fewest padded blocks
 // (narrower units would re-read the slices once per 16 or 32 columns).
-inline int any_column_blocks(int Q)
+constexpr int any_column_blocks(int Q)
 {
     const int blocks = (Q + 15) / 16;
     if (blocks <= 2) return blocks < 1 ? 1 : blocks;
     int best = 4, waste = (4 - blocks % 4) % 4 * 1000 / ((blocks + 3) / 4 * 4);
-    const int others[2] = {5, 3};
-    for (int cb : others) {
+    for (int cb = 5; cb >= 3; cb -= 2) {
         const int w = (cb - blocks % cb) % cb * 1000 / ((blocks + cb - 1) / cb * cb);
         if (w < waste) { waste = w; best = cb; }
     }
     return best;
+}
+
+// The run-time-shape MFMA kernel takes single factors whose slices start on 16-byte boundaries
+// (P a multiple of 4 floats or 2 doubles) or are at most 256 bytes long.  It pads P and Q to multiples of 16 with zeros, so a factor
+// is given to it only while the padded product is at most 3 times the real one (measured against the
+// generic kernel, 3 factors each: fp32 20x20 4 % faster at 2.56x padding, 36x36 19 % at 1.78x, 40x40
+// 18 %, 52x52 10 %, 100x100 level; fp64 20x20 9 % faster, 36x36 31 %, 34x34 26 %, 84x84 14 %, 50x50 and
+// 22x22 level, 30x30 4 % slower).
+constexpr bool any_padding_fits(int P, int Q)
+{
+    const int cols = 16 * any_column_blocks(Q);
+    const double padded = (double)((P + 15) / 16 * 16) * (double)((Q + cols - 1) / cols * cols);
+    return padded <= 3.0 * (double)P * (double)Q;
 }
 
 // Units of work of the kernels without compiled shapes: (tile t of `tiles` slice tiles, group c of
@@ -241,6 +253,16 @@ KM_HOST_DEVICE constexpr int pad_stride(int P, size_t esize)
     const int u = esize == 4 ? 4 : 2;
     return P % u ? P : (P / u % 2 ? P : P + u);
 }
+KM_HOST_DEVICE constexpr int64_t pad_lds_bytes(int P, int Q, size_t esize)
+{
+    return 2 * (int64_t)pad_tile_slices(esize, pad_columns(Q), pad_chunks(P)) * pad_stride(P, esize) * (int64_t)esize + 16;     // (16: a masked read past the last slice)
+}
+KM_HOST_DEVICE constexpr bool pad_fits(int P, int Q, size_t esize)
+{
+    if (P < 2 || P > PAD_MAXP || Q > PAD_MAXP) return false;
+    const int c = pad_columns(Q), k = pad_chunks(P), threads = 64 * c * pad_groups(c);
+    return (int64_t)pad_tile_slices(esize, c, k) * P * (int64_t)esize <= (int64_t)pad_vectors(esize, c, k) * threads * 16 && pad_lds_bytes(P, Q, esize) <= PAD_LDS_LIMIT;
+}
 // How the kernel would run a factor on `slices` slices (threads == 0: it cannot).
 struct PadShape {
     int threads = 0, tile_slices = 0, lds_bytes = 0;
@@ -249,11 +271,10 @@ struct PadShape {
 inline PadShape pad_shape(int P, int Q, size_t esize, int64_t slices)
 {
     PadShape r;
-    if (P < 2 || P > PAD_MAXP || Q > PAD_MAXP) return r;
+    if (!pad_fits(P, Q, esize)) return r;
     const int c = pad_columns(Q), k = pad_chunks(P), threads = 64 * c * pad_groups(c);
     r.tile_slices = pad_tile_slices(esize, c, k);
-    const int64_t lds = 2 * (int64_t)r.tile_slices * pad_stride(P, esize) * (int64_t)esize + 16;     // (16: a masked read past the last slice)
-    if ((int64_t)r.tile_slices * P * (int64_t)esize > (int64_t)pad_vectors(esize, c, k) * threads * 16 || lds > PAD_LDS_LIMIT) return PadShape();
+    const int64_t lds = pad_lds_bytes(P, Q, esize);
     r.threads = threads;
     r.lds_bytes = (int)lds;
     // one round of the workgroups the chip holds, each walking over its share; a multiple of 8 for the XCDs
@@ -298,7 +319,34 @@ KM_HOST_DEVICE constexpr int lane_lds_bytes(int P, int Q, int U)
 {
     return 16 * ((P + 3) / 4 * ((Q + 3) / 4 * 4) + LANE_THREADS * (U | 1));
 }
-// How the kernel would run a factor on `slices` slices (lds_bytes == 0: it cannot).
+// Factors that it is compiled for, those that lane_wins() may give it: of the generic kernel's (padded to 16s too large for the other
+// forms), of the form in registers, and of the chunked form's.
+KM_HOST_DEVICE constexpr bool lane_fits_generic(int P, int Q) { return P <= 32 || P > 64 || Q > 8; }
+KM_HOST_DEVICE constexpr bool lane_fits_chunked(int P, int Q) { return P > 32 && (P % 4 != 0 || P == 36 || Q > 16); }
+KM_HOST_DEVICE constexpr bool lane_fits_pad(int P, int Q)
+{
+    if (P > 64) return P <= 80 && Q > 64 && Q <= (P % 4 == 0 ? 72 : 76);
+    if (P > 36 || Q > 40) return false;
+    return P % 4 != 0 || (Q % 16 != 0 && (Q <= 8 ? P >= 20 && P <= 28 : Q > 16 && (P < 32 || Q > 32)));
+}
+constexpr bool lane_takes(int P, int Q)
+{
+    if (P < LANE_MINP || P > LANE_MAXP || Q < 1 || Q > LANE_MAXP) return false;
+    if (!any_padding_fits(P, Q)) return lane_fits_generic(P, Q);
+    const int columns = pad_columns(Q);
+    const bool pad = pad_fits(P, Q, sizeof(float)), chunked = !pad || (P % 4 == 0 && P > 64 && (columns == 3 || columns == 5));
+    return (pad && lane_fits_pad(P, Q)) || (chunked && lane_fits_chunked(P, Q));
+}
+// Is there a factor whose launch would be mfma_lane_sliced_multiply<G, U>?
+constexpr bool lane_compiled(int G, int U)
+{
+    for (int P = LANE_MINP; P <= LANE_MAXP; ++P)
+        if (lane_units(P) == U)
+            for (int Q = 4 * G - 3; Q <= 4 * G; ++Q)
+                if (lane_takes(P, Q)) return true;
+    return false;
+}
+// How the kernel would run a factor on `slices` slices (lds_bytes == 0: it does not).
 struct LaneShape {
     int lds_bytes = 0;
     int64_t grid = 0, per_cu = 0;          // per_cu: workgroups a compute unit holds at once
@@ -306,7 +354,7 @@ struct LaneShape {
 inline LaneShape lane_shape(int P, int Q, int64_t slices)
 {
     LaneShape r;
-    if (P < LANE_MINP || P > LANE_MAXP || Q < 1 || Q > LANE_MAXP || slices > LANE_MAX_SLICES) return r;
+    if (!lane_takes(P, Q) || slices > LANE_MAX_SLICES) return r;
     const int U = lane_units(P), G = (Q + 3) / 4;
     r.lds_bytes = lane_lds_bytes(P, Q, U);
     r.per_cu = 160 * 1024 / r.lds_bytes < lane_waves(G, U) ? 160 * 1024 / r.lds_bytes : lane_waves(G, U);
@@ -990,19 +1038,9 @@ inline km_plan_step build_step(const Problem& pr, const Options& opt, const Vari
     return st;
 }
 
-// The run-time-shape MFMA kernel takes single factors whose slices start on 16-byte boundaries
-// (P a multiple of 4 floats or 2 doubles) or are at most 256 bytes long.  It pads P and Q to multiples of 16 with zeros, so a factor
-// is given to it only while the padded product is at most 3 times the real one (measured against the
-// generic kernel, 3 factors each: fp32 20x20 4 % faster at 2.56x padding, 36x36 19 % at 1.78x, 40x40
-// 18 %, 52x52 10 %, 100x100 level; fp64 20x20 9 % faster, 36x36 31 %, 34x34 26 %, 84x84 14 %, 50x50 and
-// 22x22 level, 30x30 4 % slower).
 inline bool any_mfma_fits(const Problem& pr, int f, const Options& opt)
 {
-    const int P = pr.P[f], Q = pr.Q[f];
-    if (!(opt.kernels >> KM_KERNEL_MFMA_ANY & 1)) return false;
-    const int cols = 16 * any_column_blocks(Q);
-    const double padded = (double)((P + 15) / 16 * 16) * (double)((Q + cols - 1) / cols * cols);
-    return padded <= 3.0 * (double)P * (double)Q;
+    return (opt.kernels >> KM_KERNEL_MFMA_ANY & 1) && any_padding_fits(pr.P[f], pr.Q[f]);
 }
 
 inline void row_widths(const Problem& pr, std::vector<int64_t>& width)
@@ -1328,19 +1366,20 @@ inline bool lane_wins(const Problem& pr, const Plan& plan, size_t i)
         const bool first = i == 0, last = i + 1 == plan.steps.size();
         const double mib = (double)pr.M * (double)pr.esize / 1048576.0, in = mib * (double)st.k_in, out = mib * (double)st.k_out;
         if (in + out < 92.0) return false;
-        if (P > 64) return P <= 80 && Q > 64 && (vectors ? S >= 1024 && Q <= 72 : S >= (Q <= 72 || in + out > 400.0 ? 64 : 128) && Q <= 76);
-        if (P > 36 || Q > 40 || (Q % 16 == 0 && (vectors || in < 600.0))) return false;
-        if (vectors && (Q <= 8 ? P < 20 || P > 28 : Q <= 16 || (P >= 32 && Q <= 32))) return false;
+        if (!lane_fits_pad(P, Q)) return false;
+        if (P > 64) return S >= (vectors ? 1024 : Q <= 72 || in + out > 400.0 ? 64 : 128);
+        if (Q % 16 == 0 && in < 600.0) return false;
         if (Q <= 8 || (Q <= 10 && P > 16 && !vectors)) return true;
         if (S < LANE_SLICES) return !vectors && S >= 6 && P >= 9 && (first || in > 160.0) && (last || out > 160.0);
         if (P > 32 && Q > 32 && Q <= 36) return true;
         return !(!first && lane_cached(pr, plan.steps[i - 1])) && !(!last && lane_cached(pr, st));
     }
     if (groups < 64 || S < 16 || (S < 256 && Q > 32)) return false;
-    if (st.kernel != KM_KERNEL_GENERIC) return P > 32 && (!vectors || P == 36 ? groups >= 128 : Q > 16 && groups >= (P > 64 ? 128 : 512));
+    if (st.kernel != KM_KERNEL_GENERIC) return lane_fits_chunked(P, Q) && groups >= (!vectors || P == 36 || P > 64 ? 128 : 512);
+    if (!lane_fits_generic(P, Q)) return false;
     if (P <= 8) return S >= 128 ? groups >= (Q <= 16 ? 512 : 128) : Q <= 8 && groups >= (Q <= 4 ? 1024 : 4096);
     if (P <= 32) return groups >= (Q <= 4 ? 128 : 64);
-    return Q > 8 || P > 96 || (P > 64 && groups < 1024);
+    return Q > 8 || P > 96 || groups < 1024;
 }
 
 // The steps that the slice-per-lane kernel runs faster go to it, once the plan is made: the prices that group factors and weigh

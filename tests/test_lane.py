@@ -66,6 +66,62 @@ def test_the_list_takes_the_kernel_and_its_launches_fit(M, S, P, Q):
     assert 256 * (st["grid"] - 8) < M * S <= 2 * 256 * st["grid"]           # four tiles of 64 slices, once or twice
 
 
+def _run(tmp_path, body):
+    src, exe = tmp_path / "prog.cpp", tmp_path / "prog"
+    src.write_text('#include "paper_2401_10187_amd/csrc/plan.hpp"\n#include <cstdio>\n#include <random>\nusing namespace km;\n' + body)
+    subprocess.run(["g++", "-std=c++17", "-I", ROOT, "-o", str(exe), str(src)], check=True)
+    return subprocess.run([str(exe)], capture_output=True, text=True).stdout.strip()
+
+
+def test_the_list_covers_every_compiled_kernel(tmp_path):
+    """The pairs of chunk length and column groups that launch_lane.hpp instantiates are those of CASES."""
+    out = _run(tmp_path, """
+int main()
+{
+    for (int U : {2, 3, 4, 5, 6, 7, 9, 13})
+        for (int G = 1; G <= 32; ++G)
+            if (lane_compiled(G, U)) printf("%d,%d ", U, G);
+    printf("|");
+    for (int P = LANE_MINP; P <= LANE_MAXP; ++P) printf(" %d", lane_units(P));
+}
+""")
+    compiled, units = [half.split() for half in out.split("|")]
+    assert {"%s,%d" % (units[P - 5], (Q + 3) // 4) for _, _, P, Q in CASES} == set(compiled) and len(compiled) > 100
+
+
+def test_what_the_rule_takes_is_compiled(tmp_path):
+    """Random problems, any families of kernels: a step that the rule would give to this kernel is of a shape that it is compiled for, so the limits
+    of shapes stand in one place only."""
+    assert _run(tmp_path, """
+int main()
+{
+    const GenericKernel gen{256, 128, 32, 24576, 256, 1024, 512, 96 * 1024, 8, 256, 128, 256};
+    std::mt19937 rng(17);
+    int wins = 0;
+    for (int k = 0; k < 60000; ++k) {
+        const int n = 1 + rng() % 4;
+        int P[4], Q[4];
+        for (int i = 0; i < n; ++i) P[i] = 1 + rng() % (rng() % 2 ? 40 : 130), Q[i] = 1 + rng() % (rng() % 2 ? 40 : 130);
+        Problem pr;
+        if (make_problem(1 + (int)(rng() >> rng() % 30 >> 2), n, P, Q, KM_F32, pr) != KM_OK || (double)pr.M * (double)pr.k_in > 1e9) continue;
+        Options opt;
+        opt.kernels = rng() % 2 ? 0x27 : 0x21;
+        opt.prefer_threads = 1;                          // (a wish: the plan without this kernel)
+        Plan plan, spare;
+        if (make_plan(pr, opt, nullptr, 0, gen, plan, spare) != KM_OK) return printf("unplanned"), 1;
+        for (size_t i = 0; i < plan.steps.size(); ++i) {
+            const int p = pr.P[plan.steps[i].first_factor], q = pr.Q[plan.steps[i].first_factor];
+            if (p < LANE_MINP || p > LANE_MAXP || q > LANE_MAXP || (plan.steps[i].kernel != KM_KERNEL_GENERIC && plan.steps[i].kernel != KM_KERNEL_MFMA_ANY)) continue;
+            if (!lane_wins(pr, plan, i)) continue;
+            ++wins;
+            if (!lane_takes(p, q)) return printf("%dx%d variant %d", p, q, plan.steps[i].variant), 1;
+        }
+    }
+    printf("ok %d", wins > 5000);
+}
+""") == "ok 1"
+
+
 def test_where_the_line_lies():
     """64 workgroups of 256 slices for the generic kernel's steps, 128 with few columns, more for slices of up to 8 elements; 128 for the
     chunked form's, whose whole vectors stay with it unless columns are many; rows of 16 slices; 92 MiB for the form in registers, with
@@ -92,12 +148,7 @@ def test_rows_of_slices_are_found_exactly_up_to_the_most_slices(tmp_path):
     """The kernel's division by the slices of a row, for the first and the last slices of rows and of all: exact for as many slices as a
     launch may have, and problems of more are left to the generic kernel.  (The last slice of 1 x (5x1)^15, 2^32.5 slices, is one that it
     would put into a second row.)"""
-    src = tmp_path / "rows.cpp"
-    src.write_text("""
-#include "paper_2401_10187_amd/csrc/plan.hpp"
-#include <cstdio>
-#include <random>
-using namespace km;
+    assert _run(tmp_path, """
 static int64_t found(int64_t g, int64_t S) { return S == 1 ? g : (int64_t)(((unsigned __int128)(uint64_t)g * lane_row_magic(S)) >> 64); }
 int main()
 {
@@ -112,10 +163,7 @@ int main()
     const int64_t S = 6103515625;                        // 5^14
     printf("%d %d %d\\n", found(S - 1, S) == 0, lane_shape(5, 1, S).lds_bytes, lane_shape(5, 1, LANE_MAX_SLICES + 1).lds_bytes);
 }
-""")
-    exe = tmp_path / "rows"
-    subprocess.run(["g++", "-std=c++17", "-I", ROOT, "-o", str(exe), str(src)], check=True)
-    assert subprocess.run([str(exe)], capture_output=True, text=True).stdout.strip() == "0 0 0"
+""") == "0 0 0"
     assert [st["variant"] for st in km.plan(1, [5] * 15, [1] * 15, "float32")][:3] == [-1, LANE, LANE]
 
 
