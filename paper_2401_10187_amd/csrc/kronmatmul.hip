@@ -593,15 +593,7 @@ static km_status tune(const Problem& pr, const Options& opt, hipStream_t stream,
         best[r] = -1;
         for (int nf = 1; nf <= r && nf <= opt.max_fuse; ++nf) {
             enumerate_choices(g_variants, g_num_variants, pr, r - 1, nf, width[r], opt, cands);
-            if (nf == 1) cands.push_back(Choice());            // the generic kernel
-            if (nf == 1 && any_mfma_fits(pr, r - 1, opt)) {     // the run-time-shape MFMA kernel, both forms of it
-                Choice any;
-                any.any_mfma = true;
-                any.any_form = -1;
-                cands.push_back(any);
-                any.any_form = PAD_VARIANT;
-                if (pad_shape(pr.P[r - 1], pr.Q[r - 1], pr.esize, pr.M * (width[r] / pr.P[r - 1])).threads > 0) cands.push_back(any);
-            }
+            if (nf == 1) uncompiled_choices(pr, opt, r - 1, width[r], cands);
             float group_best = -1.f;
             Choice group_pick;
             for (const Choice& ch : cands) {

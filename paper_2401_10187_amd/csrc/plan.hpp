@@ -367,6 +367,17 @@ inline LaneShape lane_shape(int P, int Q, int64_t slices)
     return r;
 }
 
+// Makes `st` (whose factor, rows and buffers stay) a launch of that kernel.
+inline void make_lane_step(const LaneShape& sh, km_plan_step& st)
+{
+    st.kernel = KM_KERNEL_MFMA_ANY;
+    st.variant = LANE_VARIANT;
+    st.tile_slices = LANE_SLICES;
+    st.block = LANE_THREADS;
+    st.lds_bytes = sh.lds_bytes;
+    st.grid = sh.grid;
+}
+
 // The whole-row MFMA kernel: up to ROWM_MAXF factors; slices of a multiple of 8 elements are padded by 4 in
 // LDS, the operand registers hold ROWM_CHUNKS chunks of 16 rows of a factor (row_mfma_kernel.hpp says why).
 // Rows whose two buffers need more than 60 KB keep their other plans: their work takes one compute unit so
@@ -556,7 +567,7 @@ inline bool chunked_form_wins(const GenericKernel& gen, int P, int Q, size_t esi
 
 struct Choice {
     bool any_mfma = false;   // with var == nullptr: the run-time-shape MFMA kernel instead of the generic one
-    int any_form = 0;        // ... 0: the form that is estimated faster, PAD_VARIANT: factor in registers, -1: in chunks
+    int any_form = 0;        // ... 0: the form that is estimated faster, PAD_VARIANT: factor in registers, -1: in chunks, LANE_VARIANT: a slice per lane
     const Variant* var = nullptr;
     int tile_slices = 0;
     int64_t grid = 0;        // tiles (before the persistent-walk division)
@@ -992,6 +1003,10 @@ inline km_plan_step build_step(const Problem& pr, const Options& opt, const Vari
         st.tile_rows = 1;
         st.tile_slices = any_unit_slices(gen, pr.P[f], pr.esize);
         const int64_t slices = pr.M * (st.k_in / pr.P[f]);
+        if (ch.any_form == LANE_VARIANT) {
+            make_lane_step(lane_shape(pr.P[f], pr.Q[f], slices), st);
+            return st;
+        }
         const PadShape pad = pad_shape(pr.P[f], pr.Q[f], pr.esize, slices);
         bool chunked = pad.threads == 0 || ch.any_form == -1;
         if (!chunked && ch.any_form == 0) {
@@ -1382,23 +1397,20 @@ inline bool lane_wins(const Problem& pr, const Plan& plan, size_t i)
     return Q > 8 || P > 96 || groups < 1024;
 }
 
+inline bool lane_allowed(const Problem& pr, const Options& opt) { return pr.dtype == KM_F32 && (opt.kernels >> KM_KERNEL_MFMA_ANY & 1) && no_wishes(opt); }
+
 // The steps that the slice-per-lane kernel runs faster go to it, once the plan is made: the prices that group factors and weigh
 // plans against each other are those of the kernels it takes the steps from.
 inline void take_lane_steps(const Problem& pr, const Options& opt, Plan& plan)
 {
-    if (pr.dtype != KM_F32 || !(opt.kernels >> KM_KERNEL_MFMA_ANY & 1) || !no_wishes(opt)) return;
+    if (!lane_allowed(pr, opt)) return;
     for (size_t i = 0; i < plan.steps.size(); ++i) {
         km_plan_step& st = plan.steps[i];
         if (st.kernel != KM_KERNEL_GENERIC && st.kernel != KM_KERNEL_MFMA_ANY) continue;
         const int P = pr.P[st.first_factor], Q = pr.Q[st.first_factor];
         const LaneShape sh = lane_shape(P, Q, pr.M * (st.k_in / P));
         if (sh.lds_bytes == 0 || !lane_wins(pr, plan, i)) continue;
-        st.kernel = KM_KERNEL_MFMA_ANY;
-        st.variant = LANE_VARIANT;
-        st.tile_slices = LANE_SLICES;
-        st.block = LANE_THREADS;
-        st.lds_bytes = sh.lds_bytes;
-        st.grid = sh.grid;
+        make_lane_step(sh, st);
     }
 }
 
@@ -1567,6 +1579,24 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
     if (plan.ws0_bytes + plan.ws1_bytes == 0) spare = Plan();
     take_lane_steps(pr, opt, plan);
     return KM_OK;
+}
+
+// The kernels without compiled shapes that the tuner times for factor f of rows of `width` elements: the generic one, and of the run-time-shape
+// MFMA family every form that can run it, a slice per lane from as many slices on as that form is ever planned for.
+inline void uncompiled_choices(const Problem& pr, const Options& opt, int f, int64_t width, std::vector<Choice>& out)
+{
+    out.push_back(Choice());
+    const int64_t slices = pr.M * (width / pr.P[f]);
+    Choice any;
+    any.any_mfma = true;
+    if (any_mfma_fits(pr, f, opt)) {
+        any.any_form = -1;
+        out.push_back(any);
+        any.any_form = PAD_VARIANT;
+        if (pad_shape(pr.P[f], pr.Q[f], pr.esize, slices).threads > 0) out.push_back(any);
+    }
+    any.any_form = LANE_VARIANT;
+    if (lane_allowed(pr, opt) && slices > 63 * 4 * LANE_SLICES && lane_shape(pr.P[f], pr.Q[f], slices).lds_bytes > 0) out.push_back(any);
 }
 
 // The tuner's candidates besides the planner's own plan and the one it measured: the whole-row kernels wherever they fit, if the

@@ -53,7 +53,7 @@ CASES = [
     (1928, 17, 106, 22), (99, 331, 103, 27), (1639, 20, 102, 30), (127, 259, 127, 35), (127, 259, 97, 38), (97, 338, 99, 41), (127, 259, 100, 48),
     (2632, 67, 70, 67), (168, 1024, 72, 70), (359, 334, 128, 74), (352, 333, 128, 79), (1725, 19, 50, 7), (1928, 17, 51, 10), (1821, 18, 50, 13),
     # from the form with the factor in registers: rows of one slice, of a few, of part of a tile, of many; one tile to a wavefront and two
-    (712000, 1, 27, 7), (41200, 17, 31, 8), (70500, 30, 27, 20), (3600, 330, 9, 13), (1150, 330, 33, 33), (1200, 625, 17, 17), (1100, 530, 21, 21),
+    (712000, 1, 27, 7), (206400, 3, 31, 8), (64000, 11, 30, 7), (41200, 17, 31, 8), (70500, 30, 27, 20), (3600, 330, 9, 13), (1150, 330, 33, 33), (1200, 625, 17, 17), (1100, 530, 21, 21),
     (900, 400, 30, 40), (300, 629, 65, 66), (330, 512, 71, 76), (136, 1333, 68, 68),
 ]
 

@@ -68,6 +68,60 @@ int main()
     assert subprocess.run([str(exe)], capture_output=True, text=True).stdout.strip() == "ok 1 1 1"
 
 
+def test_a_slice_per_lane_is_timed_for_every_factor_it_can_run(tmp_path):
+    """Among the tuner's choices for a single factor, as the step that the planner would make of it; not in fp64, with wishes or without its family."""
+    src = tmp_path / "choices.cpp"
+    src.write_text("""
+#include "paper_2401_10187_amd/csrc/plan.hpp"
+#include <cstdio>
+#include <cstring>
+#include <random>
+using namespace km;
+int main()
+{
+    const GenericKernel gen{256, 128, 32, 24576, 256, 1024, 512, 96 * 1024, 8, 256, 128, 256};
+    std::mt19937 rng(7);
+    int same = 0, more = 0;
+    for (int k = 0; k < 20000; ++k) {
+        const int n = 1 + rng() % 3;
+        int P[3], Q[3];
+        for (int i = 0; i < n; ++i) P[i] = 1 + rng() % 90, Q[i] = 1 + rng() % 90;
+        Problem pr;
+        const bool f32 = rng() % 4 != 0;
+        if (make_problem(1 + (int)(rng() >> rng() % 28 >> 4), n, P, Q, f32 ? KM_F32 : KM_F64, pr) != KM_OK) continue;
+        Options opt;
+        opt.kernels = rng() % 5 ? 0x27 : 0x07;
+        opt.tiles_per_wg = rng() % 5 ? 0 : 4;
+        Plan plan, spare;
+        if (make_plan(pr, opt, nullptr, 0, gen, plan, spare) != KM_OK) return printf("unplanned\\n"), 1;
+        std::vector<int64_t> width;
+        row_widths(pr, width);
+        for (const km_plan_step& st : plan.steps) {
+            const int f = st.first_factor;
+            std::vector<Choice> cands;
+            uncompiled_choices(pr, opt, f, width[f + 1], cands);
+            bool timed = false;
+            for (const Choice& ch : cands) {
+                km_plan_step t = build_step(pr, opt, nullptr, f + 1, 1, ch, width, gen);
+                if (t.grid <= 0 || t.block <= 0 || t.lds_bytes < 0 || t.lds_bytes > 160 * 1024) return printf("launch\\n"), 1;
+                if (t.variant != LANE_VARIANT) continue;
+                timed = true;
+                t.src = st.src, t.dst = st.dst;
+                if (st.variant == LANE_VARIANT && memcmp(&t, &st, sizeof t) != 0) return printf("another step\\n"), 1;
+            }
+            if (timed && !(f32 && opt.kernels == 0x27 && opt.tiles_per_wg == 0 && lane_takes(P[f], Q[f]))) return printf("not allowed\\n"), 1;
+            if (!timed && st.variant == LANE_VARIANT) return printf("not timed\\n"), 1;
+            if (timed) ++(st.variant == LANE_VARIANT ? same : more);
+        }
+    }
+    printf("ok %d %d\\n", same > 1000, more > 1000);
+}
+""")
+    exe = tmp_path / "choices"
+    subprocess.run(["g++", "-std=c++17", "-I", ROOT, "-o", str(exe), str(src)], check=True)
+    assert subprocess.run([str(exe)], capture_output=True, text=True).stdout.strip() == "ok 1 1"
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,shapes", [(942, [(60, 50), (18, 8)]), (719, [(2, 1), (13, 3), (90, 76), (2, 1)]), (1024, [(24, 1), (60, 23), (5, 9)])], ids=str)
 def test_tuned_plans_launch_what_they_have_room_for(M, shapes):
