@@ -88,6 +88,13 @@ def shape_runs(P, Q):
     return "+".join("%dx(%dx%d)" % (n, p, q) for (p, q), n in runs)
 
 
+def left_in_cache(step, out_mib, keep_mib):
+    """Does a launch that is not a call's last use ordinary stores for its out_mib MiB?  The library's rule: 48 MiB to KM_OPT_KEEP_MIB, four
+    times as much for the small-factor family, half as much for a slice per lane (variant -8)."""
+    import paper_2401_10187_amd as km
+    return 48.0 <= out_mib <= keep_mib * (4.0 if step["kernel"] == km.KM_KERNEL_FUSED else 0.5 if step["variant"] == -8 else 1.0)
+
+
 def measure(name, args, headline):
     """Runs one workload: warm-up, settling, the timed steps, per-launch durations, the clock probe,
     and the comparison with the CPU oracle.  Returns the full result dictionary."""
@@ -208,11 +215,7 @@ def measure(name, args, headline):
             k = k // P[i] * Q[i]
         key = (st["kernel"], st["variant"], st["k_in"], st["k_out"])
         # did the launch before this one leave its output (this one's input) in the last-level cache?
-        # (the library's rule: not a call's last launch, 48 MiB to KM_OPT_KEEP_MIB, four times as much
-        # for the small-factor family)
-        prev = steps[len(launches) - 1] if launches else None
-        in_mib = es * M * st["k_in"] / 2.0 ** 20
-        kept_in = bool(prev and 48.0 <= in_mib <= keep_mib * (4 if prev["kernel"] == km.KM_KERNEL_FUSED else 1))
+        kept_in = bool(launches) and left_in_cache(steps[len(launches) - 1], es * M * st["k_in"] / 2.0 ** 20, keep_mib)
         launches.append(dict(key=key, ms=ms, bytes=nb, flops=fl, kept_in=kept_in,
                              name="%s[%s]" % (km.kernel_name(st["kernel"]), shape_runs(P[f0:f0 + nf], Q[f0:f0 + nf]))))
     groups = {}

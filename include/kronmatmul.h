@@ -219,7 +219,7 @@ km_status kronmatmul_cost(int M, int N, const int* P, const int* Q, km_dtype dty
  * rows and factors fit LDS.
  * KM_OPT_INSTANCE_COUNT: read-only; the number of compiled instances.
  * KM_OPT_KEEP_MIB: tuning aid (default 320); a launch that is not a call's last and writes between 48
- * and this many MiB (four times as many for the KM_KERNEL_FUSED family) uses ordinary instead of
+ * and this many MiB (four times as many for the KM_KERNEL_FUSED family, half as many for variant -8) uses ordinary instead of
  * non-temporal stores, so that the next launch finds part of the intermediate in the chip's
  * last-level cache (256 MB); 0 = non-temporal always.  It takes effect on the next call and changes
  * no result. */

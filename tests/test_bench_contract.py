@@ -50,6 +50,22 @@ def test_one_json_line_with_the_agreed_keys(workload, extra):
     assert cpu["max_rel_err_gpu_vs_oracle"] <= (1e-5 if out["dtype"] == "f32" else 1e-12)
 
 
+def test_cache_residency_follows_the_kernel_that_runs():
+    """The library's rule in kronmatmul.hip: KM_OPT_KEEP_MIB for most kernels, four times that for the small-factor one, half of
+    it for a slice per lane, which the plan names."""
+    import bench
+    import paper_2401_10187_amd as km
+    src = open(os.path.join(ROOT, "paper_2401_10187_amd", "csrc", "kronmatmul.hip")).read()
+    assert "KM_KERNEL_FUSED ? 4.0 : st.variant == LANE_VARIANT ? 0.5 : 1.0" in src and "KEEP_MIN_MIB = 48.0" in src
+    lane = km.plan(1300, [24] * 3, [24] * 3, "float32")[0]
+    form = km.plan(500, [60] * 3, [60] * 3, "float32")[0]
+    assert lane["variant"] == -8 and form["variant"] == -3
+    assert bench.left_in_cache(lane, 159.0, 320) and not bench.left_in_cache(lane, 161.0, 320) and not bench.left_in_cache(lane, 47.0, 320)
+    assert bench.left_in_cache(form, 319.0, 320) and not bench.left_in_cache(form, 321.0, 320)
+    fused = km.plan(1024, [8] * 6, [8] * 6, "float32")[0]
+    assert fused["kernel"] == km.KM_KERNEL_FUSED and bench.left_in_cache(fused, 1024.0, 320) and not bench.left_in_cache(fused, 1281.0, 320)
+
+
 def test_measured_traffic_comes_from_the_profile_summaries():
     """roofline.traffic is not a constant in bench.py: it is read from the rocprofv3 summary under
     profiles/ whose header names the workload.  Every summary's header figure must be the one its own
