@@ -77,11 +77,22 @@ def test_what_is_not_finite_stays_in_its_slice(generic_only, dtype, P):
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,shapes,tiled", [(9363, [(74, 14), (18, 5)], True), (1254, [(7, 2), (51, 23)], True),
                                             (1, [(5, 5), (5, 5), (5, 5), (2, 2)], False), (256, [(7, 2), (51, 23)], False)], ids=str)
-def test_small_mixed_problems_of_many_rows_are_tiled(M, shapes, tiled):
+@pytest.mark.parametrize("lanes", [True, False], ids=["as planned", "without a slice per lane"])
+def test_small_mixed_problems_of_many_rows_are_tiled(M, shapes, tiled, lanes):
     """Where whole rows on the FMA kernel are the slower plan, the intermediates of the tiled launches fit the static array all the
-    same.  (Those launches run in calls that bring the workspace.)"""
+    same.  (Those launches run in calls that bring the workspace.)  Some of them run with a slice per lane (variant -8); an option that asks for
+    a workgroup size no kernel has leaves those to the generic kernel."""
     P, Q = [s[0] for s in shapes], [s[1] for s in shapes]
-    rows = [s["kernel"] for s in km.plan(M, P, Q, "float32")] == [km.KM_KERNEL_ROWS]
-    assert rows != tiled
-    assert km.workspace_size(M, P, Q, "float32") <= (km.KM_STATIC_SCRATCH_BYTES if tiled else 0)
-    _check("float32", M, shapes, workspace=True)
+    old = km.get_option(km.KM_OPT_PREFER_THREADS)
+    try:
+        if not lanes:
+            km.set_option(km.KM_OPT_PREFER_THREADS, 1)
+        steps = km.plan(M, P, Q, "float32")
+        assert ([s["kernel"] for s in steps] == [km.KM_KERNEL_ROWS]) != tiled
+        if tiled:
+            assert any(s["variant"] == -8 for s in steps) == (lanes and M == 9363)
+            assert any(s["kernel"] == km.KM_KERNEL_GENERIC for s in steps) == (not lanes or M == 1254)
+        assert km.workspace_size(M, P, Q, "float32") <= (km.KM_STATIC_SCRATCH_BYTES if tiled else 0)
+        _check("float32", M, shapes, workspace=True)
+    finally:
+        km.set_option(km.KM_OPT_PREFER_THREADS, old)
