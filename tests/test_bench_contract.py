@@ -82,8 +82,12 @@ def test_measured_traffic_comes_from_the_profile_summaries():
         assert workload and traffic and algorithmic and table, path
         t, a = int(traffic.group(1)), int(algorithmic.group(1))
         assert t == int(table.group(1).replace(",", "")) and a == int(table.group(2).replace(",", "")), path
-        # measured traffic well above the algorithmic bytes would mean wasted re-reads
-        assert 0.95 * a <= t <= (1.1 * a if a > 1 << 24 else 2 * a), (path, t, a)
+        # measured traffic well above the algorithmic bytes would mean wasted re-reads.  (A slice per lane with rows of no multiple of 16
+        # slices: its runs of 256 bytes start anywhere and touch up to three lines of 128 for two, half as much again of what is written,
+        # which is half of a square factor's bytes.)
+        square = re.match(r"shape_\d+:(\d+)x\1\^\d+:f32$", workload.group(1))
+        unaligned = "km::mfma_lane" in text and square and int(square.group(1)) % 2
+        assert 0.95 * a <= t <= ((1.25 if unaligned else 1.1) * a if a > 1 << 24 else 2 * a), (path, t, a)
         if " " not in workload.group(1):          # summaries of non-default planner options carry a tag after the name
             assert bench.profile_traffic(workload.group(1)) == (t, os.path.relpath(path, ROOT)), path
     for w in [bench.HEADLINE] + bench.OTHERS:
