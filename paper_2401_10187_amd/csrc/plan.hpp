@@ -1540,8 +1540,8 @@ inline km_status make_plan(const Problem& pr, const Options& opt, const Variant*
     // plan of the FMA kernel or of tiled launches without compiled shapes.  Launches of compiled instances are
     // as quick on problems this small (16 x 16x16^3 6.9 us in three of them, 7.7 here; 128 x 32x32^2 4.9
     // and 4.7).  The others by their estimates, each within 8 % of what was measured on 700 problems: 10 x (52x50,
-    // 65x20) fp64 20.1 us in two launches, 6.6 here, 5 x 61x61^2 fp64 9.1 and 11.0; on the FMA kernel 300 x (32x32, 64x3)
-    // 19.9 and 4.5, 37 x (9x4, 15x14, 4x44) 8.5 and 10.4.  (The kernel has become a tenth quicker than the estimate since.  Level with tiled launches the single one without workspace is
+    // 65x20) fp64 20.1 us in two launches, 6.7 here, 5 x 61x61^2 fp64 9.1 and 11.0; on the FMA kernel 300 x (32x32, 64x3)
+    // 19.9 and 4.7, 37 x (9x4, 15x14, 4x44) 8.5 and 10.4.  (The kernel has become a tenth quicker than the estimate since.  Level with tiled launches the single one without workspace is
     // taken: 1000 x 50x50^2 18.3 us and 16.8, 900 rows 15.9 and 16.6; the FMA kernel stays where the two are within 5 %, since
     // short contractions make this one's estimate too low: 54 x 2x1^6 7.2 us and 7.6.)
     bool compiled = true;

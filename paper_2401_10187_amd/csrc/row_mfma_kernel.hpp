@@ -18,12 +18,12 @@
 // step's numbers are one cache line of the arguments.  No loop holds a division.  Contraction indices past P are zeroed in both
 // operands (what lies behind a slice may be NaN); rows q and columns s past the ends are computed on clamped
 // addresses and dropped.
-// Bound by latency: 10 x (52x50, 65x20), two steps, takes 4.9 us from launch to launch where an empty launch
-// takes 1.6 (5.6 before the three things above: 11 x 50x50^2 6.9 -> 6.2, 2 x 80x80^2 10.2 -> 9.3, 6 x 32x32^2 fp64 4.8 -> 4.2, 280 x (5x4, 4x17)
-// 4.5 -> 3.8; 13.6 on the FMA kernel, whose factors go through LDS and whose 130 busy threads add up 117
-// products one after the other; fp64 20.1 -> 7.0 against two launches); 200 x 50x50^2 20.0 -> 6.9 (9.3 in two launches
-// of the factor-in-register kernel), 33 x 80x80^2 20.2 -> 9.5, 300 x (32x32, 64x3) 19.9 -> 5.0, 5 x (111x82, 7x9)
-// 14.9 -> 4.9.  Sixteen wavefronts when units are many or rows few, four (four rows to a compute unit) otherwise; a
+// Bound by latency: 10 x (52x50, 65x20), two steps, takes 5.0 us from launch to launch on a stream where an empty launch
+// takes 1.6 (5.8 before the three things above: 11 x 50x50^2 7.3 -> 6.4, 2 x 80x80^2 10.4 -> 9.3, 280 x (5x4, 4x17)
+// 4.8 -> 4.1; 13.6 on the FMA kernel, whose factors go through LDS and whose 130 busy threads add up 117
+// products one after the other; fp64 20.1 -> 6.7 against two launches); 200 x 50x50^2 20.0 -> 6.7 (9.3 in two launches
+// of the factor-in-register kernel), 33 x 80x80^2 20.2 -> 9.7, 300 x (32x32, 64x3) 19.9 -> 4.7, 5 x (111x82, 7x9)
+// 14.9 -> 5.2.  Sixteen wavefronts when units are many or rows few, four (four rows to a compute unit) otherwise; a
 // first version with the factors in LDS took 8.7 us on the first of these, 1.2 of it staging them, and a loop over
 // rows around all of it 0.4 us more on every problem, though it ran once.
 // Slices of a multiple of 8 elements are padded by 4 in LDS, which spreads the 64 operand reads of an MFMA
@@ -170,7 +170,7 @@ void row_mfma_sliced_multiply(const T* __restrict__ Xg, T* __restrict__ Yg, int 
     T* buf = lds;
     T* out = lds + ra.buf_elems;
     // The last step's results go straight to Y with sixteen wavefronts or a short row, else through LDS in whole vectors (922 x
-    // 50x50^2 fp64 24.7 us straight, 23.7 through LDS; 280 x (5x4, 4x17) 4.3 and 4.6; sixteen wavefronts with both ways compiled in
+    // 50x50^2 fp64 24.7 us straight, 23.9 through LDS; 280 x (5x4, 4x17) 4.3 and 4.6; sixteen wavefronts with both ways compiled in
     // 2 % slower throughout).
     const bool straight = NW == 16 || k_out * (int)sizeof(T) <= 8192;
     for (int i = 0; i < ra.n; ++i) {
