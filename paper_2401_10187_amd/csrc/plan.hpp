@@ -322,12 +322,12 @@ KM_HOST_DEVICE constexpr int lane_lds_bytes(int P, int Q, int U)
 // Factors that it is compiled for, those that lane_wins() may give it: of the generic kernel's (padded to 16s too large for the other
 // forms), of the form in registers, and of the chunked form's.
 KM_HOST_DEVICE constexpr bool lane_fits_generic(int P, int Q) { return P <= 32 || P > 64 || Q > 8; }
-KM_HOST_DEVICE constexpr bool lane_fits_chunked(int P, int Q) { return P > 32 && (P % 4 != 0 || P == 36 || Q > 16); }
+KM_HOST_DEVICE constexpr bool lane_fits_chunked(int P, int Q) { return P > 32 && (P % 4 != 0 || P == 36 || Q <= 8 || Q > 16); }
 KM_HOST_DEVICE constexpr bool lane_fits_pad(int P, int Q)
 {
     if (P > 64) return P <= 80 && Q > 64 && Q <= (P % 4 == 0 ? 72 : 76);
     if (P > 36 || Q > 40) return false;
-    return P % 4 != 0 || (Q % 16 != 0 && (Q <= 8 ? P >= 20 && P <= 28 : Q > 16 && (P < 32 || Q > 32)));
+    return P % 4 != 0 || (Q % 16 != 0 && P >= 12 && !(P == 32 && Q <= 8));
 }
 constexpr bool lane_takes(int P, int Q)
 {
@@ -1353,22 +1353,23 @@ inline bool lane_cached(const Problem& pr, const km_plan_step& st)
     return mib > 160.0 && mib <= (st.k_in / pr.P[st.first_factor] * (int64_t)pr.esize % 64 == 0 ? 320.0 : 256.0);
 }
 
-// Does the slice-per-lane kernel beat the one that step i was given to?  Fitted to some 5000 launches, each inside its call and
-// beside the kernel that the step was given to, on 6000 problems of random sizes.  On 1300 more of them the calls that change
-// are 1.23 times as fast on average, 98 % of them as fast or faster (within 2 %), the worst 0.89.  By what the step was given to:
-// - the generic kernel: 1.35 times (20 M slices of 10x2 407 -> 208 us, 10.6 M of 17x9 288 -> 198).  From 64 workgroups of 256 slices
-//   on, 128 with up to four columns; fewer leave it a single tile's latency.  Slices of up to 8 elements, which that kernel reads
-//   without LDS, need more of both: on short rows a tile's results are in many runs and stored element by element (881 K of 8x6, 16 to a row,
-//   15.1 -> 18.8 us).  Tall slices with few columns only while they are few (249 K of 72x2 24.0 -> 21.4, 512 K of 75x2 39.6 -> 45.4).
-// - the chunked form: 1.3 times on slices that are no whole vectors, which that one deals to LDS element by element (5.9 M of 42x7 390 ->
-//   278).  Others lose what it gains elsewhere (1.3 M of 48x9 54 -> 73) but for more than 16 columns (3.6 M of 68x68 754 -> 496) and
-//   36 rows (1.07 to 1.2).
+// Does the slice-per-lane kernel beat the one that step i was given to?  Fitted to some 8000 pairs of calls, with and without it in one or
+// more of their launches, on problems of random sizes.  On 1306 more of them 875 calls change, 1.21 times as fast on average, 97 % of them as
+// fast or faster (within 2 %), the worst 0.83.  By what the step was given to:
+// - the generic kernel: 1.3 times (20.8 M slices of 10x2 408 -> 226 us, 20.1 M of 10x6 406 -> 248).  From 64 workgroups of 256 slices
+//   on (calls with 64 to 128 of them 0.6 us faster); fewer leave it a single tile's latency.  Slices of up to 8 elements, which that kernel reads
+//   without LDS, need more of both: on short rows a tile's results are in many runs and stored element by element (1.6 M of 5x31, 16 to a row,
+//   88 -> 130 us).  Tall slices with few columns only while they are few (249 K of 72x2 24.0 -> 21.4, 512 K of 75x2 39.6 -> 45.4).
+// - the chunked form: 1.34 times on slices that are no whole vectors, which that one deals to LDS element by element (6.9 M of 34x8 439 ->
+//   274).  Others lose what it gains elsewhere (1.3 M of 48x9 54 -> 73) but for more than 16 columns (3 M of 72x72 655 -> 450), 36 rows (1.07 to
+//   1.2) and small launches of few columns.
 // - the form with the factor in registers, from 92 MiB moved on; with less the one tile that a wavefront gets takes longer than the products saved.
 //   Its sixteen columns to a wavefront leave some idle, and with two, three and five wavefronts also SIMDs: up to 36 rows and 40 columns
-//   1.17 times (9.6 M of 24x24 368 -> 327, 6.6 M of 30x30 412 -> 298), 65 to 76 columns 1.27 (4 M of 69x74 939 -> 647); columns that
-//   fill the sixteens only on the largest problems (8 M of 30x32 497 -> 353, 1 M of 34x32 39 -> 51), whole vectors with less to gain still (72x72, rows of 72
-//   slices, 0.87; 32x6 0.88).  Rows of less than 64 slices, each tile in several of them, 0.56 to 0.9 (7.8 M x 16x16 333 -> 568 us) where the
-//   intermediates stay on chip or there is none; from 160 MiB on 1.12, and with few columns, few of those stores, 1.17.
+//   1.17 times (7.4 M of 33x33 536 -> 384), whole vectors 1.10 (9.6 M of 24x29 481 -> 372), 65 to 76 columns 1.29 (3.8 M of 65x65 857 -> 538); columns that
+//   fill the sixteens only on the largest problems (8 M of 30x32 497 -> 353, 1 M of 34x32 39 -> 51), whole vectors in few columns only with
+//   small results (24x12^3 of 165 MiB 1.14, 20x13^4 of 175 MiB 0.93; 72x72, rows of 72 slices, 0.87).  Rows of less than 64
+//   slices, each tile in several of them, 0.56 to 0.9 (9 M x 16x16 376 -> 645 us) where the
+//   intermediates stay on chip or there is none; from 160 MiB on 1.11, and with few columns, few of those stores, 1.16.
 //   Intermediates of 160 to 320 MiB stay with that form, which leaves them in the last-level cache (2250 x 31x31^3 whole 319 us there, 346
 //   with one launch of three here), but for 33 to 36 columns, which gain more than that costs (1.11).
 inline bool lane_wins(const Problem& pr, const Plan& plan, size_t i)
@@ -1384,17 +1385,23 @@ inline bool lane_wins(const Problem& pr, const Plan& plan, size_t i)
         if (!lane_fits_pad(P, Q)) return false;
         if (P > 64) return S >= (vectors ? 1024 : Q <= 72 || in + out > 400.0 ? 64 : 128);
         if (Q % 16 == 0 && in < 600.0) return false;
+        if (vectors && (Q <= 8 ? P < 20 || P > 28 : Q <= 16 || (P >= 32 && Q <= 32))) return S >= LANE_SLICES && in <= 180.0 && out <= 100.0;
         if (Q <= 8 || (Q <= 10 && P > 16 && !vectors)) return true;
         if (S < LANE_SLICES) return !vectors && S >= 6 && P >= 9 && (first || in > 160.0) && (last || out > 160.0);
         if (P > 32 && Q > 32 && Q <= 36) return true;
         return !(!first && lane_cached(pr, plan.steps[i - 1])) && !(!last && lane_cached(pr, st));
     }
     if (groups < 64 || S < 16 || (S < 256 && Q > 32)) return false;
-    if (st.kernel != KM_KERNEL_GENERIC) return lane_fits_chunked(P, Q) && groups >= (!vectors || P == 36 || P > 64 ? 128 : 512);
+    if (st.kernel != KM_KERNEL_GENERIC) {
+        if (!lane_fits_chunked(P, Q) || groups < 128) return false;
+        return !vectors || P == 36 || (Q <= 8 ? groups < 512 : P > 64 || groups >= 512);
+    }
     if (!lane_fits_generic(P, Q)) return false;
-    if (P <= 8) return S >= 128 ? groups >= (Q <= 16 ? 512 : 128) : Q <= 8 && groups >= (Q <= 4 ? 1024 : 4096);
-    if (P <= 32) return groups >= (Q <= 4 ? 128 : 64);
-    return Q > 8 || P > 96 || groups < 1024;
+    if (P <= 8) {
+        if (S < 128) return groups >= 512 && (Q <= 4 || (Q <= 8 && P < 8) || (Q <= 32 && P > 5 && P < 8 && groups >= 8192));
+        return groups >= (Q <= 4 ? 256 : Q <= 16 ? 128 : 64);
+    }
+    return P <= 32 || Q > 4 || P > 96 || groups < 1024;
 }
 
 inline bool lane_allowed(const Problem& pr, const Options& opt) { return pr.dtype == KM_F32 && (opt.kernels >> KM_KERNEL_MFMA_ANY & 1) && no_wishes(opt); }

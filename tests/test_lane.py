@@ -123,13 +123,13 @@ int main()
 
 
 def test_where_the_line_lies():
-    """64 workgroups of 256 slices for the generic kernel's steps, 128 with few columns, more for slices of up to 8 elements; 128 for the
+    """64 workgroups of 256 slices for the generic kernel's steps, more for slices of up to 8 elements; 128 for the
     chunked form's, whose whole vectors stay with it unless columns are many; rows of 16 slices; 92 MiB for the form in registers, with
     rows of less than 64 slices only where they gain; never in fp64, nor when an option asks for kernels or tiles."""
     def flips(M, S, P, Q, other=-1):
         return _first(M, _shapes(S, P, Q))["variant"] == other and _first(M + 1, _shapes(S, P, Q))["variant"] == LANE
-    assert flips(1008, 16, 13, 6) and flips(2032, 16, 10, 3) and flips(16368, 16, 7, 3) and flips(1022, 128, 7, 3)
-    assert flips(127, 256, 42, 15) and flips(127, 256, 36, 12) and flips(127, 256, 72, 20)
+    assert flips(1008, 16, 13, 6) and flips(1008, 16, 10, 3) and flips(8176, 16, 7, 3) and flips(510, 128, 7, 3) and flips(131056, 16, 7, 20)
+    assert flips(127, 256, 40, 8) and flips(127, 256, 42, 15) and flips(127, 256, 36, 12) and flips(127, 256, 72, 20)
     assert _first(4000, _shapes(256, 48, 12))["variant"] == -1
     assert _first(4000, _shapes(15, 13, 6))["variant"] == -1
     assert flips(1141, 320, 33, 33, PAD) and flips(709330, 1, 27, 7, PAD)
